@@ -302,7 +302,8 @@ int lstm_grow_to_lhp(const int* dims, const double* lat, int n, double eps, int 
  * other), and sums are compared as fp64: the result does not depend on the launch shape.  *rows_removed / *cols_removed (HOST, may be NULL) receive how many
  * rows / columns this call zeroed.
  *
- * Both allocate and free their own scratch and synchronise the stream.  The packed form of a model is not touched:
+ * Both use scratch of the library (512 KiB per call, of which four can run at once per GPU; what does not
+ * fit, from about 65000 rows plus twice the columns on, and further concurrent calls allocate for the call) and synchronise the stream.  The packed form of a model is not touched:
  * pass the new masks to lstm_set_weights / lstm_set_weights_h to run the pruned model.
  */
 int lstm_prune_weights(const float* W, uint8_t* mask, size_t count, double p_w, size_t* kept_before, size_t* kept_after,
@@ -314,7 +315,7 @@ int lstm_prune_rows_cols(float* W, uint8_t* mask, int M, int N, double p_r, doub
  * lstm_prune_rows_cols for callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid it): the same iteration with the same kernels and the same result, bit for bit, but the
  * scratch (row and column sums, the two thresholds, two counters) lives in a fixed device array inside the library,
- * about 256 KiB, which every GPU the library runs on holds until the process ends.  Nothing is allocated or freed, and
+ * about 384 KiB, which every GPU the library runs on holds until the process ends.  Nothing is allocated or freed, and
  * the call does not synchronise: it is asynchronous on `stream`.
  *   W, mask, M, N, p_r, p_c as lstm_prune_rows_cols (DEVICE arrays, updated in place).
  *   M <= 16384 and N <= 16384, else LSTM_ERR_ARG (the scratch is fixed); M * N is not limited otherwise.
@@ -347,7 +348,7 @@ int lstm_prune_rows_cols_static(float* W, uint8_t* mask, int M, int N, double p_
  * matrices that consume it: a hidden unit of an LSTM layer can go without changing any kept output when its column in
  * the layer's own recurrent matrix and in the next layer's input matrices is dropped too; its bias entries and its
  * rows of every matrix of the layer then go with it (row_index names them).
- * The outputs must not overlap the inputs.  Allocates and frees its own scratch and synchronises the stream.
+ * The outputs must not overlap the inputs.  Uses scratch of the library as the mask updates do and synchronises the stream.
  * LSTM_ERR_ARG: NULL where required, a non-positive size, or gates*R*N > 2^31.
  */
 int lstm_compact_rows_cols(const float* W, const uint8_t* mask, int gates, int R, int N, int32_t* row_index,

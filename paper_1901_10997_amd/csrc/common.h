@@ -464,19 +464,30 @@ struct PersistBatchedHArgs {
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
 hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int ndir, int slots, int cooperative, hipStream_t s);
 
-// Pruning mask updates (device arrays; scratch supplied by the caller of the launcher).
-size_t prune_state_bytes();
-hipError_t launch_prune_weights(const float* W, uint8_t* mask, size_t count, double p_w, unsigned* keys, void* state,
-                                unsigned long long* counters, hipStream_t s);
+// Scratch of the calls that have no handle and wait for their result (util_kernels.hip): device memory and a line of 64
+// bytes of pinned host memory, which kernels may write.
+struct ScratchArea {
+    void* dev = nullptr;
+    void* host = nullptr;
+    int device = -1, area = -1;   // area < 0: allocated for this call
+};
+hipError_t take_scratch(size_t bytes, ScratchArea* out);
+void give_scratch(ScratchArea& a);
+
+// Pruning mask updates (device arrays; scratch supplied by the caller of the launcher; the counts go to device-visible
+// memory).
+size_t prune_weights_scratch_bytes();
+hipError_t launch_prune_weights(const float* W, uint8_t* mask, size_t count, double p_w, void* scratch,
+                                unsigned long long* counts, hipStream_t s);
 size_t prune_rows_cols_scratch_bytes(int M, int N);
 hipError_t launch_prune_rows_cols(float* W, uint8_t* mask, int M, int N, unsigned k_rows, unsigned k_cols, void* scratch,
-                                  int** removed_out, hipStream_t s);
+                                  int* removed, hipStream_t s);
 int prune_rows_cols_static_max_lines();
 hipError_t launch_prune_rows_cols_static(float* W, uint8_t* mask, int M, int N, unsigned k_rows, unsigned k_cols,
                                          int* removed_dev, hipStream_t s);
 size_t compact_scratch_bytes(int gates, int R, int N);
 hipError_t launch_compact_rows_cols(const float* W, const uint8_t* mask, int gates, int R, int N, int* row_index,
-                                    int* col_index, float* Wc, uint8_t* mask_c, void* scratch, int** counts_out, hipStream_t s);
+                                    int* col_index, float* Wc, uint8_t* mask_c, void* scratch, int* counts_out, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
 // yardsticks
 hipError_t launch_copy_stream(void* dst, const void* src, size_t bytes, hipStream_t s);

@@ -2013,20 +2013,18 @@ int lstm_prune_weights(const float* W, uint8_t* mask, size_t count, double p_w, 
     if (!W || !mask || count == 0 || count > ((size_t)1 << 32) - 2 || !(p_w >= 0.0) || p_w > 1.0)
         return fail(nullptr, LSTM_ERR_ARG, "lstm_prune_weights: bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    unsigned* keys = nullptr;
-    char* small = nullptr;   // state | two counters
-    const size_t st_bytes = align256(prune_state_bytes());
-    hipError_t e = hipMalloc((void**)&keys, count * sizeof(unsigned));
-    if (e == hipSuccess) e = hipMalloc((void**)&small, st_bytes + 256);
-    unsigned long long host_cnt[2] = {0, 0};
-    if (e == hipSuccess) e = launch_prune_weights(W, mask, count, p_w, keys, small, (unsigned long long*)(small + st_bytes), s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMemcpy(host_cnt, small + st_bytes, sizeof host_cnt, hipMemcpyDeviceToHost);
-    if (keys) (void)hipFree(keys);
-    if (small) (void)hipFree(small);
+    ScratchArea area;
+    hipError_t e = take_scratch(prune_weights_scratch_bytes(), &area);
     if (e != hipSuccess) return fail_hip(nullptr, e, "lstm_prune_weights");
-    if (kept_before) *kept_before = (size_t)host_cnt[0];
-    if (kept_after) *kept_after = (size_t)host_cnt[1];
+    unsigned long long* host_cnt = (unsigned long long*)area.host;
+    e = launch_prune_weights(W, mask, count, p_w, area.dev, host_cnt, s);
+    const hipError_t es = hipStreamSynchronize(s);   // also after a failed launch: the area must not be in use any more
+    if (e == hipSuccess) e = es;
+    const size_t before = (size_t)host_cnt[0], after = (size_t)host_cnt[1];
+    give_scratch(area);
+    if (e != hipSuccess) return fail_hip(nullptr, e, "lstm_prune_weights");
+    if (kept_before) *kept_before = before;
+    if (kept_after) *kept_after = after;
     return LSTM_OK;
 }
 
@@ -2038,17 +2036,18 @@ int lstm_prune_rows_cols(float* W, uint8_t* mask, int M, int N, double p_r, doub
         return fail(nullptr, LSTM_ERR_ARG, "lstm_prune_rows_cols: bad arguments");
     hipStream_t s = (hipStream_t)stream;
     const unsigned kr = (unsigned)std::min<double>(std::ceil(p_r * M), M), kc = (unsigned)std::min<double>(std::ceil(p_c * N), N);
-    char* scratch = nullptr;
-    int* removed = nullptr;
-    int host_removed[2] = {0, 0};
-    hipError_t e = hipMalloc((void**)&scratch, prune_rows_cols_scratch_bytes(M, N));
-    if (e == hipSuccess) e = launch_prune_rows_cols(W, mask, M, N, kr, kc, scratch, &removed, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMemcpy(host_removed, removed, sizeof host_removed, hipMemcpyDeviceToHost);
-    if (scratch) (void)hipFree(scratch);
+    ScratchArea area;
+    hipError_t e = take_scratch(prune_rows_cols_scratch_bytes(M, N), &area);
     if (e != hipSuccess) return fail_hip(nullptr, e, "lstm_prune_rows_cols");
-    if (rows_removed) *rows_removed = host_removed[0];
-    if (cols_removed) *cols_removed = host_removed[1];
+    int* removed = (int*)area.host;
+    e = launch_prune_rows_cols(W, mask, M, N, kr, kc, area.dev, removed, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    const int rows = removed[0], cols = removed[1];
+    give_scratch(area);
+    if (e != hipSuccess) return fail_hip(nullptr, e, "lstm_prune_rows_cols");
+    if (rows_removed) *rows_removed = rows;
+    if (cols_removed) *cols_removed = cols;
     return LSTM_OK;
 }
 
@@ -2076,17 +2075,18 @@ int lstm_compact_rows_cols(const float* W, const uint8_t* mask, int gates, int R
         (long long)gates * R > (1ll << 31) / N)
         return fail(nullptr, LSTM_ERR_ARG, "lstm_compact_rows_cols: bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    char* scratch = nullptr;
-    int* counts = nullptr;
-    int host_counts[2] = {0, 0};
-    hipError_t e = hipMalloc((void**)&scratch, compact_scratch_bytes(gates, R, N));
-    if (e == hipSuccess) e = launch_compact_rows_cols(W, mask, gates, R, N, row_index, col_index, Wc, mask_c, scratch, &counts, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMemcpy(host_counts, counts, sizeof host_counts, hipMemcpyDeviceToHost);
-    if (scratch) (void)hipFree(scratch);
+    ScratchArea area;
+    hipError_t e = take_scratch(compact_scratch_bytes(gates, R, N), &area);
     if (e != hipSuccess) return fail_hip(nullptr, e, "lstm_compact_rows_cols");
-    *Rc = host_counts[0];
-    *Nc = host_counts[1];
+    int* counts = (int*)area.host;
+    e = launch_compact_rows_cols(W, mask, gates, R, N, row_index, col_index, Wc, mask_c, area.dev, counts, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    const int rows = counts[0], cols = counts[1];
+    give_scratch(area);
+    if (e != hipSuccess) return fail_hip(nullptr, e, "lstm_compact_rows_cols");
+    *Rc = rows;
+    *Nc = cols;
     return LSTM_OK;
 }
 

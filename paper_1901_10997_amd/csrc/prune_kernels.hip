@@ -3,98 +3,194 @@
 // magnitude sum is at or below an order statistic of the row / column sums are removed).
 //
 // Both need a k-th smallest value of non-negative floating-point numbers, whose bit patterns order like unsigned
-// integers, so the selection is a byte-wise radix select.  Weight pruning: 32-bit keys (the magnitudes), four passes,
-// each histogramming one byte of the keys that still match the prefix found so far (LDS histogram per workgroup, then
-// 256 global atomics), and a one-thread kernel that walks the 256 bins to fix the next byte of the answer; entries that
-// do not take part (mask byte 0) get the key 0xFFFFFFFF, above every magnitude.  Row/column pruning: 64-bit keys (fp64
-// sums), a few thousand of them, eight passes inside one workgroup.  Nothing returns to the host between the passes.
+// integers, so the selection is a radix select by digits of eleven and ten bits.  Weight pruning: 31-bit keys (the
+// magnitudes of the active entries), three passes over weights and mask.  Row/column pruning: 64-bit keys (fp64 sums), a
+// few thousand of them, inside one workgroup.  Nothing returns to the host between the passes.
 #include "common.h"
 
 #include <mutex>
 
 namespace l355 {
 
-struct SelectState {
-    unsigned prefix;      // bytes of the answer fixed so far (high bytes first)
-    unsigned k;           // rank (1-based) still to be found among the keys matching the prefix
-    unsigned hist[256];
+// ---- magnitude pruning of weights ------------------------------------------------------------------------------
+// Bound: HBM (three reads of W and mask for the digits, a fourth for the update; the mask bytes that change are written).
+// Every pass loads sixteen entries per thread at a time (16-byte loads of W, 4-byte loads of the mask) and counts the
+// digit of the keys that match what has been fixed so far in an LDS histogram; a workgroup adds its histogram to the
+// global one in order, so that a wave's additions are whole lines.  There is no kernel between the passes: every
+// workgroup of a pass scans the finished histogram of the one before (8 KB) for the digit that holds the rank.  One
+// workgroup of 1024 threads per compute unit keeps the number of global histogram additions small.
+// 6000 x 1500: 400 us for keys, four byte-wide passes and update, -> 51 us (45 MB per pass: 3.6 TB/s).
+struct WeightSelect {
+    unsigned hist[3][2048];         // digits: bits 30..20, 19..10, 9..0
+    unsigned prefix[2], rank[2];    // after the first and second digit: bits fixed so far, rank left among their keys
+    unsigned long long active, below[2];   // active entries; entries with a smaller first / second digit
 };
-
-__global__ void weight_keys_kernel(const float* __restrict__ W, const uint8_t* __restrict__ mask, unsigned* __restrict__ keys,
-                                   size_t n, unsigned long long* __restrict__ active)
+constexpr int kSelThreads = 1024;
+// digit d = 0, 1, 2 of a key
+__device__ __forceinline__ unsigned weight_digit(unsigned key, int d)
 {
-    unsigned long long cnt = 0;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const bool on = mask[i] != 0;
-        keys[i] = on ? (__float_as_uint(W[i]) & 0x7FFFFFFFu) : 0xFFFFFFFFu;
-        cnt += on ? 1u : 0u;
-    }
-    // one atomic per wave
-    for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
-    if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(active, cnt);
+    return d == 0 ? key >> 20 : d == 1 ? (key >> 10) & 1023u : key & 1023u;
 }
 
-__global__ void select_init_kernel(SelectState* st, const unsigned long long* count, double ratio, unsigned k_fixed)
+struct DigitScan { unsigned digit, below, in; unsigned long long total; };
+// The digit of `hist` (2048 bins) that holds rank k (1-based), how many keys lie in smaller bins and in the bin itself.
+// from_ratio: k is ceil(ratio * total) instead, at most the total.  Called by all kSelThreads threads.
+__device__ __forceinline__ DigitScan scan_digits(const unsigned* __restrict__ hist, unsigned k, bool from_ratio, double ratio, unsigned* rank_out)
 {
-    // k = ceil(ratio * count) when a count is given, else the fixed rank
-    unsigned k = k_fixed;
-    if (count) {
-        const double c = (double)*count;
-        double kk = ceil(ratio * c);
-        if (kk > c) kk = c;
-        k = (unsigned)kk;
+    __shared__ unsigned long long wtot[16];
+    __shared__ unsigned res[3];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const unsigned a = hist[2 * tid], b = hist[2 * tid + 1];
+    unsigned long long incl = (unsigned long long)a + b;
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long up = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += up;
     }
-    st->prefix = 0;
-    st->k = k;
-    for (int b = 0; b < 256; ++b) st->hist[b] = 0;
-}
-
-__global__ __launch_bounds__(256) void select_hist_kernel(const unsigned* __restrict__ keys, size_t n, SelectState* st, int shift)
-{
-    __shared__ unsigned h[256];
-    h[threadIdx.x] = 0;
+    if (lane == 63) wtot[wv] = incl;
+    if (tid == 0) res[0] = res[1] = res[2] = 0u;
     __syncthreads();
-    const unsigned prefix = st->prefix;
-    const unsigned high_mask = shift == 24 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const unsigned key = keys[i];
-        if ((key & high_mask) == (prefix & high_mask)) atomicAdd(&h[(key >> shift) & 255u], 1u);
+    unsigned long long base = 0, total = 0;
+    for (int i = 0; i < 16; ++i) {
+        if (i < wv) base += wtot[i];
+        total += wtot[i];
     }
+    if (from_ratio) {
+        const double c = (double)total, kk = ceil(ratio * c);
+        k = (unsigned)(kk > c ? c : kk);
+    }
+    const unsigned long long below = base + incl - a - b;
+    if (k > below && k <= below + a) { res[0] = 2 * tid; res[1] = (unsigned)below; res[2] = a; }
+    else if (k > below + a && k <= below + a + b) { res[0] = 2 * tid + 1; res[1] = (unsigned)below + a; res[2] = b; }
     __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], h[threadIdx.x]);
+    *rank_out = k;
+    const DigitScan d{res[0], res[1], res[2], total};
+    __syncthreads();
+    return d;
 }
 
-__global__ void select_step_kernel(SelectState* st, int shift)
+// f(index, key) for the active entries among 16 consecutive ones per thread; VEC: both addresses allow the wide loads
+template <bool VEC, class F>
+__device__ __forceinline__ void for_active_weights(const float* __restrict__ W, const uint8_t* __restrict__ mask, size_t n, F f)
 {
-    unsigned k = st->k, cum = 0;
-    int b = 0;
-    if (k > 0) {
-        for (; b < 255; ++b) {
-            if (cum + st->hist[b] >= k) break;
-            cum += st->hist[b];
+    const size_t chunk = (size_t)gridDim.x * kSelThreads * 4;
+    for (size_t i0 = ((size_t)blockIdx.x * kSelThreads + threadIdx.x) * 4; i0 < n; i0 += 4 * chunk) {
+        float w[4][4];
+        uint32_t m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t i = i0 + u * chunk;
+            if (VEC && i + 4 <= n) {
+                const float4 v = *reinterpret_cast<const float4*>(W + i);
+                w[u][0] = v.x; w[u][1] = v.y; w[u][2] = v.z; w[u][3] = v.w;
+                m[u] = *reinterpret_cast<const uint32_t*>(mask + i);
+            } else {
+                m[u] = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    w[u][j] = 0.f;
+                    if (i + j < n) { w[u][j] = W[i + j]; m[u] |= (uint32_t)mask[i + j] << (8 * j); }
+                }
+            }
         }
-        st->prefix |= (unsigned)b << shift;
-        st->k = k - cum;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            unsigned key[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) key[j] = ((m[u] >> (8 * j)) & 255u) ? (__float_as_uint(w[u][j]) & 0x7FFFFFFFu) : 0xFFFFFFFFu;
+            f(i0 + u * chunk, key, m[u]);
+        }
     }
-    for (int i = 0; i < 256; ++i) st->hist[i] = 0;
 }
 
-// mask[i] = 0 where the entry took part and its key is at or below the selected one (rank 0: nothing)
-__global__ void apply_weight_threshold_kernel(const unsigned* __restrict__ keys, uint8_t* __restrict__ mask, size_t n,
-                                              const SelectState* st, unsigned long long* __restrict__ kept_after)
+// pass D (0, 1, 2): histogram of digit D of the keys that match the digits before it
+template <int D, bool VEC>
+__global__ __launch_bounds__(kSelThreads) void weight_digit_kernel(const float* __restrict__ W, const uint8_t* __restrict__ mask,
+                                                                   size_t n, WeightSelect* __restrict__ st, double ratio)
 {
-    const bool any = st->k > 0;
-    const unsigned thr = st->prefix;
-    unsigned long long cnt = 0;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const unsigned key = keys[i];
-        const bool on = key != 0xFFFFFFFFu;
-        const bool keep = on && !(any && key <= thr);
-        if (on && !keep) mask[i] = 0;
-        cnt += keep ? 1u : 0u;
+    __shared__ unsigned h[2048];
+    for (int i = threadIdx.x; i < 2048; i += kSelThreads) h[i] = 0;
+    unsigned prefix = 0;
+    bool any = true;
+    if constexpr (D > 0) {
+        unsigned rank = D == 1 ? 0u : st->rank[0];
+        const DigitScan d = scan_digits(st->hist[D - 1], rank, D == 1, ratio, &rank);
+        any = rank > 0;
+        prefix = D == 1 ? d.digit : (st->prefix[0] << 10) | d.digit;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st->prefix[D - 1] = prefix;
+            st->rank[D - 1] = any ? rank - d.below : 0u;
+            st->below[D - 1] = d.below;
+            if (D == 1) st->active = d.total;
+        }
     }
-    for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
-    if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(kept_after, cnt);
+    __syncthreads();
+    if (any)
+        for_active_weights<VEC>(W, mask, n, [&](size_t, const unsigned (&key)[4], uint32_t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool match = D == 0 ? key[j] != 0xFFFFFFFFu : D == 1 ? (key[j] >> 20) == prefix : (key[j] >> 10) == prefix;
+                if (match) atomicAdd(&h[weight_digit(key[j], D)], 1u);
+            }
+        });
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2048; i += kSelThreads)
+        if (h[i]) atomicAdd(&st->hist[D][i], h[i]);
+}
+
+// mask byte to 0 where the entry is active and its key at or below the selected one (rank 0: nothing).  counts
+// (device-visible): active entries before and after.
+template <bool VEC>
+__global__ __launch_bounds__(kSelThreads) void weight_update_kernel(const float* __restrict__ W, uint8_t* __restrict__ mask,
+                                                                    size_t n, const WeightSelect* __restrict__ st,
+                                                                    unsigned long long* __restrict__ counts)
+{
+    unsigned rank = st->rank[1];
+    const DigitScan d = scan_digits(st->hist[2], rank, false, 0.0, &rank);
+    const unsigned thr = (st->prefix[1] << 10) | d.digit;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        counts[0] = st->active;
+        counts[1] = rank > 0 ? st->active - st->below[0] - st->below[1] - d.below - d.in : st->active;
+    }
+    if (rank == 0) return;
+    for_active_weights<VEC>(W, mask, n, [&](size_t i, const unsigned (&key)[4], uint32_t m) {
+        uint32_t left = m;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (key[j] <= thr) left &= ~(255u << (8 * j));
+        if (left == m) return;
+        if (VEC && i + 4 <= n) *reinterpret_cast<uint32_t*>(mask + i) = left;
+        else
+            for (int j = 0; j < 4; ++j)
+                if (i + j < n) mask[i + j] = (uint8_t)(left >> (8 * j));
+    });
+}
+
+size_t prune_weights_scratch_bytes() { return sizeof(WeightSelect); }
+
+template <bool VEC>
+static hipError_t prune_weights_passes(const float* W, uint8_t* mask, size_t count, double p_w, WeightSelect* st,
+                                       unsigned long long* counts, hipStream_t s)
+{
+    // sixteen entries per thread and round
+    const size_t per = (size_t)kSelThreads * 16;
+    const size_t want = (count + per - 1) / per;
+    const dim3 grid((unsigned)std::min<size_t>(want, (size_t)device_num_cus())), block(kSelThreads);
+    hipLaunchKernelGGL((weight_digit_kernel<0, VEC>), grid, block, 0, s, W, mask, count, st, p_w);
+    hipLaunchKernelGGL((weight_digit_kernel<1, VEC>), grid, block, 0, s, W, mask, count, st, p_w);
+    hipLaunchKernelGGL((weight_digit_kernel<2, VEC>), grid, block, 0, s, W, mask, count, st, p_w);
+    hipLaunchKernelGGL((weight_update_kernel<VEC>), grid, block, 0, s, W, mask, count, st, counts);
+    return hipGetLastError();
+}
+
+// scratch: prune_weights_scratch_bytes; counts: device-visible, active entries before and after
+hipError_t launch_prune_weights(const float* W, uint8_t* mask, size_t count, double p_w, void* scratch,
+                                unsigned long long* counts, hipStream_t s)
+{
+    WeightSelect* st = (WeightSelect*)scratch;
+    const hipError_t e = launch_fill_u64((unsigned long long*)st, sizeof(WeightSelect) / 8, 0ull, s);
+    if (e != hipSuccess) return e;
+    const bool vec = ((uintptr_t)W & 15) == 0 && ((uintptr_t)mask & 3) == 0;
+    return vec ? prune_weights_passes<true>(W, mask, count, p_w, st, counts, s) : prune_weights_passes<false>(W, mask, count, p_w, st, counts, s);
 }
 
 // ---- row / column pruning -------------------------------------------------------------------------------------
@@ -104,160 +200,246 @@ __global__ void apply_weight_threshold_kernel(const unsigned* __restrict__ keys,
 // thousand fp32 magnitudes is not exact in general, and the decision "sum <= threshold" must come out the same on
 // every implementation for the masks to be reproducible bit for bit.
 //
-// Both kernels stage tiles in LDS so that the global reads are coalesced whatever the direction of the sum, and one
-// wave then adds a tile's values line by line; the loads of the next tile are in flight meanwhile.
-constexpr int kSumTile = 128;   // positions of a line per tile
-
-// sums[c], 64 columns per workgroup; a wave reads 64 consecutive columns of one row per load
-__global__ __launch_bounds__(256) void col_abs_sum_f64_kernel(const float* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                              int M, int N, double* __restrict__ sums)
-{
-    __shared__ float tile[kSumTile][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + lane;
-    const bool col_ok = c < N;
-    float v[kSumTile / 4];
-    auto fetch = [&](int r0) {
-#pragma unroll
-        for (int i = 0; i < kSumTile / 4; ++i) {
-            const int r = r0 + wave + 4 * i;
-            const bool ok = col_ok && r < M;
-            const size_t idx = ok ? (size_t)r * N + c : 0;
-            const float w = W[idx];
-            const uint8_t on = mask[idx];
-            v[i] = (ok && on) ? fabsf(w) : 0.f;
-        }
-    };
-    double acc = 0.0;
-    fetch(0);
-    for (int r0 = 0; r0 < M; r0 += kSumTile) {
-#pragma unroll
-        for (int i = 0; i < kSumTile / 4; ++i) tile[wave + 4 * i][lane] = v[i];
-        __syncthreads();
-        if (r0 + kSumTile < M) fetch(r0 + kSumTile);
-        if (wave == 0) {
-#pragma unroll 16
-            for (int i = 0; i < kSumTile; ++i) acc += (double)tile[i][lane];
-        }
-        __syncthreads();
-    }
-    if (wave == 0 && col_ok) sums[c] = acc;
-}
-
-// sums[r], 64 rows per workgroup; a wave reads 64 consecutive columns of one row per load and parks them transposed
-__global__ __launch_bounds__(256) void row_abs_sum_f64_kernel(const float* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                              int M, int N, double* __restrict__ sums)
-{
-    constexpr int kRowsPerWave = 16, kChunks = kSumTile / 64;
-    __shared__ float tile[kSumTile][65];   // [position][row], odd stride: both the parking and the summing are conflict-free
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int rbase = blockIdx.x * 64;
-    float v[kRowsPerWave * kChunks];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i)
-#pragma unroll
-            for (int j = 0; j < kChunks; ++j) {
-                const int r = rbase + wave * kRowsPerWave + i, k = k0 + 64 * j + lane;
-                const bool ok = r < M && k < N;
-                const size_t idx = ok ? (size_t)r * N + k : 0;
-                const float w = W[idx];
-                const uint8_t on = mask[idx];
-                v[i * kChunks + j] = (ok && on) ? fabsf(w) : 0.f;
-            }
-    };
-    double acc = 0.0;
-    fetch(0);
-    for (int k0 = 0; k0 < N; k0 += kSumTile) {
-#pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i)
-#pragma unroll
-            for (int j = 0; j < kChunks; ++j) tile[64 * j + lane][wave * kRowsPerWave + i] = v[i * kChunks + j];
-        __syncthreads();
-        if (k0 + kSumTile < N) fetch(k0 + kSumTile);
-        if (wave == 0) {
-#pragma unroll 16
-            for (int i = 0; i < kSumTile; ++i) acc += (double)tile[i][lane];
-        }
-        __syncthreads();
-    }
-    const int r = rbase + lane;
-    if (wave == 0 && r < M) sums[r] = acc;
-}
+// Bound: the chain of dependent fp64 additions along a line (about 8 clocks each: 6000 rows = 20 us), as long as nothing
+// else sits on it.  A workgroup sums 16 lines: four waves fetch tiles of 512 positions (the loads of the tile after next
+// are in flight while the next one is parked), select by the mask, take magnitudes, widen and park them in LDS as fp64,
+// line by line; one wave, a lane per line, does nothing but 16-byte LDS reads, requested a batch ahead, and additions.
+// With 16 lines a 1500-column matrix gives 94 workgroups (64 lines: 24, which cannot pull the matrix in at the rate the
+// chain consumes it), and a tile's line pitch of 514 doubles puts the 16 lanes of a read on distinct banks.
+// 6000 x 1500: column sums 849 -> 40 us, row sums 200 -> 25 us (against one wave widening and adding 64 lines).
+constexpr int kSumLines = 16, kSumTile = 512, kSumPitch = kSumTile + 2, kSumBatch = 16;
+constexpr int kSumThreads = 320;   // one summing wave, four fetching ones
+constexpr size_t kSumLds = (size_t)2 * kSumLines * kSumPitch * sizeof(double) + (size_t)2 * kSumTile * sizeof(int);
 
 struct LineThreshold {
     double value;   // the k-th smallest sum
     unsigned any;   // 0: rank 0 was asked for, nothing is removed along this axis
-    unsigned pad;
+    unsigned count; // lines removed
 };
 
-// k-th smallest (1-based) of n non-negative doubles, whose bit patterns order like 64-bit unsigned integers: eight
-// byte-wide radix passes by one workgroup, histogram in LDS.  n is a row or column count, a few thousand.
-__global__ __launch_bounds__(1024) void select_kth_f64_kernel(const double* __restrict__ sums, int n, unsigned k,
-                                                              LineThreshold* __restrict__ out)
+// COLS: lines are columns (positions run down the rows), else rows.  VEC: four columns per load (N and both addresses
+// allow it).  AFTER (with COLS): lanes 16..31 sum the same columns over the rows that stay, i.e. those whose sum in
+// `rsums` is above the row threshold, into sums_after.
+template <bool COLS, bool VEC, bool AFTER>
+__global__ __launch_bounds__(kSumThreads) void line_abs_sum_f64_kernel(const float* __restrict__ W,
+                                                                       const uint8_t* __restrict__ mask, int M, int N,
+                                                                       double* __restrict__ sums, double* __restrict__ sums_after,
+                                                                       const double* __restrict__ rsums,
+                                                                       const LineThreshold* __restrict__ row_th)
 {
-    __shared__ unsigned hist[256];
-    __shared__ unsigned long long prefix_s;
-    __shared__ unsigned k_s;
-    if (threadIdx.x == 0) { prefix_s = 0ull; k_s = k; }
-    __syncthreads();
-    for (int shift = 56; shift >= 0 && k > 0; shift -= 8) {
-        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-        __syncthreads();
-        const unsigned long long prefix = prefix_s;
-        const unsigned long long high_mask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            const unsigned long long key = (unsigned long long)__double_as_longlong(sums[i]);
-            if ((key & high_mask) == prefix) atomicAdd(&hist[(unsigned)(key >> shift) & 255u], 1u);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned kk = k_s, cum = 0;
-            int b = 0;
-            for (; b < 255; ++b) {
-                if (cum + hist[b] >= kk) break;
-                cum += hist[b];
+    extern __shared__ __attribute__((aligned(16))) double buf[];   // [2][16][514], then [2][512] ints: row is removed
+    int* const gone = reinterpret_cast<int*>(buf + 2 * kSumLines * kSumPitch);
+    const int lane = threadIdx.x & 63;
+    const int p = (int)threadIdx.x - 64;                     // fetching thread 0..255
+    const int line0 = blockIdx.x * kSumLines;
+    const int len = COLS ? M : N, lines = COLS ? N : M;
+    const int tiles = (len + kSumTile - 1) / kSumTile;
+    constexpr int kPer = VEC ? 4 : 1;                        // columns per load
+    constexpr int kLoads = kSumLines * kSumTile / kPer / 256;
+    float w[kLoads][kPer];
+    uint32_t on[kLoads];
+    int gflag[2];
+    // (line, position) of load i of this thread; its kPer values run along the columns
+    auto place = [&](int i, int& line, int& pos) {
+        const int e = p + 256 * i;
+        constexpr int kRow = (COLS ? kSumLines : kSumTile) / kPer;   // loads per row of the tile
+        const int c = (e % kRow) * kPer, r = e / kRow;
+        line = COLS ? c : r;
+        pos = COLS ? r : c;
+    };
+    auto fetch = [&](int tile) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            int line, pos;
+            place(i, line, pos);
+            const int r = COLS ? tile * kSumTile + pos : line0 + line, c = COLS ? line0 + line : tile * kSumTile + pos;
+            const size_t idx = (r < M && c < N) ? (size_t)r * N + c : 0;   // (VEC: N % 4 == 0, a load is in or out as a whole)
+            if constexpr (VEC) {
+                const float4 v = *reinterpret_cast<const float4*>(W + idx);
+                w[i][0] = v.x; w[i][1] = v.y; w[i][2] = v.z; w[i][3] = v.w;
+                on[i] = *reinterpret_cast<const uint32_t*>(mask + idx);
+            } else {
+                w[i][0] = W[idx];
+                on[i] = mask[idx];
             }
-            prefix_s = prefix | ((unsigned long long)b << shift);
-            k_s = kk - cum;
+            if (r >= M || c >= N) on[i] = 0;
+        }
+        if constexpr (AFTER) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = tile * kSumTile + p + 256 * i;
+                gflag[i] = (r < M && rsums[r] <= row_th->value) ? 1 : 0;
+            }
+        }
+    };
+    auto park = [&](int tile) {
+        double* const b = buf + (tile & 1) * kSumLines * kSumPitch;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            int line, pos;
+            place(i, line, pos);
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                b[(line + (COLS ? j : 0)) * kSumPitch + pos + (COLS ? 0 : j)] =
+                    ((on[i] >> (8 * j)) & 255u) ? (double)fabsf(w[i][j]) : 0.0;
+        }
+        if constexpr (AFTER) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) gone[(tile & 1) * kSumTile + p + 256 * i] = gflag[i];
+        }
+    };
+    if (p >= 0) {
+        fetch(0);
+        park(0);
+        if (tiles > 1) fetch(1);
+    }
+    __syncthreads();
+    double acc = 0.0;
+    for (int tile = 0; tile < tiles; ++tile) {
+        if (p >= 0) {
+            if (tile + 1 < tiles) park(tile + 1);
+            if (tile + 2 < tiles) fetch(tile + 2);
+        } else if (lane < (AFTER ? 2 * kSumLines : kSumLines)) {
+            // positions behind the end of the line hold +0, which changes nothing
+            const int left = len - tile * kSumTile;
+            const int n = (left < kSumTile ? left + kSumBatch - 1 : kSumTile) / kSumBatch;
+            const double2* src = reinterpret_cast<const double2*>(buf + ((tile & 1) * kSumLines + (lane & 15)) * kSumPitch);
+            const int4* gsrc = reinterpret_cast<const int4*>(gone + (tile & 1) * kSumTile);
+            double2 cur[kSumBatch / 2], nxt[kSumBatch / 2];
+            int4 gcur[kSumBatch / 4];
+#pragma unroll
+            for (int i = 0; i < kSumBatch / 2; ++i) cur[i] = src[i];
+            for (int k = 0; k < n; ++k) {
+                const int kn = k + 1 < n ? k + 1 : k;
+#pragma unroll
+                for (int i = 0; i < kSumBatch / 2; ++i) nxt[i] = src[kn * (kSumBatch / 2) + i];
+                if constexpr (AFTER) {
+#pragma unroll
+                    for (int i = 0; i < kSumBatch / 4; ++i) gcur[i] = gsrc[k * (kSumBatch / 4) + i];
+#pragma unroll
+                    for (int i = 0; i < kSumBatch / 4; ++i) {
+                        const bool drop = lane >= kSumLines;
+                        if (drop && gcur[i].x) cur[2 * i].x = 0.0;
+                        if (drop && gcur[i].y) cur[2 * i].y = 0.0;
+                        if (drop && gcur[i].z) cur[2 * i + 1].x = 0.0;
+                        if (drop && gcur[i].w) cur[2 * i + 1].y = 0.0;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < kSumBatch / 2; ++i) {
+                    acc += cur[i].x;
+                    acc += cur[i].y;
+                }
+#pragma unroll
+                for (int i = 0; i < kSumBatch / 2; ++i) cur[i] = nxt[i];
+            }
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        out->value = __longlong_as_double((long long)prefix_s);
+    const int line = line0 + (lane & 15);
+    if (p < 0 && line < lines) {
+        if (lane < kSumLines) sums[line] = acc;
+        else if (AFTER && lane < 2 * kSumLines) sums_after[line] = acc;
+    }
+}
+
+// The k-th smallest (1-based) of n non-negative doubles, whose bit patterns order like 64-bit unsigned integers, and the
+// lines that go with it: those whose value in `judged` is at or below it.  One workgroup: radix select by 11-bit digits
+// (LDS histogram, the digit found by a workgroup scan), ended as soon as one sum is left, which with sums of thousands
+// of terms is after two or three digits.  out: the threshold; list (may be nullptr): the removed lines in no particular
+// order; removed: how many.  (6000 sums: 26 -> 10 us against byte-wide digits walked by one thread.)
+__global__ __launch_bounds__(1024) void select_lines_kernel(const double* __restrict__ sums, int n, unsigned k,
+                                                            const double* __restrict__ judged, LineThreshold* __restrict__ out,
+                                                            int* __restrict__ list, int* __restrict__ removed)
+{
+    __shared__ unsigned hist[2048];
+    __shared__ unsigned wtot[16];
+    __shared__ unsigned long long found_key;
+    __shared__ unsigned found_digit, found_below, found_in, nlist;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    unsigned long long prefix = 0ull;
+    unsigned kk = k;
+    if (tid == 0) nlist = 0;
+    // digits of bits 63..53, 52..42, 41..31, 30..20, 19..9, 8..0
+    for (int top = 64; top > 0 && k > 0;) {
+        const int shift = top >= 11 ? top - 11 : 0;
+        hist[tid] = 0;
+        hist[tid + 1024] = 0;
+        __syncthreads();
+        for (int i = tid; i < n; i += 1024) {
+            const unsigned long long key = (unsigned long long)__double_as_longlong(sums[i]);
+            if (top == 64 || (key >> top) == (prefix >> top)) atomicAdd(&hist[(unsigned)(key >> shift) & ((1u << (top - shift)) - 1u)], 1u);
+        }
+        __syncthreads();
+        // the bin that holds rank kk: inclusive scan over pairs of bins
+        const unsigned a = hist[2 * tid], b = hist[2 * tid + 1];
+        unsigned incl = a + b;
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned up = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += up;
+        }
+        if (lane == 63) wtot[wv] = incl;
+        __syncthreads();
+        unsigned below = incl - (a + b);
+        for (int i = 0; i < wv; ++i) below += wtot[i];
+        if (kk > below && kk <= below + a) { found_digit = 2 * tid; found_below = below; found_in = a; }
+        else if (kk > below + a && kk <= below + a + b) { found_digit = 2 * tid + 1; found_below = below + a; found_in = b; }
+        __syncthreads();
+        prefix |= (unsigned long long)found_digit << shift;
+        kk -= found_below;
+        if (found_in == 1 && shift > 0) {   // one candidate left: it is the answer
+            for (int i = tid; i < n; i += 1024) {
+                const unsigned long long key = (unsigned long long)__double_as_longlong(sums[i]);
+                if ((key >> shift) == (prefix >> shift)) found_key = key;
+            }
+            __syncthreads();
+            prefix = found_key;
+            break;
+        }
+        top = shift;
+        __syncthreads();
+    }
+    __syncthreads();
+    const double value = __longlong_as_double((long long)prefix);
+    if (k > 0) {
+        for (int i = tid; i < n; i += 1024)
+            if (judged[i] <= value) {
+                const unsigned at = atomicAdd(&nlist, 1u);
+                if (list) list[at] = i;
+            }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        out->value = value;
         out->any = k > 0 ? 1u : 0u;
-        out->pad = 0u;
+        out->count = nlist;
+        *removed = (int)nlist;
     }
 }
 
-// rows whose sum is at or below the row threshold are removed (mask and weights zeroed)
-__global__ void apply_row_threshold_kernel(float* __restrict__ W, uint8_t* __restrict__ mask, int M, int N,
-                                           const double* __restrict__ sums, const LineThreshold* __restrict__ th,
-                                           int* __restrict__ removed)
+// Mask and weights of the removed lines to zero: a wave per row clears either the whole row or the listed columns of it.
+// th[0]: rows, th[1]: columns; an axis with rank 0 removes nothing and its sums are not looked at.
+__global__ __launch_bounds__(256) void clear_lines_kernel(float* __restrict__ W, uint8_t* __restrict__ mask, int M, int N,
+                                                          const double* __restrict__ rsums, const LineThreshold* __restrict__ th,
+                                                          const int* __restrict__ col_list, int by_rows, int by_cols)
 {
-    const int r = blockIdx.x;
-    if (th->any == 0 || !(sums[r] <= th->value)) return;
-    for (int k = threadIdx.x; k < N; k += blockDim.x) {
-        mask[(size_t)r * N + k] = 0;
-        W[(size_t)r * N + k] = 0.f;
+    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (r >= M) return;
+    float* const w = W + (size_t)r * N;
+    uint8_t* const m = mask + (size_t)r * N;
+    if (by_rows && rsums[r] <= th[0].value) {
+        for (int c = lane; c < N; c += 64) { m[c] = 0; w[c] = 0.f; }
+    } else if (by_cols) {
+        const int n = (int)th[1].count;
+        for (int i = lane; i < n; i += 64) { m[col_list[i]] = 0; w[col_list[i]] = 0.f; }
     }
-    if (threadIdx.x == 0) atomicAdd(removed, 1);
 }
 
-// columns likewise; lanes over columns, blockIdx.y over row chunks
-__global__ void apply_col_threshold_kernel(float* __restrict__ W, uint8_t* __restrict__ mask, int M, int N,
-                                           const double* __restrict__ sums, const LineThreshold* __restrict__ th,
-                                           int* __restrict__ removed)
+// scratch (prune_rows_cols_scratch_bytes): row sums [M] f64 | column sums [N] f64 | column sums without the removed rows
+// [N] f64 | two thresholds.  The list of removed columns takes the place of the column sums once those have been judged.
+size_t prune_rows_cols_scratch_bytes(int M, int N)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= N || th->any == 0 || !(sums[c] <= th->value)) return;
-    const int rows_per = (M + gridDim.y - 1) / gridDim.y;
-    const int r0 = blockIdx.y * rows_per, r1 = min(M, r0 + rows_per);
-    for (int r = r0; r < r1; ++r) {
-        mask[(size_t)r * N + c] = 0;
-        W[(size_t)r * N + c] = 0.f;
-    }
-    if (blockIdx.y == 0) atomicAdd(removed, 1);
+    return ((size_t)M + 2 * (size_t)N) * sizeof(double) + 2 * sizeof(LineThreshold);
 }
 
 __global__ void clear_removed_kernel(int* removed)
@@ -265,64 +447,52 @@ __global__ void clear_removed_kernel(int* removed)
     if (threadIdx.x < 2) removed[threadIdx.x] = 0;
 }
 
-static int grid_for(size_t n)
+template <bool COLS, bool AFTER>
+static hipError_t launch_line_sums(const float* W, const uint8_t* mask, int M, int N, double* sums, double* after,
+                                   const double* rsums, const LineThreshold* th, hipStream_t s)
 {
-    size_t g = (n + 255) / 256;
-    return (int)(g > 2048 ? 2048 : (g < 1 ? 1 : g));
-}
-
-// four passes over the keys; leaves the k-th smallest key in st->prefix (st->k == 0 on entry: no selection)
-static hipError_t radix_select(const unsigned* keys, size_t n, SelectState* st, hipStream_t s)
-{
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(select_hist_kernel, dim3(grid_for(n)), dim3(256), 0, s, keys, n, st, shift);
-        hipLaunchKernelGGL(select_step_kernel, dim3(1), dim3(1), 0, s, st, shift);
-    }
-    return hipGetLastError();
-}
-
-// scratch: keys [count] u32, state (SelectState), counters 2 x u64
-hipError_t launch_prune_weights(const float* W, uint8_t* mask, size_t count, double p_w, unsigned* keys, void* state,
-                                unsigned long long* counters, hipStream_t s)
-{
-    SelectState* st = (SelectState*)state;
-    hipError_t e = launch_fill_u64(counters, 2, 0ull, s);
+    const bool vec = (N & 3) == 0 && ((uintptr_t)W & 15) == 0 && ((uintptr_t)mask & 3) == 0;
+    const void* kern = vec ? (const void*)line_abs_sum_f64_kernel<COLS, true, AFTER> : (const void*)line_abs_sum_f64_kernel<COLS, false, AFTER>;
+    static std::once_flag once[2];
+    hipError_t e = hipSuccess;
+    std::call_once(once[vec ? 1 : 0], [&] { e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSumLds); });
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(weight_keys_kernel, dim3(grid_for(count)), dim3(256), 0, s, W, mask, keys, count, counters);
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(1), 0, s, st, counters, p_w, 0u);
-    // a rank of zero (nothing to prune) stays zero through the passes; otherwise the state ends with k >= 1
-    e = radix_select(keys, count, st, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(apply_weight_threshold_kernel, dim3(grid_for(count)), dim3(256), 0, s, keys, mask, count, st, counters + 1);
-    return hipGetLastError();
-}
-size_t prune_state_bytes() { return sizeof(SelectState); }
-
-// scratch (prune_rows_cols_scratch_bytes): row sums [M] f64 | column sums [N] f64 | two thresholds | removed 2 x int
-size_t prune_rows_cols_scratch_bytes(int M, int N)
-{
-    return ((size_t)M + (size_t)N) * sizeof(double) + 2 * sizeof(LineThreshold) + 2 * sizeof(int);
+    const int lines = COLS ? N : M;
+    void* args[] = {&W, &mask, &M, &N, &sums, &after, &rsums, &th};
+    return hipLaunchKernel(kern, dim3((lines + kSumLines - 1) / kSumLines), dim3(kSumThreads), args, kSumLds, s);
 }
 
+// removed: device-visible int[2], receives the number of removed rows and columns
 hipError_t launch_prune_rows_cols(float* W, uint8_t* mask, int M, int N, unsigned k_rows, unsigned k_cols, void* scratch,
-                                  int** removed_out, hipStream_t s)
+                                  int* removed, hipStream_t s)
 {
     double* rsums = (double*)scratch;
     double* csums = rsums + M;
-    LineThreshold* th = (LineThreshold*)(csums + N);
-    int* removed = (int*)(th + 2);
-    if (removed_out) *removed_out = removed;
-    hipLaunchKernelGGL(clear_removed_kernel, dim3(1), dim3(64), 0, s, removed);
-    // both thresholds from the matrix as it came in
-    hipLaunchKernelGGL(row_abs_sum_f64_kernel, dim3((M + 63) / 64), dim3(256), 0, s, W, mask, M, N, rsums);
-    hipLaunchKernelGGL(col_abs_sum_f64_kernel, dim3((N + 63) / 64), dim3(256), 0, s, W, mask, M, N, csums);
-    hipLaunchKernelGGL(select_kth_f64_kernel, dim3(1), dim3(1024), 0, s, rsums, M, k_rows, th);
-    hipLaunchKernelGGL(select_kth_f64_kernel, dim3(1), dim3(1024), 0, s, csums, N, k_cols, th + 1);
-    // rows first, then columns judged on what the row pass left
-    hipLaunchKernelGGL(apply_row_threshold_kernel, dim3(M), dim3(256), 0, s, W, mask, M, N, rsums, th, removed);
-    hipLaunchKernelGGL(col_abs_sum_f64_kernel, dim3((N + 63) / 64), dim3(256), 0, s, W, mask, M, N, csums);
-    hipLaunchKernelGGL(apply_col_threshold_kernel, dim3((N + 255) / 256, std::min(64, (M + 63) / 64)), dim3(256), 0, s, W, mask,
-                       M, N, csums, th + 1, removed + 1);
+    double* csums_after = csums + N;
+    LineThreshold* th = (LineThreshold*)(csums_after + N);
+    int* const list = (int*)csums;
+    if (k_rows == 0 || k_cols == 0) {
+        hipLaunchKernelGGL(clear_removed_kernel, dim3(1), dim3(64), 0, s, removed);
+        if (k_rows == 0 && k_cols == 0) return hipGetLastError();
+    }
+    hipError_t e = hipSuccess;
+    // Both thresholds come from the matrix as it came in; rows are removed first and columns judged on what that leaves.
+    if (k_rows > 0) {
+        e = launch_line_sums<false, false>(W, mask, M, N, rsums, nullptr, nullptr, nullptr, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, rsums, M, k_rows, rsums, th, (int*)nullptr, removed);
+    }
+    if (k_cols > 0) {
+        // without removed rows the sums as passed in are also the ones to judge, and one pass reads both
+        double* const judged = k_rows > 0 ? csums_after : csums;
+        e = k_rows > 0 ? launch_line_sums<true, true>(W, mask, M, N, csums, csums_after, rsums, th, s)
+                       : launch_line_sums<true, false>(W, mask, M, N, csums, nullptr, nullptr, nullptr, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, csums, N, k_cols, judged, th + 1,
+                           k_rows > 0 ? list : (int*)csums_after, removed + 1);
+    }
+    hipLaunchKernelGGL(clear_lines_kernel, dim3((M + 3) / 4), dim3(256), 0, s, W, mask, M, N, rsums, th,
+                       k_rows > 0 ? list : (int*)csums_after, k_rows > 0 ? 1 : 0, k_cols > 0 ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -331,7 +501,7 @@ hipError_t launch_prune_rows_cols(float* W, uint8_t* mask, int M, int N, unsigne
 // In host code the array's name is only a handle for hipGetSymbolAddress; the address that call returns for the
 // current device is what the kernels get.
 constexpr int kStaticMaxLines = 16384;   // largest M and largest N accepted
-constexpr size_t kStaticScratchBytes = (size_t)2 * kStaticMaxLines * sizeof(double) + 256;
+constexpr size_t kStaticScratchBytes = (size_t)3 * kStaticMaxLines * sizeof(double) + 256;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -359,29 +529,18 @@ static hipError_t static_scratch_for_current_device(void** out)
     return hipSuccess;
 }
 
-__global__ void copy_removed_kernel(const int* __restrict__ removed, int* __restrict__ out)
-{
-    if (threadIdx.x < 2) out[threadIdx.x] = removed[threadIdx.x];
-}
-
 // the caller has checked M, N <= kStaticMaxLines
 hipError_t launch_prune_rows_cols_static(float* W, uint8_t* mask, int M, int N, unsigned k_rows, unsigned k_cols,
                                          int* removed_dev, hipStream_t s)
 {
-    if (prune_rows_cols_scratch_bytes(M, N) > kStaticScratchBytes) return hipErrorInvalidValue;
+    const size_t need = (prune_rows_cols_scratch_bytes(M, N) + 15) & ~(size_t)15;
+    if (need + 2 * sizeof(int) > kStaticScratchBytes) return hipErrorInvalidValue;
     void* ptr = nullptr;
-    hipError_t e = static_scratch_for_current_device(&ptr);
+    const hipError_t e = static_scratch_for_current_device(&ptr);
     if (e != hipSuccess) return e;
-    int* removed = nullptr;
-    // the launcher clears the two counters with a fill kernel and overwrites every sum and threshold it reads,
-    // so what the previous call left in the array does not matter
-    e = launch_prune_rows_cols(W, mask, M, N, k_rows, k_cols, ptr, &removed, s);
-    if (e != hipSuccess) return e;
-    if (removed_dev) {
-        hipLaunchKernelGGL(copy_removed_kernel, dim3(1), dim3(64), 0, s, removed, removed_dev);
-        e = hipGetLastError();
-    }
-    return e;
+    // every sum, list entry and threshold that is read has been written by this call, so what the previous one left in
+    // the array does not matter
+    return launch_prune_rows_cols(W, mask, M, N, k_rows, k_cols, ptr, removed_dev ? removed_dev : (int*)((char*)ptr + need), s);
 }
 
 }  // namespace l355

@@ -2,6 +2,8 @@
 // graph) and a streaming copy used to quote the achievable memory bandwidth next to the spec-sheet figure.
 #include "common.h"
 
+#include <mutex>
+
 namespace l355 {
 
 __global__ void fill_u64_kernel(unsigned long long* p, size_t n, unsigned long long v)
@@ -58,6 +60,67 @@ int device_num_cus()
             cached = 256;
     }
     return cached;
+}
+
+// ---- scratch of the calls that have no handle and wait for their result (mask updates, compaction) -----------------
+// A hipMalloc / hipFree pair per call costs more than the kernels of a small matrix, so each GPU keeps a few areas in a
+// file-scope device array (part of the loaded code object, like the code itself: given back when that is unloaded) and a
+// line of pinned host memory per area for the counts a call returns.  A call takes a free area for as long as it runs;
+// further concurrent calls, and those that need more than an area holds, allocate their own and free it.
+namespace {
+constexpr int kAreas = 4, kScratchDevices = 64;
+constexpr size_t kAreaBytes = 512 * 1024, kHostLine = 64;
+static __device__ __align__(256) unsigned char scratch_areas[kAreas * kAreaBytes];
+std::mutex g_areas_mutex;
+struct DeviceAreas {
+    char* base = nullptr;
+    char* host = nullptr;
+    bool busy[kAreas] = {};
+} g_areas[kScratchDevices];
+}  // namespace
+
+hipError_t take_scratch(size_t bytes, ScratchArea* out)
+{
+    *out = ScratchArea{};
+    hipError_t e = hipGetDevice(&out->device);
+    if (e != hipSuccess) return e;
+    if (bytes <= kAreaBytes && out->device >= 0 && out->device < kScratchDevices) {
+        std::lock_guard<std::mutex> lock(g_areas_mutex);
+        DeviceAreas& a = g_areas[out->device];
+        if (!a.base) {
+            void *d = nullptr, *h = nullptr;
+            e = hipGetSymbolAddress(&d, HIP_SYMBOL(scratch_areas));
+            if (e == hipSuccess) e = hipHostMalloc(&h, kAreas * kHostLine, hipHostMallocDefault);
+            if (e != hipSuccess) return e;
+            a.base = (char*)d;
+            a.host = (char*)h;
+        }
+        for (int i = 0; i < kAreas; ++i)
+            if (!a.busy[i]) {
+                a.busy[i] = true;
+                out->area = i;
+                out->dev = a.base + (size_t)i * kAreaBytes;
+                out->host = a.host + (size_t)i * kHostLine;
+                return hipSuccess;
+            }
+    }
+    e = hipMalloc(&out->dev, bytes);
+    if (e == hipSuccess) e = hipHostMalloc(&out->host, kHostLine, hipHostMallocDefault);
+    if (e != hipSuccess) give_scratch(*out);
+    return e;
+}
+
+// the kernels that use the area have completed
+void give_scratch(ScratchArea& a)
+{
+    if (a.area >= 0) {
+        std::lock_guard<std::mutex> lock(g_areas_mutex);
+        g_areas[a.device].busy[a.area] = false;
+    } else {
+        if (a.dev) (void)hipFree(a.dev);
+        if (a.host) (void)hipHostFree(a.host);
+    }
+    a = ScratchArea{};
 }
 
 }  // namespace l355

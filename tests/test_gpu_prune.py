@@ -99,3 +99,40 @@ def test_row_column_pruning_takes_every_line_tied_with_the_threshold(axis):
     assert (rows, cols) == ((3, 0) if axis == "rows" else (0, 3))
     gone = np.flatnonzero(~mr.any(axis=1)) if axis == "rows" else np.flatnonzero(~mr.any(axis=0))
     assert list(gone) == ([3, 40, 69] if axis == "rows" else [0, 64, 89])
+
+
+@pytest.mark.parametrize("M,N,off", [
+    (1, 512, 0), (16, 513, 0), (17, 1025, 0),        # rows: whole tiles of 512 positions, one position more, ragged lines
+    (512, 16, 0), (1025, 20, 0), (1030, 33, 0),      # columns likewise
+    (529, 36, 1), (300, 64, 3),                      # arrays that start off the alignment of the wide loads
+    (200, 83, 0),                                    # a width that does not allow them
+    (70000, 2, 0),                                   # more sums than the library's own scratch holds
+])
+def test_mask_updates_at_tile_edges_and_alignments(M, N, off):
+    """Weight, row and column pruning where the tiles of the sums, the sixteen entries per thread of the selection passes
+    and the wide loads end: bit for bit the oracle's masks, weights and counts."""
+    import torch
+    rng = np.random.default_rng(M * 7 + N)
+    W = (rng.standard_normal((M, N)) * np.exp(rng.uniform(-12, 3, (M, N)))).astype(np.float32)
+    mask = (rng.random((M, N)) < 0.7).astype(np.uint8)
+    W[mask == 0] = np.float32(np.nan)                                     # never looked at
+    Wp, mp = _dev(np.zeros(M * N + off, np.float32)), _dev(np.zeros(M * N + off, np.uint8))
+
+    def load(Wh, mh):
+        Wp[off:].copy_(torch.from_numpy(Wh.ravel()))
+        mp[off:].copy_(torch.from_numpy(mh.ravel()))
+        return Wp.data_ptr() + 4 * off, mp.data_ptr() + off
+
+    a, b = load(W, mask)
+    before, after = B.lstm_prune_weights(a, b, M * N, 0.4)
+    ref = oprune.prune_weights(W, mask, 0.4)
+    np.testing.assert_array_equal(mp[off:].cpu().numpy().reshape(M, N), ref)
+    assert (before, after) == (int(mask.sum()), int(ref.sum()))
+    for pr, pc in ((0.3, 0.3), (0.3, 0.0), (0.0, 0.3), (0.0, 0.0)):
+        a, b = load(W, mask)
+        rows, cols = B.lstm_prune_rows_cols(a, b, M, N, pr, pc)
+        Wr, mr = oprune.prune_rows_cols(W, mask, pr, pc)
+        np.testing.assert_array_equal(mp[off:].cpu().numpy().reshape(M, N), mr)
+        np.testing.assert_array_equal(Wp[off:].cpu().numpy().reshape(M, N).view(np.uint32), Wr.view(np.uint32))
+        r_ref, c_ref = oprune.prune_rows_cols_lines(W, mask, pr, pc)
+        assert (rows, cols) == (int(r_ref.sum()), int(c_ref.sum()))
