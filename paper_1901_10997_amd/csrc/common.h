@@ -245,39 +245,38 @@ struct PersistMfmaArgs {
     int T, B, H, reverse;
 };
 bool persist_mfma_supported(int B, int H);
-// fp32 dense recurrence at small and medium batch with the time loop on the device (all directions of a layer per launch)
-struct PersistDenseDir {
-    const float* P;            // [T*B][4H]
-    const float* Wh;           // [4H][H] fp32, packed rows
-    const float* c0;           // [B][H] or nullptr
-    float* y;                  // h_t -> y[(t*B + b)*y_ld + j]
+// fp32 dense recurrence, LSTM and H-LSTM cells, batch columns four at a time (all directions of a layer per launch)
+struct PersistQuadDir {
+    const float* P;            // [T*Bld][4H] (H-LSTM: [4G]): input projection incl. bias
+    const float* Wf;           // W_h / W1h in fragment order (launch_to_frag16)
+    const float* W2f;          // H-LSTM: W2 in fragment order by gate
+    const float* bias2;        // H-LSTM: [4H] packed
+    const float* h0;           // [B][H] or nullptr
+    const float* c0;
+    float* y;                  // h_t -> y[(t*Bld + b)*y_ld + j]
     int y_ld;
     float* hT;
     float* cT;
     int reverse;
-    int has_h0;                // exchange buffer 0 holds h0 (set by the launcher)
 };
-struct PersistDenseArgs {
-    PersistDenseDir d[2];
-    float* hx;                 // per direction two exchange buffers of ceil(H/16) * Bp * 16 words (Bp: B rounded up to the
-                               // row blocks), all zero at launch
+struct PersistQuadArgs {
+    PersistQuadDir d[2];
+    int T, B, Bld, H, G, ndir;    // G = 0: LSTM cell
+    int device_scope_only;        // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
+    int poll_pace;                // pace_poll units in front of a device-wide poll
     int* timeout_flag;
     unsigned spin_limit;
-    int T, B, H, ndir;
-    int Bld;                   // rows per timestep in P and y (>= B: the launch may cover a run of the batch's columns)
-    int gm, gn;                // row blocks, workgroups per row block (set by the launcher)
-    int poll_pace;             // pace_poll units in front of a step's first read of h (exchange.h)
-    unsigned long long* xcc_ids;  // [ndir * row blocks][64] tagged slots for the XCD ids of a group's workgroups (zero or
-                               // older tags only), or nullptr: no hand-over through one XCD's L2
-    unsigned tag_base;         // the XCD ids of this launch carry tag_base + 1
-    int xcd_local;             // block ids grouped by XCD (set by the launcher)
-    int device_scope_only;     // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
+    // set by the launcher
+    int quads, mq, groups, gn, xcd_local;
+    unsigned *hx, *ux;
+    unsigned long long* xcc_ids;
 };
-size_t persist_dense_f32_ids_count();   // 8-byte slots behind xcc_ids
-bool persist_dense_f32_supported(int B, int H, int ndir);
-size_t persist_dense_f32_exchange_floats(int B, int H, int ndir);
-// h0[d]: fp32 [B][H] of direction d or nullptr
-hipError_t launch_persist_dense_f32(PersistDenseArgs& a, const float* const* h0, bool cooperative, hipStream_t s);
+bool persist_quad_supported(int B, int H, int G, int ndir);
+size_t persist_quad_exchange_words(int B, int H, int G, int ndir);
+void persist_quad_describe(int B, int H, int G, int ndir, char* buf, size_t n);
+hipError_t launch_persist_quad(PersistQuadArgs& a, unsigned* words, bool cooperative, hipStream_t s);
+size_t frag16_floats(int rows, int cols);
+hipError_t launch_to_frag16(const float* W, int rows, int cols, bool by_gate, float* out, hipStream_t s);
 size_t persist_mfma_exchange_bytes(int B, int H);
 size_t persist_mfma_flag_count(int B, int H);   // 32-bit words of flag storage, XCD id slots included
 size_t persist_mfma_ids_offset(int B, int H);   // word offset of the XCD id slots inside it

@@ -114,14 +114,14 @@ static float host_bf16_to_f32(uint16_t b)
 constexpr int kMaxRecurrentSlots = 24;
 struct LaunchCut { int passes = 0, chunks = 0; };
 template <class Fits>
-static bool choose_cut(int B, int Dn, Fits fits, LaunchCut* out)
+static bool choose_cut(int B, int Dn, Fits fits, LaunchCut* out, int min_cols = 2)
 {
     for (int total = 1; total <= 8; ++total)
         for (int passes = 1; passes <= Dn; ++passes) {
             if (total % passes) continue;
             const int chunks = total / passes, nd = Dn / passes;
             const int lo = B / chunks, hi = (B + chunks - 1) / chunks;
-            if (lo < 2) continue;
+            if (lo < min_cols) continue;
             if (fits(hi, nd) && (lo == hi || fits(lo, nd))) {
                 out->passes = passes;
                 out->chunks = chunks;
@@ -140,10 +140,10 @@ static inline int chunk_begin(int B, int chunks, int c) { return (int)((long lon
 // or an exchange inside one XCD, already puts the first poll round where it succeeds).
 constexpr int kPollPaceHlstmB1 = 10;
 constexpr int kPollPaceBatchedDeviceWide = 8;
-// dense fp32 recurrence at small and medium batch, first read of h in a step (its own stores just in front of it): layers of
-// 256 to 1024 units at batch 4 to 64 are fastest between 16 and 24 (H = 800, both directions, batch 16: 1665 us per layer
-// unpaced, 1567 at 16, 1453 at 24, 1503 at 32; H = 256, batch 16: 2.48 us per step unpaced, 2.31 at 16, 2.54 at 24)
-constexpr int kPollPaceDenseNarrow = 16, kPollPaceDenseWide = 24;
+// Dense fp32 recurrence with a device-wide exchange and nothing between a publication and the next read: broad optimum from
+// 10 to 18 (800 units, batch 4: 2.42 us per step unpaced, 2.18 at 10, 1.94 at 14, 2.20 at 24; H-LSTM 1500/1500, batch 1:
+// 8.80, 8.31, 8.14, 8.46).
+constexpr int kPollPaceQuad = 13;
 // the yardsticks try these and report the fastest
 static const int kYardstickPaces[] = {0, 6, 10, 12, 16};
 
@@ -342,28 +342,20 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
     return LSTM_OK;
 }
 
-// A row-major fp32 matrix W[rows][cols] in the fragment order of the 16x16x4 matrix instruction: tile (nb, kb) is 64 lanes
-// x 4 values, lane l holding W[16 nb + l % 16][16 kb + 4 (l / 16) .. + 3]; zero beyond the matrix (launch_proj_mfma).
-static std::vector<float> to_frag16(const float* W, int rows, int cols)
+// Fragment-ordered copy (launch_to_frag16) of the dense matrix already on the device.
+static int add_frag16(lstm_t* m, PackedMat& p, bool by_gate)
 {
-    const int NB = (rows + 15) / 16, KB = (cols + 15) / 16;
-    std::vector<float> out((size_t)NB * KB * 256, 0.0f);
-    for (int nb = 0; nb < NB; ++nb)
-        for (int kb = 0; kb < KB; ++kb) {
-            float* tile = out.data() + ((size_t)nb * KB + kb) * 256;
-            for (int l = 0; l < 64; ++l) {
-                const int n = 16 * nb + (l & 15), k0 = 16 * kb + 4 * (l >> 4);
-                if (n >= rows) continue;
-                for (int c = 0; c < 4 && k0 + c < cols; ++c) tile[4 * l + c] = W[(size_t)n * cols + k0 + c];
-            }
-        }
-    return out;
+    HIP_TRY(m, hipMalloc((void**)&p.dense_frag16, frag16_floats(p.rows, p.cols) * sizeof(float)));
+    HIP_TRY(m, launch_to_frag16((const float*)p.dense, p.rows, p.cols, by_gate, p.dense_frag16, nullptr));
+    HIP_TRY(m, hipStreamSynchronize(nullptr));
+    return LSTM_OK;
 }
 
+enum { kFragNone = 0, kFragRows = 1, kFragByGate = 2 };   // fragment-ordered copy of a dense fp32 matrix: none, as stored, by gate
 // Pack one matrix W[4H][cols] (ABI row order q*H + j) with its optional mask into device storage.
 static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t* mask, int H, int cols, bool compressed,
                        bool bf16, bool keep_dense, int quarter_slots = 0, int gate_col_stride = 0, int soft_slots = 0,
-                       bool frag16 = false, bool q16_gather16 = false)
+                       int frag16 = kFragNone, bool q16_gather16 = false)
 {
     free_mat(out);
     const int rows = 4 * H;
@@ -392,7 +384,10 @@ static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t*
             float* d = nullptr;
             HIP_TRY(m, upload(&d, buf));
             out.dense = d;
-            if (frag16 && cols % 4 == 0) HIP_TRY(m, upload(&out.dense_frag16, to_frag16(buf.data(), rows, cols)));
+            if (frag16 != kFragNone) {
+                const int rc = add_frag16(m, out, frag16 == kFragByGate);
+                if (rc != LSTM_OK) return rc;
+            }
         }
         if (!compressed) return LSTM_OK;
     }
@@ -699,9 +694,9 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     x.set = false;
     const bool bf16 = (m->dtype == LSTM_BF16);
     // W_x is kept in both forms when compressed: large T*B projections run dense on the matrix cores
-    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 0, !bf16, true);
+    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 0, !bf16 && D % 4 == 0 ? kFragRows : kFragNone, true);
     if (rc != LSTM_OK) return rc;
-    rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots);
+    rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 0, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
     std::vector<float> bp(rows);
     for (int rp = 0; rp < rows; ++rp) bp[rp] = b[(rp & 3) * H + (rp >> 2)];
@@ -760,12 +755,12 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     LayerDir& x = m->ld[(size_t)layer * m->Dn + direction];
     x.set = false;
     // hidden layers: 4G rows, packed row 4g+q; kept dense as well for the projection on the matrix cores
-    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 0, true);
+    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 0, D % 4 == 0 ? kFragRows : kFragNone);
     if (rc != LSTM_OK) return rc;
-    rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 12);
+    rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 12, kFragRows);
     if (rc != LSTM_OK) return rc;
     // gate outputs: 4H rows, packed row 4j+q, columns = hidden units of the row's own gate
-    rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 12);
+    rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 12, kFragByGate);
     if (rc != LSTM_OK) return rc;
     std::vector<float> bp1((size_t)4 * G), bp2((size_t)4 * H);
     for (int rp = 0; rp < 4 * G; ++rp) bp1[rp] = b1[(size_t)(rp & 3) * G + (rp >> 2)];
@@ -805,8 +800,20 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, total;
 };
+// launches of the dense fp32 persistent recurrence that layer l takes
+static bool quad_cut(const lstm_t* m, int l, int B, LaunchCut* cut)
+{
+    const int H = m->hid(l), G = m->ghid(l);
+    return m->dtype == LSTM_F32 && (B >= 2 || m->G > 0) &&
+           choose_cut(B, m->Dn, [&](int b, int nd) { return persist_quad_supported(b, H, G, nd); }, cut, 1);
+}
+// exchange words per launch of that layer (the longest run of batch columns)
+static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
+{
+    return align256(4 * persist_quad_exchange_words((B + cut.chunks - 1) / cut.chunks, m->hid(l), m->ghid(l), m->Dn / cut.passes)) / 4;
+}
 static Workspace carve(const lstm_t* m, int T, int B)
 {
     Workspace w{};
@@ -866,20 +873,6 @@ static Workspace carve(const lstm_t* m, int T, int B)
             w.mflag_off = off;
             off += align256(flags * sizeof(unsigned));
         }
-    } else if (m->G == 0) {
-        // fp32 dense persistent recurrence at small and medium batch: the same two regions (whether a layer's recurrent
-        // matrix is held dense is not known before its weights are set, so every width the kernel takes is provided for)
-        size_t xfloats = 0;
-        for (int l = 0; l < m->L; ++l) {
-            const int Hl = m->hid(l);
-            LaunchCut cut;
-            if (choose_cut(B, m->Dn, [&](int b, int nd) { return persist_dense_f32_supported(b, Hl, nd); }, &cut))
-                for (int b : {(B + cut.chunks - 1) / cut.chunks, B / cut.chunks})
-                    xfloats = std::max(xfloats, persist_dense_f32_exchange_floats(b, Hl, m->Dn / cut.passes));
-        }
-        off += align256(xfloats * sizeof(float));
-        w.mflag_off = off;
-        if (xfloats > 0) off += align256(persist_dense_f32_ids_count() * sizeof(unsigned long long));
     }
     // H-LSTM: hidden-layer activations of the current step, [B][4G] per direction (stepwise paths); the small-batch
     // persistent kernel uses both directions' storage as one array of [k][columns of a batch group] blocks
@@ -887,6 +880,14 @@ static Workspace carve(const lstm_t* m, int T, int B)
         w.U_off[d] = off;
         if (m->G > 0 && d < m->Dn) off += align256(((size_t)B + 3) * 4 * m->G * sizeof(float) + ((size_t)B / 2 + 1) * 256);
     }
+    // exchange regions of the dense fp32 persistent recurrence, one per launch of the forward so that one fill serves all
+    // (whether a layer's recurrent matrices are held dense is not known before its weights are set)
+    w.qx_off = off;
+    for (int l = 0; l < m->L; ++l) {
+        LaunchCut cut;
+        if (quad_cut(m, l, B, &cut)) w.qx_words += quad_launch_words(m, l, B, cut) * cut.passes * cut.chunks;
+    }
+    off += align256(w.qx_words * sizeof(unsigned));
     w.total = off;
     return w;
 }
@@ -990,6 +991,68 @@ static int take_b1_tags(lstm_t* m, unsigned n, size_t slots, hipStream_t s, unsi
     return LSTM_OK;
 }
 
+// Exchange regions of the dense fp32 persistent recurrence inside one forward.
+struct QuadRegions {
+    unsigned* next = nullptr;   // the next launch's region; nullptr: the regions have not been cleared yet
+};
+
+// Recurrence of layer l with its dense fp32 matrices (W_h; H-LSTM: W1h and W2), time loop on the device.  *done is left
+// false when some direction holds another form or no shape takes the layer.
+static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const float* h0, const float* c0, float* Yout, int y_ld,
+                          float* hT, float* cT, const char* proj, const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s, bool* done)
+{
+    const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l), R = 4 * (G > 0 ? G : H);
+    if (m->plan == LSTM_PLAN_STEPWISE) return LSTM_OK;
+    for (int d = 0; d < Dn; ++d) {
+        const LayerDir& w = m->ld[(size_t)l * Dn + d];
+        if (w.wh.compressed || !w.wh.dense_frag16 || (G > 0 && (w.w2.compressed || !w.w2.dense_frag16))) return LSTM_OK;
+    }
+    LaunchCut cut;
+    if (!quad_cut(m, l, B, &cut)) return LSTM_OK;
+    if (!reg.next) {
+        reg.next = (unsigned*)(base + ws.qx_off);
+        HIP_TRY(m, launch_fill_u64((unsigned long long*)reg.next, align256(ws.qx_words * 4) / 8, 0ull, s));
+    }
+    const size_t words = quad_launch_words(m, l, B, cut);
+    for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
+        const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
+        const int nd = Dn / cut.passes, d_lo = pass * nd;
+        const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
+        PersistQuadArgs a{};
+        for (int d = d_lo; d < d_lo + nd; ++d) {
+            const LayerDir& w = m->ld[(size_t)l * Dn + d];
+            const size_t so = m->soff((size_t)l * Dn + d) * B + (size_t)b_lo * H;
+            PersistQuadDir& q = a.d[d - d_lo];
+            q.P = P[d] + (size_t)b_lo * R;
+            q.Wf = w.wh.dense_frag16;
+            q.W2f = w.w2.dense_frag16;
+            q.bias2 = w.bias2;
+            q.h0 = h0 ? h0 + so : nullptr;
+            q.c0 = c0 ? c0 + so : nullptr;
+            q.y = Yout + (size_t)b_lo * y_ld + (size_t)d * H; q.y_ld = y_ld;
+            q.hT = hT ? hT + so : nullptr;
+            q.cT = cT ? cT + so : nullptr;
+            q.reverse = d;
+            if (chunk == 0) {
+                char tag[128], shape[48], cuts[24] = "";
+                persist_quad_describe(bn, H, G, nd, shape, sizeof shape);
+                if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, "(batch/%d)", cut.chunks);
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-%s%s%s;", l, d, proj, G > 0 ? "hlstm" : "f32", shape, cuts);
+                m->last_plan += tag;
+            }
+        }
+        a.T = T; a.B = bn; a.Bld = B; a.H = H; a.G = G; a.ndir = nd;
+        a.device_scope_only = m->device_scope_only;
+        a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
+        a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceQuad;
+        ProfSpan span(m, s, 1);
+        HIP_TRY(m, launch_persist_quad(a, reg.next, m->launch_mode() != 0, s));
+        reg.next += words;
+    }
+    *done = true;
+    return LSTM_OK;
+}
+
 // H-LSTM stack (fp32).  Per layer and direction: the hidden layers' input side for all timesteps as one projection
 // (P1 = W1x.x + b1, 4G rows), then per step the hidden layers (stage 1) and the gate outputs with the cell update
 // (stage 2).
@@ -1007,6 +1070,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
     bool hslots_clean = false;   // exchange slots and flags zeroed during this forward (tags then restart at 1)
     int hslots_H = 0, hslots_G = 0;   // widths of the layer the region was last laid out for
     unsigned htag = 0;
+    QuadRegions quad;
     for (int l = 0; l < L; ++l) {
         const int H = m->hid(l), G = m->ghid(l);
         const int D = m->in_dim(l);
@@ -1045,6 +1109,12 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
             } else {
                 HIP_TRY(m, launch_proj_dense(X, false, D, w.wx.dense, false, w.bias, P[d], M, 4 * G, D, s));
             }
+        }
+        {
+            bool done = false;
+            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_dense[0] ? "dense" : "csr", ws, base, quad, s, &done);
+            if (rc != LSTM_OK) return rc;
+            if (done) continue;
         }
         // small batch, W1h and W2 of every direction row-compressed with rows of at most 256 kept entries (the
         // quarter-wave form): one launch per layer with the time loop on the device
@@ -1306,6 +1376,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
     bool mflags_clean = false;   // zeroed during this forward (tags then restart at 1)
     int mflags_H = 0;            // width of the layer the flags were last laid out for
     unsigned mtag = 0;
+    QuadRegions quad;
     bool prev_has_bf16 = false;  // the layer below left a bf16 copy of its hidden sequence in Ybf[(l-1)&1]
     m->last_plan.clear();
     if (m->G > 0) return forward_hlstm(m, T, B, x, h0, c0, y, hT, cT, ws, base, s);
@@ -1533,62 +1604,13 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             prev_has_bf16 = true;
             continue;
         }
-        // ---- recurrence, fp32 dense at small and medium batch, time loop on the device (all directions in one launch):
-        // W_h as matrix-instruction operand fragments in registers, h_t through flagged exchange buffers
-        {
-            bool dense_f32 = !bf16 && B >= 2 && m->plan != LSTM_PLAN_STEPWISE;
-            for (int d = 0; d < Dn; ++d) {
-                const LayerDir& w = m->ld[(size_t)l * Dn + d];
-                dense_f32 = dense_f32 && mode[d] == 0 && !w.wh.compressed && w.wh.dense;
-            }
-            LaunchCut cut;
-            if (dense_f32 && choose_cut(B, Dn, [&](int b, int nd) { return persist_dense_f32_supported(b, H, nd); }, &cut)) {
-                for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
-                    const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
-                    const int nd = Dn / cut.passes, d_lo = pass * nd;
-                    const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
-                    // the exchange buffers start every launch with all stamps clear
-                    HIP_TRY(m, launch_fill_f32((float*)hx, persist_dense_f32_exchange_floats(bn, H, nd), 0.0f, s));
-                    PersistDenseArgs a{};
-                    const float* h0d[2] = {nullptr, nullptr};
-                    for (int d = d_lo; d < d_lo + nd; ++d) {
-                        const LayerDir& w = m->ld[(size_t)l * Dn + d];
-                        const size_t n = (size_t)l * Dn + d;
-                        const size_t so = m->soff(n) * B + (size_t)b_lo * H;
-                        PersistDenseDir& q = a.d[d - d_lo];
-                        q.P = P[d] + (size_t)b_lo * 4 * H;
-                        q.Wh = (const float*)w.wh.dense;
-                        q.c0 = c0 ? c0 + so : nullptr;
-                        q.y = Yout + (size_t)b_lo * y_ld + (size_t)d * H; q.y_ld = y_ld;
-                        q.hT = hT ? hT + so : nullptr;
-                        q.cT = cT ? cT + so : nullptr;
-                        q.reverse = d;
-                        h0d[d - d_lo] = h0 ? h0 + so : nullptr;
-                        if (chunk == 0) {
-                            char cuts[24] = "";
-                            if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, "(batch/%d)", cut.chunks);
-                            std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-f32%s;", l, d,
-                                          proj_runs_dense(w.wx, M, D, bf16) ? "dense" : "csr", cuts);
-                            m->last_plan += tag;
-                        }
-                    }
-                    a.hx = (float*)hx;
-                    if (!mflags_clean) {
-                        HIP_TRY(m, launch_fill_u64((unsigned long long*)mflags, persist_dense_f32_ids_count(), 0ull, s));
-                        mflags_clean = true;
-                        mtag = 0;
-                    }
-                    a.xcc_ids = (unsigned long long*)mflags;
-                    a.tag_base = mtag++;
-                    a.device_scope_only = m->device_scope_only;
-                    a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
-                    a.T = T; a.B = bn; a.Bld = B; a.H = H; a.ndir = nd;
-                    a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : (H <= 512 ? kPollPaceDenseNarrow : kPollPaceDenseWide);
-                    ProfSpan span(m, s, 1);
-                    HIP_TRY(m, launch_persist_dense_f32(a, h0d, m->launch_mode() != 0, s));
-                }
-                continue;
-            }
+        // ---- recurrence, fp32 dense at small and medium batch, time loop on the device (all directions in one launch)
+        if (mode[0] == 0 && mode[Dn - 1] == 0) {
+            bool done = false;
+            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_runs_dense(m->ld[(size_t)l * Dn].wx, M, D, bf16) ? "dense" : "csr",
+                                          ws, base, quad, s, &done);
+            if (rc != LSTM_OK) return rc;
+            if (done) continue;
         }
         // ---- recurrence, small-batch row-compressed, time loop on the device (all directions in one launch): W_h in
         // the quarter-wave form (rows of at most 256 kept entries)
@@ -2172,7 +2194,8 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     } else if (e == hipSuccess) {
         e = upload(&dW, W);
         // as lstm_set_weights stores an input-side matrix: once more in fragment order, for batches of at most 64 rows
-        if (e == hipSuccess && batch <= 64) e = upload(&dWf, to_frag16(W.data(), n, n));
+        if (e == hipSuccess && batch <= 64) e = hipMalloc((void**)&dWf, frag16_floats(n, n) * sizeof(float));
+        if (e == hipSuccess && batch <= 64) e = launch_to_frag16(dW, n, n, false, dWf, s);
     }
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);

@@ -424,3 +424,23 @@ def test_hlstm_auto_format_compresses_up_to_half_kept():
     desc, _ = check_case(inputs.make_case(_hw(86, 1, False, 48, 96, 96, 3, 4), 3), B.LSTM_FMT_AUTO, PAUTO)
     assert "dense" in desc.split("rec=")[1], desc
 
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, G, T, B -- dense H-LSTM cells with the time loop on the device: batch columns four at a time
+    (1, False, 20, 3, 2, 5, 1),          # less than one tile of units, one column of a quad
+    (2, True, 33, 64, 64, 6, 4),         # whole tiles, one k-block per wave in half of the waves
+    (1, True, 24, 130, 65, 5, 7),        # gate width below the hidden width, ragged second quad
+    (1, False, 40, 65, 200, 4, 3),       # ... and above it
+    (1, True, 16, 400, 400, 4, 18),      # groups of one XCD with two quads per pass, the last one ragged
+    (2, False, 32, 640, 640, 3, 16),     # part of the second product's weights in LDS
+    (1, True, 16, 800, 800, 3, 16),      # ... with groups across XCDs
+    (1, False, 16, 1300, 1290, 2, 1),    # twelve k-blocks per wave
+    (1, True, 16, 1100, 1100, 2, 9),     # both directions do not fit one grid: a launch each
+])
+def test_hlstm_dense_persistent(shape):
+    L, bidir, D, H, G, T, Bn = shape
+    for rs in (False, True):
+        case = inputs.make_case(_hw(87, L, bidir, D, H, G, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, G, D)))), k=H + Bn, random_state=rs)
+        desc, _ = check_case(case, DENSE, PAUTO, cooperative=rs)
+        assert "rec=persist-dense-hlstm" in desc, desc

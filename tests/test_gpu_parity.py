@@ -798,3 +798,18 @@ def test_yardsticks_run_and_are_plausible():
         B.lstm_bench_barrier(257, 12)
     with pytest.raises(B.LstmError):
         B.lstm_bench_mfma(7)
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, T, B -- dense fp32 layers, batch columns four at a time: shapes of the planner's table
+    (1, True, 24, 128, 5, 70),       # several groups per XCD, four tiles per workgroup
+    (1, True, 24, 200, 4, 150),      # passes of two and four quads with a ragged last pass
+    (1, False, 24, 513, 4, 9),       # one k beyond a k-block, three quads
+    (1, False, 16, 1900, 2, 12),     # sixteen k-blocks per wave, three passes of one quad
+    (1, True, 24, 850, 3, 16),       # part of the weights in LDS
+])
+def test_dense_f32_quads(shape):
+    L, bidir, D, H, T, Bn = shape
+    case = inputs.make_case(_wl(99, L, bidir, D, H, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, D)))), k=H + Bn, random_state=True)
+    desc, _ = check_case(case, DENSE, PAUTO)
+    assert "rec=persist-dense-f32(" in desc, desc
