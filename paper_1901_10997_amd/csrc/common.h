@@ -17,6 +17,9 @@ struct PackedMat {
     void* dense = nullptr;       // [rows][cols], fp32 or bf16 bits; +0 where the mask is 0
     float* dense_frag16 = nullptr;  // fp32 input-side matrices: `dense` once more in the fragment order of the 16x16x4
                                     // matrix instruction (launch_proj_mfma), for products with at most 64 input rows
+    uint16_t* dense_frag32 = nullptr;  // bf16 recurrent matrices: `dense` in the operand order of the 16x16x32 matrix instruction
+    uint16_t* dense_pad = nullptr;  // bf16 input-side matrices: rows of pad_ld elements, every part of the input (one per
+    int pad_ld = 0;                 // direction of the layer below) padded with zeros to a multiple of 32; may be `dense` itself
     int64_t nnz = 0;             // compressed: kept positions (== popcount of the mask)
     int32_t* row_ptr = nullptr;  // device [rows+1]
     uint16_t* col16 = nullptr;   // device [nnz]  (cols <= 65536)
@@ -245,6 +248,41 @@ struct PersistMfmaArgs {
     int T, B, H, reverse;
 };
 bool persist_mfma_supported(int B, int H);
+// bf16 dense recurrence at any batch from 2 (all directions of a layer per launch)
+struct PersistRowsDir {
+    const float* P;            // [T*B][4H]
+    const uint16_t* Wf;        // W_h in operand order (launch_to_frag32)
+    const float* h0;           // [B][H] or nullptr
+    const float* c0;
+    float* y;                  // h_t fp32 -> y[(t*B + b)*y_ld + j], or nullptr
+    int y_ld;
+    uint16_t* yb;              // h_t bf16 -> yb[(t*B + b)*yb_ld + j], zeros up to yb_width (a multiple of 4), or nullptr
+    int yb_ld, yb_width;
+    float* hT;
+    float* cT;
+    int reverse;
+};
+struct PersistRowsArgs {
+    PersistRowsDir d[2];
+    int T, B, H, ndir;
+    int device_scope_only;     // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
+    int poll_pace;             // pace_poll units in front of a device-wide poll
+    int* timeout_flag;
+    unsigned spin_limit;
+    // set by the launcher
+    int rows, groups, gn, xcd_local;
+    unsigned long long* hx;
+    unsigned long long* xcc_ids;
+};
+bool persist_rows_bf16_supported(int B, int H, int ndir);
+bool persist_rows_bf16_one_pass(int B, int H, int ndir);   // no group of workgroups has more than 16 batch rows
+size_t persist_rows_bf16_exchange_words(int B, int H, int ndir);
+void persist_rows_bf16_describe(int B, int H, int ndir, char* buf, size_t n);
+hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, unsigned long long* words, bool cooperative, hipStream_t s);
+size_t frag32_elements(int rows, int cols);
+hipError_t launch_to_frag32(const uint16_t* W, int rows, int cols, uint16_t* out, hipStream_t s);
+hipError_t launch_pad_rows_bf16(const uint16_t* src, int src_ld, int rows, int parts, int part_cols, int part_pitch, uint16_t* dst,
+                                hipStream_t s);
 // fp32 dense recurrence, LSTM and H-LSTM cells, batch columns four at a time (all directions of a layer per launch)
 struct PersistQuadDir {
     const float* P;            // [T*Bld][4H] (H-LSTM: [4G]): input projection incl. bias

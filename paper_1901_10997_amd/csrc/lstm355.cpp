@@ -149,6 +149,8 @@ static const int kYardstickPaces[] = {0, 6, 10, 12, 16};
 
 static void free_mat(PackedMat& p)
 {
+    if (p.dense_pad && p.dense_pad != p.dense) (void)hipFree(p.dense_pad);
+    if (p.dense_frag32) (void)hipFree(p.dense_frag32);
     if (p.dense) (void)hipFree(p.dense);
     if (p.dense_frag16) (void)hipFree(p.dense_frag16);
     if (p.row_ptr) (void)hipFree(p.row_ptr);
@@ -347,6 +349,30 @@ static int add_frag16(lstm_t* m, PackedMat& p, bool by_gate)
 {
     HIP_TRY(m, hipMalloc((void**)&p.dense_frag16, frag16_floats(p.rows, p.cols) * sizeof(float)));
     HIP_TRY(m, launch_to_frag16((const float*)p.dense, p.rows, p.cols, by_gate, p.dense_frag16, nullptr));
+    HIP_TRY(m, hipStreamSynchronize(nullptr));
+    return LSTM_OK;
+}
+
+// Operand-ordered copy (launch_to_frag32) of a bf16 recurrent matrix already on the device.
+static int add_frag32(lstm_t* m, PackedMat& p)
+{
+    HIP_TRY(m, hipMalloc((void**)&p.dense_frag32, frag32_elements(p.rows, p.cols) * sizeof(uint16_t)));
+    HIP_TRY(m, launch_to_frag32((const uint16_t*)p.dense, p.rows, p.cols, p.dense_frag32, nullptr));
+    HIP_TRY(m, hipStreamSynchronize(nullptr));
+    return LSTM_OK;
+}
+
+// elements of a padded part (a direction of the layer below, or the input) of a bf16 row
+static int pad32(int n) { return (n + 31) & ~31; }
+
+// Zero-padded copy of a bf16 input-side matrix whose rows consist of `parts` parts; the matrix itself where nothing is to pad.
+static int add_padded(lstm_t* m, PackedMat& p, int parts)
+{
+    const int part = p.cols / parts, pitch = pad32(part);
+    p.pad_ld = parts * pitch;
+    if (pitch == part) { p.dense_pad = (uint16_t*)p.dense; return LSTM_OK; }
+    HIP_TRY(m, hipMalloc((void**)&p.dense_pad, (size_t)p.rows * p.pad_ld * sizeof(uint16_t)));
+    HIP_TRY(m, launch_pad_rows_bf16((const uint16_t*)p.dense, p.cols, p.rows, parts, part, pitch, p.dense_pad, nullptr));
     HIP_TRY(m, hipStreamSynchronize(nullptr));
     return LSTM_OK;
 }
@@ -587,7 +613,7 @@ static bool proj_runs_dense(const PackedMat& wx, int M, int D, bool bf16)
 {
     if (!wx.dense) return false;
     if (!wx.compressed) return true;
-    if (!proj_mfma_supported(bf16, D, D)) return false;
+    if (!bf16 && !proj_mfma_supported(false, D, D)) return false;
     if (M >= 256) return true;
     return M <= 64 && wx.dense_frag16 != nullptr && (double)wx.nnz >= 0.04 * (double)wx.rows * (double)wx.cols;
 }
@@ -698,6 +724,11 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     if (rc != LSTM_OK) return rc;
     rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 0, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
+    if (bf16) {
+        rc = add_padded(m, x.wx, layer == 0 ? 1 : m->Dn);
+        if (rc == LSTM_OK && !compressed) rc = add_frag32(m, x.wh);
+        if (rc != LSTM_OK) return rc;
+    }
     std::vector<float> bp(rows);
     for (int rp = 0; rp < rows; ++rp) bp[rp] = b[(rp & 3) * H + (rp >> 2)];
     if (x.bias) { (void)hipFree(x.bias); x.bias = nullptr; }
@@ -800,7 +831,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, total;
 };
 // launches of the dense fp32 persistent recurrence that layer l takes
 static bool quad_cut(const lstm_t* m, int l, int B, LaunchCut* cut)
@@ -840,8 +871,11 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // next layer's projection) and a bf16 copy of h0
     for (int i = 0; i < 2; ++i) {
         w.Yb_off[i] = off;
-        if (m->dtype == LSTM_BF16) off += align256(M * m->Dn * H * sizeof(uint16_t));
+        if (m->dtype == LSTM_BF16) off += align256(M * m->Dn * (size_t)pad32((int)H) * sizeof(uint16_t));
     }
+    // ... and the input's rows padded to whole K blocks of the projection
+    w.xp_off = off;
+    if (m->dtype == LSTM_BF16 && pad32(m->D0) != m->D0) off += align256(M * (size_t)pad32(m->D0) * sizeof(uint16_t));
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
@@ -888,6 +922,11 @@ static Workspace carve(const lstm_t* m, int T, int B)
         if (quad_cut(m, l, B, &cut)) w.qx_words += quad_launch_words(m, l, B, cut) * cut.passes * cut.chunks;
     }
     off += align256(w.qx_words * sizeof(unsigned));
+    // ... and of the bf16 one
+    w.rx_off = off;
+    if (m->dtype == LSTM_BF16 && B >= 2)
+        for (int l = 0; l < m->L; ++l) w.rx_words += persist_rows_bf16_exchange_words(B, m->hid(l), m->Dn);
+    off += align256(w.rx_words * sizeof(unsigned long long));
     w.total = off;
     return w;
 }
@@ -1377,6 +1416,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
     int mflags_H = 0;            // width of the layer the flags were last laid out for
     unsigned mtag = 0;
     QuadRegions quad;
+    unsigned long long* rows_next = nullptr;   // next exchange region of the bf16 recurrence; nullptr: not cleared yet
     bool prev_has_bf16 = false;  // the layer below left a bf16 copy of its hidden sequence in Ybf[(l-1)&1]
     m->last_plan.clear();
     if (m->G > 0) return forward_hlstm(m, T, B, x, h0, c0, y, hT, cT, ws, base, s);
@@ -1415,6 +1455,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         const int D = m->in_dim(l);
         const void* X = (l == 0) ? x : (prev_has_bf16 ? (const void*)Ybf[(l - 1) & 1] : (const void*)Ybuf[(l - 1) & 1]);
         const bool x_is_bf16 = bf16 && (l == 0 || prev_has_bf16);
+        const uint16_t* Xpad = prev_has_bf16 ? Ybf[(l - 1) & 1] : nullptr;   // X with its parts padded (PackedMat::dense_pad)
         prev_has_bf16 = false;
         float* Yout = (l == L - 1) ? y : Ybuf[l & 1];
         const int y_ld = Dn * H;
@@ -1502,7 +1543,8 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             if (mode[d] == 1 || mode[d] == 2) continue;
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
             ProfSpan span(m, s, 0);
-            const bool dense_proj = proj_runs_dense(w.wx, M, D, bf16);
+            // (a padded input is laid out for the dense product only)
+            const bool dense_proj = proj_runs_dense(w.wx, M, D, bf16) || (Xpad && w.wx.pad_ld != D);
             if (!dense_proj && w.wx.ell_val && proj_ell_small_supported(M, 4 * H, D, w.wx.slots)) {
                 // few input rows: lanes over the kept entries of a row (no transpose of X)
                 HIP_TRY(m, launch_proj_ell_small(X, x_is_bf16, D, bf16 && !x_is_bf16, w.wx.ell_val, w.wx.ell_col, w.wx.slots,
@@ -1513,6 +1555,15 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                     xt_ready = true;
                 }
                 HIP_TRY(m, launch_proj_csr(XT, w.wx.row_ptr, w.wx.col16, w.wx.val, w.bias, P[d], M, 4 * H, s));
+            } else if (x_is_bf16 && w.wx.dense_pad) {
+                if (!Xpad) {   // the caller's input
+                    Xpad = (const uint16_t*)x;
+                    if (w.wx.pad_ld != D) {
+                        HIP_TRY(m, launch_pad_rows_bf16((const uint16_t*)x, D, M, 1, D, w.wx.pad_ld, (uint16_t*)(base + ws.xp_off), s));
+                        Xpad = (const uint16_t*)(base + ws.xp_off);
+                    }
+                }
+                HIP_TRY(m, launch_proj_mfma(Xpad, true, w.wx.pad_ld, w.wx.dense_pad, true, w.bias, P[d], M, 4 * H, w.wx.pad_ld, s));
             } else if (proj_mfma_supported(bf16, D, D)) {
                 HIP_TRY(m, launch_proj_mfma(X, x_is_bf16, D, w.wx.dense, bf16, w.bias, P[d], M, 4 * H, D, s, bf16 ? nullptr : w.wx.dense_frag16));
             } else {
@@ -1523,7 +1574,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         bool dense_bf16 = bf16;
         for (int d = 0; d < Dn; ++d) dense_bf16 = dense_bf16 && mode[d] == 0 && !m->ld[(size_t)l * Dn + d].wh.compressed;
         const bool mfma_ok = dense_bf16 && step_mfma_supported(B, H);
-        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H)) {
+        // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 to 2 times (1024 units: batch 64 2.2 against 3.7 us per
+        // step, 128 2.5 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
+        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H) && !persist_rows_bf16_one_pass(B, H, Dn)) {
             // time loop on the device: W_h stays in registers, h_t travels through flagged exchange buffers
             uint16_t* Yb = Ybf[l & 1];
             if (!mflags_clean || mflags_H != H) {
@@ -1559,6 +1612,45 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 m->last_plan += tag;
                 HIP_TRY(m, launch_persist_mfma_bf16(a, h0 ? h0 + m->soff(n) * B : nullptr, m->launch_mode() != 0, s));
             }
+            prev_has_bf16 = true;
+            continue;
+        }
+        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_rows_bf16_supported(B, H, Dn)) {
+            // every other width and batch: groups of workgroups over runs of batch rows, all directions in one launch
+            if (!rows_next) {
+                rows_next = (unsigned long long*)(base + ws.rx_off);
+                HIP_TRY(m, launch_fill_u64(rows_next, ws.rx_words, 0ull, s));
+            }
+            PersistRowsArgs a{};
+            const int pitch = pad32(H);
+            char shape[48];
+            persist_rows_bf16_describe(B, H, Dn, shape, sizeof shape);
+            for (int d = 0; d < Dn; ++d) {
+                const LayerDir& w = m->ld[(size_t)l * Dn + d];
+                const size_t so = m->soff((size_t)l * Dn + d) * B;
+                PersistRowsDir& q = a.d[d];
+                q.P = P[d];
+                q.Wf = w.wh.dense_frag32;
+                q.h0 = h0 ? h0 + so : nullptr;
+                q.c0 = c0 ? c0 + so : nullptr;
+                // the layer above reads the bf16 copy; only the last layer's fp32 sequence leaves the library
+                q.y = (l == L - 1) ? Yout + (size_t)d * H : nullptr;
+                q.y_ld = y_ld;
+                q.yb = (l == L - 1) ? nullptr : Ybf[l & 1] + (size_t)d * pitch;
+                q.yb_ld = Dn * pitch; q.yb_width = pitch;
+                q.hT = hT ? hT + so : nullptr;
+                q.cT = cT ? cT + so : nullptr;
+                q.reverse = d;
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=dense,rec=persist-mfma-rows%s;", l, d, shape);
+                m->last_plan += tag;
+            }
+            a.T = T; a.B = B; a.H = H; a.ndir = Dn;
+            a.device_scope_only = m->device_scope_only;
+            a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
+            a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceQuad;
+            ProfSpan span(m, s, 1);
+            HIP_TRY(m, launch_persist_rows_bf16(a, rows_next, m->launch_mode() != 0, s));
+            rows_next += persist_rows_bf16_exchange_words(B, H, Dn);
             prev_has_bf16 = true;
             continue;
         }

@@ -813,3 +813,23 @@ def test_dense_f32_quads(shape):
     case = inputs.make_case(_wl(99, L, bidir, D, H, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, D)))), k=H + Bn, random_state=True)
     desc, _ = check_case(case, DENSE, PAUTO)
     assert "rec=persist-dense-f32(" in desc, desc
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, T, B -- bf16 dense layers whose width or batch the 32-row tiles do not take
+    (1, False, 5, 3, 4, 2),          # less than a tile of units, input padded from 5 to 32
+    (2, True, 33, 100, 6, 3),        # upper layer reads two padded directions
+    (2, False, 64, 130, 5, 17),      # a row block and one row
+    (1, True, 40, 257, 4, 70),       # groups of one XCD, two row blocks per pass, ragged
+    (2, False, 317, 1197, 3, 20),    # the compacted language model
+    (1, False, 31, 1280, 3, 5),      # five k-blocks per wave
+    (1, True, 24, 1000, 3, 130),     # several passes
+    (1, False, 16, 2047, 2, 9),      # eight k-blocks per wave, last word of the exchange partly beyond the layer
+    (3, True, 20, 36, 7, 33),
+])
+def test_bf16_rows(shape):
+    L, bidir, D, H, T, Bn = shape
+    for rs in (False, True):
+        case = inputs.make_case(_wl(88, L, bidir, D, H, T, Bn, dtype="bf16", a=min(0.2, 1.5 / np.sqrt(max(H, D)))), k=H + Bn, random_state=rs)
+        desc, _ = check_case(case, DENSE, PAUTO, cooperative=rs)
+        assert "persist-mfma-rows" in desc, desc
