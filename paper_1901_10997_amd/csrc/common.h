@@ -18,8 +18,9 @@ struct PackedMat {
     float* dense_frag16 = nullptr;  // fp32 input-side matrices: `dense` once more in the fragment order of the 16x16x4
                                     // matrix instruction (launch_proj_mfma), for products with at most 64 input rows
     uint16_t* dense_frag32 = nullptr;  // bf16 recurrent matrices: `dense` in the operand order of the 16x16x32 matrix instruction
-    uint16_t* dense_pad = nullptr;  // bf16 input-side matrices: rows of pad_ld elements, every part of the input (one per
-    int pad_ld = 0;                 // direction of the layer below) padded with zeros to a multiple of 32; may be `dense` itself
+    void* dense_pad = nullptr;   // input-side matrices for the matrix-core projections: rows of pad_ld elements, zero-padded to a
+    int pad_ld = 0;              // multiple of 4 (fp32), or of 32 in every part of the input, one per direction of the layer
+                                 // below (bf16); `dense` itself where there is nothing to pad
     int64_t nnz = 0;             // compressed: kept positions (== popcount of the mask)
     int32_t* row_ptr = nullptr;  // device [rows+1]
     uint16_t* col16 = nullptr;   // device [nnz]  (cols <= 65536)
@@ -281,8 +282,8 @@ void persist_rows_bf16_describe(int B, int H, int ndir, char* buf, size_t n);
 hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, unsigned long long* words, bool cooperative, hipStream_t s);
 size_t frag32_elements(int rows, int cols);
 hipError_t launch_to_frag32(const uint16_t* W, int rows, int cols, uint16_t* out, hipStream_t s);
-hipError_t launch_pad_rows_bf16(const uint16_t* src, int src_ld, int rows, int parts, int part_cols, int part_pitch, uint16_t* dst,
-                                hipStream_t s);
+hipError_t launch_pad_rows(const void* src, bool bf16, int src_ld, int rows, int parts, int part_cols, int part_pitch, void* dst,
+                           hipStream_t s);
 // fp32 dense recurrence, LSTM and H-LSTM cells, batch columns four at a time (all directions of a layer per launch)
 struct PersistQuadDir {
     const float* P;            // [T*Bld][4H] (H-LSTM: [4G]): input projection incl. bias

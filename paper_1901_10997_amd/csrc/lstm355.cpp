@@ -364,15 +364,17 @@ static int add_frag32(lstm_t* m, PackedMat& p)
 
 // elements of a padded part (a direction of the layer below, or the input) of a bf16 row
 static int pad32(int n) { return (n + 31) & ~31; }
+static int pad4(int n) { return (n + 3) & ~3; }   // ... and of an fp32 row, for its 16-byte loads
 
-// Zero-padded copy of a bf16 input-side matrix whose rows consist of `parts` parts; the matrix itself where nothing is to pad.
-static int add_padded(lstm_t* m, PackedMat& p, int parts)
+// Zero-padded copy of an input-side matrix whose rows consist of `parts` parts (fp32: one); the matrix itself where nothing
+// is to pad.
+static int add_padded(lstm_t* m, PackedMat& p, bool bf16, int parts)
 {
-    const int part = p.cols / parts, pitch = pad32(part);
+    const int part = p.cols / parts, pitch = bf16 ? pad32(part) : pad4(part);
     p.pad_ld = parts * pitch;
-    if (pitch == part) { p.dense_pad = (uint16_t*)p.dense; return LSTM_OK; }
-    HIP_TRY(m, hipMalloc((void**)&p.dense_pad, (size_t)p.rows * p.pad_ld * sizeof(uint16_t)));
-    HIP_TRY(m, launch_pad_rows_bf16((const uint16_t*)p.dense, p.cols, p.rows, parts, part, pitch, p.dense_pad, nullptr));
+    if (pitch == part) { p.dense_pad = p.dense; return LSTM_OK; }
+    HIP_TRY(m, hipMalloc(&p.dense_pad, (size_t)p.rows * p.pad_ld * (bf16 ? sizeof(uint16_t) : sizeof(float))));
+    HIP_TRY(m, launch_pad_rows(p.dense, bf16, p.cols, p.rows, parts, part, pitch, p.dense_pad, nullptr));
     HIP_TRY(m, hipStreamSynchronize(nullptr));
     return LSTM_OK;
 }
@@ -609,11 +611,10 @@ static int create_model(int layers, int input_dim, const int* hidden_dims, const
 // weights (the projection over the kept entries, tried before this is asked, takes the large sparse cases); with at most
 // 64 input rows the stream over the fragment-ordered dense copy beats the lanes-over-entries kernel down to 5 % kept at
 // every width from 256 to 4096 (batch 16: 14.5 against 15.9 us at n = 4096, 4.2 against 7.1 us at n = 1024).
-static bool proj_runs_dense(const PackedMat& wx, int M, int D, bool bf16)
+static bool proj_runs_dense(const PackedMat& wx, int M)
 {
     if (!wx.dense) return false;
     if (!wx.compressed) return true;
-    if (!bf16 && !proj_mfma_supported(false, D, D)) return false;
     if (M >= 256) return true;
     return M <= 64 && wx.dense_frag16 != nullptr && (double)wx.nnz >= 0.04 * (double)wx.rows * (double)wx.cols;
 }
@@ -720,15 +721,13 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     x.set = false;
     const bool bf16 = (m->dtype == LSTM_BF16);
     // W_x is kept in both forms when compressed: large T*B projections run dense on the matrix cores
-    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 0, !bf16 && D % 4 == 0 ? kFragRows : kFragNone, true);
+    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 0, bf16 ? kFragNone : kFragRows, true);
     if (rc != LSTM_OK) return rc;
     rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 0, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
-    if (bf16) {
-        rc = add_padded(m, x.wx, layer == 0 ? 1 : m->Dn);
-        if (rc == LSTM_OK && !compressed) rc = add_frag32(m, x.wh);
-        if (rc != LSTM_OK) return rc;
-    }
+    rc = add_padded(m, x.wx, bf16, bf16 && layer > 0 ? m->Dn : 1);
+    if (rc == LSTM_OK && bf16 && !compressed) rc = add_frag32(m, x.wh);
+    if (rc != LSTM_OK) return rc;
     std::vector<float> bp(rows);
     for (int rp = 0; rp < rows; ++rp) bp[rp] = b[(rp & 3) * H + (rp >> 2)];
     if (x.bias) { (void)hipFree(x.bias); x.bias = nullptr; }
@@ -786,7 +785,8 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     LayerDir& x = m->ld[(size_t)layer * m->Dn + direction];
     x.set = false;
     // hidden layers: 4G rows, packed row 4g+q; kept dense as well for the projection on the matrix cores
-    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 0, D % 4 == 0 ? kFragRows : kFragNone);
+    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 0, kFragRows);
+    if (rc == LSTM_OK) rc = add_padded(m, x.wx, false, 1);
     if (rc != LSTM_OK) return rc;
     rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 12, kFragRows);
     if (rc != LSTM_OK) return rc;
@@ -874,8 +874,16 @@ static Workspace carve(const lstm_t* m, int T, int B)
         if (m->dtype == LSTM_BF16) off += align256(M * m->Dn * (size_t)pad32((int)H) * sizeof(uint16_t));
     }
     // ... and the input's rows padded to whole K blocks of the projection
+    // (fp32: the rows of whichever layer's input is not a multiple of 4 wide)
     w.xp_off = off;
-    if (m->dtype == LSTM_BF16 && pad32(m->D0) != m->D0) off += align256(M * (size_t)pad32(m->D0) * sizeof(uint16_t));
+    size_t xp_bytes = 0;
+    if (m->dtype == LSTM_BF16) {
+        if (pad32(m->D0) != m->D0) xp_bytes = M * (size_t)pad32(m->D0) * sizeof(uint16_t);
+    } else {
+        for (int l = 0; l < m->L; ++l)
+            if (m->in_dim(l) % 4 != 0) xp_bytes = std::max(xp_bytes, M * (size_t)pad4(m->in_dim(l)) * sizeof(float));
+    }
+    off += align256(xp_bytes);
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
@@ -1127,12 +1135,13 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 return fail(m, LSTM_ERR_ARG, "lstm_forward: persistent plan not available for this shape");
         }
         bool xt_ready = false;
+        const float* Xpad = nullptr;   // X with rows padded as PackedMat::dense_pad is
         bool proj_dense[2] = {false, false};
         for (int d = 0; d < Dn; ++d) {
             if (persist[d]) continue;
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
             ProfSpan span(m, s, 0);
-            const bool dense_proj = proj_runs_dense(w.wx, M, D, false);
+            const bool dense_proj = proj_runs_dense(w.wx, M);
             proj_dense[d] = dense_proj;
             if (!dense_proj && w.wx.ell_val && proj_ell_small_supported(M, 4 * G, D, w.wx.slots)) {
                 HIP_TRY(m, launch_proj_ell_small(X, false, D, false, w.wx.ell_val, w.wx.ell_col, w.wx.slots, w.bias, P[d], M,
@@ -1143,10 +1152,15 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                     xt_ready = true;
                 }
                 HIP_TRY(m, launch_proj_csr(XT, w.wx.row_ptr, w.wx.col16, w.wx.val, w.bias, P[d], M, 4 * G, s));
-            } else if (proj_mfma_supported(false, D, D)) {
-                HIP_TRY(m, launch_proj_mfma(X, false, D, w.wx.dense, false, w.bias, P[d], M, 4 * G, D, s, w.wx.dense_frag16));
             } else {
-                HIP_TRY(m, launch_proj_dense(X, false, D, w.wx.dense, false, w.bias, P[d], M, 4 * G, D, s));
+                if (!Xpad) {
+                    Xpad = (const float*)X;
+                    if (w.wx.pad_ld != D) {
+                        HIP_TRY(m, launch_pad_rows(X, false, D, M, 1, D, w.wx.pad_ld, base + ws.xp_off, s));
+                        Xpad = (const float*)(base + ws.xp_off);
+                    }
+                }
+                HIP_TRY(m, launch_proj_mfma(Xpad, false, w.wx.pad_ld, w.wx.dense_pad, false, w.bias, P[d], M, 4 * G, w.wx.pad_ld, s, w.wx.dense_frag16));
             }
         }
         {
@@ -1455,7 +1469,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         const int D = m->in_dim(l);
         const void* X = (l == 0) ? x : (prev_has_bf16 ? (const void*)Ybf[(l - 1) & 1] : (const void*)Ybuf[(l - 1) & 1]);
         const bool x_is_bf16 = bf16 && (l == 0 || prev_has_bf16);
-        const uint16_t* Xpad = prev_has_bf16 ? Ybf[(l - 1) & 1] : nullptr;   // X with its parts padded (PackedMat::dense_pad)
+        const bool prev_bf16 = prev_has_bf16;   // X is the layer below's bf16 copy, its parts padded (PackedMat::dense_pad)
         prev_has_bf16 = false;
         float* Yout = (l == L - 1) ? y : Ybuf[l & 1];
         const int y_ld = Dn * H;
@@ -1525,17 +1539,23 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 proj_q16_used = true;
             }
         }
+        // X as the matrix-core products read it: rows padded as PackedMat::dense_pad is
+        const void* Xpad = prev_bf16 ? X : nullptr;
+        auto padded_x = [&](const PackedMat& wx) -> hipError_t {
+            if (Xpad) return hipSuccess;
+            if (wx.pad_ld == D) { Xpad = X; return hipSuccess; }
+            Xpad = base + ws.xp_off;
+            return launch_pad_rows(X, bf16, D, M, 1, D, wx.pad_ld, base + ws.xp_off, s);
+        };
         if (!pair_done && Dn == 2 && !bf16 && M > 64 && mode[0] != 1 && mode[0] != 2 && mode[1] != 1 && mode[1] != 2) {
             // fp32, both directions dense on the matrix cores: one launch (they read the same X).  (At most 64 input rows:
             // one stream over the fragment-ordered weights per direction, below.)
             const LayerDir& w0 = m->ld[(size_t)l * Dn], & w1 = m->ld[(size_t)l * Dn + 1];
-            auto dense_ok = [&](const LayerDir& w) {
-                return w.wx.dense && (!w.wx.compressed || M >= 256) && proj_mfma_supported(false, D, D);
-            };
-            if (dense_ok(w0) && dense_ok(w1)) {
+            if (proj_runs_dense(w0.wx, M) && proj_runs_dense(w1.wx, M)) {
                 ProfSpan span(m, s, 0);
-                HIP_TRY(m, launch_proj_mfma_f32_pair((const float*)X, D, (const float*)w0.wx.dense, w0.bias, P[0],
-                                                     (const float*)w1.wx.dense, w1.bias, P[1], M, 4 * H, D, s));
+                HIP_TRY(m, padded_x(w0.wx));
+                HIP_TRY(m, launch_proj_mfma_f32_pair((const float*)Xpad, w0.wx.pad_ld, (const float*)w0.wx.dense_pad, w0.bias, P[0],
+                                                     (const float*)w1.wx.dense_pad, w1.bias, P[1], M, 4 * H, w0.wx.pad_ld, s));
                 pair_done = true;
             }
         }
@@ -1544,7 +1564,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
             ProfSpan span(m, s, 0);
             // (a padded input is laid out for the dense product only)
-            const bool dense_proj = proj_runs_dense(w.wx, M, D, bf16) || (Xpad && w.wx.pad_ld != D);
+            const bool dense_proj = proj_runs_dense(w.wx, M) || (prev_bf16 && w.wx.pad_ld != D);
             if (!dense_proj && w.wx.ell_val && proj_ell_small_supported(M, 4 * H, D, w.wx.slots)) {
                 // few input rows: lanes over the kept entries of a row (no transpose of X)
                 HIP_TRY(m, launch_proj_ell_small(X, x_is_bf16, D, bf16 && !x_is_bf16, w.wx.ell_val, w.wx.ell_col, w.wx.slots,
@@ -1555,17 +1575,11 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                     xt_ready = true;
                 }
                 HIP_TRY(m, launch_proj_csr(XT, w.wx.row_ptr, w.wx.col16, w.wx.val, w.bias, P[d], M, 4 * H, s));
-            } else if (x_is_bf16 && w.wx.dense_pad) {
-                if (!Xpad) {   // the caller's input
-                    Xpad = (const uint16_t*)x;
-                    if (w.wx.pad_ld != D) {
-                        HIP_TRY(m, launch_pad_rows_bf16((const uint16_t*)x, D, M, 1, D, w.wx.pad_ld, (uint16_t*)(base + ws.xp_off), s));
-                        Xpad = (const uint16_t*)(base + ws.xp_off);
-                    }
-                }
-                HIP_TRY(m, launch_proj_mfma(Xpad, true, w.wx.pad_ld, w.wx.dense_pad, true, w.bias, P[d], M, 4 * H, w.wx.pad_ld, s));
-            } else if (proj_mfma_supported(bf16, D, D)) {
-                HIP_TRY(m, launch_proj_mfma(X, x_is_bf16, D, w.wx.dense, bf16, w.bias, P[d], M, 4 * H, D, s, bf16 ? nullptr : w.wx.dense_frag16));
+            } else if (x_is_bf16 || !bf16) {
+                HIP_TRY(m, padded_x(w.wx));
+                HIP_TRY(m, launch_proj_mfma(Xpad, bf16, w.wx.pad_ld, w.wx.dense_pad, bf16, w.bias, P[d], M, 4 * H, w.wx.pad_ld, s, w.wx.dense_frag16));
+            } else if (proj_mfma_supported(true, D, D)) {   // fp32 hidden sequence of a bf16 layer below, rounded on load
+                HIP_TRY(m, launch_proj_mfma(X, false, D, w.wx.dense, true, w.bias, P[d], M, 4 * H, D, s));
             } else {
                 HIP_TRY(m, launch_proj_dense(X, x_is_bf16, D, w.wx.dense, bf16, w.bias, P[d], M, 4 * H, D, s));
             }
@@ -1699,7 +1713,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         // ---- recurrence, fp32 dense at small and medium batch, time loop on the device (all directions in one launch)
         if (mode[0] == 0 && mode[Dn - 1] == 0) {
             bool done = false;
-            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_runs_dense(m->ld[(size_t)l * Dn].wx, M, D, bf16) ? "dense" : "csr",
+            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_runs_dense(m->ld[(size_t)l * Dn].wx, M) ? "dense" : "csr",
                                           ws, base, quad, s, &done);
             if (rc != LSTM_OK) return rc;
             if (done) continue;
@@ -1747,7 +1761,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                         char cuts[24] = "";
                         if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, ",batch/%d", cut.chunks);
                         std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-q16%s(s%d,u%d,b%d%s);", l, d,
-                                      proj_q16_used ? "q16" : proj_runs_dense(w.wx, M, D, bf16) ? "dense" : "csr",
+                                      proj_q16_used ? "q16" : proj_runs_dense(w.wx, M) ? "dense" : "csr",
                                       w.wh.q16_ovf_ptr ? "+ovf" : "", q16, upw, bw, cuts);
                         m->last_plan += tag;
                     }
@@ -1780,7 +1794,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 if (c0) HIP_TRY(m, hipMemcpyAsync(cbuf[d], c0 + m->soff(n) * B, (size_t)B * H * sizeof(float), hipMemcpyDeviceToDevice, s));
                 else HIP_TRY(m, launch_fill_f32(cbuf[d], (size_t)B * H, 0.0f, s));
                 std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=stepwise-csr-paired;", l, d,
-                              proj_q16_used ? "q16" : proj_runs_dense(w.wx, M, D, bf16) ? "dense" : "csr");
+                              proj_q16_used ? "q16" : proj_runs_dense(w.wx, M) ? "dense" : "csr");
                 m->last_plan += tag;
             }
             for (int step = 0; step < T; ++step) {
@@ -1822,7 +1836,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             float* cTn = cT ? cT + m->soff(n) * B : nullptr;
             static const char* const names[4] = {"stepwise", "persist_b1", "persist_b1", "persist_b1"};
             std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s%s,rec=%s-%s%s;", l, d, (mode[d] == 1 || mode[d] == 2) ? "fused-" : "",
-                          proj_q16_used ? "q16" : ((mode[d] == 1 || mode[d] == 2) ? !w.wx.compressed : proj_runs_dense(w.wx, M, D, bf16)) ? "dense" : "csr",
+                          proj_q16_used ? "q16" : ((mode[d] == 1 || mode[d] == 2) ? !w.wx.compressed : proj_runs_dense(w.wx, M)) ? "dense" : "csr",
                           names[mode[d]], w.wh.compressed ? "csr" : "dense",
                           (mode[d] == 1 && (w.wx.slots_trim || w.wh.slots_trim)) ? "+ovf" : "");
             m->last_plan += tag;

@@ -409,25 +409,4 @@ hipError_t launch_to_frag32(const uint16_t* W, int rows, int cols, uint16_t* out
     return hipGetLastError();
 }
 
-// bf16 rows [rows][parts * part_cols] -> [rows][parts * part_pitch], each part padded with zeros (src pitch src_ld)
-__global__ __launch_bounds__(256) void pad_rows_bf16_kernel(const uint16_t* __restrict__ src, int src_ld, int rows, int parts, int part_cols,
-                                                            int part_pitch, uint16_t* __restrict__ dst)
-{
-    const int ld = parts * part_pitch;
-    const size_t n = (size_t)rows * ld;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const size_t r = i / ld;
-        const int c = (int)(i - r * ld), p = c / part_pitch, k = c - p * part_pitch;
-        dst[i] = k < part_cols ? src[r * src_ld + (size_t)p * part_cols + k] : (uint16_t)0;
-    }
-}
-hipError_t launch_pad_rows_bf16(const uint16_t* src, int src_ld, int rows, int parts, int part_cols, int part_pitch, uint16_t* dst, hipStream_t s)
-{
-    const size_t n = (size_t)rows * parts * part_pitch;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(pad_rows_bf16_kernel, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, src, src_ld, rows, parts,
-                       part_cols, part_pitch, dst);
-    return hipGetLastError();
-}
-
 }  // namespace l355

@@ -48,6 +48,29 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s)
     return hipGetLastError();
 }
 
+// rows [rows][parts * part_cols] (pitch src_ld) -> [rows][parts * part_pitch], each part padded with zeros
+template <typename E>
+__global__ __launch_bounds__(256) void pad_rows_kernel(const E* __restrict__ src, int src_ld, int rows, int parts, int part_cols,
+                                                       int part_pitch, E* __restrict__ dst)
+{
+    const int ld = parts * part_pitch;
+    for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += gridDim.x * 4)
+        for (int c = threadIdx.x & 63; c < ld; c += 64) {
+            const int p = c / part_pitch, k = c - p * part_pitch;
+            dst[(size_t)r * ld + c] = k < part_cols ? src[(size_t)r * src_ld + p * part_cols + k] : (E)0;
+        }
+}
+hipError_t launch_pad_rows(const void* src, bool bf16, int src_ld, int rows, int parts, int part_cols, int part_pitch, void* dst, hipStream_t s)
+{
+    if (rows <= 0) return hipSuccess;
+    const dim3 grid((unsigned)std::min((rows + 3) / 4, 8192)), block(256);
+    if (bf16)
+        hipLaunchKernelGGL(pad_rows_kernel<uint16_t>, grid, block, 0, s, (const uint16_t*)src, src_ld, rows, parts, part_cols, part_pitch, (uint16_t*)dst);
+    else
+        hipLaunchKernelGGL(pad_rows_kernel<float>, grid, block, 0, s, (const float*)src, src_ld, rows, parts, part_cols, part_pitch, (float*)dst);
+    return hipGetLastError();
+}
+
 int device_num_cus()
 {
     static int cached = 0;

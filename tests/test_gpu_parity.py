@@ -833,3 +833,17 @@ def test_bf16_rows(shape):
         case = inputs.make_case(_wl(88, L, bidir, D, H, T, Bn, dtype="bf16", a=min(0.2, 1.5 / np.sqrt(max(H, D)))), k=H + Bn, random_state=rs)
         desc, _ = check_case(case, DENSE, PAUTO, cooperative=rs)
         assert "persist-mfma-rows" in desc, desc
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, T, B, dtype -- input widths that no 16-byte load divides: rows padded for the matrix-core projections
+    (2, True, 37, 51, 9, 11, "f32"),     # more than 64 input rows, both directions in one launch
+    (2, False, 45, 147, 6, 3, "f32"),    # at most 64
+    (2, False, 581, 33, 1, 1, "f32"),
+    (2, True, 41, 51, 40, 30, "bf16"),   # more than 1024 rows
+    (1, False, 333, 129, 50, 45, "bf16"),
+])
+def test_projection_of_odd_input_widths(shape):
+    L, bidir, D, H, T, Bn, dtype = shape
+    case = inputs.make_case(_wl(93, L, bidir, D, H, T, Bn, dtype=dtype, a=0.08), k=D, random_state=True)
+    check_case(case, DENSE, PAUTO)
