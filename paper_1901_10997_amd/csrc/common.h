@@ -15,8 +15,9 @@ struct PackedMat {
     int rows = 0, cols = 0;
     bool compressed = false;
     void* dense = nullptr;       // [rows][cols], fp32 or bf16 bits; +0 where the mask is 0
-    float* dense_frag16 = nullptr;  // fp32 input-side matrices: `dense` once more in the fragment order of the 16x16x4
-                                    // matrix instruction (launch_proj_mfma), for products with at most 64 input rows
+    float* dense_frag16 = nullptr;  // fp32: the dense matrix in the fragment order of the 16-row matrix instructions: input-side
+                                    // ones for products with at most 64 input rows (launch_proj_mfma), recurrent ones for
+                                    // persist_quad.hip (compressed ones: where LSTM_FMT_AUTO was asked for)
     uint16_t* dense_frag32 = nullptr;  // bf16 recurrent matrices: `dense` in the operand order of the 16x16x32 matrix instruction
     void* dense_pad = nullptr;   // input-side matrices for the matrix-core projections: rows of pad_ld elements, zero-padded to a
     int pad_ld = 0;              // multiple of 4 (fp32), or of 32 in every part of the input, one per direction of the layer
@@ -277,6 +278,7 @@ struct PersistRowsArgs {
 };
 bool persist_rows_bf16_supported(int B, int H, int ndir);
 bool persist_rows_bf16_one_pass(int B, int H, int ndir);   // no group of workgroups has more than 16 batch rows
+double persist_rows_bf16_step_us(int B, int H, int ndir);   // modelled time of a step
 size_t persist_rows_bf16_exchange_words(int B, int H, int ndir);
 void persist_rows_bf16_describe(int B, int H, int ndir, char* buf, size_t n);
 hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, unsigned long long* words, bool cooperative, hipStream_t s);
@@ -311,11 +313,13 @@ struct PersistQuadArgs {
     unsigned long long* xcc_ids;
 };
 bool persist_quad_supported(int B, int H, int G, int ndir);
+double persist_quad_step_us(int B, int H, int G, int ndir);   // modelled time of a step
 size_t persist_quad_exchange_words(int B, int H, int G, int ndir);
 void persist_quad_describe(int B, int H, int G, int ndir, char* buf, size_t n);
 hipError_t launch_persist_quad(PersistQuadArgs& a, unsigned* words, bool cooperative, hipStream_t s);
 size_t frag16_floats(int rows, int cols);
 hipError_t launch_to_frag16(const float* W, int rows, int cols, bool by_gate, float* out, hipStream_t s);
+hipError_t launch_csr_to_frag16(const int* row_ptr, const uint16_t* col, const float* val, int rows, int cols, bool by_gate, float* out, hipStream_t s);
 size_t persist_mfma_exchange_bytes(int B, int H);
 size_t persist_mfma_flag_count(int B, int H);   // 32-bit words of flag storage, XCD id slots included
 size_t persist_mfma_ids_offset(int B, int H);   // word offset of the XCD id slots inside it

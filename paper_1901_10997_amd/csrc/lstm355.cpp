@@ -353,6 +353,15 @@ static int add_frag16(lstm_t* m, PackedMat& p, bool by_gate)
     return LSTM_OK;
 }
 
+// The same copy of a row-compressed matrix.
+static int add_frag16_csr(lstm_t* m, PackedMat& p, bool by_gate)
+{
+    HIP_TRY(m, hipMalloc((void**)&p.dense_frag16, frag16_floats(p.rows, p.cols) * sizeof(float)));
+    HIP_TRY(m, launch_csr_to_frag16(p.row_ptr, p.col16, p.val, p.rows, p.cols, by_gate, p.dense_frag16, nullptr));
+    HIP_TRY(m, hipStreamSynchronize(nullptr));
+    return LSTM_OK;
+}
+
 // Operand-ordered copy (launch_to_frag32) of a bf16 recurrent matrix already on the device.
 static int add_frag32(lstm_t* m, PackedMat& p)
 {
@@ -725,6 +734,11 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     if (rc != LSTM_OK) return rc;
     rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 0, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
+    // LSTM_FMT_AUTO leaves the choice of the recurrence kernel to each call (layer_takes_quads): the dense one needs its copy
+    if (format == LSTM_FMT_AUTO && compressed && !bf16 && persist_quad_supported(1, H, 0, 1)) {
+        rc = add_frag16_csr(m, x.wh, false);
+        if (rc != LSTM_OK) return rc;
+    }
     rc = add_padded(m, x.wx, bf16, bf16 && layer > 0 ? m->Dn : 1);
     if (rc == LSTM_OK && bf16 && !compressed) rc = add_frag32(m, x.wh);
     if (rc != LSTM_OK) return rc;
@@ -792,6 +806,10 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     if (rc != LSTM_OK) return rc;
     // gate outputs: 4H rows, packed row 4j+q, columns = hidden units of the row's own gate
     rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 12, kFragByGate);
+    if (rc == LSTM_OK && format == LSTM_FMT_AUTO && compressed && persist_quad_supported(1, H, G, 1)) {   // as in lstm_set_weights
+        rc = add_frag16_csr(m, x.wh, false);
+        if (rc == LSTM_OK) rc = add_frag16_csr(m, x.w2, true);
+    }
     if (rc != LSTM_OK) return rc;
     std::vector<float> bp1((size_t)4 * G), bp2((size_t)4 * H);
     for (int rp = 0; rp < 4 * G; ++rp) bp1[rp] = b1[(size_t)(rp & 3) * G + (rp >> 2)];
@@ -837,8 +855,7 @@ struct Workspace {
 static bool quad_cut(const lstm_t* m, int l, int B, LaunchCut* cut)
 {
     const int H = m->hid(l), G = m->ghid(l);
-    return m->dtype == LSTM_F32 && (B >= 2 || m->G > 0) &&
-           choose_cut(B, m->Dn, [&](int b, int nd) { return persist_quad_supported(b, H, G, nd); }, cut, 1);
+    return m->dtype == LSTM_F32 && choose_cut(B, m->Dn, [&](int b, int nd) { return persist_quad_supported(b, H, G, nd); }, cut, 1);
 }
 // exchange words per launch of that layer (the longest run of batch columns)
 static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
@@ -932,7 +949,7 @@ static Workspace carve(const lstm_t* m, int T, int B)
     off += align256(w.qx_words * sizeof(unsigned));
     // ... and of the bf16 one
     w.rx_off = off;
-    if (m->dtype == LSTM_BF16 && B >= 2)
+    if (m->dtype == LSTM_BF16)
         for (int l = 0; l < m->L; ++l) w.rx_words += persist_rows_bf16_exchange_words(B, m->hid(l), m->Dn);
     off += align256(w.rx_words * sizeof(unsigned long long));
     w.total = off;
@@ -1043,19 +1060,91 @@ struct QuadRegions {
     unsigned* next = nullptr;   // the next launch's region; nullptr: the regions have not been cleared yet
 };
 
-// Recurrence of layer l with its dense fp32 matrices (W_h; H-LSTM: W1h and W2), time loop on the device.  *done is left
-// false when some direction holds another form or no shape takes the layer.
-static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const float* h0, const float* c0, float* Yout, int y_ld,
-                          float* hT, float* cT, const char* proj, const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s, bool* done)
+// Batch-1 kernels of one direction with all of its matrices row-compressed.
+static int b1_slots(const PackedMat& p) { return p.slots_trim > 0 ? p.slots_trim : p.slots; }   // held in registers: the trimmed slices where they exist
+static bool sparse_b1_ok(const LayerDir& w, int H, int D_in, int nl)
 {
-    const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l), R = 4 * (G > 0 ? G : H);
-    if (m->plan == LSTM_PLAN_STEPWISE) return LSTM_OK;
+    return w.wx.compressed && w.wh.compressed && (w.wx.ell_val || w.wx.slots_trim) && (w.wh.ell_val || w.wh.slots_trim) &&
+           persist_b1_sparse_supported(H, D_in, b1_slots(w.wx), b1_slots(w.wh), nl);
+}
+static bool hlstm_b1_ok(const LayerDir& w, int H, int G, int D)
+{
+    return w.wx.compressed && w.wh.compressed && w.w2.compressed && w.wx.ell_val && w.wh.ell_val && w.w2.ell_val &&
+           persist_b1_hlstm_supported(H, G, D, w.wx.slots, w.wh.slots, w.w2.slots);
+}
+
+// Step times (microseconds, MI355X) of the recurrences that compete with the dense ones of persist_quad.hip and
+// persist_rows_bf16.hip, rough fits to measured steps at 64 to 2000 units, batch 1 to 64 and 5 to 40 % kept: within 10 % for nine
+// of ten.
+static double b1_dense_step_us(int H) { return H <= 448 ? 0.8 + 0.0017 * H : 1.5 + 0.0004 * H; }
+constexpr double kB1CsrStepUs = 1.8, kB1HlstmStepUs = 2.9;   // latency of the exchanges: nearly the same at every width and density
+constexpr double kSeparateProjUs = 20.0;   // launches and gaps a fused batch-1 kernel does not have
+constexpr double kDenseSetupUs = 10.0;     // dense weights to read before the first step; short sequences stay where they are
+static double batched_csr_step_us(const lstm_t* m, int l, int B)
+{
+    const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
+    int slots = 0, upw = 0, bw = 0, ug = 0, bg = 0;
     for (int d = 0; d < Dn; ++d) {
         const LayerDir& w = m->ld[(size_t)l * Dn + d];
-        if (w.wh.compressed || !w.wh.dense_frag16 || (G > 0 && (w.w2.compressed || !w.w2.dense_frag16))) return LSTM_OK;
+        if (w.wh.q16_slots <= 0 || (G > 0 && w.w2.q16_slots <= 0)) return 1e9;   // one or two launches per step
+        slots = std::max(slots, std::max(w.wh.q16_slots, G > 0 ? w.w2.q16_slots : 0));
     }
     LaunchCut cut;
-    if (!quad_cut(m, l, B, &cut)) return LSTM_OK;
+    int nd_used = 0;
+    if (!choose_cut(B, Dn, [&](int b, int nd) {
+            nd_used = nd;
+            return G > 0 ? persist_batched_h_plan(b, H, G, slots, nd, &upw, &bw, &ug, &bg) : persist_batched_q16_plan(b, H, slots, nd, &upw, &bw, &ug, &bg);
+        }, &cut))
+        return 1e9;
+    const bool local = ug <= 64 && ((nd_used * bg + 7) / 8) * ug <= device_num_cus() / 8;
+    const double gathers = 0.01 * slots * upw * bw, words = 0.001 * H * bw;
+    return cut.passes * cut.chunks * (G > 0 ? (local ? 2.4 : 5.3) + 1.36 * gathers + 0.44 * words : (local ? 1.34 : 1.83) + 0.76 * gathers + 0.10 * words);
+}
+
+// Does the dense fp32 recurrence with the time loop on the device take layer l?  It multiplies the zeros of a mask too, but a
+// step of a narrow layer is the exchange's latency and not the products, its own is the shortest (one wait per step, both
+// directions in one launch), and it holds rows of any length: 64 to 256 units at 5 to 24 % kept 1.15 to 2 times faster than the
+// row-compressed kernels, from about 450 slower (H-LSTM 1.1 to 1.6 times up to 256), and 2 to 6 times where rows are too long
+// for those and each step would be a launch.  Only where LSTM_FMT_AUTO left the choice open (the copy exists) and by 5 % of the
+// modelled time, as neither model is better than that.
+static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
+{
+    const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
+    if (m->plan == LSTM_PLAN_STEPWISE) return false;
+    int csr = 0;
+    for (int d = 0; d < Dn; ++d) {
+        const LayerDir& w = m->ld[(size_t)l * Dn + d];
+        if (!w.wh.dense_frag16 || (G > 0 && !w.w2.dense_frag16)) return false;
+        csr += w.wh.compressed;
+    }
+    LaunchCut cut;
+    if (!quad_cut(m, l, B, &cut)) return false;
+    if (B > 1 && csr < Dn) return true;
+    if (m->plan == LSTM_PLAN_PERSISTENT && (G == 0 || csr > 0)) return false;
+    double us = T * cut.passes * cut.chunks * persist_quad_step_us((B + cut.chunks - 1) / cut.chunks, H, G, Dn / cut.passes), other = 0;
+    if (B > 1) {
+        us += kDenseSetupUs;
+        other = T * batched_csr_step_us(m, l, B);
+    } else {
+        if (m->waves_per_group > 0) return csr == 0 && G > 0;   // a launch shape the caller set for the batch-1 kernels
+        us += kSeparateProjUs;
+        for (int d = 0; d < Dn; ++d) {
+            const LayerDir& w = m->ld[(size_t)l * Dn + d];
+            if (G > 0) other += hlstm_b1_ok(w, H, G, m->in_dim(l)) ? T * kB1HlstmStepUs : 1e9;
+            else if (w.wh.compressed) other += sparse_b1_ok(w, H, m->in_dim(l), 1) ? T * kB1CsrStepUs : 1e9;
+            else other += persist_b1_dense_supported(H) ? T * b1_dense_step_us(H) : 1e9;
+        }
+    }
+    return us < 0.95 * other;
+}
+
+// Recurrence of layer l with its dense fp32 matrices (W_h; H-LSTM: W1h and W2), time loop on the device.
+static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const float* h0, const float* c0, float* Yout, int y_ld,
+                          float* hT, float* cT, const char* proj, const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s)
+{
+    const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l), R = 4 * (G > 0 ? G : H);
+    LaunchCut cut;
+    quad_cut(m, l, B, &cut);
     if (!reg.next) {
         reg.next = (unsigned*)(base + ws.qx_off);
         HIP_TRY(m, launch_fill_u64((unsigned long long*)reg.next, align256(ws.qx_words * 4) / 8, 0ull, s));
@@ -1096,7 +1185,6 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
         HIP_TRY(m, launch_persist_quad(a, reg.next, m->launch_mode() != 0, s));
         reg.next += words;
     }
-    *done = true;
     return LSTM_OK;
 }
 
@@ -1125,12 +1213,11 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
         float* Yout = (l == L - 1) ? y : Ybuf[l & 1];
         const int y_ld = Dn * H;
         // batch 1 with all three matrices row-compressed and small enough for registers: time loop on the device
+        const bool quads = layer_takes_quads(m, l, T, B);
         bool persist[2] = {false, false};
         for (int d = 0; d < Dn; ++d) {
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
-            persist[d] = B == 1 && m->plan != LSTM_PLAN_STEPWISE && w.wx.compressed && w.wh.compressed && w.w2.compressed &&
-                         w.wx.ell_val && w.wh.ell_val && w.w2.ell_val &&
-                         persist_b1_hlstm_supported(H, G, D, w.wx.slots, w.wh.slots, w.w2.slots);
+            persist[d] = B == 1 && m->plan != LSTM_PLAN_STEPWISE && !quads && hlstm_b1_ok(w, H, G, D);
             if (m->plan == LSTM_PLAN_PERSISTENT && B == 1 && !persist[d])
                 return fail(m, LSTM_ERR_ARG, "lstm_forward: persistent plan not available for this shape");
         }
@@ -1163,11 +1250,10 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 HIP_TRY(m, launch_proj_mfma(Xpad, false, w.wx.pad_ld, w.wx.dense_pad, false, w.bias, P[d], M, 4 * G, w.wx.pad_ld, s, w.wx.dense_frag16));
             }
         }
-        {
-            bool done = false;
-            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_dense[0] ? "dense" : "csr", ws, base, quad, s, &done);
+        if (quads) {
+            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_dense[0] ? "dense" : "csr", ws, base, quad, s);
             if (rc != LSTM_OK) return rc;
-            if (done) continue;
+            continue;
         }
         // small batch, W1h and W2 of every direction row-compressed with rows of at most 256 kept entries (the
         // quarter-wave form): one launch per layer with the time loop on the device
@@ -1437,12 +1523,6 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
 
     unsigned tag0 = 0;   // base of the tags the next batch-1 launch uses
     auto take_tags = [&](int T_) -> int { return take_b1_tags(m, (unsigned)T_, m->xchg_slots, s, &tag0); };
-    // slot count the batch-1 kernel will hold in registers: the trimmed slices where they exist
-    auto b1_slots = [](const PackedMat& p) { return p.slots_trim > 0 ? p.slots_trim : p.slots; };
-    auto sparse_ok = [&](const LayerDir& w, int H, int D_in, int nl) {
-        return w.wx.compressed && w.wh.compressed && (w.wx.ell_val || w.wx.slots_trim) && (w.wh.ell_val || w.wh.slots_trim) &&
-               persist_b1_sparse_supported(H, D_in, b1_slots(w.wx), b1_slots(w.wh), nl);
-    };
     auto fill_sparse_layer = [&](SparseLayerArgs& a, const LayerDir& w, size_t n, float* yout, int y_ld) {
         if (w.wx.slots_trim > 0) {
             a.ell_val_x = w.wx.ell_val_trim; a.ell_col_x = w.wx.ell_col_trim; a.slots_x = w.wx.slots_trim;
@@ -1477,8 +1557,8 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         char tag[128];
 
         // ---- batch 1, row-compressed, two stacked unidirectional layers in one launch (diagonal wavefront)
-        if (try_persist && Dn == 1 && l + 1 < L && m->hid(l + 1) == H && sparse_ok(m->ld[l], H, D, 2) &&
-            sparse_ok(m->ld[l + 1], H, D, 2)) {
+        if (try_persist && Dn == 1 && l + 1 < L && m->hid(l + 1) == H && sparse_b1_ok(m->ld[l], H, D, 2) &&
+            sparse_b1_ok(m->ld[l + 1], H, D, 2)) {
             ProfSpan span(m, s, 1);
             int rc = take_tags(T);
             if (rc != LSTM_OK) return rc;
@@ -1498,11 +1578,17 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         }
 
         // ---- decide per direction
+        const bool quads = layer_takes_quads(m, l, T, B);
+        // bf16, batch 1, two dense directions: the batch-1 kernel takes them one after the other, the row groups' both at once
+        const bool rows_b1 = bf16 && try_persist && Dn == 2 && m->plan == LSTM_PLAN_AUTO && m->waves_per_group == 0 &&
+                             !m->ld[(size_t)l * Dn].wh.compressed && !m->ld[(size_t)l * Dn + 1].wh.compressed &&
+                             persist_rows_bf16_supported(1, H, 2) && persist_b1_dense_supported(H) &&
+                             T * persist_rows_bf16_step_us(1, H, 2) + kSeparateProjUs < 0.95 * 2 * T * b1_dense_step_us(H);
         int mode[2] = {0, 0};  // 0 stepwise, 1 persistent sparse (fused), 2 persistent dense fused, 3 persistent dense + projection kernel
         for (int d = 0; d < Dn; ++d) {
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
-            if (try_persist) {
-                if (w.wh.compressed) mode[d] = sparse_ok(w, H, D, 1) ? 1 : 0;
+            if (try_persist && !quads && !rows_b1) {
+                if (w.wh.compressed) mode[d] = sparse_b1_ok(w, H, D, 1) ? 1 : 0;
                 else if (persist_b1_dense_fusable(H, D)) mode[d] = 2;
                 else if (persist_b1_dense_supported(H)) mode[d] = 3;
             }
@@ -1710,13 +1796,12 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             prev_has_bf16 = true;
             continue;
         }
-        // ---- recurrence, fp32 dense at small and medium batch, time loop on the device (all directions in one launch)
-        if (mode[0] == 0 && mode[Dn - 1] == 0) {
-            bool done = false;
-            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_runs_dense(m->ld[(size_t)l * Dn].wx, M) ? "dense" : "csr",
-                                          ws, base, quad, s, &done);
+        // ---- recurrence, fp32 over dense copies, time loop on the device (all directions in one launch)
+        if (quads) {
+            const char* proj = proj_q16_used ? "q16" : proj_runs_dense(m->ld[(size_t)l * Dn].wx, M) ? "dense" : "csr";
+            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj, ws, base, quad, s);
             if (rc != LSTM_OK) return rc;
-            if (done) continue;
+            continue;
         }
         // ---- recurrence, small-batch row-compressed, time loop on the device (all directions in one launch): W_h in
         // the quarter-wave form (rows of at most 256 kept entries)

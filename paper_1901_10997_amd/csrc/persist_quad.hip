@@ -450,6 +450,7 @@ constexpr int kQuadShapeCount = (int)(sizeof(kQuadShapes) / sizeof(kQuadShapes[0
 
 struct QuadPlan {
     const QuadShape* shape = nullptr;
+    double us = 1e30;   // modelled step time
     int mq = 0, groups = 0, gn = 0, xcd_local = 0;
     size_t lds = 0;
 };
@@ -485,7 +486,7 @@ QuadPlan quad_plan(int B, int H, int G, int ndir)
             const double pass = stages * ((local ? 0.42 : 0.63) + 0.0097 * sh.qp * sh.nt * sh.kb * 4 + 0.045 * sh.qp * sh.nt) + 0.033 * sh.qp * words_kb;
             const double us = passes * pass + (passes == 1 ? stages * (local ? 0.29 : 0.59) : 0.0);
             if (us < best_us) {
-                best_us = us;
+                best_us = best.us = us;
                 best.shape = &sh;
                 best.mq = mq; best.groups = groups; best.gn = gn; best.xcd_local = local; best.lds = lds;
             }
@@ -504,6 +505,7 @@ bool persist_quad_supported(int B, int H, int G, int ndir)
 // exchange words of one launch: h, then u, then (8-byte) XCD id slots of the groups
 static size_t quad_h_words(int B, int H, int ndir) { return (size_t)ndir * ((B + 3) / 4) * 8 * ((H + 15) / 16) * 16; }
 static size_t quad_u_words(int B, int G, int ndir) { return (size_t)ndir * ((B + 3) / 4) * ((G + 15) / 16) * 256; }
+double persist_quad_step_us(int B, int H, int G, int ndir) { return quad_plan(B, H, G, ndir).us; }
 size_t persist_quad_exchange_words(int B, int H, int G, int ndir)
 {
     return quad_h_words(B, H, ndir) + quad_u_words(B, G, ndir) + (size_t)ndir * ((B + 3) / 4) * 64 * 2;
@@ -569,6 +571,26 @@ hipError_t launch_to_frag16(const float* W, int rows, int cols, bool by_gate, fl
 {
     const size_t g = (frag16_floats(rows, cols) / 4 + 255) / 256;
     hipLaunchKernelGGL(to_frag16_kernel, dim3((unsigned)std::min<size_t>(g, 8192)), dim3(256), 0, s, W, rows, cols, by_gate ? 1 : 0, (float4*)out);
+    return hipGetLastError();
+}
+
+// The same copy of a masked matrix from its row-compressed form: out is zero, a wave per row puts the kept entries in place.
+__global__ __launch_bounds__(256) void csr_to_frag16_kernel(const int* __restrict__ row_ptr, const uint16_t* __restrict__ col, const float* __restrict__ val,
+                                                            int rows, int KB, int by_gate, float* __restrict__ out)
+{
+    const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (n >= rows) return;
+    const int r = n & 15, l = by_gate ? (r >> 2) | ((r & 3) << 2) : r;
+    for (int e = row_ptr[n] + (threadIdx.x & 63); e < row_ptr[n + 1]; e += 64) {
+        const int k = col[e];
+        out[(((size_t)(n >> 4) * KB + (k >> 4)) * 64 + 16 * ((k & 15) >> 2) + l) * 4 + (k & 3)] = val[e];
+    }
+}
+hipError_t launch_csr_to_frag16(const int* row_ptr, const uint16_t* col, const float* val, int rows, int cols, bool by_gate, float* out, hipStream_t s)
+{
+    const hipError_t e = launch_fill_f32(out, frag16_floats(rows, cols), 0.0f, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(csr_to_frag16_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, row_ptr, col, val, rows, (cols + 15) / 16, by_gate ? 1 : 0, out);
     return hipGetLastError();
 }
 

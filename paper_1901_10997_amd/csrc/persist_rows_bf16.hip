@@ -296,6 +296,7 @@ constexpr int kRowsShapeCount = (int)(sizeof(kRowsShapes) / sizeof(kRowsShapes[0
 
 struct RowsPlan {
     const RowsShape* shape = nullptr;
+    double us = 1e30;   // modelled step time
     int rows = 0, groups = 0, gn = 0, xcd_local = 0;
     size_t lds = 0;
 };
@@ -327,7 +328,7 @@ RowsPlan rows_plan(int B, int H, int ndir)
             const double pass = (local ? 0.95 : 1.1) + 0.027 * sh.nt * sh.kb + (local ? 0.02 : 0.04) * sh.nt + (local ? 0.016 : 0.01) * h_kb;
             const double us = passes * pass + (passes == 1 ? (local ? 0.32 : 0.56) : 0.0);
             if (us < best_us) {
-                best_us = us;
+                best_us = best.us = us;
                 best.shape = &sh;
                 best.rows = rows; best.groups = groups; best.gn = gn; best.xcd_local = local; best.lds = lds;
             }
@@ -340,8 +341,9 @@ RowsPlan rows_plan(int B, int H, int ndir)
 bool persist_rows_bf16_one_pass(int B, int H, int ndir) { return persist_rows_bf16_supported(B, H, ndir) && rows_plan(B, H, ndir).rows <= 16; }
 bool persist_rows_bf16_supported(int B, int H, int ndir)
 {
-    return B >= 2 && H >= 1 && ndir >= 1 && ndir <= 2 && rows_plan(B, H, ndir).shape != nullptr;
+    return B >= 1 && H >= 1 && ndir >= 1 && ndir <= 2 && rows_plan(B, H, ndir).shape != nullptr;
 }
+double persist_rows_bf16_step_us(int B, int H, int ndir) { return rows_plan(B, H, ndir).us; }
 // 8-byte words of one launch: h, then the XCD id slots of the groups
 static size_t rows_h_words(const RowsPlan& p, int H, int ndir) { return (size_t)ndir * p.groups * 2 * ((H + 31) / 32) * 8 * p.rows; }
 size_t persist_rows_bf16_exchange_words(int B, int H, int ndir)

@@ -444,3 +444,19 @@ def test_hlstm_dense_persistent(shape):
         case = inputs.make_case(_hw(87, L, bidir, D, H, G, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, G, D)))), k=H + Bn, random_state=rs)
         desc, _ = check_case(case, DENSE, PAUTO, cooperative=rs)
         assert "rec=persist-dense-hlstm" in desc, desc
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, G, T, B, keep -- masked H-LSTM layers the planner gives to the dense recurrence
+    (2, True, 24, 67, 50, 40, 6, 0.2),
+    (1, False, 40, 100, 130, 40, 1, 0.1),
+    (1, True, 33, 131, 131, 30, 1, 0.15),
+    (1, False, 16, 1300, 1290, 2, 3, 0.4),
+])
+def test_hlstm_masked_in_the_dense_recurrence(shape):
+    L, bidir, D, H, G, T, Bn, keep = shape
+    case = inputs.make_case(_hw(88, L, bidir, D, H, G, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, G))), keep=keep), k=H, random_state=True)
+    desc, _ = check_case(case, AUTO, PAUTO)
+    assert desc.count("rec=persist-dense-hlstm(") == L * (2 if bidir else 1), desc
+    desc, _ = check_case(case, CSR, PAUTO)
+    assert "persist-dense" not in desc, desc

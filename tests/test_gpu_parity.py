@@ -847,3 +847,24 @@ def test_projection_of_odd_input_widths(shape):
     L, bidir, D, H, T, Bn, dtype = shape
     case = inputs.make_case(_wl(93, L, bidir, D, H, T, Bn, dtype=dtype, a=0.08), k=D, random_state=True)
     check_case(case, DENSE, PAUTO)
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, T, B, dtype, keep, plan -- layers the planner gives to the dense recurrences of persist_quad.hip and
+    # persist_rows_bf16.hip: narrow masked ones, rows too long for the row-compressed kernels, two dense directions at batch 1
+    (2, True, 24, 67, 40, 6, "f32", 0.2, "persist-dense-f32("),
+    (1, False, 40, 150, 40, 1, "f32", 0.1, "persist-dense-f32("),
+    (1, True, 33, 131, 30, 1, "f32", 0.15, "persist-dense-f32("),
+    (1, False, 16, 1900, 3, 2, "f32", 0.24, "persist-dense-f32("),
+    (1, True, 24, 130, 30, 1, "f32", None, "persist-dense-f32("),
+    (2, True, 24, 515, 30, 1, "bf16", None, "persist-mfma-rows("),
+    (1, False, 24, 800, 4, 6, "f32", 0.1, "persist_batched-q16"),    # wide and sparse: the row-compressed kernel
+])
+def test_planner_between_dense_and_compressed_recurrence(shape):
+    L, bidir, D, H, T, Bn, dtype, keep, plan = shape
+    case = inputs.make_case(_wl(94, L, bidir, D, H, T, Bn, dtype=dtype, a=min(0.3, 1.5 / np.sqrt(H)), keep=keep), k=H, random_state=True)
+    desc, _ = check_case(case, AUTO, PAUTO)
+    assert desc.count("rec=" + plan) == L * (2 if bidir else 1), desc
+    if keep is not None:      # a format the caller names is the one that runs
+        desc, _ = check_case(case, CSR, PAUTO)
+        assert "persist-dense" not in desc, desc
