@@ -19,7 +19,7 @@
 // so that one exchange, one reduction and one round of gates serve all of them.
 //
 // Exchange: values carry their own readiness, as 32-bit words with one bit of the step count in a bit the value leaves
-// free: |h| <= 1, so bit 30; u >= 0, so the sign.  h has two buffers per quad, step tag g (2 for the first step) in buffer
+// free: |h| <= 1, so bit 30 (a NaN gets it back on reading, see unstamped); u >= 0, so the sign.  h has two buffers per quad, step tag g (2 for the first step) in buffer
 // g & 1 with stamp (g >> 1) & 1; u one, stamped (s + 1) & 1: it is rewritten only after every workgroup has published
 // an h that needed all of it.  All buffers are zero at launch.  A wave loads its own K slice straight into operand
 // registers and repeats the load until every word is stamped (bounded).  Layouts of a quad, in the order of a wave's lanes (four columns
@@ -58,6 +58,13 @@ __device__ __forceinline__ float quad_sum(const f32x4& a)
     const float k13 = __uint_as_float(s13[0]) + __uint_as_float(s13[1]);
     const auto sr = __builtin_amdgcn_permlane16_swap(__float_as_uint(k02), __float_as_uint(k13), false, false);
     return __uint_as_float(sr[0]) + __uint_as_float(sr[1]);
+}
+// A published word without its stamp.  A NaN has bit 30 set itself and |h| <= 1 else: without that bit a (quiet) NaN is a pattern
+// of at least 1.5, from which the addition carries into bit 30 again.  strip: kHBit, or 0 to take the word as it is.
+__device__ __forceinline__ float unstamped(unsigned v, unsigned strip)
+{
+    const unsigned carried = (v & (kHBit - 1u)) + 0x00400000u;
+    return __uint_as_float((v & ~strip) | (carried & strip));
 }
 // Counts a failed round of a bounded wait; true when the wait is to be given up.
 __device__ __forceinline__ bool give_up(unsigned& spins, unsigned limit, int* flag)
@@ -272,7 +279,7 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
                 pace_poll(a.poll_pace);
                 unsigned spins = 0;
                 for (;;) {
-                    bool ok = true;
+                    unsigned differ = 0;
                     // a block beyond K reads the last one again (its weights are zero)
 #pragma unroll
                     for (int c = 0; c < QP; ++c)
@@ -284,8 +291,8 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
                     for (int c = 0; c < QP; ++c)
 #pragma unroll
                         for (int q = 0; q < KB; ++q)
-                            ok = ok && (((fr[c][q] ^ want) & kHBit) == 0u || (tail_dead && kb0 + q >= KBh - 1));
-                    if (!__builtin_amdgcn_ballot_w64(!ok) || give_up(spins, a.spin_limit, a.timeout_flag)) break;
+                            differ |= tail_dead && kb0 + q >= KBh - 1 ? 0u : fr[c][q] ^ want;
+                    if (!__builtin_amdgcn_ballot_w64((differ & kHBit) != 0u) || give_up(spins, a.spin_limit, a.timeout_flag)) break;
                 }
             } else {
 #pragma unroll
@@ -309,13 +316,13 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
 #pragma unroll
                 for (int n = 0; n < NT; ++n) acc[c][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
             if (s > 0 || h0) {
-                const unsigned strip = s > 0 ? ~kHBit : ~0u;
+                const unsigned strip = s > 0 ? kHBit : 0u;               // h0 is taken as it is
 #pragma unroll
                 for (int q = 0; q < KB; ++q)
                     if (q < KB - 1 || all_kb) {
                         float av[QP];
 #pragma unroll
-                        for (int c = 0; c < QP; ++c) av[c] = __uint_as_float(fr[c][q] & strip);
+                        for (int c = 0; c < QP; ++c) av[c] = unstamped(fr[c][q], strip);
                         float4 w[NT];
 #pragma unroll
                         for (int n = 0; n < NT; ++n) w[n] = n < N1 ? w1[n < N1 ? n : 0][q] : wl[((n - N1) * KB + q) * 64];

@@ -13,7 +13,7 @@
 // so the batch is dealt over as many groups as fit, which makes each group's h, the volume every workgroup reads per step,
 // small.
 //
-// Exchange: |h| <= 1 leaves bit 14 of a bf16 pattern free; it carries one bit of the step count (step tag g, 2 for the first
+// Exchange: |h| <= 1 leaves bit 14 of a bf16 pattern free (a NaN gets it back on reading, see unstamped); it carries one bit of the step count (step tag g, 2 for the first
 // step, in buffer g & 1 with stamp (g >> 1) & 1; both buffers zero at launch).  h lies in operand order, [k / 8][row][8], so a
 // wave loads 16 bytes per lane straight into operand registers and repeats the load until every live element is stamped
 // (bounded); a tile publishes the 4 units of a row as one 8-byte word.  A workgroup writes h_t after all of its waves have
@@ -41,6 +41,17 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_mov_f(float v)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+// Four published values without their stamps.  A NaN has bit 14 set itself and |h| <= 1 else: without that bit a (quiet) NaN is
+// a pattern of at least 0x3FC0 (1.5), from which the addition carries into bit 14 again.  The halves apart: 32-bit operations.
+__device__ __forceinline__ unsigned unstamped_pair(unsigned v)
+{
+    const unsigned carried = (v & 0x3FFF3FFFu) + 0x00400040u;
+    return (v & 0xBFFFBFFFu) | (carried & 0x40004000u);
+}
+__device__ __forceinline__ unsigned long long unstamped(unsigned long long v)
+{
+    return (unsigned long long)unstamped_pair((unsigned)(v >> 32)) << 32 | unstamped_pair((unsigned)v);
 }
 // Lanes 4j..4j+3 hold gates 0..3 of a unit, v[b] for batch rows b = 0..3: afterwards lane 4j + q holds in v[g] gate g of row q.
 __device__ __forceinline__ void quad_transpose(float (&v)[4], int lane)
@@ -172,14 +183,13 @@ __global__ __launch_bounds__(kRTH) void persist_rows_bf16_kernel(PersistRowsArgs
                         fr[q].x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         fr[q].y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
-                    bool ok = true;
+                    unsigned long long differ = 0;
 #pragma unroll
                     for (int q = 0; q < KB; ++q) {
                         const bool tail = kb0 + q >= KBt - 1;                    // wave-uniform
-                        ok = ok && (((fr[q].x ^ want) & kStamps) == 0ull || (tail && dead0)) &&
-                             (((fr[q].y ^ want) & kStamps) == 0ull || (tail && dead1));
+                        differ |= (tail && dead0 ? 0ull : fr[q].x ^ want) | (tail && dead1 ? 0ull : fr[q].y ^ want);
                     }
-                    if (!__builtin_amdgcn_ballot_w64(!ok)) break;
+                    if (!__builtin_amdgcn_ballot_w64((differ & kStamps) != 0ull)) break;
                     if (++spins > a.spin_limit) {
                         __hip_atomic_store(a.timeout_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         break;
@@ -188,8 +198,8 @@ __global__ __launch_bounds__(kRTH) void persist_rows_bf16_kernel(PersistRowsArgs
                 }
 #pragma unroll
                 for (int q = 0; q < KB; ++q) {
-                    fr[q].x &= ~kStamps;
-                    fr[q].y &= ~kStamps;
+                    fr[q].x = unstamped(fr[q].x);
+                    fr[q].y = unstamped(fr[q].y);
                 }
             } else if (h0) {
 #pragma unroll

@@ -6,7 +6,7 @@ from oracle import hlstm_oracle as horc
 from oracle import lstm_oracle as lorc
 from paper_1901_10997_amd import binding as B
 from paper_1901_10997_amd import inputs
-from parity_util import check_case, compare, run_gpu
+from parity_util import F32_MAX_ABS, check_case, compare, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -460,3 +460,16 @@ def test_hlstm_masked_in_the_dense_recurrence(shape):
     assert desc.count("rec=persist-dense-hlstm(") == L * (2 if bidir else 1), desc
     desc, _ = check_case(case, CSR, PAUTO)
     assert "persist-dense" not in desc, desc
+
+
+@pytest.mark.parametrize("shape", [(1, True, 24, 70, 65, 5, 6), (1, False, 16, 400, 400, 4, 2)])
+def test_hlstm_nan_state_in_the_dense_recurrence(shape):
+    """A NaN hidden state enters every hidden unit's sum and leaves its ReLU as 0, as in the equations evaluated one by one;
+    the unit whose cell state is NaN stays NaN."""
+    L, bidir, D, H, G, T, Bn = shape
+    case = inputs.make_case(_hw(89, L, bidir, D, H, G, T, Bn, a=min(0.3, 1.5 / np.sqrt(H))), k=H, random_state=True)
+    case.c0[:, Bn - 1, H // 2] = np.nan
+    got, desc = run_gpu(case, DENSE, PAUTO)
+    assert "rec=persist-dense-hlstm" in desc, desc
+    for g, r in zip(got, horc.forward_case(case)):
+        np.testing.assert_allclose(g, r, rtol=0, atol=F32_MAX_ABS, equal_nan=True)

@@ -868,3 +868,29 @@ def test_planner_between_dense_and_compressed_recurrence(shape):
     if keep is not None:      # a format the caller names is the one that runs
         desc, _ = check_case(case, CSR, PAUTO)
         assert "persist-dense" not in desc, desc
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, T, B, dtype, keep, plan -- kernels whose exchanged values carry their stamp in a bit that a NaN uses too
+    (1, True, 24, 70, 5, 6, "f32", None, "persist-dense-f32("),
+    (1, False, 16, 513, 4, 2, "f32", None, "persist-dense-f32("),
+    (1, True, 33, 131, 30, 1, "f32", 0.2, "persist-dense-f32("),      # a masked layer in the dense recurrence
+    (1, True, 24, 100, 5, 6, "bf16", None, "persist-mfma-rows("),
+    (1, True, 24, 515, 30, 1, "bf16", None, "persist-mfma-rows("),
+])
+def test_nan_state_reaches_every_unit_of_its_own_sequence(shape):
+    """One NaN in a cell state: that unit at the first step, every unit from the second on, no other batch row."""
+    L, bidir, D, H, T, Bn, dtype, keep, plan = shape
+    case = inputs.make_case(_wl(95, L, bidir, D, H, T, Bn, dtype=dtype, a=min(0.2, 1.5 / np.sqrt(H)), keep=keep), k=H, random_state=True)
+    (y0, hT0, cT0), _ = run_gpu(case)
+    unit, b = H // 2, Bn - 1
+    case.c0[:, b, unit] = np.nan
+    (y, hT, cT), desc = run_gpu(case)
+    assert "rec=" + plan in desc, desc
+    for d in range(2 if bidir else 1):
+        yd = y[::-1, b, d * H:(d + 1) * H] if d else y[:, b, :H]
+        assert np.flatnonzero(np.isnan(yd[0])).tolist() == [unit]
+        assert np.isnan(yd[1:]).all() and np.isnan(hT[d, b]).all() and np.isnan(cT[d, b]).all()
+    others = np.arange(Bn) != b
+    for got, ref in ((y, y0), (hT, hT0), (cT, cT0)):
+        np.testing.assert_array_equal(got[:, others], ref[:, others])
