@@ -1224,7 +1224,30 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
         bool xt_ready = false;
         const float* Xpad = nullptr;   // X with rows padded as PackedMat::dense_pad is
         bool proj_dense[2] = {false, false};
-        for (int d = 0; d < Dn; ++d) {
+        auto padded_x = [&](const PackedMat& wx) -> hipError_t {
+            if (Xpad) return hipSuccess;
+            Xpad = (const float*)X;
+            if (wx.pad_ld == D) return hipSuccess;
+            Xpad = (const float*)(base + ws.xp_off);
+            return launch_pad_rows(X, false, D, M, 1, D, wx.pad_ld, base + ws.xp_off, s);
+        };
+        bool pair_done = false;
+        if (Dn == 2 && M > 64 && !persist[0] && !persist[1]) {
+            // Both directions dense on the matrix cores: one launch (they read the same X), the second direction's tiles fill the
+            // last wave of the first's.  Two workgroups share a compute unit: at 4800 rows and 640 units a direction's 760 tiles
+            // are 1.5 waves of 512, both directions' 1520 three (H-LSTM 3 x 640 bidirectional, batch 16: 5559 -> 5278 us); 800
+            // units (950 tiles, 1.9 waves): no change.  At most 64 rows: one stream over the fragment-ordered weights per
+            // direction, below.
+            const LayerDir& w0 = m->ld[(size_t)l * Dn], & w1 = m->ld[(size_t)l * Dn + 1];
+            if (proj_runs_dense(w0.wx, M) && proj_runs_dense(w1.wx, M)) {
+                ProfSpan span(m, s, 0);
+                HIP_TRY(m, padded_x(w0.wx));
+                HIP_TRY(m, launch_proj_mfma_f32_pair(Xpad, w0.wx.pad_ld, (const float*)w0.wx.dense_pad, w0.bias, P[0],
+                                                     (const float*)w1.wx.dense_pad, w1.bias, P[1], M, 4 * G, w0.wx.pad_ld, s));
+                proj_dense[0] = proj_dense[1] = pair_done = true;
+            }
+        }
+        for (int d = 0; d < Dn && !pair_done; ++d) {
             if (persist[d]) continue;
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
             ProfSpan span(m, s, 0);
@@ -1240,13 +1263,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 }
                 HIP_TRY(m, launch_proj_csr(XT, w.wx.row_ptr, w.wx.col16, w.wx.val, w.bias, P[d], M, 4 * G, s));
             } else {
-                if (!Xpad) {
-                    Xpad = (const float*)X;
-                    if (w.wx.pad_ld != D) {
-                        HIP_TRY(m, launch_pad_rows(X, false, D, M, 1, D, w.wx.pad_ld, base + ws.xp_off, s));
-                        Xpad = (const float*)(base + ws.xp_off);
-                    }
-                }
+                HIP_TRY(m, padded_x(w.wx));
                 HIP_TRY(m, launch_proj_mfma(Xpad, false, w.wx.pad_ld, w.wx.dense_pad, false, w.bias, P[d], M, 4 * G, w.wx.pad_ld, s, w.wx.dense_frag16));
             }
         }

@@ -473,3 +473,18 @@ def test_hlstm_nan_state_in_the_dense_recurrence(shape):
     assert "rec=persist-dense-hlstm" in desc, desc
     for g, r in zip(got, horc.forward_case(case)):
         np.testing.assert_allclose(g, r, rtol=0, atol=F32_MAX_ABS, equal_nan=True)
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, G, T, B -- both directions' dense input products in one launch from 65 input rows on
+    (2, True, 36, 40, 40, 16, 4),        # 64 rows: a launch each
+    (2, True, 36, 40, 40, 13, 5),        # 65 rows: one row in the second tile
+    (2, True, 35, 33, 50, 43, 3),        # 129 rows, widths that are padded (D, and 2 H of the second layer)
+    (1, True, 34, 300, 320, 40, 16),     # 640 rows, tiles of both sizes' ranges
+])
+def test_hlstm_both_directions_projected_together(shape):
+    L, bidir, D, H, G, T, Bn = shape
+    case = inputs.make_case(_hw(90, L, bidir, D, H, G, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, G, D)))), k=T, random_state=True)
+    for plan in (PAUTO, STEP):
+        desc, _ = check_case(case, DENSE, plan)
+        assert desc.count("proj=dense") == 2 * L, desc
