@@ -57,7 +57,8 @@ enum {
     LSTM_FMT_AUTO = 0,          /* library chooses from the mask density: row-compressed up to 25 % kept (H-LSTM: 50 %);
                                    within 5 % of that the second direction of a layer follows the first; fp32 recurrent
                                    matrices are then also held dense, and each call takes the recurrence that is faster at
-                                   its T and B */
+                                   its T and B (the dense one multiplies the mask's zeros: a NaN or an infinity in h then
+                                   reaches every unit of its batch column) */
     LSTM_FMT_DENSE_MASKED = 1,  /* dense matrix with +0 stored where Msk = 0 */
     LSTM_FMT_ROW_COMPRESSED = 2 /* per row: the kept positions only, ascending column order */
 };
