@@ -1138,6 +1138,45 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     return us < 0.95 * other;
 }
 
+// Batch 1: do layers l and l + 1, unidirectional and row-compressed, run in one launch (diagonal wavefront)?
+static bool runs_wavefront(const lstm_t* m, int l, int B)
+{
+    const int H = m->hid(l), D = m->in_dim(l);
+    return B == 1 && m->plan != LSTM_PLAN_STEPWISE && m->Dn == 1 && l + 1 < m->L && m->hid(l + 1) == H &&
+           sparse_b1_ok(m->ld[l], H, D, 2) && sparse_b1_ok(m->ld[l + 1], H, D, 2);
+}
+
+// How each direction of an LSTM layer runs its recurrence: 0 a launch per step or a kernel over all directions, 1 batch-1
+// row-compressed with its input product fused, 2 batch-1 dense fused, 3 batch-1 dense behind a projection kernel.
+static void choose_modes(const lstm_t* m, int l, int T, int B, bool quads, int (&mode)[2])
+{
+    const int Dn = m->Dn, H = m->hid(l), D = m->in_dim(l);
+    mode[0] = mode[1] = 0;
+    if (B != 1 || m->plan == LSTM_PLAN_STEPWISE || quads) return;
+    // bf16, two dense directions: the batch-1 kernel takes them one after the other, the row groups' both at once
+    if (m->dtype == LSTM_BF16 && Dn == 2 && m->plan == LSTM_PLAN_AUTO && m->waves_per_group == 0 &&
+        !m->ld[(size_t)l * Dn].wh.compressed && !m->ld[(size_t)l * Dn + 1].wh.compressed &&
+        persist_rows_bf16_supported(1, H, 2) && persist_b1_dense_supported(H) &&
+        T * persist_rows_bf16_step_us(1, H, 2) + kSeparateProjUs < 0.95 * 2 * T * b1_dense_step_us(H))
+        return;
+    for (int d = 0; d < Dn; ++d) {
+        const LayerDir& w = m->ld[(size_t)l * Dn + d];
+        if (w.wh.compressed) mode[d] = sparse_b1_ok(w, H, D, 1) ? 1 : 0;
+        else if (persist_b1_dense_fusable(H, D)) mode[d] = 2;
+        else if (persist_b1_dense_supported(H)) mode[d] = 3;
+    }
+}
+
+// Does a direction of layer l multiply its input rows inside its recurrence kernel?  Those kernels step through rows of
+// in_dim(l) elements and know nothing of padding.
+static bool fuses_input(const lstm_t* m, int l, int T, int B)
+{
+    if (runs_wavefront(m, l, B)) return true;
+    int mode[2];
+    choose_modes(m, l, T, B, layer_takes_quads(m, l, T, B), mode);
+    return mode[0] == 1 || mode[0] == 2 || mode[1] == 1 || mode[1] == 2;
+}
+
 // Recurrence of layer l with its dense fp32 matrices (W_h; H-LSTM: W1h and W2), time loop on the device.
 static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const float* h0, const float* c0, float* Yout, int y_ld,
                           float* hT, float* cT, const char* proj, const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s)
@@ -1570,12 +1609,10 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         prev_has_bf16 = false;
         float* Yout = (l == L - 1) ? y : Ybuf[l & 1];
         const int y_ld = Dn * H;
-        const bool try_persist = (B == 1 && m->plan != LSTM_PLAN_STEPWISE);
         char tag[128];
 
         // ---- batch 1, row-compressed, two stacked unidirectional layers in one launch (diagonal wavefront)
-        if (try_persist && Dn == 1 && l + 1 < L && m->hid(l + 1) == H && sparse_b1_ok(m->ld[l], H, D, 2) &&
-            sparse_b1_ok(m->ld[l + 1], H, D, 2)) {
+        if (runs_wavefront(m, l, B)) {
             ProfSpan span(m, s, 1);
             int rc = take_tags(T);
             if (rc != LSTM_OK) return rc;
@@ -1596,19 +1633,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
 
         // ---- decide per direction
         const bool quads = layer_takes_quads(m, l, T, B);
-        // bf16, batch 1, two dense directions: the batch-1 kernel takes them one after the other, the row groups' both at once
-        const bool rows_b1 = bf16 && try_persist && Dn == 2 && m->plan == LSTM_PLAN_AUTO && m->waves_per_group == 0 &&
-                             !m->ld[(size_t)l * Dn].wh.compressed && !m->ld[(size_t)l * Dn + 1].wh.compressed &&
-                             persist_rows_bf16_supported(1, H, 2) && persist_b1_dense_supported(H) &&
-                             T * persist_rows_bf16_step_us(1, H, 2) + kSeparateProjUs < 0.95 * 2 * T * b1_dense_step_us(H);
-        int mode[2] = {0, 0};  // 0 stepwise, 1 persistent sparse (fused), 2 persistent dense fused, 3 persistent dense + projection kernel
+        int mode[2];
+        choose_modes(m, l, T, B, quads, mode);
         for (int d = 0; d < Dn; ++d) {
-            const LayerDir& w = m->ld[(size_t)l * Dn + d];
-            if (try_persist && !quads && !rows_b1) {
-                if (w.wh.compressed) mode[d] = sparse_b1_ok(w, H, D, 1) ? 1 : 0;
-                else if (persist_b1_dense_fusable(H, D)) mode[d] = 2;
-                else if (persist_b1_dense_supported(H)) mode[d] = 3;
-            }
             if (m->plan == LSTM_PLAN_PERSISTENT && mode[d] == 0 && B == 1)
                 return fail(m, LSTM_ERR_ARG, "lstm_forward: persistent plan not available for this shape");
         }
@@ -1740,6 +1767,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             }
             PersistRowsArgs a{};
             const int pitch = pad32(H);
+            // The layer above reads the bf16 copy, padded for the matrix-core product, unless it takes its input inside a
+            // batch-1 recurrence: fp32 rows as they are, then.  Only the last layer's fp32 sequence leaves the library.
+            const bool rows_f32 = l == L - 1 || fuses_input(m, l + 1, T, B);
             char shape[48];
             persist_rows_bf16_describe(B, H, Dn, shape, sizeof shape);
             for (int d = 0; d < Dn; ++d) {
@@ -1750,10 +1780,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 q.Wf = w.wh.dense_frag32;
                 q.h0 = h0 ? h0 + so : nullptr;
                 q.c0 = c0 ? c0 + so : nullptr;
-                // the layer above reads the bf16 copy; only the last layer's fp32 sequence leaves the library
-                q.y = (l == L - 1) ? Yout + (size_t)d * H : nullptr;
+                q.y = rows_f32 ? Yout + (size_t)d * H : nullptr;
                 q.y_ld = y_ld;
-                q.yb = (l == L - 1) ? nullptr : Ybf[l & 1] + (size_t)d * pitch;
+                q.yb = rows_f32 ? nullptr : Ybf[l & 1] + (size_t)d * pitch;
                 q.yb_ld = Dn * pitch; q.yb_width = pitch;
                 q.hT = hT ? hT + so : nullptr;
                 q.cT = cT ? cT + so : nullptr;
@@ -1768,7 +1797,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             ProfSpan span(m, s, 1);
             HIP_TRY(m, launch_persist_rows_bf16(a, rows_next, m->launch_mode() != 0, s));
             rows_next += persist_rows_bf16_exchange_words(B, H, Dn);
-            prev_has_bf16 = true;
+            prev_has_bf16 = !rows_f32;
             continue;
         }
         if (mfma_ok) {

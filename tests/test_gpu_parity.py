@@ -894,3 +894,20 @@ def test_nan_state_reaches_every_unit_of_its_own_sequence(shape):
     others = np.arange(Bn) != b
     for got, ref in ((y, y0), (hT, hT0), (cT, cT0)):
         np.testing.assert_array_equal(got[:, others], ref[:, others])
+
+
+@pytest.mark.parametrize("masked", [(0, 1), (1, 0), (0, 1, 0), (0, "d0"), (0, "d1")])
+@pytest.mark.parametrize("H", [500, 515, 512])
+def test_bf16_batch1_stacks_of_dense_and_masked_layers(H, masked):
+    """A dense layer in the row groups' recurrence below or above layers whose batch-1 kernel fuses its input product: that
+    kernel reads rows of 2 H values whatever the dense layer pads its own to.  masked: per layer 0, 1 or the one direction."""
+    L = len(masked)
+    case = inputs.make_case(_wl(97, L, True, 40, H, 35, 1, dtype="bf16", a=0.06, keep=0.1), k=H + 10 * L, random_state=True)
+    for l in range(L):
+        for d in range(2):
+            if masked[l] not in (1, f"d{d}"):
+                case.weights[(l, d)].update(Mx=None, Mh=None)
+    desc, _ = check_case(case, AUTO, PAUTO)
+    dense = [l for l in range(L) if masked[l] == 0]
+    assert desc.count("rec=persist-mfma-rows") == 2 * len(dense), desc
+    assert "proj=fused-csr" in desc, desc
