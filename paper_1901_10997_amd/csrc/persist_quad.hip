@@ -19,10 +19,14 @@
 // so that one exchange, one reduction and one round of gates serve all of them.
 //
 // Exchange: values carry their own readiness, as 32-bit words with one bit of the step count in a bit the value leaves
-// free: |h| <= 1, so bit 30 (a NaN gets it back on reading, see unstamped); u >= 0, so the sign.  h has two buffers per quad, step tag g (2 for the first step) in buffer
-// g & 1 with stamp (g >> 1) & 1; u one, stamped (s + 1) & 1: it is rewritten only after every workgroup has published
-// an h that needed all of it.  All buffers are zero at launch.  A wave loads its own K slice straight into operand
-// registers and repeats the load until every word is stamped (bounded).  Layouts of a quad, in the order of a wave's lanes (four columns
+// free: |h| <= 1, so bit 30 (a NaN gets it back on reading, see unstamped); u >= 0, so the sign.  h has two buffers per
+// quad, step tag g (2 for the first step) in buffer g & 1 with stamp (g >> 1) & 1; u one, stamped (s + 1) & 1.  All
+// buffers are zero at launch.  u(s+1) is written only after its producer has received every h of step s, each of which was
+// published after its workgroup had read all of u(s); a workgroup without a unit of h (G > H) publishes none that anybody
+// could wait for, so it has no second product and never reads u.  h of tag g + 2 takes the place of tag g only after its
+// producer has received every h of tag g + 1 and every u of that step; each workgroup owns units of at least one of the
+// two and had read tag g before it published them.  A wave loads its own K slice straight into operand registers and
+// repeats the load until every word is stamped (bounded).  Layouts of a quad, in the order of a wave's lanes (four columns
 // apart in memory, a load would touch four times the lines): h [k][column]; u [k / 4][gate][column][k % 4], the operand
 // order of the second product, whose sixteen blocks are four gates (each with its own u) x four k.
 //
@@ -119,6 +123,7 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
     const int reverse = D.reverse;
 
     const int KBh = (H + 15) >> 4, KBg = (G + 15) >> 4;
+    const bool owns_h = 4 * wg * NT < H;                                 // of the whole workgroup
     // K blocks: waves 0..3, one per SIMD, take KB each; waves 4..7 KB or, where that covers K, one less
     const int hi = (KBh > KBg ? KBh : KBg) <= 8 * KB - 4 ? KB - 1 : KB;
     const int kb0 = wave < 4 ? wave * KB : 4 * KB + (wave - 4) * hi;
@@ -355,7 +360,7 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
             switch_buffers();
         }
         if constexpr (HL) {
-            for (int pass = 0; pass < passes; ++pass) {
+            for (int pass = 0; owns_h && pass < passes; ++pass) {
                 // ---- second product: four gates x four k per instruction, one register of u each
                 unsigned long long fu[QP][KB][2];
                 const unsigned want = ((unsigned)s + 1u) << 31;

@@ -488,3 +488,18 @@ def test_hlstm_both_directions_projected_together(shape):
     for plan in (PAUTO, STEP):
         desc, _ = check_case(case, DENSE, plan)
         assert desc.count("proj=dense") == 2 * L, desc
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, G, T, B, keep, fmt, recurrence -- gate layers much wider or narrower than the hidden state: workgroups
+    # that own units of one vector only; long sequences
+    (1, False, 40, 65, 200, 300, 3, None, DENSE, "persist-dense-hlstm"),
+    (1, True, 24, 100, 300, 300, 18, None, DENSE, "persist-dense-hlstm"),     # passes
+    (1, False, 24, 300, 100, 300, 5, None, DENSE, "persist-dense-hlstm"),
+    (2, False, 24, 60, 180, 300, 4, 0.2, AUTO, "persist-dense-hlstm"),
+])
+def test_hlstm_gate_width_far_from_the_hidden_width(shape):
+    L, bidir, D, H, G, T, Bn, keep, fmt, rec = shape
+    case = inputs.make_case(_hw(96, L, bidir, D, H, G, T, Bn, a=0.5 / np.sqrt(max(H, G) * (keep or 1.0)), keep=keep), k=H, random_state=True)
+    desc, _ = check_case(case, fmt, PAUTO)
+    assert desc.count("rec=" + rec) == L * (2 if bidir else 1), desc
