@@ -23,9 +23,11 @@
 //         flag to the step tag.  A consumer's first wave polls the flags of its batch group; after a barrier the
 //         workgroup copies the vector with device-scope 8-byte loads, all of a thread's loads in flight at once.
 //         (An acquire fence followed by ordinary cached loads measured three times slower for these 50 KB.)
-// One array per vector is enough: u_{t+1} is written only after its producer has received every h_t of the batch
-// group, and each of those was published after its producer had finished reading u_t (and the same with the roles
-// swapped).  Where the batch groups fit one XCD each and the launch has verified the placement from the hardware's
+// One array and one flag per vector are enough: u_{t+1} is written, and its flag raised, only after the producer has
+// received every h_t of the batch group, and each of those was published after its producer had finished reading u_t; a
+// workgroup that owns no output unit (G > H) publishes no h that anybody could wait for, so it has no second half and
+// reads neither u nor the flags.  h_{t+1} is published only after every workgroup's flag for u_{t+1}, which each raises
+// (units of u or not) after it has finished reading h_t.  Where the batch groups fit one XCD each and the launch has verified the placement from the hardware's
 // XCD ids, h, u and the flags are stored at workgroup scope and meet in that XCD's L2 (exchange.h).
 // All waits are bounded: on expiry a device flag is raised, every wave stops waiting, the kernel drains.
 #include <type_traits>
@@ -126,6 +128,7 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
     float c = 0.f;
     if (lane < 16 && ok2 && D.c0) c = D.c0[(size_t)(b0 + pb) * H + unit_l];
     const int poll_i = lane < a.ug ? lane : a.ug - 1;
+    const bool owns_h = ugi * upb < H;                    // of the whole workgroup
 
     // The few entries of rows longer than 16 S (at most 6 per wave; most waves have none): lane e holds entry e of the
     // wave's run of per-unit lists -- value, LDS byte offset of its column, and the lane that collects its gate's total
@@ -268,6 +271,7 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
         __syncthreads();
         if (tid == 0) exchange_store(flags + ugi, tag, same_xcd);
+        if (!owns_h) continue;
         // ---- stage 2: gate outputs from u_t, cell update
         if (wave == 0) {
             unsigned spins = 0;

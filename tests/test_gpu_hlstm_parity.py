@@ -497,6 +497,10 @@ def test_hlstm_both_directions_projected_together(shape):
     (1, True, 24, 100, 300, 300, 18, None, DENSE, "persist-dense-hlstm"),     # passes
     (1, False, 24, 300, 100, 300, 5, None, DENSE, "persist-dense-hlstm"),
     (2, False, 24, 60, 180, 300, 4, 0.2, AUTO, "persist-dense-hlstm"),
+    (1, True, 24, 40, 400, 300, 5, 0.1, CSR, "persist_batched-hlstm"),
+    (1, False, 24, 400, 40, 300, 9, 0.1, CSR, "persist_batched-hlstm"),
+    (1, False, 24, 40, 400, 300, 1, 0.1, CSR, "persist_b1-hlstm"),
+    (1, True, 24, 400, 40, 300, 1, 0.1, CSR, "persist_b1-hlstm"),
 ])
 def test_hlstm_gate_width_far_from_the_hidden_width(shape):
     L, bidir, D, H, G, T, Bn, keep, fmt, rec = shape
