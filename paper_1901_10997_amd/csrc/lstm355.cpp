@@ -849,7 +849,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, h0_off, total;
 };
 // launches of the dense fp32 persistent recurrence that layer l takes
 static bool quad_cut(const lstm_t* m, int l, int B, LaunchCut* cut)
@@ -861,6 +861,10 @@ static bool quad_cut(const lstm_t* m, int l, int B, LaunchCut* cut)
 static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
 {
     return align256(4 * persist_quad_exchange_words((B + cut.chunks - 1) / cut.chunks, m->hid(l), m->ghid(l), m->Dn / cut.passes)) / 4;
+}
+static size_t state_floats(const lstm_t* m, int B)   // of all layers and directions
+{
+    return m->soff((size_t)m->L * m->Dn) * (size_t)B;
 }
 static Workspace carve(const lstm_t* m, int T, int B)
 {
@@ -952,6 +956,9 @@ static Workspace carve(const lstm_t* m, int T, int B)
     if (m->dtype == LSTM_BF16)
         for (int l = 0; l < m->L; ++l) w.rx_words += persist_rows_bf16_exchange_words(B, m->hid(l), m->Dn);
     off += align256(w.rx_words * sizeof(unsigned long long));
+    // copy of h0 where the call returns hT in its place (lstm_forward)
+    w.h0_off = off;
+    off += align256(state_floats(m, B) * sizeof(float));
     w.total = off;
     return w;
 }
@@ -1545,6 +1552,15 @@ int lstm_forward(lstm_t* m, int T, int B, const void* x, const float* h0, const 
     m->capturing = (cap != hipStreamCaptureStatusNone);
     m->cap_cleared = false;
     m->cap_tag = 0;
+    // State updated in place: with more than one timestep every workgroup has read its h0 before it publishes the h that
+    // the writers of hT wait for; with a single one nothing keeps a kernel's first workgroup from storing hT before its
+    // last has read h0, so that reads a copy.  (c0 is read by the lanes that write cT.)
+    const size_t sn = state_floats(m, B);
+    if (T == 1 && h0 && hT && h0 < hT + sn && hT < h0 + sn) {
+        float* const copy = (float*)((char*)workspace + ws.h0_off);
+        HIP_TRY(m, hipMemcpyAsync(copy, h0, sn * sizeof(float), hipMemcpyDeviceToDevice, s));
+        h0 = copy;
+    }
     const int rc_run = run_forward(m, T, B, x, h0, c0, y, hT, cT, ws, (char*)workspace, s);
     m->capturing = false;
     return rc_run;

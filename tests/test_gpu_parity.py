@@ -911,3 +911,32 @@ def test_bf16_batch1_stacks_of_dense_and_masked_layers(H, masked):
     dense = [l for l in range(L) if masked[l] == 0]
     assert desc.count("rec=persist-mfma-rows") == 2 * len(dense), desc
     assert "proj=fused-csr" in desc, desc
+
+
+@pytest.mark.parametrize("L,bidir,H,Bn,dtype,keep", [
+    (1, False, 800, 16, "f32", None), (2, True, 130, 5, "f32", None), (1, False, 1197, 20, "bf16", None),
+    (2, False, 1024, 64, "bf16", None), (2, False, 300, 1, "f32", 0.2), (2, True, 200, 6, "f32", 0.1)])
+def test_state_carried_in_place_one_step_at_a_time(L, bidir, H, Bn, dtype, keep):
+    """Streaming, a timestep per call, the state written where it was read: the same bits as with separate buffers."""
+    import torch
+    steps = 12
+    case = inputs.make_case(_wl(98, L, bidir, 40, H, steps, Bn, dtype=dtype, a=min(0.2, 1.5 / np.sqrt(H)), keep=keep), k=H, random_state=True)
+    m = B.Lstm(L, 40, H, bidir, B.LSTM_BF16 if dtype == "bf16" else B.LSTM_F32)
+    m.set_weights_from(case.weights, AUTO)
+    x = torch.from_numpy(case.x).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ws = torch.empty(B.lstm_workspace_bytes(m.handle, 1, Bn), dtype=torch.uint8, device="cuda")
+    y = torch.empty((steps, Bn, m.ndir * H), device="cuda")
+    outs = []
+    for in_place in (False, True):
+        h, c = torch.from_numpy(case.h0).cuda(), torch.from_numpy(case.c0).cuda()
+        for t in range(steps):
+            hn, cn = (h, c) if in_place else (torch.empty_like(h), torch.empty_like(c))
+            B.lstm_forward(m.handle, 1, Bn, x[t].data_ptr(), h.data_ptr(), c.data_ptr(), y[t].data_ptr(), hn.data_ptr(),
+                           cn.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+            h, c = hn, cn
+        torch.cuda.synchronize()
+        B.lstm_check(m.handle)
+        outs.append((y.cpu().numpy().copy(), h.cpu().numpy(), c.cpu().numpy()))
+    m.close()
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a, b)
