@@ -1186,7 +1186,7 @@ static bool fuses_input(const lstm_t* m, int l, int T, int B)
 
 // Recurrence of layer l with its dense fp32 matrices (W_h; H-LSTM: W1h and W2), time loop on the device.
 static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const float* h0, const float* c0, float* Yout, int y_ld,
-                          float* hT, float* cT, const char* proj, const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s)
+                          float* hT, float* cT, const char* const (&proj)[2], const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l), R = 4 * (G > 0 ? G : H);
     LaunchCut cut;
@@ -1219,7 +1219,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
                 char tag[128], shape[48], cuts[24] = "";
                 persist_quad_describe(bn, H, G, nd, shape, sizeof shape);
                 if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, "(batch/%d)", cut.chunks);
-                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-%s%s%s;", l, d, proj, G > 0 ? "hlstm" : "f32", shape, cuts);
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-%s%s%s;", l, d, proj[d], G > 0 ? "hlstm" : "f32", shape, cuts);
                 m->last_plan += tag;
             }
         }
@@ -1314,7 +1314,8 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
             }
         }
         if (quads) {
-            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj_dense[0] ? "dense" : "csr", ws, base, quad, s);
+            const char* const proj[2] = {proj_dense[0] ? "dense" : "csr", proj_dense[1] ? "dense" : "csr"};
+            const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj, ws, base, quad, s);
             if (rc != LSTM_OK) return rc;
             continue;
         }
@@ -1658,7 +1659,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         // ---- input projection for every timestep (only the modes that need P)
         bool xt_ready = false;
         bool pair_done = false;
-        bool proj_q16_used = false;
+        const char* proj[2] = {"csr", "csr"};   // what ran, for the plan description
         {
             // Row-compressed W_x in the quarter-wave form, many input rows, few kept weights: gathers and vector
             // multiply-adds over the kept entries only.  (Bound by LDS bandwidth at 16 bytes per four multiply-adds;
@@ -1682,7 +1683,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 a.X = (const float*)X; a.ldx = D; a.M = M; a.K = D; a.H = H;
                 HIP_TRY(m, launch_proj_q16(a, Dn, pslots, s));
                 pair_done = true;
-                proj_q16_used = true;
+                proj[0] = proj[1] = "q16";
             }
         }
         // X as the matrix-core products read it: rows padded as PackedMat::dense_pad is
@@ -1703,6 +1704,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 HIP_TRY(m, launch_proj_mfma_f32_pair((const float*)Xpad, w0.wx.pad_ld, (const float*)w0.wx.dense_pad, w0.bias, P[0],
                                                      (const float*)w1.wx.dense_pad, w1.bias, P[1], M, 4 * H, w0.wx.pad_ld, s));
                 pair_done = true;
+                proj[0] = proj[1] = "dense";
             }
         }
         for (int d = 0; d < Dn && !pair_done; ++d) {
@@ -1711,6 +1713,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             ProfSpan span(m, s, 0);
             // (a padded input is laid out for the dense product only)
             const bool dense_proj = proj_runs_dense(w.wx, M) || (prev_bf16 && w.wx.pad_ld != D);
+            if (dense_proj) proj[d] = "dense";
             if (!dense_proj && w.wx.ell_val && proj_ell_small_supported(M, 4 * H, D, w.wx.slots)) {
                 // few input rows: lanes over the kept entries of a row (no transpose of X)
                 HIP_TRY(m, launch_proj_ell_small(X, x_is_bf16, D, bf16 && !x_is_bf16, w.wx.ell_val, w.wx.ell_col, w.wx.slots,
@@ -1860,7 +1863,6 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         }
         // ---- recurrence, fp32 over dense copies, time loop on the device (all directions in one launch)
         if (quads) {
-            const char* proj = proj_q16_used ? "q16" : proj_runs_dense(m->ld[(size_t)l * Dn].wx, M) ? "dense" : "csr";
             const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj, ws, base, quad, s);
             if (rc != LSTM_OK) return rc;
             continue;
@@ -1908,8 +1910,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                         char cuts[24] = "";
                         if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, ",batch/%d", cut.chunks);
                         std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-q16%s(s%d,u%d,b%d%s);", l, d,
-                                      proj_q16_used ? "q16" : proj_runs_dense(w.wx, M) ? "dense" : "csr",
-                                      w.wh.q16_ovf_ptr ? "+ovf" : "", q16, upw, bw, cuts);
+                                      proj[d], w.wh.q16_ovf_ptr ? "+ovf" : "", q16, upw, bw, cuts);
                         m->last_plan += tag;
                     }
                 }
@@ -1940,8 +1941,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 ev[d] = w.wh.ell_val; ec[d] = w.wh.ell_col; sl[d] = w.wh.slots;
                 if (c0) HIP_TRY(m, hipMemcpyAsync(cbuf[d], c0 + m->soff(n) * B, (size_t)B * H * sizeof(float), hipMemcpyDeviceToDevice, s));
                 else HIP_TRY(m, launch_fill_f32(cbuf[d], (size_t)B * H, 0.0f, s));
-                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=stepwise-csr-paired;", l, d,
-                              proj_q16_used ? "q16" : proj_runs_dense(w.wx, M) ? "dense" : "csr");
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=stepwise-csr-paired;", l, d, proj[d]);
                 m->last_plan += tag;
             }
             for (int step = 0; step < T; ++step) {
@@ -1983,7 +1983,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             float* cTn = cT ? cT + m->soff(n) * B : nullptr;
             static const char* const names[4] = {"stepwise", "persist_b1", "persist_b1", "persist_b1"};
             std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s%s,rec=%s-%s%s;", l, d, (mode[d] == 1 || mode[d] == 2) ? "fused-" : "",
-                          proj_q16_used ? "q16" : ((mode[d] == 1 || mode[d] == 2) ? !w.wx.compressed : proj_runs_dense(w.wx, M)) ? "dense" : "csr",
+                          mode[d] == 1 || mode[d] == 2 ? (w.wx.compressed ? "csr" : "dense") : proj[d],
                           names[mode[d]], w.wh.compressed ? "csr" : "dense",
                           (mode[d] == 1 && (w.wx.slots_trim || w.wh.slots_trim)) ? "+ovf" : "");
             m->last_plan += tag;

@@ -940,3 +940,16 @@ def test_state_carried_in_place_one_step_at_a_time(L, bidir, H, Bn, dtype, keep)
     m.close()
     for a, b in zip(*outs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("bidir,D,H,T,Bn", [(True, 41, 51, 7, 5), (False, 64, 130, 9, 6)])
+def test_plan_names_the_projection_that_ran(bidir, D, H, T, Bn):
+    """A masked bf16 layer over a dense one of a width that is padded: fewer than 256 rows, yet only the dense product
+    reads padded rows."""
+    case = inputs.make_case(_wl(97, 2, bidir, D, H, T, Bn, dtype="bf16", a=0.1, keep=0.2), k=H, random_state=True)
+    for d in range(2 if bidir else 1):
+        case.weights[(0, d)].update(Mx=None, Mh=None)
+    desc, _ = check_case(case, AUTO, PAUTO)
+    for d in range(2 if bidir else 1):
+        assert f"l0.d{d}:proj=dense,rec=persist-mfma-rows" in desc, desc
+        assert f"l1.d{d}:proj=dense,rec=persist_batched-q16" in desc, desc
