@@ -620,10 +620,14 @@ static int create_model(int layers, int input_dim, const int* hidden_dims, const
 // weights (the projection over the kept entries, tried before this is asked, takes the large sparse cases); with at most
 // 64 input rows the stream over the fragment-ordered dense copy beats the lanes-over-entries kernel down to 5 % kept at
 // every width from 256 to 4096 (batch 16: 14.5 against 15.9 us at n = 4096, 4.2 against 7.1 us at n = 1024).
-static bool proj_runs_dense(const PackedMat& wx, int M)
+// x_f32: fp32 rows under bf16 weights (the hidden sequence a row-compressed recurrence leaves).  They are rounded on load
+// and not padded, so a width that the matrix-core product does not take stays with the kept entries (masked bf16 2 x 1197,
+// 700 rows: 534 us per forward with the plain tiled product, 391 over the kept entries).
+static bool proj_runs_dense(const PackedMat& wx, int M, bool x_f32 = false)
 {
     if (!wx.dense) return false;
     if (!wx.compressed) return true;
+    if (x_f32 && !proj_mfma_supported(true, wx.cols, wx.cols)) return false;
     if (M >= 256) return true;
     return M <= 64 && wx.dense_frag16 != nullptr && (double)wx.nnz >= 0.04 * (double)wx.rows * (double)wx.cols;
 }
@@ -1712,7 +1716,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
             ProfSpan span(m, s, 0);
             // (a padded input is laid out for the dense product only)
-            const bool dense_proj = proj_runs_dense(w.wx, M) || (prev_bf16 && w.wx.pad_ld != D);
+            const bool dense_proj = proj_runs_dense(w.wx, M, bf16 && !x_is_bf16) || (prev_bf16 && w.wx.pad_ld != D);
             if (dense_proj) proj[d] = "dense";
             if (!dense_proj && w.wx.ell_val && proj_ell_small_supported(M, 4 * H, D, w.wx.slots)) {
                 // few input rows: lanes over the kept entries of a row (no transpose of X)

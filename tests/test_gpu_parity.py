@@ -953,3 +953,16 @@ def test_plan_names_the_projection_that_ran(bidir, D, H, T, Bn):
     for d in range(2 if bidir else 1):
         assert f"l0.d{d}:proj=dense,rec=persist-mfma-rows" in desc, desc
         assert f"l1.d{d}:proj=dense,rec=persist_batched-q16" in desc, desc
+
+
+@pytest.mark.parametrize("bidir,D,H,T,Bn,keep,upper", [
+    (False, 45, 203, 45, 8, 0.2, "csr"),     # 360 rows of 203 fp32 values under bf16 weights: the kept entries
+    (True, 45, 101, 45, 8, 0.2, "csr"),
+    (False, 45, 200, 45, 8, 0.2, "dense"),   # 200: rounded on load by the matrix-core product
+])
+def test_masked_bf16_projection_of_odd_widths_over_the_kept_entries(bidir, D, H, T, Bn, keep, upper):
+    case = inputs.make_case(_wl(97, 2, bidir, D, H, T, Bn, dtype="bf16", a=0.08, keep=keep), k=H, random_state=True)
+    desc, _ = check_case(case, AUTO, PAUTO)
+    for d in range(2 if bidir else 1):
+        assert f"l0.d{d}:proj=dense,rec=persist_batched-q16" in desc, desc     # bf16 input rows: padded
+        assert f"l1.d{d}:proj={upper},rec=persist_batched-q16" in desc, desc
