@@ -276,12 +276,16 @@ struct PersistRowsArgs {
     unsigned long long* hx;
     unsigned long long* xcc_ids;
 };
-bool persist_rows_bf16_supported(int B, int H, int ndir);
-bool persist_rows_bf16_one_pass(int B, int H, int ndir);   // no group of workgroups has more than 16 batch rows
-double persist_rows_bf16_step_us(int B, int H, int ndir);   // modelled time of a step
-size_t persist_rows_bf16_exchange_words(int B, int H, int ndir);
-void persist_rows_bf16_describe(int B, int H, int ndir, char* buf, size_t n);
-hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, unsigned long long* words, bool cooperative, hipStream_t s);
+struct PersistRowsPlan {   // how a launch of (B, H, ndir) is laid out
+    int shape = -1;        // entry of the kernel's table; < 0: none fits
+    double us = 1e30;      // modelled time of a step
+    int rows = 0, groups = 0, gn = 0, xcd_local = 0;
+    size_t lds = 0;
+};
+PersistRowsPlan persist_rows_bf16_plan(int B, int H, int ndir);
+size_t persist_rows_bf16_exchange_words(const PersistRowsPlan& p, int H, int ndir);
+void persist_rows_bf16_describe(const PersistRowsPlan& p, char* buf, size_t n);
+hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, const PersistRowsPlan& p, unsigned long long* words, bool cooperative, hipStream_t s);
 size_t frag32_elements(int rows, int cols);
 hipError_t launch_to_frag32(const uint16_t* W, int rows, int cols, uint16_t* out, hipStream_t s);
 hipError_t launch_pad_rows(const void* src, bool bf16, int src_ld, int rows, int parts, int part_cols, int part_pitch, void* dst,
@@ -312,11 +316,16 @@ struct PersistQuadArgs {
     unsigned *hx, *ux;
     unsigned long long* xcc_ids;
 };
-bool persist_quad_supported(int B, int H, int G, int ndir);
-double persist_quad_step_us(int B, int H, int G, int ndir);   // modelled time of a step
+struct PersistQuadPlan {   // how a launch of (B, H, G, ndir) is laid out
+    int shape = -1;        // entry of the kernel's table; < 0: none fits
+    double us = 1e30;      // modelled time of a step
+    int mq = 0, groups = 0, gn = 0, xcd_local = 0;
+    size_t lds = 0;
+};
+PersistQuadPlan persist_quad_plan(int B, int H, int G, int ndir);
 size_t persist_quad_exchange_words(int B, int H, int G, int ndir);
-void persist_quad_describe(int B, int H, int G, int ndir, char* buf, size_t n);
-hipError_t launch_persist_quad(PersistQuadArgs& a, unsigned* words, bool cooperative, hipStream_t s);
+void persist_quad_describe(const PersistQuadPlan& p, char* buf, size_t n);
+hipError_t launch_persist_quad(PersistQuadArgs& a, const PersistQuadPlan& p, unsigned* words, bool cooperative, hipStream_t s);
 size_t frag16_floats(int rows, int cols);
 hipError_t launch_to_frag16(const float* W, int rows, int cols, bool by_gate, float* out, hipStream_t s);
 hipError_t launch_csr_to_frag16(const int* row_ptr, const uint16_t* col, const float* val, int rows, int cols, bool by_gate, float* out, hipStream_t s);

@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -14,6 +15,16 @@
 #include "common.h"
 
 using namespace l355;
+
+// Launches over a layer's directions and batch columns: `passes` over the directions, times `chunks` runs of columns.
+struct LaunchCut { int passes = 0, chunks = 0; };
+// How the dense recurrences with the time loop on the device lay out one layer at a batch size.
+struct DensePlans {
+    int B = 0;
+    LaunchCut cut;                // fp32: launches (chunks = 0: no form fits) ...
+    PersistQuadPlan quad[2];      // ... of the longer and the shorter runs of columns
+    PersistRowsPlan rows;         // bf16
+};
 
 struct lstm355 {
     int L = 0, D0 = 0, H = 0, Dn = 1, dtype = LSTM_F32;
@@ -45,6 +56,8 @@ struct lstm355 {
     std::vector<int> Hs, Gs;
     std::vector<size_t> state_off;       // state_off[l*Dn + d]: hidden units in front of that cell in h0/c0/hT/cT
     size_t xchg_slots = 0;               // 64-bit slots in xchg
+    mutable std::mutex plans_mutex;      // dense_plans of each layer at the batch size it was last asked for
+    mutable std::vector<DensePlans> plans;
     int hid(int l) const { return Hs[(size_t)l]; }
     int ghid(int l) const { return Gs[(size_t)l]; }
     int in_dim(int l) const { return l == 0 ? D0 : Dn * Hs[(size_t)l - 1]; }
@@ -112,7 +125,6 @@ static float host_bf16_to_f32(uint16_t b)
 // `fits(columns, directions)` accepts for its longest and shortest run wins; at most eight launches per layer.
 // slots of the quarter-wave form the small-batch recurrences take (rows of up to 16 x 24 = 384 kept entries)
 constexpr int kMaxRecurrentSlots = 24;
-struct LaunchCut { int passes = 0, chunks = 0; };
 template <class Fits>
 static bool choose_cut(int B, int Dn, Fits fits, LaunchCut* out, int min_cols = 2)
 {
@@ -739,7 +751,7 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 0, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
     // LSTM_FMT_AUTO leaves the choice of the recurrence kernel to each call (layer_takes_quads): the dense one needs its copy
-    if (format == LSTM_FMT_AUTO && compressed && !bf16 && persist_quad_supported(1, H, 0, 1)) {
+    if (format == LSTM_FMT_AUTO && compressed && !bf16 && persist_quad_plan(1, H, 0, 1).shape >= 0) {
         rc = add_frag16_csr(m, x.wh, false);
         if (rc != LSTM_OK) return rc;
     }
@@ -810,7 +822,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     if (rc != LSTM_OK) return rc;
     // gate outputs: 4H rows, packed row 4j+q, columns = hidden units of the row's own gate
     rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 12, kFragByGate);
-    if (rc == LSTM_OK && format == LSTM_FMT_AUTO && compressed && persist_quad_supported(1, H, G, 1)) {   // as in lstm_set_weights
+    if (rc == LSTM_OK && format == LSTM_FMT_AUTO && compressed && persist_quad_plan(1, H, G, 1).shape >= 0) {   // as in lstm_set_weights
         rc = add_frag16_csr(m, x.wh, false);
         if (rc == LSTM_OK) rc = add_frag16_csr(m, x.w2, true);
     }
@@ -855,11 +867,27 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 struct Workspace {
     size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, h0_off, total;
 };
-// launches of the dense fp32 persistent recurrence that layer l takes
-static bool quad_cut(const lstm_t* m, int l, int B, LaunchCut* cut)
+// Plans of layer l at batch B.  They follow from the shape alone, but a search over the kernels' shape tables takes
+// microseconds and a forward needs each several times, so the handle keeps the last batch size's.
+static DensePlans dense_plans(const lstm_t* m, int l, int B)
 {
+    std::lock_guard<std::mutex> lock(m->plans_mutex);
+    m->plans.resize((size_t)m->L);
+    DensePlans& p = m->plans[(size_t)l];
+    if (p.B == B) return p;
     const int H = m->hid(l), G = m->ghid(l);
-    return m->dtype == LSTM_F32 && choose_cut(B, m->Dn, [&](int b, int nd) { return persist_quad_supported(b, H, G, nd); }, cut, 1);
+    p = DensePlans{};
+    p.B = B;
+    if (m->dtype == LSTM_BF16) {
+        p.rows = persist_rows_bf16_plan(B, H, m->Dn);
+    } else {
+        const auto plan = [&](int b, int nd) { return persist_quad_plan(b, H, G, nd); };
+        if (choose_cut(B, m->Dn, [&](int b, int nd) { return plan(b, nd).shape >= 0; }, &p.cut, 1)) {
+            p.quad[0] = plan((B + p.cut.chunks - 1) / p.cut.chunks, m->Dn / p.cut.passes);
+            p.quad[1] = B % p.cut.chunks == 0 ? p.quad[0] : plan(B / p.cut.chunks, m->Dn / p.cut.passes);
+        }
+    }
+    return p;
 }
 // exchange words per launch of that layer (the longest run of batch columns)
 static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
@@ -951,14 +979,14 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // (whether a layer's recurrent matrices are held dense is not known before its weights are set)
     w.qx_off = off;
     for (int l = 0; l < m->L; ++l) {
-        LaunchCut cut;
-        if (quad_cut(m, l, B, &cut)) w.qx_words += quad_launch_words(m, l, B, cut) * cut.passes * cut.chunks;
+        const LaunchCut cut = dense_plans(m, l, B).cut;
+        if (cut.chunks > 0) w.qx_words += quad_launch_words(m, l, B, cut) * cut.passes * cut.chunks;
     }
     off += align256(w.qx_words * sizeof(unsigned));
     // ... and of the bf16 one
     w.rx_off = off;
     if (m->dtype == LSTM_BF16)
-        for (int l = 0; l < m->L; ++l) w.rx_words += persist_rows_bf16_exchange_words(B, m->hid(l), m->Dn);
+        for (int l = 0; l < m->L; ++l) w.rx_words += persist_rows_bf16_exchange_words(dense_plans(m, l, B).rows, m->hid(l), m->Dn);
     off += align256(w.rx_words * sizeof(unsigned long long));
     // copy of h0 where the call returns hT in its place (lstm_forward)
     w.h0_off = off;
@@ -1128,11 +1156,11 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
         if (!w.wh.dense_frag16 || (G > 0 && !w.w2.dense_frag16)) return false;
         csr += w.wh.compressed;
     }
-    LaunchCut cut;
-    if (!quad_cut(m, l, B, &cut)) return false;
+    const DensePlans p = dense_plans(m, l, B);
+    if (p.cut.chunks == 0) return false;
     if (B > 1 && csr < Dn) return true;
     if (m->plan == LSTM_PLAN_PERSISTENT && (G == 0 || csr > 0)) return false;
-    double us = T * cut.passes * cut.chunks * persist_quad_step_us((B + cut.chunks - 1) / cut.chunks, H, G, Dn / cut.passes), other = 0;
+    double us = T * p.cut.passes * p.cut.chunks * p.quad[0].us, other = 0;
     if (B > 1) {
         us += kDenseSetupUs;
         other = T * batched_csr_step_us(m, l, B);
@@ -1166,10 +1194,10 @@ static void choose_modes(const lstm_t* m, int l, int T, int B, bool quads, int (
     if (B != 1 || m->plan == LSTM_PLAN_STEPWISE || quads) return;
     // bf16, two dense directions: the batch-1 kernel takes them one after the other, the row groups' both at once
     if (m->dtype == LSTM_BF16 && Dn == 2 && m->plan == LSTM_PLAN_AUTO && m->waves_per_group == 0 &&
-        !m->ld[(size_t)l * Dn].wh.compressed && !m->ld[(size_t)l * Dn + 1].wh.compressed &&
-        persist_rows_bf16_supported(1, H, 2) && persist_b1_dense_supported(H) &&
-        T * persist_rows_bf16_step_us(1, H, 2) + kSeparateProjUs < 0.95 * 2 * T * b1_dense_step_us(H))
-        return;
+        !m->ld[(size_t)l * Dn].wh.compressed && !m->ld[(size_t)l * Dn + 1].wh.compressed && persist_b1_dense_supported(H)) {
+        const PersistRowsPlan rows = dense_plans(m, l, 1).rows;
+        if (rows.shape >= 0 && T * rows.us + kSeparateProjUs < 0.95 * 2 * T * b1_dense_step_us(H)) return;
+    }
     for (int d = 0; d < Dn; ++d) {
         const LayerDir& w = m->ld[(size_t)l * Dn + d];
         if (w.wh.compressed) mode[d] = sparse_b1_ok(w, H, D, 1) ? 1 : 0;
@@ -1193,8 +1221,8 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
                           float* hT, float* cT, const char* const (&proj)[2], const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l), R = 4 * (G > 0 ? G : H);
-    LaunchCut cut;
-    quad_cut(m, l, B, &cut);
+    const DensePlans p = dense_plans(m, l, B);
+    const LaunchCut& cut = p.cut;
     if (!reg.next) {
         reg.next = (unsigned*)(base + ws.qx_off);
         HIP_TRY(m, launch_fill_u64((unsigned long long*)reg.next, align256(ws.qx_words * 4) / 8, 0ull, s));
@@ -1204,6 +1232,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
         const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
         const int nd = Dn / cut.passes, d_lo = pass * nd;
         const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
+        const PersistQuadPlan& plan = p.quad[bn == (B + cut.chunks - 1) / cut.chunks ? 0 : 1];
         PersistQuadArgs a{};
         for (int d = d_lo; d < d_lo + nd; ++d) {
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
@@ -1221,7 +1250,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
             q.reverse = d;
             if (chunk == 0) {
                 char tag[128], shape[48], cuts[24] = "";
-                persist_quad_describe(bn, H, G, nd, shape, sizeof shape);
+                persist_quad_describe(plan, shape, sizeof shape);
                 if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, "(batch/%d)", cut.chunks);
                 std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-%s%s%s;", l, d, proj[d], G > 0 ? "hlstm" : "f32", shape, cuts);
                 m->last_plan += tag;
@@ -1232,7 +1261,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
         a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
         a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceQuad;
         ProfSpan span(m, s, 1);
-        HIP_TRY(m, launch_persist_quad(a, reg.next, m->launch_mode() != 0, s));
+        HIP_TRY(m, launch_persist_quad(a, plan, reg.next, m->launch_mode() != 0, s));
         reg.next += words;
     }
     return LSTM_OK;
@@ -1743,7 +1772,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         const bool mfma_ok = dense_bf16 && step_mfma_supported(B, H);
         // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 to 2 times (1024 units: batch 64 2.2 against 3.7 us per
         // step, 128 2.5 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
-        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H) && !persist_rows_bf16_one_pass(B, H, Dn)) {
+        PersistRowsPlan rows;
+        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE) rows = dense_plans(m, l, B).rows;
+        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H) && (rows.shape < 0 || rows.rows > 16)) {
             // time loop on the device: W_h stays in registers, h_t travels through flagged exchange buffers
             uint16_t* Yb = Ybf[l & 1];
             if (!mflags_clean || mflags_H != H) {
@@ -1782,7 +1813,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             prev_has_bf16 = true;
             continue;
         }
-        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_rows_bf16_supported(B, H, Dn)) {
+        if (rows.shape >= 0) {
             // every other width and batch: groups of workgroups over runs of batch rows, all directions in one launch
             if (!rows_next) {
                 rows_next = (unsigned long long*)(base + ws.rx_off);
@@ -1794,7 +1825,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             // batch-1 recurrence: fp32 rows as they are, then.  Only the last layer's fp32 sequence leaves the library.
             const bool rows_f32 = l == L - 1 || fuses_input(m, l + 1, T, B);
             char shape[48];
-            persist_rows_bf16_describe(B, H, Dn, shape, sizeof shape);
+            persist_rows_bf16_describe(rows, shape, sizeof shape);
             for (int d = 0; d < Dn; ++d) {
                 const LayerDir& w = m->ld[(size_t)l * Dn + d];
                 const size_t so = m->soff((size_t)l * Dn + d) * B;
@@ -1818,8 +1849,8 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
             a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceQuad;
             ProfSpan span(m, s, 1);
-            HIP_TRY(m, launch_persist_rows_bf16(a, rows_next, m->launch_mode() != 0, s));
-            rows_next += persist_rows_bf16_exchange_words(B, H, Dn);
+            HIP_TRY(m, launch_persist_rows_bf16(a, rows, rows_next, m->launch_mode() != 0, s));
+            rows_next += persist_rows_bf16_exchange_words(rows, H, Dn);
             prev_has_bf16 = !rows_f32;
             continue;
         }

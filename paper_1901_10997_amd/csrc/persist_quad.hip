@@ -459,22 +459,16 @@ const QuadShape kQuadShapes[] = {
 #undef Q_L
 #undef Q_H
 constexpr int kQuadShapeCount = (int)(sizeof(kQuadShapes) / sizeof(kQuadShapes[0]));
-
-struct QuadPlan {
-    const QuadShape* shape = nullptr;
-    double us = 1e30;   // modelled step time
-    int mq = 0, groups = 0, gn = 0, xcd_local = 0;
-    size_t lds = 0;
-};
+}  // namespace
 
 // Shape, quads per group and placement of the lowest estimated step time in microseconds: per pass and product a fixed
 // part, the matrix instructions, the reduction and gates of a (tile, quad) pair; the operand words; and the part of the
 // exchange that other passes would hide.  The constants are a fit to 700 measured (shape, groups, placement) points over
 // 100 to 1900 units and batches of 1 to 64 (standard error 12 %, which the choice needs only near ties).
-QuadPlan quad_plan(int B, int H, int G, int ndir)
+PersistQuadPlan persist_quad_plan(int B, int H, int G, int ndir)
 {
-    QuadPlan best;
-    double best_us = 1e30;
+    PersistQuadPlan best;
+    if (B < 1 || H < 1 || G < 0 || ndir < 1 || ndir > 2) return best;
     const bool hl = G > 0;
     const int kblocks = std::max((H + 15) / 16, (G + 15) / 16);
     const int tiles = std::max((H + 3) / 4, (G + 3) / 4);
@@ -484,7 +478,8 @@ QuadPlan quad_plan(int B, int H, int G, int ndir)
         const QuadShape& sh = kQuadShapes[i];
         if (sh.hl != hl || sh.kb * kQW < kblocks) continue;
         const int gn = (tiles + sh.nt - 1) / sh.nt;
-        for (int groups = 1; groups <= quads; ++groups) {
+        // (more groups than that fit neither way, so the loop ends there whatever the batch)
+        for (int groups = 1; groups <= quads && ndir * groups * gn <= cus; ++groups) {
             const int mq = (quads + groups - 1) / groups;
             if ((quads + mq - 1) / mq != groups) continue;   // a group would be left without a quad
             const int passes = (mq + sh.qp - 1) / sh.qp;
@@ -493,51 +488,42 @@ QuadPlan quad_plan(int B, int H, int G, int ndir)
             if (lds > 160 * 1024) continue;
             const int per_xcd = (ndir * groups + 7) / 8;
             const int local = gn <= 64 && per_xcd * gn <= cus / 8;
-            if (!local && ndir * groups * gn > cus) continue;
             const double words_kb = (16.0 * H + 64.0 * G) / 1e3;             // operand words of a quad and step
             const double pass = stages * ((local ? 0.42 : 0.63) + 0.0097 * sh.qp * sh.nt * sh.kb * 4 + 0.045 * sh.qp * sh.nt) + 0.033 * sh.qp * words_kb;
             const double us = passes * pass + (passes == 1 ? stages * (local ? 0.29 : 0.59) : 0.0);
-            if (us < best_us) {
-                best_us = best.us = us;
-                best.shape = &sh;
+            if (us < best.us) {
+                best.us = us;
+                best.shape = i;
                 best.mq = mq; best.groups = groups; best.gn = gn; best.xcd_local = local; best.lds = lds;
             }
         }
     }
     return best;
 }
-}  // namespace
-
-bool persist_quad_supported(int B, int H, int G, int ndir)
-{
-    if (B < 1 || H < 1 || G < 0 || ndir < 1 || ndir > 2) return false;
-    return quad_plan(B, H, G, ndir).shape != nullptr;
-}
 
 // exchange words of one launch: h, then u, then (8-byte) XCD id slots of the groups
 static size_t quad_h_words(int B, int H, int ndir) { return (size_t)ndir * ((B + 3) / 4) * 8 * ((H + 15) / 16) * 16; }
 static size_t quad_u_words(int B, int G, int ndir) { return (size_t)ndir * ((B + 3) / 4) * ((G + 15) / 16) * 256; }
-double persist_quad_step_us(int B, int H, int G, int ndir) { return quad_plan(B, H, G, ndir).us; }
 size_t persist_quad_exchange_words(int B, int H, int G, int ndir)
 {
     return quad_h_words(B, H, ndir) + quad_u_words(B, G, ndir) + (size_t)ndir * ((B + 3) / 4) * 64 * 2;
 }
 
-void persist_quad_describe(int B, int H, int G, int ndir, char* buf, size_t n)
+void persist_quad_describe(const PersistQuadPlan& p, char* buf, size_t n)
 {
-    const QuadPlan p = quad_plan(B, H, G, ndir);
-    std::snprintf(buf, n, "(t%d,k%d,q%d,%dx%d%s)", p.shape->nt, p.shape->kb, p.shape->qp, p.groups, p.mq, p.xcd_local ? ",xcd" : "");
+    const QuadShape& sh = kQuadShapes[p.shape];
+    std::snprintf(buf, n, "(t%d,k%d,q%d,%dx%d%s)", sh.nt, sh.kb, sh.qp, p.groups, p.mq, p.xcd_local ? ",xcd" : "");
 }
 
-// words: the launch's exchange region, all zero
-hipError_t launch_persist_quad(PersistQuadArgs& a, unsigned* words, bool cooperative, hipStream_t s)
+// p: the plan of (a.B, a.H, a.G, a.ndir); words: the launch's exchange region, all zero
+hipError_t launch_persist_quad(PersistQuadArgs& a, const PersistQuadPlan& p, unsigned* words, bool cooperative, hipStream_t s)
 {
     if (a.B <= 0 || a.H <= 0 || a.T <= 0) return hipSuccess;
-    const QuadPlan p = quad_plan(a.B, a.H, a.G, a.ndir);
-    if (!p.shape) return hipErrorInvalidValue;
+    if (p.shape < 0) return hipErrorInvalidValue;
+    const QuadShape& sh = kQuadShapes[p.shape];
     a.quads = (a.B + 3) / 4;
     a.mq = p.mq; a.groups = p.groups; a.gn = p.gn; a.xcd_local = p.xcd_local;
-    if (p.xcd_local || p.mq > p.shape->qp) a.poll_pace = 0;   // visible by the time the first read arrives, or other passes in between
+    if (p.xcd_local || p.mq > sh.qp) a.poll_pace = 0;   // visible by the time the first read arrives, or other passes in between
     a.hx = words;
     a.ux = words + quad_h_words(a.B, a.H, a.ndir);
     a.xcc_ids = (unsigned long long*)(a.ux + quad_u_words(a.B, a.G, a.ndir));
@@ -548,16 +534,16 @@ hipError_t launch_persist_quad(PersistQuadArgs& a, unsigned* words, bool coopera
         static std::mutex mu;
         static size_t allowed[kQuadShapeCount];
         std::lock_guard<std::mutex> lock(mu);
-        size_t& have = allowed[p.shape - kQuadShapes];
+        size_t& have = allowed[p.shape];
         if (have < p.lds) {
-            hipError_t e = hipFuncSetAttribute(p.shape->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            hipError_t e = hipFuncSetAttribute(sh.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
             have = 160 * 1024;
         }
     }
     void* kargs[] = {(void*)&a};
-    if (cooperative) return hipLaunchCooperativeKernel(p.shape->kernel, dim3(grid), dim3(kQTH), kargs, (unsigned)p.lds, s);
-    return hipLaunchKernel(p.shape->kernel, dim3(grid), dim3(kQTH), kargs, p.lds, s);
+    if (cooperative) return hipLaunchCooperativeKernel(sh.kernel, dim3(grid), dim3(kQTH), kargs, (unsigned)p.lds, s);
+    return hipLaunchKernel(sh.kernel, dim3(grid), dim3(kQTH), kargs, p.lds, s);
 }
 
 // A row-major fp32 matrix W[rows][cols] in the fragment order of the 16-row matrix instructions: tile (nb, kb) is 64 lanes x

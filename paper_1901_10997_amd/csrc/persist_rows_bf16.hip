@@ -303,29 +303,23 @@ const RowsShape kRowsShapes[] = {
 };
 #undef R_S
 constexpr int kRowsShapeCount = (int)(sizeof(kRowsShapes) / sizeof(kRowsShapes[0]));
-
-struct RowsPlan {
-    const RowsShape* shape = nullptr;
-    double us = 1e30;   // modelled step time
-    int rows = 0, groups = 0, gn = 0, xcd_local = 0;
-    size_t lds = 0;
-};
+}  // namespace
 
 // Shape, rows per group and placement of the lowest estimated step time in microseconds: per pass a fixed part, the matrix
 // instructions, the tiles' partial sums, the h that is read (KB); and the part of the exchange that other passes would
 // hide.  The constants are a fit to 1200 measured (shape, groups, placement) points over 64 to 2000 units and batches of 3
 // to 256 (standard error 10 %).
-RowsPlan rows_plan(int B, int H, int ndir)
+PersistRowsPlan persist_rows_bf16_plan(int B, int H, int ndir)
 {
-    RowsPlan best;
-    double best_us = 1e30;
+    PersistRowsPlan best;
+    if (B < 1 || H < 1 || ndir < 1 || ndir > 2) return best;
     const int kblocks = (H + 31) / 32, tiles = (H + 3) / 4, cus = device_num_cus();
     for (int i = 0; i < kRowsShapeCount; ++i) {
         const RowsShape& sh = kRowsShapes[i];
         if (sh.kb * kRW < kblocks) continue;
         const int gn = (tiles + sh.nt - 1) / sh.nt;
         const int most = std::min(B, 64);
-        for (int groups = 1; groups <= most; ++groups) {
+        for (int groups = 1; groups <= most && ndir * groups * gn <= cus; ++groups) {   // (more fit neither way)
             const int rows = (B + groups - 1) / groups;
             if ((B + rows - 1) / rows != groups) continue;   // a group would be left without a row
             const int passes = (rows + 15) / 16;
@@ -333,46 +327,36 @@ RowsPlan rows_plan(int B, int H, int ndir)
             if (lds > 160 * 1024) continue;
             const int per_xcd = (ndir * groups + 7) / 8;
             const int local = gn <= 64 && per_xcd * gn <= cus / 8;
-            if (!local && ndir * groups * gn > cus) continue;
             const double h_kb = std::min(rows, 16) * H * 2e-3;
             const double pass = (local ? 0.95 : 1.1) + 0.027 * sh.nt * sh.kb + (local ? 0.02 : 0.04) * sh.nt + (local ? 0.016 : 0.01) * h_kb;
             const double us = passes * pass + (passes == 1 ? (local ? 0.32 : 0.56) : 0.0);
-            if (us < best_us) {
-                best_us = best.us = us;
-                best.shape = &sh;
+            if (us < best.us) {
+                best.us = us;
+                best.shape = i;
                 best.rows = rows; best.groups = groups; best.gn = gn; best.xcd_local = local; best.lds = lds;
             }
         }
     }
     return best;
 }
-}  // namespace
 
-bool persist_rows_bf16_one_pass(int B, int H, int ndir) { return persist_rows_bf16_supported(B, H, ndir) && rows_plan(B, H, ndir).rows <= 16; }
-bool persist_rows_bf16_supported(int B, int H, int ndir)
-{
-    return B >= 1 && H >= 1 && ndir >= 1 && ndir <= 2 && rows_plan(B, H, ndir).shape != nullptr;
-}
-double persist_rows_bf16_step_us(int B, int H, int ndir) { return rows_plan(B, H, ndir).us; }
 // 8-byte words of one launch: h, then the XCD id slots of the groups
-static size_t rows_h_words(const RowsPlan& p, int H, int ndir) { return (size_t)ndir * p.groups * 2 * ((H + 31) / 32) * 8 * p.rows; }
-size_t persist_rows_bf16_exchange_words(int B, int H, int ndir)
+static size_t rows_h_words(const PersistRowsPlan& p, int H, int ndir) { return (size_t)ndir * p.groups * 2 * ((H + 31) / 32) * 8 * p.rows; }
+size_t persist_rows_bf16_exchange_words(const PersistRowsPlan& p, int H, int ndir)
 {
-    const RowsPlan p = rows_plan(B, H, ndir);
-    return p.shape ? rows_h_words(p, H, ndir) + (size_t)ndir * p.groups * 64 : 0;
+    return p.shape >= 0 ? rows_h_words(p, H, ndir) + (size_t)ndir * p.groups * 64 : 0;
 }
-void persist_rows_bf16_describe(int B, int H, int ndir, char* buf, size_t n)
+void persist_rows_bf16_describe(const PersistRowsPlan& p, char* buf, size_t n)
 {
-    const RowsPlan p = rows_plan(B, H, ndir);
-    std::snprintf(buf, n, "(t%d,k%d,%dx%d%s)", p.shape->nt, p.shape->kb, p.groups, p.rows, p.xcd_local ? ",xcd" : "");
+    std::snprintf(buf, n, "(t%d,k%d,%dx%d%s)", kRowsShapes[p.shape].nt, kRowsShapes[p.shape].kb, p.groups, p.rows, p.xcd_local ? ",xcd" : "");
 }
 
-// words: the launch's exchange region, all zero
-hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, unsigned long long* words, bool cooperative, hipStream_t s)
+// p: the plan of (a.B, a.H, a.ndir); words: the launch's exchange region, all zero
+hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, const PersistRowsPlan& p, unsigned long long* words, bool cooperative, hipStream_t s)
 {
     if (a.B <= 0 || a.H <= 0 || a.T <= 0) return hipSuccess;
-    const RowsPlan p = rows_plan(a.B, a.H, a.ndir);
-    if (!p.shape) return hipErrorInvalidValue;
+    if (p.shape < 0) return hipErrorInvalidValue;
+    const void* const kernel = kRowsShapes[p.shape].kernel;
     a.rows = p.rows; a.groups = p.groups; a.gn = p.gn; a.xcd_local = p.xcd_local;
     if (p.xcd_local || p.rows > 16) a.poll_pace = 0;   // visible by the time the first read arrives, or other passes in between
     a.hx = words;
@@ -384,16 +368,16 @@ hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, unsigned long long* word
         static std::mutex mu;
         static bool allowed[kRowsShapeCount];
         std::lock_guard<std::mutex> lock(mu);
-        bool& have = allowed[p.shape - kRowsShapes];
+        bool& have = allowed[p.shape];
         if (!have) {
-            const hipError_t e = hipFuncSetAttribute(p.shape->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
             have = true;
         }
     }
     void* kargs[] = {(void*)&a};
-    if (cooperative) return hipLaunchCooperativeKernel(p.shape->kernel, dim3(grid), dim3(kRTH), kargs, (unsigned)p.lds, s);
-    return hipLaunchKernel(p.shape->kernel, dim3(grid), dim3(kRTH), kargs, p.lds, s);
+    if (cooperative) return hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(kRTH), kargs, (unsigned)p.lds, s);
+    return hipLaunchKernel(kernel, dim3(grid), dim3(kRTH), kargs, p.lds, s);
 }
 
 // A row-major bf16 matrix W[rows][cols] in the operand order of the 16x16x32 matrix instruction: tile (nb, kb) is 64 lanes x

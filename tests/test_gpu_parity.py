@@ -966,3 +966,26 @@ def test_masked_bf16_projection_of_odd_widths_over_the_kept_entries(bidir, D, H,
     for d in range(2 if bidir else 1):
         assert f"l0.d{d}:proj=dense,rec=persist_batched-q16" in desc, desc     # bf16 input rows: padded
         assert f"l1.d{d}:proj={upper},rec=persist_batched-q16" in desc, desc
+
+
+@pytest.mark.parametrize("Bn,dtype", [(64, "f32"), (1024, "f32"), (1024, "bf16")])
+def test_host_side_of_a_forward_does_not_grow_with_the_batch(Bn, dtype):
+    """The launch shapes of a layer are searched once per batch size, not several times per layer and call.  Five layers are a
+    dozen or two launches; the bound is ten times what those take and a third of what the searches took at batch 1024."""
+    import time
+    import torch
+    m = B.Lstm(5, 64, 128, False, B.LSTM_BF16 if dtype == "bf16" else B.LSTM_F32)
+    rng = np.random.default_rng(3)
+    draw = lambda r, c: rng.uniform(-0.05, 0.05, (r, c)).astype(np.float32)
+    m.set_weights_from({(l, 0): dict(Wx=draw(512, 64 if l == 0 else 128), Wh=draw(512, 128), b=np.zeros(512, np.float32))
+                        for l in range(5)})
+    x = torch.randn(4, Bn, 64, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    best = 1e9
+    for _ in range(20):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        m.forward(x, check=False)
+        best = min(best, time.perf_counter() - t0)
+    torch.cuda.synchronize()
+    m.close()
+    assert best < 400e-6, best
