@@ -1159,7 +1159,7 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     const DensePlans p = dense_plans(m, l, B);
     if (p.cut.chunks == 0) return false;
     if (B > 1 && csr < Dn) return true;
-    if (m->plan == LSTM_PLAN_PERSISTENT && (G == 0 || csr > 0)) return false;
+    if (m->plan == LSTM_PLAN_PERSISTENT) return false;   // asks for the kernels of the matrices' own form
     double us = T * p.cut.passes * p.cut.chunks * p.quad[0].us, other = 0;
     if (B > 1) {
         us += kDenseSetupUs;
