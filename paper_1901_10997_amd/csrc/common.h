@@ -515,6 +515,8 @@ struct PersistBatchedHArgs {
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
 hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int ndir, int slots, int cooperative, hipStream_t s);
 
+// Lets `kernel` be launched with up to `bytes` of dynamic LDS on the current device (util_kernels.hip).
+hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
 // Scratch of the calls that have no handle and wait for their result (util_kernels.hip): device memory and a line of 64
 // bytes of pinned host memory, which kernels may write.
 struct ScratchArea {

@@ -38,8 +38,6 @@
 #include "device_math.h"
 #include "exchange.h"
 
-#include <mutex>
-
 namespace l355 {
 
 namespace {
@@ -531,15 +529,8 @@ hipError_t launch_persist_quad(PersistQuadArgs& a, const PersistQuadPlan& p, uns
     // every workgroup must be resident at the same time: at most one per compute unit
     if (grid > device_num_cus()) return hipErrorCooperativeLaunchTooLarge;
     if (p.lds > 64 * 1024) {
-        static std::mutex mu;
-        static size_t allowed[kQuadShapeCount];
-        std::lock_guard<std::mutex> lock(mu);
-        size_t& have = allowed[p.shape];
-        if (have < p.lds) {
-            hipError_t e = hipFuncSetAttribute(sh.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            have = 160 * 1024;
-        }
+        const hipError_t e = allow_dynamic_lds(sh.kernel, 160 * 1024);
+        if (e != hipSuccess) return e;
     }
     void* kargs[] = {(void*)&a};
     if (cooperative) return hipLaunchCooperativeKernel(sh.kernel, dim3(grid), dim3(kQTH), kargs, (unsigned)p.lds, s);

@@ -26,8 +26,6 @@
 #include "device_math.h"
 #include "exchange.h"
 
-#include <mutex>
-
 namespace l355 {
 
 namespace {
@@ -365,15 +363,8 @@ hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, const PersistRowsPlan& p
     // every workgroup must be resident at the same time: at most one per compute unit
     if (grid > device_num_cus()) return hipErrorCooperativeLaunchTooLarge;
     if (p.lds > 64 * 1024) {
-        static std::mutex mu;
-        static bool allowed[kRowsShapeCount];
-        std::lock_guard<std::mutex> lock(mu);
-        bool& have = allowed[p.shape];
-        if (!have) {
-            const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            have = true;
-        }
+        const hipError_t e = allow_dynamic_lds(kernel, 160 * 1024);
+        if (e != hipSuccess) return e;
     }
     void* kargs[] = {(void*)&a};
     if (cooperative) return hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(kRTH), kargs, (unsigned)p.lds, s);

@@ -453,9 +453,7 @@ static hipError_t launch_line_sums(const float* W, const uint8_t* mask, int M, i
 {
     const bool vec = (N & 3) == 0 && ((uintptr_t)W & 15) == 0 && ((uintptr_t)mask & 3) == 0;
     const void* kern = vec ? (const void*)line_abs_sum_f64_kernel<COLS, true, AFTER> : (const void*)line_abs_sum_f64_kernel<COLS, false, AFTER>;
-    static std::once_flag once[2];
-    hipError_t e = hipSuccess;
-    std::call_once(once[vec ? 1 : 0], [&] { e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSumLds); });
+    const hipError_t e = allow_dynamic_lds(kern, kSumLds);
     if (e != hipSuccess) return e;
     const int lines = COLS ? N : M;
     void* args[] = {&W, &mask, &M, &N, &sums, &after, &rsums, &th};

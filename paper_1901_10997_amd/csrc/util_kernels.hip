@@ -2,7 +2,9 @@
 // graph) and a streaming copy used to quote the achievable memory bandwidth next to the spec-sheet figure.
 #include "common.h"
 
+#include <map>
 #include <mutex>
+#include <utility>
 
 namespace l355 {
 
@@ -83,6 +85,23 @@ int device_num_cus()
             cached = 256;
     }
     return cached;
+}
+
+// The limit belongs to the device as well as the kernel.  It is set once for each pair (or again for a larger size); a call
+// that fails leaves nothing behind, so the next one tries again.
+hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
+{
+    static std::mutex mu;
+    static std::map<std::pair<int, const void*>, size_t> allowed;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto it = allowed.find({dev, kernel});
+    if (it != allowed.end() && it->second >= bytes) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) allowed[{dev, kernel}] = bytes;
+    return e;
 }
 
 // ---- scratch of the calls that have no handle and wait for their result (mask updates, compaction) -----------------

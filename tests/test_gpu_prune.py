@@ -136,3 +136,41 @@ def test_mask_updates_at_tile_edges_and_alignments(M, N, off):
         np.testing.assert_array_equal(Wp[off:].cpu().numpy().reshape(M, N).view(np.uint32), Wr.view(np.uint32))
         r_ref, c_ref = oprune.prune_rows_cols_lines(W, mask, pr, pc)
         assert (rows, cols) == (int(r_ref.sum()), int(c_ref.sum()))
+
+
+def test_mask_updates_from_more_threads_than_scratch_areas():
+    """Eight threads, a stream each, at once: four can have an area of the library's scratch, the others (and the matrix with
+    more sums than an area holds) allocate for the call.  Every thread's masks, weights and counts are the oracle's."""
+    import threading
+    import torch
+    shapes = [(300, 200), (257, 131), (64, 1000), (70000, 2), (512, 512), (1000, 96), (33, 77), (400, 301)]
+    rng = np.random.default_rng(77)
+    host = [(rng.standard_normal(s).astype(np.float32), (rng.random(s) < 0.7).astype(np.uint8)) for s in shapes]
+    want = []
+    for W, mask in host:
+        m1 = oprune.prune_weights(W, mask, 0.4)
+        W2, m2 = oprune.prune_rows_cols(W, m1, 0.2, 0.1)
+        want.append((int(mask.sum()), int(m1.sum()), W2, m2))
+    start, errors = threading.Barrier(len(shapes)), []
+
+    def work(i):
+        try:
+            (W, mask), (M, N), stream = host[i], shapes[i], torch.cuda.Stream()
+            start.wait()
+            for _ in range(6):
+                with torch.cuda.stream(stream):
+                    dW, dm = _dev(W), _dev(mask)
+                    got = B.lstm_prune_weights(dW.data_ptr(), dm.data_ptr(), M * N, 0.4, stream.cuda_stream)
+                    B.lstm_prune_rows_cols(dW.data_ptr(), dm.data_ptr(), M, N, 0.2, 0.1, stream.cuda_stream)
+                    assert got == want[i][:2], (i, got)
+                    np.testing.assert_array_equal(dm.cpu().numpy(), want[i][3])
+                    np.testing.assert_array_equal(dW.cpu().numpy().view(np.uint32), want[i][2].view(np.uint32))
+        except BaseException as e:   # reported by the main thread
+            errors.append((i, e))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(shapes))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
