@@ -250,6 +250,35 @@ struct PersistMfmaArgs {
     int T, B, H, reverse;
 };
 bool persist_mfma_supported(int B, int H);
+// fp32 dense recurrence of narrow layers over many batch columns (all directions of a layer per launch)
+struct PersistDenseDir {
+    const float* P;            // [T*Bld][4H]
+    const float* Wh;           // [4H][H] fp32, packed rows
+    const float* c0;           // [B][H] or nullptr
+    float* y;                  // h_t -> y[(t*Bld + b)*y_ld + j]
+    int y_ld;
+    float* hT;
+    float* cT;
+    int reverse;
+    int has_h0;                // exchange buffer 1 holds h0 (set by the launcher)
+};
+struct PersistDenseArgs {
+    PersistDenseDir d[2];
+    int* timeout_flag;
+    unsigned spin_limit;
+    int T, B, Bld, H, ndir;    // Bld: rows per timestep in P and y (>= B: the launch may cover a run of the batch's columns)
+    int poll_pace;             // pace_poll units in front of a step's first read of h (exchange.h)
+    int device_scope_only;     // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
+    // set by the launcher
+    int gm, gn, xcd_local;     // row blocks, workgroups per row block, block ids grouped by XCD
+    float* hx;                 // per direction two exchange buffers of ceil(H/16) * Bp * 16 words (Bp: B rounded up to the row blocks)
+    unsigned long long* xcc_ids;  // [ndir * row blocks][64] slots for the XCD ids of a group's workgroups
+};
+int persist_dense_f32_row_blocks(int B, int H, int ndir);   // 16-row blocks per workgroup, 0: not taken
+double persist_dense_f32_step_us(int mt, int B, int H, int ndir);   // modelled time of a step
+size_t persist_dense_f32_exchange_words(int mt, int B, int H, int ndir);
+// h0[d]: fp32 [B][H] of direction d or nullptr
+hipError_t launch_persist_dense_f32(PersistDenseArgs& a, int mt, const float* const* h0, unsigned* words, bool cooperative, hipStream_t s);
 // bf16 dense recurrence at any batch from 2 (all directions of a layer per launch)
 struct PersistRowsDir {
     const float* P;            // [T*B][4H]
@@ -323,6 +352,7 @@ struct PersistQuadPlan {   // how a launch of (B, H, G, ndir) is laid out
     size_t lds = 0;
 };
 PersistQuadPlan persist_quad_plan(int B, int H, int G, int ndir);
+double persist_quad_many_columns_us(const PersistQuadPlan& p, int H, int ndir);
 size_t persist_quad_exchange_words(int B, int H, int G, int ndir);
 void persist_quad_describe(const PersistQuadPlan& p, char* buf, size_t n);
 hipError_t launch_persist_quad(PersistQuadArgs& a, const PersistQuadPlan& p, unsigned* words, bool cooperative, hipStream_t s);

@@ -13,6 +13,17 @@ __device__ __forceinline__ u64 pack_slot(float v, unsigned tag)
     return ((u64)tag << 32) | (u64)__float_as_uint(v);
 }
 
+// fp32 values of h published as one word, with one bit of the step count in the top exponent bit (clear in every |value| < 2).
+constexpr unsigned kHStampBit = 0x40000000u;
+// A published word without its stamp.  A NaN has bit 30 set itself and |h| <= 1 else: without that bit a (quiet) NaN is a pattern
+// of at least 1.5, from which the addition carries into bit 30 again.  strip: kHStampBit, or 0 to take the word
+// as it is.
+__device__ __forceinline__ float unstamped(unsigned v, unsigned strip)
+{
+    const unsigned carried = (v & (kHStampBit - 1u)) + 0x00400000u;
+    return __uint_as_float((v & ~strip) | (carried & strip));
+}
+
 // Pacing of a poll that would otherwise follow the wave's own publication at once.  A device-scope store takes about
 // 0.3 us plus half a load round trip to become visible to the other XCDs; a poll round issued before that comes back
 // without the value and the next round costs a whole further round trip (about 1 us with a few thousand slots polled by

@@ -23,6 +23,8 @@ struct DensePlans {
     int B = 0;
     LaunchCut cut;                // fp32: launches (chunks = 0: no form fits) ...
     PersistQuadPlan quad[2];      // ... of the longer and the shorter runs of columns
+    LaunchCut tile_cut;           // fp32 LSTM layers whose many columns go faster as tiles (persist_dense_f32.hip); chunks = 0: none
+    int tile_rows[2] = {0, 0};    // 16-row blocks per workgroup, as above
     PersistRowsPlan rows;         // bf16
 };
 
@@ -156,6 +158,8 @@ constexpr int kPollPaceBatchedDeviceWide = 8;
 // 10 to 18 (800 units, batch 4: 2.42 us per step unpaced, 2.18 at 10, 1.94 at 14, 2.20 at 24; H-LSTM 1500/1500, batch 1:
 // 8.80, 8.31, 8.14, 8.46).
 constexpr int kPollPaceQuad = 13;
+// ... and of its form for many columns (H = 256, batch 16: 2.48 us per step unpaced, 2.31 at 16, 2.54 at 24)
+constexpr int kPollPaceTiles = 16;
 // the yardsticks try these and report the fastest
 static const int kYardstickPaces[] = {0, 6, 10, 12, 16};
 
@@ -886,6 +890,20 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
             p.quad[0] = plan((B + p.cut.chunks - 1) / p.cut.chunks, m->Dn / p.cut.passes);
             p.quad[1] = B % p.cut.chunks == 0 ? p.quad[0] : plan(B / p.cut.chunks, m->Dn / p.cut.passes);
         }
+        // Both fits are within 10 % in nineteen of twenty points, and where they are level so are the kernels.  Up to 64 columns
+        // the quads win at every width.
+        LaunchCut c;
+        if (G == 0 && p.cut.chunks > 0 && B * m->Dn > 64 &&
+            choose_cut(B, m->Dn, [&](int b, int nd) { return persist_dense_f32_row_blocks(b, H, nd) > 0; }, &c)) {
+            const int nd = m->Dn / c.passes, hi = (B + c.chunks - 1) / c.chunks, lo = B / c.chunks;
+            const int mt = persist_dense_f32_row_blocks(hi, H, nd);
+            if (c.passes * c.chunks * persist_dense_f32_step_us(mt, hi, H, nd) <
+                p.cut.passes * p.cut.chunks * persist_quad_many_columns_us(p.quad[0], H, m->Dn / p.cut.passes)) {
+                p.tile_cut = c;
+                p.tile_rows[0] = mt;
+                p.tile_rows[1] = persist_dense_f32_row_blocks(lo, H, nd);
+            }
+        }
     }
     return p;
 }
@@ -893,6 +911,13 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
 static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
 {
     return align256(4 * persist_quad_exchange_words((B + cut.chunks - 1) / cut.chunks, m->hid(l), m->ghid(l), m->Dn / cut.passes)) / 4;
+}
+static size_t tile_launch_words(const lstm_t* m, int l, int B, const DensePlans& p)
+{
+    const LaunchCut& cut = p.tile_cut;
+    const int nd = m->Dn / cut.passes;
+    return align256(4 * std::max(persist_dense_f32_exchange_words(p.tile_rows[0], (B + cut.chunks - 1) / cut.chunks, m->hid(l), nd),
+                                 persist_dense_f32_exchange_words(p.tile_rows[1], B / cut.chunks, m->hid(l), nd))) / 4;
 }
 static size_t state_floats(const lstm_t* m, int B)   // of all layers and directions
 {
@@ -979,8 +1004,11 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // (whether a layer's recurrent matrices are held dense is not known before its weights are set)
     w.qx_off = off;
     for (int l = 0; l < m->L; ++l) {
-        const LaunchCut cut = dense_plans(m, l, B).cut;
-        if (cut.chunks > 0) w.qx_words += quad_launch_words(m, l, B, cut) * cut.passes * cut.chunks;
+        const DensePlans p = dense_plans(m, l, B);
+        size_t words = 0;
+        if (p.cut.chunks > 0) words = quad_launch_words(m, l, B, p.cut) * p.cut.passes * p.cut.chunks;
+        if (p.tile_cut.chunks > 0) words = std::max(words, tile_launch_words(m, l, B, p) * p.tile_cut.passes * p.tile_cut.chunks);
+        w.qx_words += words;
     }
     off += align256(w.qx_words * sizeof(unsigned));
     // ... and of the bf16 one
@@ -1216,17 +1244,64 @@ static bool fuses_input(const lstm_t* m, int l, int T, int B)
     return mode[0] == 1 || mode[0] == 2 || mode[1] == 1 || mode[1] == 2;
 }
 
+// As run_quad_layer below, with the tiles of persist_dense_f32.hip.
+static int run_tile_layer(lstm_t* m, int l, int T, int B, const DensePlans& p, float* const* P, const float* h0, const float* c0,
+                          float* Yout, int y_ld, float* hT, float* cT, const char* const (&proj)[2], QuadRegions& reg, hipStream_t s)
+{
+    const int Dn = m->Dn, H = m->hid(l);
+    const LaunchCut& cut = p.tile_cut;
+    const size_t words = tile_launch_words(m, l, B, p);
+    for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
+        const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
+        const int nd = Dn / cut.passes, d_lo = pass * nd;
+        const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
+        const int mt = p.tile_rows[bn == (B + cut.chunks - 1) / cut.chunks ? 0 : 1];
+        PersistDenseArgs a{};
+        const float* h0d[2] = {nullptr, nullptr};
+        for (int d = d_lo; d < d_lo + nd; ++d) {
+            const LayerDir& w = m->ld[(size_t)l * Dn + d];
+            const size_t so = m->soff((size_t)l * Dn + d) * B + (size_t)b_lo * H;
+            PersistDenseDir& q = a.d[d - d_lo];
+            q.P = P[d] + (size_t)b_lo * 4 * H;
+            q.Wh = (const float*)w.wh.dense;
+            q.c0 = c0 ? c0 + so : nullptr;
+            q.y = Yout + (size_t)b_lo * y_ld + (size_t)d * H; q.y_ld = y_ld;
+            q.hT = hT ? hT + so : nullptr;
+            q.cT = cT ? cT + so : nullptr;
+            q.reverse = d;
+            h0d[d - d_lo] = h0 ? h0 + so : nullptr;
+            if (chunk == 0) {
+                char tag[96], cuts[24] = "";
+                if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, "(batch/%d)", cut.chunks);
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-f32(rows%d)%s;", l, d, proj[d], 16 * mt, cuts);
+                m->last_plan += tag;
+            }
+        }
+        a.T = T; a.B = bn; a.Bld = B; a.H = H; a.ndir = nd;
+        a.device_scope_only = m->device_scope_only;
+        a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
+        a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceTiles;
+        ProfSpan span(m, s, 1);
+        HIP_TRY(m, launch_persist_dense_f32(a, mt, h0d, reg.next, m->launch_mode() != 0, s));
+        reg.next += words;
+    }
+    return LSTM_OK;
+}
+
 // Recurrence of layer l with its dense fp32 matrices (W_h; H-LSTM: W1h and W2), time loop on the device.
 static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const float* h0, const float* c0, float* Yout, int y_ld,
                           float* hT, float* cT, const char* const (&proj)[2], const Workspace& ws, char* base, QuadRegions& reg, hipStream_t s)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l), R = 4 * (G > 0 ? G : H);
     const DensePlans p = dense_plans(m, l, B);
-    const LaunchCut& cut = p.cut;
     if (!reg.next) {
         reg.next = (unsigned*)(base + ws.qx_off);
         HIP_TRY(m, launch_fill_u64((unsigned long long*)reg.next, align256(ws.qx_words * 4) / 8, 0ull, s));
     }
+    bool dense = true;
+    for (int d = 0; d < Dn; ++d) dense = dense && m->ld[(size_t)l * Dn + d].wh.dense;
+    if (dense && p.tile_cut.chunks > 0) return run_tile_layer(m, l, T, B, p, P, h0, c0, Yout, y_ld, hT, cT, proj, reg, s);
+    const LaunchCut& cut = p.cut;
     const size_t words = quad_launch_words(m, l, B, cut);
     for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
         const int pass = launch / cut.chunks, chunk = launch % cut.chunks;

@@ -43,7 +43,7 @@ namespace l355 {
 namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int kQW = 8, kQTH = 512;
-constexpr unsigned kHBit = 0x40000000u, kUBit = 0x80000000u;
+constexpr unsigned kHBit = kHStampBit, kUBit = 0x80000000u;
 
 // one fp32 word of a lane moved inside its 16-lane row
 template <int CTRL>
@@ -60,13 +60,6 @@ __device__ __forceinline__ float quad_sum(const f32x4& a)
     const float k13 = __uint_as_float(s13[0]) + __uint_as_float(s13[1]);
     const auto sr = __builtin_amdgcn_permlane16_swap(__float_as_uint(k02), __float_as_uint(k13), false, false);
     return __uint_as_float(sr[0]) + __uint_as_float(sr[1]);
-}
-// A published word without its stamp.  A NaN has bit 30 set itself and |h| <= 1 else: without that bit a (quiet) NaN is a pattern
-// of at least 1.5, from which the addition carries into bit 30 again.  strip: kHBit, or 0 to take the word as it is.
-__device__ __forceinline__ float unstamped(unsigned v, unsigned strip)
-{
-    const unsigned carried = (v & (kHBit - 1u)) + 0x00400000u;
-    return __uint_as_float((v & ~strip) | (carried & strip));
 }
 // Counts a failed round of a bounded wait; true when the wait is to be given up.
 __device__ __forceinline__ bool give_up(unsigned& spins, unsigned limit, int* flag)
@@ -497,6 +490,18 @@ PersistQuadPlan persist_quad_plan(int B, int H, int G, int ndir)
         }
     }
     return best;
+}
+
+// Time of a step of an LSTM plan where many columns meet a narrow layer: a fit to 700 measured points of 16 to 512 units and 80
+// to 4096 columns (standard error 8 %), with the terms that the choice of a shape can do without (groups that share an XCD's
+// L2, more items of a pass than waves).  persist_quad_plan's own model is up to 40 % low there.
+double persist_quad_many_columns_us(const PersistQuadPlan& p, int H, int ndir)
+{
+    const QuadShape& sh = kQuadShapes[p.shape];
+    const int items = sh.qp * sh.nt, passes = (p.mq + sh.qp - 1) / sh.qp;
+    const double pass = 0.50 + (p.xcd_local ? 0.0 : 0.10) + 0.0073 * items * sh.kb * 4 + 0.048 * items + 0.023 * std::max(0, items - 8) +
+                        0.023 * sh.qp * 16e-3 * H + 0.030 * sh.qp * ((ndir * p.groups + 7) / 8);
+    return passes * pass + (passes == 1 ? 0.35 : 0.0);
 }
 
 // exchange words of one launch: h, then u, then (8-byte) XCD id slots of the groups

@@ -989,3 +989,35 @@ def test_host_side_of_a_forward_does_not_grow_with_the_batch(Bn, dtype):
     torch.cuda.synchronize()
     m.close()
     assert best < 400e-6, best
+
+
+@pytest.mark.parametrize("shape", [
+    # L, bidir, D, H, T, B -- narrow dense fp32 layers over many columns: sixteen batch rows per tile
+    (1, False, 20, 64, 5, 500),      # one row block per workgroup, ragged
+    (1, True, 24, 100, 4, 200),      # two, both directions
+    (2, False, 33, 128, 4, 1000),    # four, k-blocks per wave: one
+    (1, False, 24, 201, 4, 500),     # two k-blocks per wave, the last one ragged
+    (1, True, 16, 37, 3, 2100),
+    (1, False, 16, 128, 3, 2101),    # runs of 1050 and 1051 columns
+])
+def test_dense_f32_many_columns(shape):
+    L, bidir, D, H, T, Bn = shape
+    for rs in (False, True):
+        case = inputs.make_case(_wl(99, L, bidir, D, H, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, D)))), k=H + Bn, random_state=rs)
+        desc, _ = check_case(case, DENSE, PAUTO, cooperative=rs)
+        assert desc.count("rec=persist-dense-f32(rows") == L * (2 if bidir else 1), desc
+
+
+@pytest.mark.parametrize("shape", [
+    (1, False, 24, 150, 4, 60),      # several quads in a pass, passes
+    (1, True, 24, 300, 4, 130),
+])
+def test_dense_f32_quads_in_passes(shape):
+    L, bidir, D, H, T, Bn = shape
+    case = inputs.make_case(_wl(99, L, bidir, D, H, T, Bn, a=min(0.3, 1.5 / np.sqrt(max(H, D)))), k=H + Bn, random_state=True)
+    desc, _ = check_case(case, DENSE, PAUTO)
+    assert "rec=persist-dense-f32(t" in desc, desc
+
+
+def test_nan_state_over_many_columns():
+    test_nan_state_reaches_every_unit_of_its_own_sequence((1, True, 24, 100, 5, 200, "f32", None, "persist-dense-f32(rows"))
