@@ -25,8 +25,8 @@
 //         (An acquire fence followed by ordinary cached loads measured three times slower for these 50 KB.)
 // One array and one flag per vector are enough: u_{t+1} is written, and its flag raised, only after the producer has
 // received every h_t of the batch group, and each of those was published after its producer had finished reading u_t; a
-// workgroup that owns no output unit (G > H) publishes no h that anybody could wait for, so it has no second half and
-// reads neither u nor the flags.  h_{t+1} is published only after every workgroup's flag for u_{t+1}, which each raises
+// workgroup that owns no output unit (G > H) publishes no h that anybody could wait for, so it reads neither u nor the
+// flags and nothing of its second half is used.  h_{t+1} is published only after every workgroup's flag for u_{t+1}, which each raises
 // (units of u or not) after it has finished reading h_t.  Where the batch groups fit one XCD each and the launch has verified the placement from the hardware's
 // XCD ids, h, u and the flags are stored at workgroup scope and meet in that XCD's L2 (exchange.h).
 // All waits are bounded: on expiry a device flag is raised, every wave stops waiting, the kernel drains.
@@ -271,9 +271,8 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
         __syncthreads();
         if (tid == 0) exchange_store(flags + ugi, tag, same_xcd);
-        if (!owns_h) continue;
         // ---- stage 2: gate outputs from u_t, cell update
-        if (wave == 0) {
+        if (wave == 0 && owns_h) {
             unsigned spins = 0;
             while (__hip_atomic_load(flags + poll_i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != tag) {
                 if (++spins > a.spin_limit) {
@@ -291,7 +290,7 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
             // flight at once
             const u64* src = reinterpret_cast<const u64*>(xu);
             u64* dst = reinterpret_cast<u64*>(ubuf);
-            const int nw = 2 * G * BW;   // 4G*BW floats, two to a load
+            const int nw = owns_h ? 2 * G * BW : 0;   // 4G*BW floats, two to a load
             for (int e0 = tid; e0 < nw; e0 += 16 * nthreads) {
                 u64 v[16];
 #pragma unroll
