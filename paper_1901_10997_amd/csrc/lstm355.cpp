@@ -1179,10 +1179,12 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
     if (m->plan == LSTM_PLAN_STEPWISE) return false;
     int csr = 0;
+    bool one_slice = true;   // every row of the row-compressed matrices in a single 64-lane slice
     for (int d = 0; d < Dn; ++d) {
         const LayerDir& w = m->ld[(size_t)l * Dn + d];
         if (!w.wh.dense_frag16 || (G > 0 && !w.w2.dense_frag16)) return false;
         csr += w.wh.compressed;
+        one_slice = one_slice && w.wh.ell_val && w.wh.slots == 1 && (G == 0 || (w.w2.ell_val && w.w2.slots == 1));
     }
     const DensePlans p = dense_plans(m, l, B);
     if (p.cut.chunks == 0) return false;
@@ -1192,6 +1194,10 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     if (B > 1) {
         us += kDenseSetupUs;
         other = T * batched_csr_step_us(m, l, B);
+        // From 2048 columns on (both directions counted) a step of an H-LSTM layer with such short rows is two full launches,
+        // level with the quads or up to a tenth faster (200 units, 6 % kept: 68 against 75 us); with longer rows or an LSTM
+        // cell the quads are 1.1 to 3 times faster.
+        if (other >= 1e9 && G > 0 && one_slice && B * Dn >= 2048 && hstep_pair_supported(H, G, 1, 1)) return false;
     } else {
         if (m->waves_per_group > 0) return csr == 0 && G > 0;   // a launch shape the caller set for the batch-1 kernels
         us += kSeparateProjUs;

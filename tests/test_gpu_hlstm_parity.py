@@ -507,3 +507,11 @@ def test_hlstm_gate_width_far_from_the_hidden_width(shape):
     case = inputs.make_case(_hw(96, L, bidir, D, H, G, T, Bn, a=0.5 / np.sqrt(max(H, G) * (keep or 1.0)), keep=keep), k=H, random_state=True)
     desc, _ = check_case(case, fmt, PAUTO)
     assert desc.count("rec=" + rec) == L * (2 if bidir else 1), desc
+
+
+@pytest.mark.parametrize("bidir,H,keep,Bn,rec", [(True, 160, 0.06, 1024, "hlstm-stepwise-pair-csr"), (False, 357, 0.06, 2048, "hlstm-stepwise-pair-csr"),
+                                                 (True, 200, 0.45, 1024, "persist-dense-hlstm")])
+def test_hlstm_short_rows_over_many_columns(bidir, H, keep, Bn, rec):
+    case = inputs.make_case(_hw(88, 1, bidir, 16, H, H, 2, Bn, a=0.1, keep=keep), k=H, random_state=True)
+    desc, _ = check_case(case, AUTO, PAUTO, oracle_cols=[0, 3, 511, Bn - 1])
+    assert desc.count("rec=" + rec) == (2 if bidir else 1), desc
