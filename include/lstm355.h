@@ -125,7 +125,9 @@ const char* lstm_last_error(const lstm_t* m);
  * The library copies everything; the caller may free its arrays on return.  Synchronous.
  * Device memory held per (layer, direction): the input-side matrix is always kept dense (4H * D_l values; in fp32
  * models a second time in the operand order of the matrix instruction, for products with at most 64 input rows) and,
- * when row-compressed, in the compressed forms as well; the recurrent matrix in the one form its kernels read.
+ * when row-compressed, in the compressed forms as well; the recurrent matrix in the forms its kernels read: compressed,
+ * or dense (4H * H values, and once more in the operand order of the matrix instruction where a kernel holds it so), or,
+ * for the fp32 matrices that LSTM_FMT_AUTO compressed, compressed and in that order (1500 units: 7 + 36 MB at 10 % kept).
  */
 int lstm_set_weights(lstm_t* m, int layer, int direction,
                      const float* Wx, const uint8_t* mask_x,
@@ -160,9 +162,9 @@ size_t lstm_workspace_bytes(const lstm_t* m, int T, int B);
  *   stream              hipStream_t passed as void*; NULL = the default stream
  * Asynchronous on `stream`: no host synchronisation and no allocation inside.  T = 0 or B = 0 is a
  * no-op that returns LSTM_OK.  Two forwards on the same handle must not overlap in time.  The persistent kernels
- * (batch 1, small-batch row-compressed, and large-batch bf16) occupy every compute unit for the duration of a layer: forwards issued
- * on other streams at the same time wait for them (cooperative launch) or, with ordinary launches, may make the
- * bounded waits expire (LSTM_ERR_TIMEOUT from lstm_check).
+ * (every plan but the stepwise ones) occupy up to every compute unit for the duration of a layer: forwards issued on other
+ * streams at the same time wait for them (cooperative launch) or, with ordinary launches, may make the bounded waits
+ * expire (LSTM_ERR_TIMEOUT from lstm_check).
  * Graph capture: a forward may be issued on a stream that is being captured (hipStreamBeginCapture); the library
  * notices and records a form that can be replayed any number of times, between eager forwards or other graphs of the
  * same handle: exchange state is cleared by fill kernels inside the graph (no memset nodes), the step tags of the

@@ -705,9 +705,11 @@ const char* lstm_last_error(const lstm_t* m) { return m ? m->err.c_str() : g_cre
 static bool auto_compressed(const lstm_t* m, int layer, int direction, bool masked, size_t kept, size_t total)
 {
     if (!masked) return false;
-    // The H-LSTM has no matrix-core path for dense weights at small batch, and its row-compressed kernels beat the dense
-    // ones up to half the entries kept (800/800, two directions, batch 16, 40 % kept: 135 us per step dense, 37 compressed
-    // with a launch per stage, 21 with the time loop on the device).
+    // Up to half the entries an H-LSTM keeps both forms and each call takes the faster (layer_takes_quads), since which one
+    // that is depends on the batch: 800/800, 40 % kept, microseconds per step with the projection: batch 1 3.2 compressed
+    // and 4.7 dense, batch 16 in two directions 21.5 and 11.4 (20 % kept: 7.8 and 11.4).  With more than
+    // half kept, rows from 800 units on are longer than the 384 entries the small-batch kernel takes, from 900 units on than
+    // the 448 of the batch-1 kernel.
     const double limit = m->G > 0 ? 0.50 : 0.25;
     const double density = (double)kept / (double)total;
     if (m->Dn == 2) {
@@ -1851,8 +1853,8 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         bool dense_bf16 = bf16;
         for (int d = 0; d < Dn; ++d) dense_bf16 = dense_bf16 && mode[d] == 0 && !m->ld[(size_t)l * Dn + d].wh.compressed;
         const bool mfma_ok = dense_bf16 && step_mfma_supported(B, H);
-        // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 to 2 times (1024 units: batch 64 2.2 against 3.7 us per
-        // step, 128 2.5 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
+        // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 times (1024 units: batch 64 2.4 against 3.7 us per
+        // step, 128 2.8 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
         PersistRowsPlan rows;
         if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE) rows = dense_plans(m, l, B).rows;
         if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H) && (rows.shape < 0 || rows.rows > 16)) {

@@ -31,8 +31,8 @@
 // order of the second product, whose sixteen blocks are four gates (each with its own u) x four k.
 //
 // Bound: the matrix instruction (8.8 clocks with two waves per SIMD issuing) plus one exchange per product plus the
-// reduction and the gates.  Microseconds per step of the recurrence, both directions, batch 16: 256 units 1.89 -> 1.0,
-// 800 units 4.8 -> 3.3 (against 16-column tiles of the 16x16x4 instruction across the device); H-LSTM 640/640 91 -> 4.9
+// reduction and the gates.  Microseconds per step of the recurrence, both directions, batch 16: 256 units 1.89 -> 0.85,
+// 800 units 4.8 -> 2.8 (against 16-column tiles of the 16x16x4 instruction across the device); H-LSTM 640/640 91 -> 4.4
 // (against a launch per product).
 #include "common.h"
 #include "device_math.h"

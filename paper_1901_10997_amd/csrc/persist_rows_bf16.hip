@@ -20,8 +20,8 @@
 // read h_{t-1} (barrier), and each of those was published after its workgroup had read h_{t-2} from the buffer h_t goes to.
 //
 // Bound: the exchange and the chain around it.  Two layers of 1197 units, batch 20: 18.8 us per step with a launch per
-// step and layer, 2.35 here (382 against 3069 us per forward of 70 steps); one layer of 1024, batch 64: 3.7 us with the 32-row
-// tiles, 2.4 here.
+// step and layer, 2.5 here (388 against 3063 us per forward of 70 steps); one layer of 1024: batch 64 3.7 us with the 32-row
+// tiles, 2.4 here, batch 128 4.3 and 2.8.
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"
