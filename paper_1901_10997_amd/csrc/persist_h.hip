@@ -23,8 +23,8 @@
 // each h_t was published only after its producer had finished reading u_t (and the same with the roles swapped).
 // A workgroup that owns units of one vector only (G and H apart) publishes nothing after reading the other operand that
 // anybody could wait for, so it does not read it: no output units, no wait for u; no hidden units, no wait for h.  What
-// that half of its step computes is not used.  (The wait alone, as a length of zero: with a branch around each half the
-// common case of equal widths measured up to 1.5 % slower, 1500/1500 119.8 -> 121.6 us per sequence of 35.)
+// that half of its step computes is not used.  (In a form of the kernel of its own, APART: lengths that differ by workgroup
+// cost the common case of equal widths up to 1.3 %, 625/625 in two directions 126.4 -> 128.1 us per sequence of 20.)
 // The input row x_{t+2} is requested at the top of step t, parked in LDS at the top of step t+1 (before the wait), and
 // its products are accumulated after h_{t+1} has been published, off the critical path.
 // All waits are bounded: on expiry a device flag is raised, every wave stops waiting and the kernel drains.
@@ -80,7 +80,8 @@ __device__ __forceinline__ void gather_stamped_pairs(const u64* src, int npairs,
 
 }  // namespace
 
-template <int NZ, int MAXT>
+// APART: the last workgroups own units of one vector only
+template <int NZ, int MAXT, bool APART>
 __global__ __launch_bounds__(MAXT) void persist_b1_hlstm_kernel(PersistHArgs a)
 {
     extern __shared__ float lds[];  // hbuf[H (+1: ubuf is copied in 8-byte pairs)] | ubuf[4G] | xbuf[2][D] | pub[4 * waves]
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(MAXT) void persist_b1_hlstm_kernel(PersistHArgs a)
     const int unit = blockIdx.x * nwaves + wave;    // hidden-layer unit g in stage 1, output unit j in stage 2
     const bool act1 = unit < G, act2 = unit < H;
     // what the workgroup waits for: h where it owns hidden units, pairs of u where it owns output units
-    const int poll_h = blockIdx.x * nwaves < G ? H : 0, poll_u = blockIdx.x * nwaves < H ? 2 * G : 0;
+    const int poll_h = !APART || blockIdx.x * nwaves < G ? H : 0, poll_u = !APART || blockIdx.x * nwaves < H ? 2 * G : 0;
 
     constexpr int NZP = (NZ + 1) / 2;
     float v1x[4][NZ], v1h[4][NZ], v2[4][NZ];
@@ -264,7 +265,8 @@ static hipError_t launch_hl_nz(PersistHArgs a, bool coop, hipStream_t s)
     if (blocks > device_num_cus()) return hipErrorCooperativeLaunchTooLarge;
     const size_t lds = ((size_t)a.H + 1 + 4 * (size_t)a.G + 2 * (size_t)a.D + 4 * waves) * sizeof(float);
     void* args[] = {(void*)&a};
-    const void* kern = (const void*)persist_b1_hlstm_kernel<NZ, MAXT>;
+    const void* kern = (blocks - 1) * waves >= std::min(a.H, a.G) ? (const void*)persist_b1_hlstm_kernel<NZ, MAXT, true>
+                                                                  : (const void*)persist_b1_hlstm_kernel<NZ, MAXT, false>;
     // every workgroup must be resident at the same time: at most one per compute unit
     if (coop) return hipLaunchCooperativeKernel(kern, dim3(blocks), dim3(MAXT), args, (unsigned)lds, s);
     return hipLaunchKernel(kern, dim3(blocks), dim3(MAXT), args, lds, s);
