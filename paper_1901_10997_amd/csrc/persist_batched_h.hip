@@ -26,9 +26,10 @@
 // One array and one flag per vector are enough: u_{t+1} is written, and its flag raised, only after the producer has
 // received every h_t of the batch group, and each of those was published after its producer had finished reading u_t; a
 // workgroup that owns no output unit (G > H) publishes no h that anybody could wait for, so it reads neither u nor the
-// flags and nothing of its second half is used.  h_{t+1} is published only after every workgroup's flag for u_{t+1}, which each raises
-// (units of u or not) after it has finished reading h_t.  Where the batch groups fit one XCD each and the launch has verified the placement from the hardware's
-// XCD ids, h, u and the flags are stored at workgroup scope and meet in that XCD's L2 (exchange.h).
+// flags and nothing of its second half is used.  h_{t+1} is published only after every workgroup's flag for u_{t+1},
+// which each raises (units of u or not) after it has finished reading h_t.  Where the batch groups fit one XCD each and
+// the launch has verified the placement from the hardware's XCD ids, h, u and the flags are stored at workgroup scope and
+// meet in that XCD's L2 (exchange.h).
 // All waits are bounded: on expiry a device flag is raised, every wave stops waiting, the kernel drains.
 #include <type_traits>
 #include "common.h"

@@ -18,16 +18,16 @@
 //
 // Hidden-state exchange: B x H fp32 values per direction and step, every workgroup of a block of batch rows needing all
 // of them.  The values carry their own readiness: |h| <= 1, so bit 30 of the fp32 pattern (the top exponent bit) is free
-// and holds one bit of the step count (a NaN gets it back on reading: unstamped in exchange.h).  A workgroup stores its 16 MT x 8 block of h_t into a [K blocks][rows][16] buffer
-// with device-scope stores, each word stamped; a wave reads its operand fragments of h_{t-1} with device-scope loads and
-// repeats the read until every word carries the stamp of step t-1 (bounded).  No flag, no wait for the stores'
-// acknowledgement, no second round trip.  Two buffers alternate, step tag g (g = 2 for the first step of a launch) going
-// to buffer g & 1 with stamp (g >> 1) & 1, so consecutive uses of a buffer alternate the stamp; the launcher clears the
-// buffers in front of every launch (all stamps 0), and h0, if given, is placed by a kernel of its own where step 0 reads
-// it (buffer 1, unstamped, taken as it is).  A workgroup writes h_t only after all of its waves have read h_{t-1}
-// (barrier), whose producers each stored it after all of their waves had read h_{t-2} from the buffer h_t goes to.
-// The first read of a step is paced (exchange.h): issued right behind the workgroup's own stores it would come back
-// unstamped and cost a second round.  Every wait is bounded.
+// and holds one bit of the step count (a NaN gets it back on reading: unstamped in exchange.h).  A workgroup stores its
+// 16 MT x 8 block of h_t into a [K blocks][rows][16] buffer with device-scope stores, each word stamped; a wave reads its
+// operand fragments of h_{t-1} with device-scope loads and repeats the read until every word carries the stamp of step
+// t-1 (bounded).  No flag, no wait for the stores' acknowledgement, no second round trip.  Two buffers alternate, step
+// tag g (g = 2 for the first step of a launch) going to buffer g & 1 with stamp (g >> 1) & 1, so consecutive uses of a
+// buffer alternate the stamp; the launcher clears the buffers in front of every launch (all stamps 0), and h0, if given,
+// is placed by a kernel of its own where step 0 reads it (buffer 1, unstamped, taken as it is).  A workgroup writes h_t
+// only after all of its waves have read h_{t-1} (barrier), whose producers each stored it after all of their waves had
+// read h_{t-2} from the buffer h_t goes to.  The first read of a step is paced (exchange.h): issued right behind the
+// workgroup's own stores it would come back unstamped and cost a second round.  Every wait is bounded.
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"

@@ -21,15 +21,16 @@
 // Exchange: values carry their own readiness, as 32-bit words with one bit of the step count in a bit the value leaves
 // free: |h| <= 1, so bit 30 (a NaN gets it back on reading, see unstamped); u >= 0, so the sign.  h has two buffers per
 // quad, step tag g (2 for the first step) in buffer g & 1 with stamp (g >> 1) & 1; u one, stamped (s + 1) & 1.  All
-// buffers are zero at launch.  u(s+1) is written only after its producer has received every h of step s, each of which was
-// published after its workgroup had read all of u(s); a workgroup without a unit of h (G > H) publishes none that anybody
-// could wait for, so it has no second product and never reads u.  (A form of the kernel of its own, SPARE: the branch in the loop
-// costs narrow layers up to 2 % where no workgroup takes it, 74 units, both directions, batch 37: 1.99 -> 2.02 us per step with its projection.)  h of tag g + 2 takes the place of tag g only after its
-// producer has received every h of tag g + 1 and every u of that step; each workgroup owns units of at least one of the
-// two and had read tag g before it published them.  A wave loads its own K slice straight into operand registers and
-// repeats the load until every word is stamped (bounded).  Layouts of a quad, in the order of a wave's lanes (four columns
-// apart in memory, a load would touch four times the lines): h [k][column]; u [k / 4][gate][column][k % 4], the operand
-// order of the second product, whose sixteen blocks are four gates (each with its own u) x four k.
+// buffers are zero at launch.  u(s+1) is written only after its producer has received every h of step s, each of which
+// was published after its workgroup had read all of u(s); a workgroup without a unit of h (G > H) publishes none that
+// anybody could wait for, so it has no second product and never reads u.  (A form of the kernel of its own, SPARE: the
+// branch in the loop costs narrow layers up to 2 % where no workgroup takes it, 74 units, both directions, batch 37: 1.99
+// -> 2.02 us per step with its projection.)  h of tag g + 2 takes the place of tag g only after its producer has received
+// every h of tag g + 1 and every u of that step; each workgroup owns units of at least one of the two and had read tag g
+// before it published them.  A wave loads its own K slice straight into operand registers and repeats the load until
+// every word is stamped (bounded).  Layouts of a quad, in the order of a wave's lanes (four columns apart in memory, a
+// load would touch four times the lines): h [k][column]; u [k / 4][gate][column][k % 4], the operand order of the second
+// product, whose sixteen blocks are four gates (each with its own u) x four k.
 //
 // Bound: the matrix instruction (8.8 clocks with two waves per SIMD issuing) plus one exchange per product plus the
 // reduction and the gates.  Microseconds per step of the recurrence, both directions, batch 16: 256 units 1.89 -> 0.85,

@@ -13,11 +13,12 @@
 // so the batch is dealt over as many groups as fit, which makes each group's h, the volume every workgroup reads per step,
 // small.
 //
-// Exchange: |h| <= 1 leaves bit 14 of a bf16 pattern free (a NaN gets it back on reading, see unstamped); it carries one bit of the step count (step tag g, 2 for the first
-// step, in buffer g & 1 with stamp (g >> 1) & 1; both buffers zero at launch).  h lies in operand order, [k / 8][row][8], so a
-// wave loads 16 bytes per lane straight into operand registers and repeats the load until every live element is stamped
-// (bounded); a tile publishes the 4 units of a row as one 8-byte word.  A workgroup writes h_t after all of its waves have
-// read h_{t-1} (barrier), and each of those was published after its workgroup had read h_{t-2} from the buffer h_t goes to.
+// Exchange: |h| <= 1 leaves bit 14 of a bf16 pattern free (a NaN gets it back on reading, see unstamped); it carries one
+// bit of the step count (step tag g, 2 for the first step, in buffer g & 1 with stamp (g >> 1) & 1; both buffers zero at
+// launch).  h lies in operand order, [k / 8][row][8], so a wave loads 16 bytes per lane straight into operand registers
+// and repeats the load until every live element is stamped (bounded); a tile publishes the 4 units of a row as one 8-byte
+// word.  A workgroup writes h_t after all of its waves have read h_{t-1} (barrier), and each of those was published after
+// its workgroup had read h_{t-2} from the buffer h_t goes to.
 //
 // Bound: the exchange and the chain around it.  Two layers of 1197 units, batch 20: 18.8 us per step with a launch per
 // step and layer, 2.5 here (388 against 3063 us per forward of 70 steps); one layer of 1024: batch 64 3.7 us with the 32-row
