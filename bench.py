@@ -293,7 +293,9 @@ def main():
                     "us_per_forward": per_fwd_us, "launches_per_forward": prof["proj_launches"] // max(args.steps, 1)}
         else:
             tf = flops / (per_fwd_us * 1e-6) / 1e12
-            peak = 2500.0 if dtype == B.LSTM_BF16 else 157.3
+            # fp32 operands as two fp16 planes: three products of the fp16 matrix instruction each
+            split = "proj=dense-split" in plan_desc
+            peak = 2500.0 if dtype == B.LSTM_BF16 else 2500.0 / 3 if split else 157.3
             proj = {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak,
                     "flops_per_forward": flops, "us_per_forward": per_fwd_us, "launches_per_forward": prof["proj_launches"] // max(args.steps, 1)}
     measured = None
@@ -315,10 +317,11 @@ def main():
                     "mfma_f32_random_operands_TFLOPs": f_r, "mfma_f32_random_operands_clock_GHz": f_r_ghz}
         roofline["frac_of_measured_copy"] = achieved / measured["copy_GBps"]
         if proj and proj["bound"] == "mfma":
-            key = "mfma_bf16" if dtype == B.LSTM_BF16 else "mfma_f32"
-            proj["measured_peak"] = measured[key + "_TFLOPs"]
+            key = "mfma_bf16" if dtype == B.LSTM_BF16 or split else "mfma_f32"
+            products = 3 if dtype != B.LSTM_BF16 and split else 1
+            proj["measured_peak"] = measured[key + "_TFLOPs"] / products
             proj["frac_of_measured"] = proj["achieved"] / proj["measured_peak"]
-            proj["measured_peak_random_operands"] = measured[key + "_random_operands_TFLOPs"]
+            proj["measured_peak_random_operands"] = measured[key + "_random_operands_TFLOPs"] / products
             proj["frac_of_measured_random_operands"] = proj["achieved"] / proj["measured_peak_random_operands"]
             # the vendor library's product of the first layer's projection shape, same operand and output types (fp32
             # out), as a yardstick of what this shape reaches on this device; it is not part of the path

@@ -22,6 +22,10 @@ struct PackedMat {
     void* dense_pad = nullptr;   // input-side matrices for the matrix-core projections: rows of pad_ld elements, zero-padded to a
     int pad_ld = 0;              // multiple of 4 (fp32), or of 32 in every part of the input, one per direction of the layer
                                  // below (bf16); `dense` itself where there is nothing to pad
+    // fp32 input-side matrices: `dense_pad` as two fp16 planes and the rows' scales (proj_split.hip); nullptr where a row does
+    // not fit the form
+    uint16_t* split = nullptr;
+    float* split_unscale = nullptr;
     int64_t nnz = 0;             // compressed: kept positions (== popcount of the mask)
     int32_t* row_ptr = nullptr;  // device [rows+1]
     uint16_t* col16 = nullptr;   // device [nnz]  (cols <= 65536)
@@ -91,6 +95,32 @@ hipError_t launch_proj_mfma(const void* X, bool x_bf16, int ldx, const void* W, 
                             int M, int N, int K, hipStream_t s, const float* W_frag16 = nullptr);
 hipError_t launch_proj_mfma_f32_pair(const float* X, int ldx, const float* W0, const float* bias0, float* P0,
                                      const float* W1, const float* bias1, float* P1, int M, int N, int K, hipStream_t s);
+// The same fp32 product on the fp16 matrix instruction, both operands as two fp16 planes (proj_split.hip).
+struct ProjSplitDir {
+    const uint16_t* W;            // [N] rows of split_row_halves(K)
+    const float* w_unscale;       // [N]
+    const float* bias;
+    float* P;                     // [M][N]
+    const float* Wd;              // the same rows as fp32, K elements each
+    const int32_t* row_ptr;       // row-compressed form, or nullptr
+    const uint16_t* col;
+    const float* val;
+};
+struct ProjSplitArgs {
+    ProjSplitDir d[2];
+    const uint16_t* Xs;           // [M] rows of split_row_halves(K), launch_split_rows
+    const float* x_unscale;       // [M]
+    const float* X;               // the same rows as fp32
+    int ldx;
+    int M, N, K, ndir;
+    int gm, gn, npid;             // set by the launcher
+};
+size_t split_row_halves(int K);
+hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, hipStream_t s);
+constexpr int kSplitMinK = 64;
+bool proj_split_supported(int M, int N, int K, int ndir);   // and faster than the fp32 instruction
+double proj_split_us(int M, int N, int K, int ndir, bool masked);   // modelled time, with launch_split_rows
+hipError_t launch_proj_split(const ProjSplitArgs& a, hipStream_t s);
 // XT[k][m] = (float) X[m][k]   (optionally rounding fp32 -> bf16 -> fp32 on the way)
 hipError_t launch_transpose_to_f32(const void* X, bool x_bf16, int ldx, float* XT, int M, int K, bool round_bf16,
                                    hipStream_t s);

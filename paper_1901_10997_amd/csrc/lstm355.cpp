@@ -41,6 +41,7 @@ struct lstm355 {
     int device_scope_only = 0;           // 1: no hand-over through an XCD's L2 (environment LSTM355_L2_HANDOVER=0)
     int poll_pace = -1;                  // pace_poll units where a kernel paces a poll; -1: each kernel's measured default (environment LSTM355_POLL_PACE)
     double sparse_proj_max_density = 0.18;   // projection over the kept entries up to this kept fraction (environment LSTM355_SPARSE_PROJ_MAX_DENSITY)
+    bool sparse_proj_given = false;          // ... whatever the modelled times say, then
     int plan = LSTM_PLAN_AUTO;
     int waves_per_group = 0;
     int cooperative = 0;
@@ -167,6 +168,8 @@ static void free_mat(PackedMat& p)
 {
     if (p.dense_pad && p.dense_pad != p.dense) (void)hipFree(p.dense_pad);
     if (p.dense_frag32) (void)hipFree(p.dense_frag32);
+    if (p.split) (void)hipFree(p.split);
+    if (p.split_unscale) (void)hipFree(p.split_unscale);
     if (p.dense) (void)hipFree(p.dense);
     if (p.dense_frag16) (void)hipFree(p.dense_frag16);
     if (p.row_ptr) (void)hipFree(p.row_ptr);
@@ -404,6 +407,26 @@ static int add_padded(lstm_t* m, PackedMat& p, bool bf16, int parts)
     return LSTM_OK;
 }
 
+// Two fp16 planes of an fp32 input-side matrix for proj_split.hip, made from the padded rows already on the device.
+static int add_split(lstm_t* m, PackedMat& p)
+{
+    if (p.pad_ld < kSplitMinK) return LSTM_OK;
+    std::vector<float> unscale((size_t)p.rows);
+    HIP_TRY(m, hipMalloc((void**)&p.split, (size_t)p.rows * split_row_halves(p.pad_ld) * sizeof(uint16_t)));
+    HIP_TRY(m, hipMalloc((void**)&p.split_unscale, unscale.size() * sizeof(float)));
+    HIP_TRY(m, launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr));
+    HIP_TRY(m, hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost));
+    for (float u : unscale)
+        if (!std::isfinite(u)) {   // a row whose weights do not fit: the matrix stays with the fp32 instruction
+            (void)hipFree(p.split);
+            (void)hipFree(p.split_unscale);
+            p.split = nullptr;
+            p.split_unscale = nullptr;
+            break;
+        }
+    return LSTM_OK;
+}
+
 enum { kFragNone = 0, kFragRows = 1, kFragByGate = 2 };   // fragment-ordered copy of a dense fp32 matrix: none, as stored, by gate
 // Pack one matrix W[4H][cols] (ABI row order q*H + j) with its optional mask into device storage.
 static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t* mask, int H, int cols, bool compressed,
@@ -613,7 +636,10 @@ static int create_model(int layers, int input_dim, const int* hidden_dims, const
         if (v > 0) m->spin_limit = (unsigned)v;
     }
     if (const char* l2 = std::getenv("LSTM355_L2_HANDOVER")) m->device_scope_only = (std::atoi(l2) == 0) ? 1 : 0;
-    if (const char* sp = std::getenv("LSTM355_SPARSE_PROJ_MAX_DENSITY")) m->sparse_proj_max_density = std::atof(sp);
+    if (const char* sp = std::getenv("LSTM355_SPARSE_PROJ_MAX_DENSITY")) {
+        m->sparse_proj_max_density = std::atof(sp);
+        m->sparse_proj_given = true;
+    }
     if (const char* pp = std::getenv("LSTM355_POLL_PACE")) m->poll_pace = std::max(-1, std::min(255, std::atoi(pp)));
     hipError_t e = hipGetDevice(&m->device);
     // two cells (directions, or two stacked layers) x two parities; H-LSTM: h slots, then the 4G hidden-layer slots
@@ -762,6 +788,7 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
         if (rc != LSTM_OK) return rc;
     }
     rc = add_padded(m, x.wx, bf16, bf16 && layer > 0 ? m->Dn : 1);
+    if (rc == LSTM_OK && !bf16) rc = add_split(m, x.wx);
     if (rc == LSTM_OK && bf16 && !compressed) rc = add_frag32(m, x.wh);
     if (rc != LSTM_OK) return rc;
     std::vector<float> bp(rows);
@@ -823,6 +850,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     // hidden layers: 4G rows, packed row 4g+q; kept dense as well for the projection on the matrix cores
     int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 0, kFragRows);
     if (rc == LSTM_OK) rc = add_padded(m, x.wx, false, 1);
+    if (rc == LSTM_OK) rc = add_split(m, x.wx);
     if (rc != LSTM_OK) return rc;
     rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 12, kFragRows);
     if (rc != LSTM_OK) return rc;
@@ -871,7 +899,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, h0_off, total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, total;
 };
 // Plans of layer l at batch B.  They follow from the shape alone, but a search over the kernels' shape tables takes
 // microseconds and a forward needs each several times, so the handle keeps the last batch size's.
@@ -964,6 +992,15 @@ static Workspace carve(const lstm_t* m, int T, int B)
             if (m->in_dim(l) % 4 != 0) xp_bytes = std::max(xp_bytes, M * (size_t)pad4(m->in_dim(l)) * sizeof(float));
     }
     off += align256(xp_bytes);
+    // fp32 models: a layer's input rows as two fp16 planes, and their scales
+    w.sx_off = off;
+    if (m->dtype == LSTM_F32) {
+        size_t halves = 0;
+        for (int l = 0; l < m->L; ++l) halves = std::max(halves, split_row_halves(pad4(m->in_dim(l))));
+        off += align256(M * halves * sizeof(uint16_t));
+    }
+    w.su_off = off;
+    if (m->dtype == LSTM_F32) off += align256(M * sizeof(float));
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
@@ -1252,6 +1289,42 @@ static bool fuses_input(const lstm_t* m, int l, int T, int B)
     return mode[0] == 1 || mode[0] == 2 || mode[1] == 1 || mode[1] == 2;
 }
 
+// Does the projection of M rows through this matrix run on the fp16 matrix instruction?
+static bool proj_runs_split(const PackedMat& wx, int M, int ndir)
+{
+    return wx.split != nullptr && proj_split_supported(M, wx.rows, wx.pad_ld, ndir);
+}
+
+// Modelled time of the projection over the kept entries (7 shapes, 2 to 17 % kept: within 20 %): products by slot, the passes over
+// the rows of X per group of 32 units, and a constant per group and tile.  Against the fp16 matrix instruction: 4800 rows of 1600
+// for 800 units in two directions 263 / 440 / 752 us at 2 / 10 / 17 % kept against 250; 700 rows of 1500 for 1500 units 45 / 72 / 98
+// against 71; 80 rows of 800 for 800 units 8 / 11 / 13 against 18.
+static double proj_q16_us(int M, int H, int D, int slots, int ndir)
+{
+    const double groups = (H + 31) / 32 * (double)ndir;
+    return 7.0 + 1e-6 * M * (3.2 * H * ndir * slots + groups * (0.087 * D + 558.0));
+}
+
+// Input projection of n directions of a layer on the fp16 matrix instruction; X: rows padded as PackedMat::dense_pad is.
+static int run_split_proj(lstm_t* m, const LayerDir* const* w, float* const* P, int n, const float* X, int M, const Workspace& ws,
+                          char* base, hipStream_t s)
+{
+    const PackedMat& p0 = w[0]->wx;
+    ProjSplitArgs a{};
+    uint16_t* const xs = (uint16_t*)(base + ws.sx_off);
+    float* const xu = (float*)(base + ws.su_off);
+    HIP_TRY(m, launch_split_rows(X, p0.pad_ld, M, p0.pad_ld, xs, xu, s));
+    for (int d = 0; d < n; ++d) {
+        const PackedMat& p = w[d]->wx;
+        a.d[d] = ProjSplitDir{p.split, p.split_unscale, w[d]->bias, P[d], (const float*)p.dense_pad,
+                              p.compressed ? p.row_ptr : nullptr, p.col16, p.val};
+    }
+    a.Xs = xs; a.x_unscale = xu; a.X = X; a.ldx = p0.pad_ld;
+    a.M = M; a.N = p0.rows; a.K = p0.pad_ld; a.ndir = n;
+    HIP_TRY(m, launch_proj_split(a, s));
+    return LSTM_OK;
+}
+
 // As run_quad_layer below, with the tiles of persist_dense_f32.hip.
 static int run_tile_layer(lstm_t* m, int l, int T, int B, const DensePlans& p, float* const* P, const float* h0, const float* c0,
                           float* Yout, int y_ld, float* hT, float* cT, const char* const (&proj)[2], QuadRegions& reg, hipStream_t s)
@@ -1385,7 +1458,8 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
         }
         bool xt_ready = false;
         const float* Xpad = nullptr;   // X with rows padded as PackedMat::dense_pad is
-        bool proj_dense[2] = {false, false};
+        bool proj_dense[2] = {false, false}, proj_split = false;
+        auto proj_name = [&](int d) { return proj_split ? "dense-split" : proj_dense[d] ? "dense" : "csr"; };
         auto padded_x = [&](const PackedMat& wx) -> hipError_t {
             if (Xpad) return hipSuccess;
             Xpad = (const float*)X;
@@ -1394,7 +1468,27 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
             return launch_pad_rows(X, false, D, M, 1, D, wx.pad_ld, base + ws.xp_off, s);
         };
         bool pair_done = false;
-        if (Dn == 2 && M > 64 && !persist[0] && !persist[1]) {
+        {
+            // one launch for the directions that need P (they read the same X) where all of them have the form
+            const LayerDir* sw[2];
+            float* sp[2];
+            int n = 0;
+            bool ok = true;
+            for (int d = 0; d < Dn; ++d) {
+                if (persist[d]) continue;
+                sw[n] = &m->ld[(size_t)l * Dn + d];
+                sp[n] = P[d];
+                ok = ok && proj_runs_split(sw[n++]->wx, M, Dn);
+            }
+            if (n > 0 && ok) {
+                ProfSpan span(m, s, 0);
+                HIP_TRY(m, padded_x(sw[0]->wx));
+                const int rc = run_split_proj(m, sw, sp, n, Xpad, M, ws, base, s);
+                if (rc != LSTM_OK) return rc;
+                proj_dense[0] = proj_dense[1] = proj_split = pair_done = true;
+            }
+        }
+        if (!pair_done && Dn == 2 && M > 64 && !persist[0] && !persist[1]) {
             // Both directions dense on the matrix cores: one launch (they read the same X), the second direction's tiles fill the
             // last wave of the first's.  Two workgroups share a compute unit: at 4800 rows and 640 units a direction's 760 tiles
             // are 1.5 waves of 512, both directions' 1520 three (H-LSTM 3 x 640 bidirectional, batch 16: 5559 -> 5278 us); 800
@@ -1430,7 +1524,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
             }
         }
         if (quads) {
-            const char* const proj[2] = {proj_dense[0] ? "dense" : "csr", proj_dense[1] ? "dense" : "csr"};
+            const char* const proj[2] = {proj_name(0), proj_name(1)};
             const int rc = run_quad_layer(m, l, T, B, P, h0, c0, Yout, y_ld, hT, cT, proj, ws, base, quad, s);
             if (rc != LSTM_OK) return rc;
             continue;
@@ -1493,7 +1587,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                         char cuts[24] = "";
                         if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, ",batch/%d", cut.chunks);
                         std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-hlstm-csr%s(s%d,u%d,b%d%s);", l, d,
-                                      proj_dense[d] ? "dense" : "csr", trimmed ? "+ovf" : "", nz, upw, bw, cuts);
+                                      proj_name(d), trimmed ? "+ovf" : "", nz, upw, bw, cuts);
                         m->last_plan += tag;
                     }
                 }
@@ -1525,7 +1619,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 const size_t n = (size_t)l * Dn + d;
                 if (c0) HIP_TRY(m, hipMemcpyAsync(cbuf[d], c0 + m->soff(n) * B, (size_t)B * H * sizeof(float), hipMemcpyDeviceToDevice, s));
                 else HIP_TRY(m, launch_fill_f32(cbuf[d], (size_t)B * H, 0.0f, s));
-                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=hlstm-stepwise-pair-csr;", l, d, proj_dense[d] ? "dense" : "csr");
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=hlstm-stepwise-pair-csr;", l, d, proj_name(d));
                 m->last_plan += tag;
             }
             for (int step = 0; step < T; ++step) {
@@ -1608,7 +1702,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
             if (c0) HIP_TRY(m, hipMemcpyAsync(cbuf[d], c0 + m->soff(n) * B, (size_t)B * H * sizeof(float), hipMemcpyDeviceToDevice, s));
             else HIP_TRY(m, launch_fill_f32(cbuf[d], (size_t)B * H, 0.0f, s));
             std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=hlstm-stepwise-%s;", l, d,
-                          proj_dense[d] ? "dense" : "csr", w.wh.compressed ? "csr" : "dense");
+                          proj_name(d), w.wh.compressed ? "csr" : "dense");
             m->last_plan += tag;
             for (int step = 0; step < T; ++step) {
                 const int t = d ? (T - 1 - step) : step;
@@ -1788,7 +1882,10 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                        (double)p.nnz <= m->sparse_proj_max_density * (double)p.rows * (double)p.cols;
                 pslots = std::max(pslots, p.q16_slots);
             }
-            if (q16p && proj_q16_supported(M, H, D, pslots)) {
+            bool split = !m->sparse_proj_given;
+            for (int d = 0; d < Dn && q16p; ++d) split = split && proj_runs_split(m->ld[(size_t)l * Dn + d].wx, M, Dn);
+            if (q16p && proj_q16_supported(M, H, D, pslots) &&
+                !(split && proj_split_us(M, 4 * H, D, Dn, true) < 0.9 * proj_q16_us(M, H, D, pslots, Dn))) {
                 ProfSpan span(m, s, 0);
                 ProjQ16Args a{};
                 for (int d = 0; d < Dn; ++d) {
@@ -1810,6 +1907,26 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             Xpad = base + ws.xp_off;
             return launch_pad_rows(X, bf16, D, M, 1, D, wx.pad_ld, base + ws.xp_off, s);
         };
+        if (!pair_done && !bf16) {
+            const LayerDir* sw[2];
+            float* sp[2];
+            int n = 0;
+            bool ok = true;
+            for (int d = 0; d < Dn; ++d) {
+                if (mode[d] == 1 || mode[d] == 2) continue;
+                sw[n] = &m->ld[(size_t)l * Dn + d];
+                sp[n] = P[d];
+                ok = ok && proj_runs_split(sw[n++]->wx, M, Dn);
+            }
+            if (n > 0 && ok) {
+                ProfSpan span(m, s, 0);
+                HIP_TRY(m, padded_x(sw[0]->wx));
+                const int rc = run_split_proj(m, sw, sp, n, (const float*)Xpad, M, ws, base, s);
+                if (rc != LSTM_OK) return rc;
+                pair_done = true;
+                proj[0] = proj[1] = "dense-split";
+            }
+        }
         if (!pair_done && Dn == 2 && !bf16 && M > 64 && mode[0] != 1 && mode[0] != 2 && mode[1] != 1 && mode[1] != 2) {
             // fp32, both directions dense on the matrix cores: one launch (they read the same X).  (At most 64 input rows:
             // one stream over the fragment-ordered weights per direction, below.)
@@ -2538,10 +2655,21 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     }
     float *dX = nullptr, *dW = nullptr, *dWf = nullptr, *dB = nullptr, *dY = nullptr, *dXT = nullptr, *dval = nullptr, *dev_ = nullptr;
     int32_t* drp = nullptr;
-    uint16_t *dcol = nullptr, *dec = nullptr;
+    uint16_t *dcol = nullptr, *dec = nullptr, *dXs = nullptr, *dWs = nullptr;
+    float *dxu = nullptr, *dwu = nullptr;
+    bool split = format == LSTM_FMT_DENSE_MASKED && proj_split_supported(batch, n, n, 1);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = LSTM_OK;
     auto run = [&]() -> hipError_t {
+        if (split) {
+            const hipError_t e = launch_split_rows(dX, n, batch, n, dXs, dxu, s);
+            if (e != hipSuccess) return e;
+            ProjSplitArgs a{};
+            a.d[0] = ProjSplitDir{dWs, dwu, dB, dY, dW, nullptr, nullptr, nullptr};
+            a.Xs = dXs; a.x_unscale = dxu; a.X = dX; a.ldx = n;
+            a.M = batch; a.N = n; a.K = n; a.ndir = 1;
+            return launch_proj_split(a, s);
+        }
         if (use_ell) return launch_proj_ell_small(dX, false, n, false, dev_, dec, slots, dB, dY, batch, n, n, s);
         if (format == LSTM_FMT_ROW_COMPRESSED) {
             hipError_t e = launch_transpose_to_f32(dX, false, n, dXT, batch, n, false, s);
@@ -2567,6 +2695,17 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
         // as lstm_set_weights stores an input-side matrix: once more in fragment order, for batches of at most 64 rows
         if (e == hipSuccess && batch <= 64) e = hipMalloc((void**)&dWf, frag16_floats(n, n) * sizeof(float));
         if (e == hipSuccess && batch <= 64) e = launch_to_frag16(dW, n, n, false, dWf, s);
+        if (split) {   // ... and as two fp16 planes
+            std::vector<float> unscale((size_t)n);
+            if (e == hipSuccess) e = hipMalloc((void**)&dXs, (size_t)batch * split_row_halves(n) * sizeof(uint16_t));
+            if (e == hipSuccess) e = hipMalloc((void**)&dxu, (size_t)batch * sizeof(float));
+            if (e == hipSuccess) e = hipMalloc((void**)&dWs, (size_t)n * split_row_halves(n) * sizeof(uint16_t));
+            if (e == hipSuccess) e = hipMalloc((void**)&dwu, (size_t)n * sizeof(float));
+            if (e == hipSuccess) e = launch_split_rows(dW, n, n, n, dWs, dwu, s);
+            if (e == hipSuccess) e = hipMemcpyAsync(unscale.data(), dwu, unscale.size() * sizeof(float), hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            for (float u : unscale) split = split && std::isfinite(u);
+        }
     }
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -2582,7 +2721,8 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     else *avg_us = (double)ms * 1000.0 / iters;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    for (void* p_ : {(void*)dX, (void*)dW, (void*)dWf, (void*)dB, (void*)dY, (void*)dXT, (void*)dval, (void*)drp, (void*)dcol, (void*)dev_, (void*)dec})
+    for (void* p_ : {(void*)dX, (void*)dW, (void*)dWf, (void*)dB, (void*)dY, (void*)dXT, (void*)dval, (void*)drp, (void*)dcol, (void*)dev_, (void*)dec,
+                     (void*)dXs, (void*)dWs, (void*)dxu, (void*)dwu})
         if (p_) (void)hipFree(p_);
     return rc;
 }
