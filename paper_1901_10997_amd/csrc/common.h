@@ -26,6 +26,9 @@ struct PackedMat {
     // not fit the form
     uint16_t* split = nullptr;
     float* split_unscale = nullptr;
+    // fp32 recurrent matrices with dense_frag16: the same for persist_split.hip
+    uint16_t* rec_split = nullptr;
+    float* rec_unscale = nullptr;
     int64_t nnz = 0;             // compressed: kept positions (== popcount of the mask)
     int32_t* row_ptr = nullptr;  // device [rows+1]
     uint16_t* col16 = nullptr;   // device [nnz]  (cols <= 65536)
@@ -354,6 +357,8 @@ struct PersistQuadDir {
     const float* P;            // [T*Bld][4H] (H-LSTM: [4G]): input projection incl. bias
     const float* Wf;           // W_h / W1h in fragment order (launch_to_frag16)
     const float* W2f;          // H-LSTM: W2 in fragment order by gate
+    const uint16_t* Ws;        // persist_split.hip: W_h as two fp16 planes (launch_to_frag_split) and its rows' scales
+    const float* w_unscale;
     const float* bias2;        // H-LSTM: [4H] packed
     const float* h0;           // [B][H] or nullptr
     const float* c0;
@@ -386,6 +391,13 @@ double persist_quad_many_columns_us(const PersistQuadPlan& p, int H, int ndir);
 size_t persist_quad_exchange_words(int B, int H, int G, int ndir);
 void persist_quad_describe(const PersistQuadPlan& p, char* buf, size_t n);
 hipError_t launch_persist_quad(PersistQuadArgs& a, const PersistQuadPlan& p, unsigned* words, bool cooperative, hipStream_t s);
+// the same layers with the product on the fp16 matrix instruction (LSTM cells; PersistQuadDir::Ws)
+PersistQuadPlan persist_split_plan(int B, int H, int ndir);
+size_t persist_split_exchange_words(int B, int H, int ndir);
+void persist_split_describe(const PersistQuadPlan& p, char* buf, size_t n);
+hipError_t launch_persist_split(PersistQuadArgs& a, const PersistQuadPlan& p, unsigned* words, bool cooperative, hipStream_t s);
+size_t frag_split_halves(int rows, int cols);
+hipError_t launch_to_frag_split(const float* Wf, int rows, int cols, uint16_t* out, float* unscale, hipStream_t s);   // from launch_to_frag16's order
 size_t frag16_floats(int rows, int cols);
 hipError_t launch_to_frag16(const float* W, int rows, int cols, bool by_gate, float* out, hipStream_t s);
 hipError_t launch_csr_to_frag16(const int* row_ptr, const uint16_t* col, const float* val, int rows, int cols, bool by_gate, float* out, hipStream_t s);

@@ -32,6 +32,32 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f)
 }
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
+// ---- fp32 rows as two fp16 planes (proj_split.hip, persist_split.hip)
+// A row is scaled by a power of two that brings its largest magnitude into [2^14, 2^15); what is kept beside the planes is
+// 2^-e of the scale 2^e, or a mark where the row does not fit: a non-finite value, a largest magnitude outside 2^-60 .. 2^60,
+// or too many that are smaller than the largest by 2^-16 and more, which keep fewer than 22 bits (a 2^-40th of the
+// largest).  A few of those are what any distribution gives (normal values: one in 20000); they would only show where
+// everything else of the row met zeros.
+constexpr unsigned kNonFinite = 0x7f800000u, kTooWide = 0x7fc00000u;
+constexpr float kSplitSmall = 0.25f;   // scaled magnitude below which a value counts as small
+struct SplitScale {
+    float scale;
+    bool usable;
+};
+// big: bits of the row's largest magnitude (NaN and infinity come out on top)
+__device__ __forceinline__ SplitScale split_scale(unsigned big)
+{
+    const int e = (int)(big >> 23);
+    const bool usable = big == 0 || (e >= 127 - 60 && e <= 127 + 60);
+    return SplitScale{usable && big ? __uint_as_float((unsigned)(127 + 14 + 127 - e) << 23) : 1.f, usable};
+}
+__device__ __forceinline__ float split_unscale(const SplitScale& sc, unsigned big, int small, int nonzero)
+{
+    if (big >= kNonFinite) return __uint_as_float(kNonFinite);
+    if (!sc.usable || small > nonzero / 64 + (nonzero >= 8 ? 2 : 0)) return __uint_as_float(kTooWide);
+    return 1.f / sc.scale;
+}
+
 // sum over the 64 lanes of a wavefront; every lane receives the total
 __device__ __forceinline__ float wave_sum(float v)
 {

@@ -23,6 +23,8 @@ struct DensePlans {
     int B = 0;
     LaunchCut cut;                // fp32: launches (chunks = 0: no form fits) ...
     PersistQuadPlan quad[2];      // ... of the longer and the shorter runs of columns
+    LaunchCut split_cut;          // fp32 LSTM layers with the product on the fp16 matrix instruction; chunks = 0: none
+    PersistQuadPlan split[2];
     LaunchCut tile_cut;           // fp32 LSTM layers whose many columns go faster as tiles (persist_dense_f32.hip); chunks = 0: none
     int tile_rows[2] = {0, 0};    // 16-row blocks per workgroup, as above
     PersistRowsPlan rows;         // bf16
@@ -170,6 +172,8 @@ static void free_mat(PackedMat& p)
     if (p.dense_frag32) (void)hipFree(p.dense_frag32);
     if (p.split) (void)hipFree(p.split);
     if (p.split_unscale) (void)hipFree(p.split_unscale);
+    if (p.rec_split) (void)hipFree(p.rec_split);
+    if (p.rec_unscale) (void)hipFree(p.rec_unscale);
     if (p.dense) (void)hipFree(p.dense);
     if (p.dense_frag16) (void)hipFree(p.dense_frag16);
     if (p.row_ptr) (void)hipFree(p.row_ptr);
@@ -407,6 +411,19 @@ static int add_padded(lstm_t* m, PackedMat& p, bool bf16, int parts)
     return LSTM_OK;
 }
 
+// A matrix with a row that does not fit two fp16 planes (marked in its scales) stays with the fp32 instruction.
+static void drop_unfit(const std::vector<float>& unscale, uint16_t*& planes, float*& scales)
+{
+    for (float u : unscale)
+        if (!std::isfinite(u)) {
+            (void)hipFree(planes);
+            (void)hipFree(scales);
+            planes = nullptr;
+            scales = nullptr;
+            return;
+        }
+}
+
 // Two fp16 planes of an fp32 input-side matrix for proj_split.hip, made from the padded rows already on the device.
 static int add_split(lstm_t* m, PackedMat& p)
 {
@@ -416,14 +433,20 @@ static int add_split(lstm_t* m, PackedMat& p)
     HIP_TRY(m, hipMalloc((void**)&p.split_unscale, unscale.size() * sizeof(float)));
     HIP_TRY(m, launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr));
     HIP_TRY(m, hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost));
-    for (float u : unscale)
-        if (!std::isfinite(u)) {   // a row whose weights do not fit: the matrix stays with the fp32 instruction
-            (void)hipFree(p.split);
-            (void)hipFree(p.split_unscale);
-            p.split = nullptr;
-            p.split_unscale = nullptr;
-            break;
-        }
+    drop_unfit(unscale, p.split, p.split_unscale);
+    return LSTM_OK;
+}
+
+// The same of a recurrent matrix with its fp32 fragment order on the device, for persist_split.hip.
+static int add_rec_split(lstm_t* m, PackedMat& p)
+{
+    if (!p.dense_frag16 || persist_split_plan(4, p.cols, 1).shape < 0) return LSTM_OK;
+    std::vector<float> unscale((size_t)p.rows);
+    HIP_TRY(m, hipMalloc((void**)&p.rec_split, frag_split_halves(p.rows, p.cols) * sizeof(uint16_t)));
+    HIP_TRY(m, hipMalloc((void**)&p.rec_unscale, unscale.size() * sizeof(float)));
+    HIP_TRY(m, launch_to_frag_split(p.dense_frag16, p.rows, p.cols, p.rec_split, p.rec_unscale, nullptr));
+    HIP_TRY(m, hipMemcpy(unscale.data(), p.rec_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost));
+    drop_unfit(unscale, p.rec_split, p.rec_unscale);
     return LSTM_OK;
 }
 
@@ -789,6 +812,7 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     }
     rc = add_padded(m, x.wx, bf16, bf16 && layer > 0 ? m->Dn : 1);
     if (rc == LSTM_OK && !bf16) rc = add_split(m, x.wx);
+    if (rc == LSTM_OK && !bf16) rc = add_rec_split(m, x.wh);
     if (rc == LSTM_OK && bf16 && !compressed) rc = add_frag32(m, x.wh);
     if (rc != LSTM_OK) return rc;
     std::vector<float> bp(rows);
@@ -920,6 +944,14 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
             p.quad[0] = plan((B + p.cut.chunks - 1) / p.cut.chunks, m->Dn / p.cut.passes);
             p.quad[1] = B % p.cut.chunks == 0 ? p.quad[0] : plan(B / p.cut.chunks, m->Dn / p.cut.passes);
         }
+        const auto split = [&](int b, int nd) { return persist_split_plan(b, H, nd); };
+        if (G == 0 && choose_cut(B, m->Dn, [&](int b, int nd) { return split(b, nd).shape >= 0; }, &p.split_cut, 1)) {
+            const LaunchCut& c = p.split_cut;
+            p.split[0] = split((B + c.chunks - 1) / c.chunks, m->Dn / c.passes);
+            p.split[1] = B % c.chunks == 0 ? p.split[0] : split(B / c.chunks, m->Dn / c.passes);
+            // (level within the models' errors: the fp32 instruction)
+            if (p.cut.chunks > 0 && 0.97 * p.cut.passes * p.cut.chunks * p.quad[0].us <= c.passes * c.chunks * p.split[0].us) p.split_cut.chunks = 0;
+        }
         // Both fits are within 10 % in nineteen of twenty points, and where they are level so are the kernels.  Up to 64 columns
         // the quads win at every width.
         LaunchCut c;
@@ -941,6 +973,17 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
 static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
 {
     return align256(4 * persist_quad_exchange_words((B + cut.chunks - 1) / cut.chunks, m->hid(l), m->ghid(l), m->Dn / cut.passes)) / 4;
+}
+static size_t split_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
+{
+    return align256(4 * persist_split_exchange_words((B + cut.chunks - 1) / cut.chunks, m->hid(l), m->Dn / cut.passes)) / 4;
+}
+// Does layer l's dense recurrence run on the fp16 matrix instruction?
+static bool quads_run_split(const lstm_t* m, int l, const DensePlans& p)
+{
+    bool have = p.split_cut.chunks > 0;
+    for (int d = 0; d < m->Dn; ++d) have = have && m->ld[(size_t)l * m->Dn + d].wh.rec_split;
+    return have;
 }
 static size_t tile_launch_words(const lstm_t* m, int l, int B, const DensePlans& p)
 {
@@ -1046,6 +1089,7 @@ static Workspace carve(const lstm_t* m, int T, int B)
         const DensePlans p = dense_plans(m, l, B);
         size_t words = 0;
         if (p.cut.chunks > 0) words = quad_launch_words(m, l, B, p.cut) * p.cut.passes * p.cut.chunks;
+        if (p.split_cut.chunks > 0) words = std::max(words, split_launch_words(m, l, B, p.split_cut) * p.split_cut.passes * p.split_cut.chunks);
         if (p.tile_cut.chunks > 0) words = std::max(words, tile_launch_words(m, l, B, p) * p.tile_cut.passes * p.tile_cut.chunks);
         w.qx_words += words;
     }
@@ -1226,10 +1270,12 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
         one_slice = one_slice && w.wh.ell_val && w.wh.slots == 1 && (G == 0 || (w.w2.ell_val && w.w2.slots == 1));
     }
     const DensePlans p = dense_plans(m, l, B);
-    if (p.cut.chunks == 0) return false;
+    const bool split = quads_run_split(m, l, p);
+    const LaunchCut& cut = split ? p.split_cut : p.cut;
+    if (cut.chunks == 0) return false;
     if (B > 1 && csr < Dn) return true;
     if (m->plan == LSTM_PLAN_PERSISTENT) return false;   // asks for the kernels of the matrices' own form
-    double us = T * p.cut.passes * p.cut.chunks * p.quad[0].us, other = 0;
+    double us = T * cut.passes * cut.chunks * (split ? p.split : p.quad)[0].us, other = 0;
     if (B > 1) {
         us += kDenseSetupUs;
         other = T * batched_csr_step_us(m, l, B);
@@ -1382,13 +1428,14 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
     bool dense = true;
     for (int d = 0; d < Dn; ++d) dense = dense && m->ld[(size_t)l * Dn + d].wh.dense;
     if (dense && p.tile_cut.chunks > 0) return run_tile_layer(m, l, T, B, p, P, h0, c0, Yout, y_ld, hT, cT, proj, reg, s);
-    const LaunchCut& cut = p.cut;
-    const size_t words = quad_launch_words(m, l, B, cut);
+    const bool split = quads_run_split(m, l, p);
+    const LaunchCut& cut = split ? p.split_cut : p.cut;
+    const size_t words = split ? split_launch_words(m, l, B, cut) : quad_launch_words(m, l, B, cut);
     for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
         const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
         const int nd = Dn / cut.passes, d_lo = pass * nd;
         const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
-        const PersistQuadPlan& plan = p.quad[bn == (B + cut.chunks - 1) / cut.chunks ? 0 : 1];
+        const PersistQuadPlan& plan = (split ? p.split : p.quad)[bn == (B + cut.chunks - 1) / cut.chunks ? 0 : 1];
         PersistQuadArgs a{};
         for (int d = d_lo; d < d_lo + nd; ++d) {
             const LayerDir& w = m->ld[(size_t)l * Dn + d];
@@ -1397,6 +1444,8 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
             q.P = P[d] + (size_t)b_lo * R;
             q.Wf = w.wh.dense_frag16;
             q.W2f = w.w2.dense_frag16;
+            q.Ws = w.wh.rec_split;
+            q.w_unscale = w.wh.rec_unscale;
             q.bias2 = w.bias2;
             q.h0 = h0 ? h0 + so : nullptr;
             q.c0 = c0 ? c0 + so : nullptr;
@@ -1406,7 +1455,8 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
             q.reverse = d;
             if (chunk == 0) {
                 char tag[128], shape[48], cuts[24] = "";
-                persist_quad_describe(plan, shape, sizeof shape);
+                if (split) persist_split_describe(plan, shape, sizeof shape);
+                else persist_quad_describe(plan, shape, sizeof shape);
                 if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, "(batch/%d)", cut.chunks);
                 std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-dense-%s%s%s;", l, d, proj[d], G > 0 ? "hlstm" : "f32", shape, cuts);
                 m->last_plan += tag;
@@ -1417,7 +1467,8 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
         a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
         a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceQuad;
         ProfSpan span(m, s, 1);
-        HIP_TRY(m, launch_persist_quad(a, plan, reg.next, m->launch_mode() != 0, s));
+        HIP_TRY(m, split ? launch_persist_split(a, plan, reg.next, m->launch_mode() != 0, s)
+                         : launch_persist_quad(a, plan, reg.next, m->launch_mode() != 0, s));
         reg.next += words;
     }
     return LSTM_OK;

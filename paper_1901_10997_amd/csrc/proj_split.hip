@@ -28,13 +28,9 @@ constexpr int kXcds = 8;
 constexpr int kGroupM = 4;
 
 // ---- rows into two fp16 planes
-// out: per row KB blocks of 128 bytes, 32 hi values then 32 lo values of k = 32 kb ..; unscale: 2^-e of the row's scale 2^e, NaN where
-// the row cannot be represented (see split_rows_kernel).
+// out: per row KB blocks of 128 bytes, 32 hi values then 32 lo values of k = 32 kb ..; unscale: 2^-e of the row's scale 2^e, or a mark
+// where the row does not fit (device_math.h).
 constexpr int kSplitRowsPerBlock = 4;
-// A row is marked where its values do not fit: a non-finite one, a largest magnitude outside 2^-60 .. 2^60, or too many that are
-// smaller than the largest by 2^-16 and more, which keep fewer than 22 bits (a 2^-40th of the largest).  A few of those are
-// what any distribution gives (normal values: one in 20000); they would only show where everything else of the row met zeros.
-constexpr unsigned kNonFinite = 0x7f800000u, kTooWide = 0x7fc00000u;   // marks in place of a row's 2^-e
 
 __device__ __forceinline__ uint32_t pack_f16x2(_Float16 a, _Float16 b)
 {
@@ -62,9 +58,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) big = max(big, (unsigned)__shfl_xor((int)big, o, 64));
-        const int e = (int)(big >> 23);             // biased exponent of the largest
-        const bool usable = big == 0 || (e >= 127 - 60 && e <= 127 + 60);
-        const float scale = usable && big ? __uint_as_float((unsigned)(127 + 14 + 127 - e) << 23) : 1.f;
+        const SplitScale sc = split_scale(big);
         int small = 0, nonzero = 0;
         uint16_t* dst = out + (size_t)m * KB * 64;
         for (int k = VEC * lane; k < 32 * KB; k += VEC * 64) {
@@ -79,9 +73,9 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
             _Float16 hi[VEC], lo[VEC];
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
-                const float s = v[i] * scale;
+                const float s = v[i] * sc.scale;
                 nonzero += v[i] != 0.f;
-                small += v[i] != 0.f && fabsf(s) < 0.25f;
+                small += v[i] != 0.f && fabsf(s) < kSplitSmall;
                 hi[i] = (_Float16)s;
                 lo[i] = (_Float16)(s - (float)hi[i]);
             }
@@ -96,8 +90,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) { small += __shfl_xor(small, o, 64); nonzero += __shfl_xor(nonzero, o, 64); }
-        if (lane == 0)
-            unscale[m] = big >= 0x7f800000u ? __uint_as_float(kNonFinite) : (!usable || small > nonzero / 64 + (nonzero >= 8 ? 2 : 0)) ? __uint_as_float(kTooWide) : 1.f / scale;
+        if (lane == 0) unscale[m] = split_unscale(sc, big, small, nonzero);
     }
 }
 
