@@ -14,6 +14,7 @@ namespace l355 {
 struct PackedMat {
     int rows = 0, cols = 0;
     bool compressed = false;
+    bool many_zeros = false;     // a mask that keeps less than three in five
     void* dense = nullptr;       // [rows][cols], fp32 or bf16 bits; +0 where the mask is 0
     float* dense_frag16 = nullptr;  // fp32: the dense matrix in the fragment order of the 16-row matrix instructions: input-side
                                     // ones for products with at most 64 input rows (launch_proj_mfma), recurrent ones for
@@ -116,12 +117,13 @@ struct ProjSplitArgs {
     const float* X;               // the same rows as fp32
     int ldx;
     int M, N, K, ndir;
+    int masked;                   // W has many zeros: sums in two stages
     int gm, gn, npid;             // set by the launcher
 };
 size_t split_row_halves(int K);
 hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, hipStream_t s);
 constexpr int kSplitMinK = 64;
-bool proj_split_supported(int M, int N, int K, int ndir);   // and faster than the fp32 instruction
+bool proj_split_supported(int M, int N, int K, int ndir, bool masked);   // and faster than the fp32 instruction
 double proj_split_us(int M, int N, int K, int ndir, bool masked);   // modelled time, with launch_split_rows
 hipError_t launch_proj_split(const ProjSplitArgs& a, hipStream_t s);
 // XT[k][m] = (float) X[m][k]   (optionally rounding fp32 -> bf16 -> fp32 on the way)

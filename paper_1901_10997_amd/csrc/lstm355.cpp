@@ -461,6 +461,11 @@ static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t*
     out.rows = rows;
     out.cols = cols;
     out.compressed = compressed;
+    if (mask) {
+        size_t kept = 0;
+        for (size_t i = 0; i < (size_t)rows * cols; ++i) kept += mask[i];
+        out.many_zeros = (double)kept < 0.6 * (double)rows * (double)cols;
+    }
     auto abi_row = [H](int rp) { return (rp & 3) * H + (rp >> 2); };
     if (!compressed || keep_dense) {
         const size_t n = (size_t)rows * cols;
@@ -1338,7 +1343,7 @@ static bool fuses_input(const lstm_t* m, int l, int T, int B)
 // Does the projection of M rows through this matrix run on the fp16 matrix instruction?
 static bool proj_runs_split(const PackedMat& wx, int M, int ndir)
 {
-    return wx.split != nullptr && proj_split_supported(M, wx.rows, wx.pad_ld, ndir);
+    return wx.split != nullptr && proj_split_supported(M, wx.rows, wx.pad_ld, ndir, wx.many_zeros);
 }
 
 // Modelled time of the projection over the kept entries (7 shapes, 2 to 17 % kept: within 20 %): products by slot, the passes over
@@ -1367,6 +1372,7 @@ static int run_split_proj(lstm_t* m, const LayerDir* const* w, float* const* P, 
     }
     a.Xs = xs; a.x_unscale = xu; a.X = X; a.ldx = p0.pad_ld;
     a.M = M; a.N = p0.rows; a.K = p0.pad_ld; a.ndir = n;
+    for (int d = 0; d < n; ++d) a.masked |= w[d]->wx.many_zeros;
     HIP_TRY(m, launch_proj_split(a, s));
     return LSTM_OK;
 }
@@ -1933,7 +1939,10 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                        (double)p.nnz <= m->sparse_proj_max_density * (double)p.rows * (double)p.cols;
                 pslots = std::max(pslots, p.q16_slots);
             }
-            bool split = !m->sparse_proj_given;
+            // In front of a recurrence whose gates keep no more than the absolute error of their exponentials, the sums over the
+            // kept entries stay: two fp16 planes and 16 terms at a time are twice as far from 64 bits (1.5e-7 against 0.8e-7 of
+            // the product's norm), which showed in the cell states (2 x 307, 17 % kept: 2.2e-7 against 1.9e-7).
+            bool split = !m->sparse_proj_given && quads && quads_run_split(m, l, dense_plans(m, l, B));
             for (int d = 0; d < Dn && q16p; ++d) split = split && proj_runs_split(m->ld[(size_t)l * Dn + d].wx, M, Dn);
             if (q16p && proj_q16_supported(M, H, D, pslots) &&
                 !(split && proj_split_us(M, 4 * H, D, Dn, true) < 0.9 * proj_q16_us(M, H, D, pslots, Dn))) {
@@ -2671,6 +2680,7 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     std::vector<int32_t> rp((size_t)n + 1, 0);
     std::vector<uint16_t> col;
     std::vector<float> val;
+    size_t kept_all = 0;
     for (int r = 0; r < n; ++r) {
         for (int k = 0; k < n; ++k) {
             float w;
@@ -2684,6 +2694,7 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
                 kept = keep >= 1.0 || rng.uniform() < keep;
             }
             W[(size_t)r * n + k] = kept ? w : 0.0f;
+            kept_all += kept;
             if (kept && format == LSTM_FMT_ROW_COMPRESSED) { col.push_back((uint16_t)k); val.push_back(w); }
         }
         rp[(size_t)r + 1] = (int32_t)col.size();
@@ -2708,7 +2719,8 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     int32_t* drp = nullptr;
     uint16_t *dcol = nullptr, *dec = nullptr, *dXs = nullptr, *dWs = nullptr;
     float *dxu = nullptr, *dwu = nullptr;
-    bool split = format == LSTM_FMT_DENSE_MASKED && proj_split_supported(batch, n, n, 1);
+    const bool zeros = (double)kept_all < 0.6 * (double)nn;
+    bool split = format == LSTM_FMT_DENSE_MASKED && proj_split_supported(batch, n, n, 1, zeros);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = LSTM_OK;
     auto run = [&]() -> hipError_t {
@@ -2718,7 +2730,7 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
             ProjSplitArgs a{};
             a.d[0] = ProjSplitDir{dWs, dwu, dB, dY, dW, nullptr, nullptr, nullptr};
             a.Xs = dXs; a.x_unscale = dxu; a.X = dX; a.ldx = n;
-            a.M = batch; a.N = n; a.K = n; a.ndir = 1;
+            a.M = batch; a.N = n; a.K = n; a.ndir = 1; a.masked = zeros;
             return launch_proj_split(a, s);
         }
         if (use_ell) return launch_proj_ell_small(dX, false, n, false, dev_, dec, slots, dB, dY, batch, n, n, s);

@@ -170,10 +170,10 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
 
     // h of item j as step tag `tag` of its buffers.  Lane 4 u + p of a row: unit u, plane p; the four units of a plane are gathered
     // in lane p.  Columns beyond the batch are published as well (readers wait for every word; what such a column holds is
-    // never used).  odd: not a number, or (h0) not within 1.
-    auto publish = [&](float h, bool odd, unsigned tag, int pass, int j) {
+    // never used).
+    auto publish = [&](float h, unsigned tag, int pass, int j) {
         const _Float16 hi = (_Float16)h, lo = (_Float16)((h - (float)hi) * kLoScale);
-        const unsigned bits = odd ? 0x7E00u : half_bits(gate == 0 ? hi : lo);
+        const unsigned bits = half_bits(gate == 0 ? hi : lo);
         const unsigned w0 = bits | (dpp_word<0x104>(bits) << 16), w1 = dpp_word<0x108>(bits) | (dpp_word<0x10C>(bits) << 16);
         if (lr < 2 && have_quad(pass, j) && unit[j] < H) {   // (lanes 0 and 1: the first unit of the four)
             const unsigned mark = ((w0 | w1) & 0x40004000u) ? kOddMark : 0u;
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
         for (int j = 0; j < kMine; ++j)
             if (live[j]) {
                 const float h = h0 && have_col(pass, j) && unit[j] < H ? h0[(size_t)(col[j] + 4 * QP * pass) * H + unit[j]] : 0.f;
-                publish(h, !(fabsf(h) <= 1.f), 2u, pass, j);
+                publish(fabsf(h) <= 1.f ? h : __uint_as_float(0x7fc00000u), 2u, pass, j);   // beyond 1: marked as a NaN is
             }
 
     float p_next[kMine];
@@ -204,6 +204,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     };
     load_p(0);
     int buf = 0;                                                         // of the partial tiles
+    const float near = gate == 3 ? kTanhNear : -1.f;                     // the candidate's tanh
     float lo_scale;                                                      // in a register: the sum of the planes is one instruction
     asm volatile("v_mov_b32 %0, 0x39800000" : "=v"(lo_scale));           // 2^-12
     // where the sum of this thread's item and row lies in a partial tile (see below)
@@ -340,11 +341,12 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                     const float pre = fmaf(sum, us[j], p_cur[j]);
                     const bool cand = gate == 3;
                     const float rr = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f((cand ? 2.8853900817779268f : -1.4426950408889634f) * pre));
-                    const float gv = cand ? fmaf(-2.0f, rr, 1.0f) : rr;
+                    float gv = cand ? fmaf(-2.0f, rr, 1.0f) : rr;
+                    gv = fabsf(pre) < near ? tanhf_near(pre) : gv;
                     const float f = dpp_mov<0x00>(gv), ig = dpp_mov<0x55>(gv), o = dpp_mov<0xAA>(gv), g = dpp_mov<0xFF>(gv);   // of a lane quad
                     const float c = fmaf(f, c_prev, ig * g);
-                    const float h = o * tanhf_fast(c);
-                    if (!last) publish(h, h != h, (unsigned)s + 3u, pass, j);
+                    const float h = o * tanhf_exact(c);
+                    if (!last) publish(h, (unsigned)s + 3u, pass, j);
                     *cp = c;
                     // outputs after the publication: nothing on the way of h
                     if (have_col(pass, j) && unit[j] < H && gate == 0) {

@@ -195,7 +195,14 @@ __device__ __forceinline__ void f32_tiles(const ProjSplitArgs& a, int dir, int m
     }
 }
 
-template <int TM, int TN, int WM, int WN, int NST>   // wave tile, waves, slabs in the LDS ring
+// TM x TN: 32 x 32 tiles of a wave; WM x WN waves; NST slabs in the LDS ring; STAGED: sums in two stages.
+// STAGED (masked weights): the accumulators are added up and cleared every kStage slabs.  An fp32 sum that meets a mask's zeros
+// rounds once per kept term; an instruction over 16 k rounds whether they are zeros or not, 3 K / 16 times in all.  In two
+// stages the terms are a small part of the sum when they are rounded: K 1600, 15 % kept, error against 64 bits relative to the
+// product's norm: fp32 instruction 2.8e-7, one stage 3.8e-7, two 1.5e-7 (310 us against 271, 4800 x 3200 in two directions; dense
+// weights 7.2e-7, 4.6e-7 and 1.7e-7).
+constexpr int kStage = 4;
+template <int TM, int TN, int WM, int WN, int NST, bool STAGED>
 __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitArgs a)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32, NW = WM * WN;
@@ -237,13 +244,16 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
         const int m0 = tile_m * BM, n0 = (tn_all - dir * a.gn) * BN;
         if (pid != (int)blockIdx.x) __builtin_amdgcn_s_barrier();
 
-        f32x16 acc[TM][TN];
+        f32x16 acc[TM][TN], total[STAGED ? TM : 1][STAGED ? TN : 1];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+                for (int v = 0; v < 16; ++v) {
+                    acc[i][j][v] = 0.f;
+                    if (STAGED) total[STAGED ? i : 0][STAGED ? j : 0][v] = 0.f;
+                }
 
         // direct loads: instruction q of a slab covers LDS rows 8 q .. 8 q + 7 of the combined [X rows | W rows]
         // (eight rows of one operand: scalar base pointer, one 32-bit element offset per instruction and lane)
@@ -348,6 +358,17 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
                 mma(al, bh);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (STAGED && (kt % kStage == kStage - 1 || kt == KB - 1)) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            total[STAGED ? i : 0][STAGED ? j : 0][v] += acc[i][j][v];
+                            acc[i][j][v] = kt == KB - 1 ? total[STAGED ? i : 0][STAGED ? j : 0][v] : 0.f;
+                        }
+            }
         }
         // ---- P = acc * 2^-(ex + ew) + bias; accumulator register v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
         const float* bias = a.d[dir].bias;
@@ -395,7 +416,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
     }
 }
 
-template <int TM, int TN, int WM, int WN, int NST>
+template <int TM, int TN, int WM, int WN, int NST, bool STAGED>
 static hipError_t launch_tiles(ProjSplitArgs a, int per_cu, hipStream_t s)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
@@ -403,10 +424,10 @@ static hipError_t launch_tiles(ProjSplitArgs a, int per_cu, hipStream_t s)
     a.gn = (a.N + BN - 1) / BN;
     a.npid = ((a.gm * a.gn * a.ndir + kXcds - 1) / kXcds) * kXcds;
     const int lds = NST * (BM + BN) * 128;
-    const hipError_t e = hipFuncSetAttribute((const void*)proj_split_kernel<TM, TN, WM, WN, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = hipFuncSetAttribute((const void*)proj_split_kernel<TM, TN, WM, WN, NST, STAGED>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     const int slots = std::max(kXcds, device_num_cus() * per_cu / kXcds * kXcds);
-    hipLaunchKernelGGL((proj_split_kernel<TM, TN, WM, WN, NST>), dim3(std::min(a.npid, slots)), dim3(64 * WM * WN), lds, s, a);
+    hipLaunchKernelGGL((proj_split_kernel<TM, TN, WM, WN, NST, STAGED>), dim3(std::min(a.npid, slots)), dim3(64 * WM * WN), lds, s, a);
     return hipGetLastError();
 }
 
@@ -422,13 +443,14 @@ static const SplitShape kSplitShapes[] = {{256, 256, 1, 3.05, 2.0, 5.5}, {128, 2
                                           {64, 128, 2, 0.548, 0.55, 1.0}, {64, 64, 2, 0.30, 0.35, 0.8}};
 static const double kLaunchUs = 2.5;
 
-static int choose_shape(int M, int N, int K, int ndir, double* us)
+// masked: the sums in two stages need twice the accumulators, which the largest tile has no registers for
+static int choose_shape(int M, int N, int K, int ndir, bool masked, double* us)
 {
     const double cus = device_num_cus();
     const int KB = (K + 31) / 32;
-    int best = 0;
+    int best = 1;
     *us = 1e30;
-    for (int i = 0; i < (int)(sizeof kSplitShapes / sizeof kSplitShapes[0]); ++i) {
+    for (int i = masked ? 1 : 0; i < (int)(sizeof kSplitShapes / sizeof kSplitShapes[0]); ++i) {
         const SplitShape& h = kSplitShapes[i];
         const double tiles = (double)((M + h.bm - 1) / h.bm) * ((N + h.bn - 1) / h.bn) * ndir, r = tiles / cus;
         // two workgroups of a compute unit share it: its second tile is half free
@@ -442,21 +464,18 @@ static int choose_shape(int M, int N, int K, int ndir, double* us)
 double proj_split_us(int M, int N, int K, int ndir, bool masked)
 {
     double us;
-    const int shape = choose_shape(M, N, K, ndir, &us);
-    // Full grids of the largest tiles run at the device's power limit, and a mask's zeros switch little: 4800 x 3200 x 1600 in two
-    // directions 325 us with dense weights, 250 with up to 17 % kept.
-    if (masked && shape == 0) us *= 0.8;
+    (void)choose_shape(M, N, K, ndir, masked, &us);
     return us + 3 * kLaunchUs + 8.0 * M * K / 5.4e6;   // the pass over X, its launch and the gaps
 }
 
 // More than 64 input rows, K from 64 on (with fewer terms the fp32 instruction's sum is as close to the exact one) and
 // large enough that the pass over X is made up for.
-bool proj_split_supported(int M, int N, int K, int ndir)
+bool proj_split_supported(int M, int N, int K, int ndir, bool masked)
 {
     if (M <= 64 || K < kSplitMinK || K % 4 != 0) return false;
     const double tiles = (double)((M + 63) / 64) * ((N + 63) / 64) * ndir;
     const double f32_us = 2 * kLaunchUs + (K + 31) / 32 * std::max(0.83, 0.66 * tiles / device_num_cus());   // 64 x 64 tiles, fp32
-    return proj_split_us(M, N, K, ndir, false) < f32_us;
+    return proj_split_us(M, N, K, ndir, masked) < f32_us;
 }
 
 hipError_t launch_proj_split(const ProjSplitArgs& a, hipStream_t s)
@@ -464,12 +483,20 @@ hipError_t launch_proj_split(const ProjSplitArgs& a, hipStream_t s)
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (a.K % 4 != 0 || a.ldx % 4 != 0) return hipErrorInvalidValue;
     double us;
-    switch (choose_shape(a.M, a.N, a.K, a.ndir, &us)) {
-        case 0: return launch_tiles<4, 2, 2, 4, 2>(a, 1, s);
-        case 1: return launch_tiles<2, 2, 2, 4, 2>(a, 1, s);
-        case 2: return launch_tiles<2, 2, 2, 2, 2>(a, 2, s);
-        case 3: return launch_tiles<2, 1, 1, 4, 3>(a, 2, s);
-        default: return launch_tiles<1, 1, 2, 2, 4>(a, 2, s);
+    const int shape = choose_shape(a.M, a.N, a.K, a.ndir, a.masked != 0, &us);
+    if (a.masked)
+        switch (shape) {
+            case 1: return launch_tiles<2, 2, 2, 4, 2, true>(a, 1, s);
+            case 2: return launch_tiles<2, 2, 2, 2, 2, true>(a, 2, s);
+            case 3: return launch_tiles<2, 1, 1, 4, 3, true>(a, 2, s);
+            default: return launch_tiles<1, 1, 2, 2, 4, true>(a, 2, s);
+        }
+    switch (shape) {
+        case 0: return launch_tiles<4, 2, 2, 4, 2, false>(a, 1, s);
+        case 1: return launch_tiles<2, 2, 2, 4, 2, false>(a, 1, s);
+        case 2: return launch_tiles<2, 2, 2, 2, 2, false>(a, 2, s);
+        case 3: return launch_tiles<2, 1, 1, 4, 3, false>(a, 2, s);
+        default: return launch_tiles<1, 1, 2, 2, 4, false>(a, 2, s);
     }
 }
 

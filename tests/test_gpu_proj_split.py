@@ -34,6 +34,20 @@ def test_product_over_the_tile_shapes(n, batch):
         assert np.max(np.abs(d)) <= 8 * _bound(n) * np.sqrt(np.mean(ref ** 2))
 
 
+@pytest.mark.parametrize("n,batch", [(1032, 130), (6404, 300), (2400, 1500), (4100, 1900)])
+def test_masked_product_in_two_stages(n, batch):
+    """Weights with many zeros: sums in two stages.  What K rounded sums would add is gone: per stage of 128 k 24 rounded sums
+    of a share of the result, then one per stage."""
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((batch, n)).astype(np.float32)
+    W = (rng.uniform(-0.1, 0.1, (n, n)) * (rng.random((n, n)) < 0.15)).astype(np.float32)
+    _, y = B.lstm_bench_matmul(n, batch, 1.0, B.LSTM_FMT_DENSE_MASKED, iters=1, want_product=True, X=X, W=W, mask=(W != 0).astype(np.uint8))
+    rows = slice(max(0, batch - 160), batch)
+    ref = X[rows].astype(np.float64) @ W.astype(np.float64).T
+    bound = 2.0 ** -23 * 4 + 2.0 ** -24 * np.sqrt(24 + n / 128)
+    assert np.linalg.norm(y[rows] - ref) <= bound * np.linalg.norm(ref), (np.linalg.norm(y[rows] - ref) / np.linalg.norm(ref), bound)
+
+
 def test_rows_that_do_not_fit_two_fp16_planes():
     """Rows of any scale, with zeros, denormals, values far below the largest, infinities and NaN give what fp32 arithmetic
     gives: every finite row within the fp32 bound of its own result, every other one its infinities and NaN."""
