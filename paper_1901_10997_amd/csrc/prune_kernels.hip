@@ -200,39 +200,151 @@ hipError_t launch_prune_weights(const float* W, uint8_t* mask, size_t count, dou
 // thousand fp32 magnitudes is not exact in general, and the decision "sum <= threshold" must come out the same on
 // every implementation for the masks to be reproducible bit for bit.
 //
-// Bound: the chain of dependent fp64 additions along a line (about 8 clocks each: 6000 rows = 20 us), as long as nothing
-// else sits on it.  A workgroup sums 16 lines: four waves fetch tiles of 512 positions (the loads of the tile after next
-// are in flight while the next one is parked), select by the mask, take magnitudes, widen and park them in LDS as fp64,
-// line by line; one wave, a lane per line, does nothing but 16-byte LDS reads, requested a batch ahead, and additions.
-// With 16 lines a 1500-column matrix gives 94 workgroups (64 lines: 24, which cannot pull the matrix in at the rate the
-// chain consumes it), and a tile's line pitch of 514 doubles puts the 16 lanes of a read on distinct banks.
-// 6000 x 1500: column sums 849 -> 40 us, row sums 200 -> 25 us (against one wave widening and adding 64 lines).
-constexpr int kSumLines = 16, kSumTile = 512, kSumPitch = kSumTile + 2, kSumBatch = 16;
-constexpr int kSumThreads = 320;   // one summing wave, four fetching ones
-constexpr size_t kSumLds = (size_t)2 * kSumLines * kSumPitch * sizeof(double) + (size_t)2 * kSumTile * sizeof(int);
-
 struct LineThreshold {
     double value;   // the k-th smallest sum
     unsigned any;   // 0: rank 0 was asked for, nothing is removed along this axis
     unsigned count; // lines removed
 };
 
-// COLS: lines are columns (positions run down the rows), else rows.  VEC: four columns per load (N and both addresses
-// allow it).  AFTER (with COLS): lanes 16..31 sum the same columns over the rows that stay, i.e. those whose sum in
-// `rsums` is above the row threshold, into sums_after.
-template <bool COLS, bool VEC, bool AFTER>
-__global__ __launch_bounds__(kSumThreads) void line_abs_sum_f64_kernel(const float* __restrict__ W,
-                                                                       const uint8_t* __restrict__ mask, int M, int N,
-                                                                       double* __restrict__ sums, double* __restrict__ sums_after,
-                                                                       const double* __restrict__ rsums,
-                                                                       const LineThreshold* __restrict__ row_th)
+// Row sums.  Bound: one read of the matrix.  The order needs a chain of dependent additions only where an addition rounds,
+// and most rows never round: every fp32 magnitude is a multiple of the last place of the smallest one that is not zero
+// (2^q), and while the whole sum is below 2^(q + 53) every partial sum in any order is a multiple of 2^q below it, which
+// fp64 holds exactly.  So the lanes of a wave sum a row together with its smallest magnitude, and the sum stands if it is
+// below 2^(q + 52) (one bit spared: a sum that itself has rounded is off by a few 2^-53 per addition).  Otherwise, also for
+// infinities and NaN, the wave sums the row again as the chain.  Weights left by magnitude pruning stop at its threshold and
+// pass (6000 of them from a twentieth to four standard deviations: 43 bits); of rows of 1500 normal deviates one in 300
+// fails.
+// 6000 x 1500 (45 MB), four waves per workgroup: 25.0 -> 8.5..9.5 us against the chain for every row, normal deviates 18, 46
+// where every row fails (magnitudes over 15 e-folds); 16384 x 500 22.1 -> 9.9, 3000 x 3000 21.8 -> 8.5 (normal 25.6).
+constexpr int kRowWaves = 4;       // waves (rows) per workgroup
+constexpr int kChainTile = 384;    // positions of a row in LDS at a time
+
+// One row by a whole wave, in index order.  Lanes fetch a tile of positions (the next one is in flight meanwhile: a tile is
+// long enough to cover the latency) and park it as fp64; every lane adds them all, from LDS reads requested a batch ahead.
+// buf: the wave's own [kChainTile].
+__device__ __forceinline__ double chain_sum(const float* __restrict__ w_row, const uint8_t* __restrict__ mask_row, unsigned len, double* buf)
+{
+    const int lane = threadIdx.x & 63;
+    constexpr int kMine = kChainTile / 64, kBatch = 8, kBatches = kChainTile / 2 / kBatch;
+    float w[kMine];
+    uint8_t on[kMine];
+    auto fetch = [&](unsigned t) {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const unsigned pos = t + lane + 64 * i, at = pos < len ? pos : 0;
+            w[i] = w_row[at];
+            on[i] = pos < len ? mask_row[at] : (uint8_t)0;
+        }
+    };
+    fetch(0);
+    double acc = 0.0;
+    for (unsigned t = 0; t < len; t += kChainTile) {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) buf[lane + 64 * i] = on[i] ? (double)fabsf(w[i]) : 0.0;
+        if (t + kChainTile < len) fetch(t + kChainTile);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const double2* const src = reinterpret_cast<const double2*>(buf);
+        const unsigned left = len - t;                                      // positions behind the end hold +0, which changes nothing
+        const int n = left < kChainTile ? (int)(left + 2 * kBatch - 1) / (2 * kBatch) : kBatches;
+        double2 cur[kBatch], nxt[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) cur[i] = src[i];
+        for (int k = 0; k < n; ++k) {
+            const int kn = k + 1 < n ? k + 1 : k;
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) nxt[i] = src[kn * kBatch + i];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                acc += cur[i].x;
+                acc += cur[i].y;
+            }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) cur[i] = nxt[i];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    return acc;
+}
+
+// Row sums, a wave per row.  VEC: four entries per load (N and both addresses allow it).
+template <bool VEC>
+__global__ __launch_bounds__(64 * kRowWaves) void row_abs_sum_kernel(const float* __restrict__ W, const uint8_t* __restrict__ mask, int M, int N,
+                                                                     double* __restrict__ sums)
+{
+    __shared__ __attribute__((aligned(16))) double chain[kRowWaves][kChainTile];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, r = blockIdx.x * kRowWaves + wv;
+    if (r >= M) return;
+    const size_t first = (size_t)r * N;
+    constexpr int kPer = VEC ? 4 : 1, kAhead = VEC ? 4 : 8;
+    // sum of magnitudes and the smallest one's bits minus one, which puts zeros (they limit nothing) above all others
+    double sum = 0.0;
+    unsigned least = 0xFFFFFFFFu;
+    const unsigned n = (unsigned)N;                                      // (positions past the end of the longest row fit 32 bits)
+    for (unsigned c0 = lane * kPer; c0 < n; c0 += kAhead * 64 * kPer) {
+        float w[kAhead][kPer];
+        uint32_t on[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const unsigned c = c0 + u * 64 * kPer;
+            const size_t idx = first + (c < n ? c : 0);                  // (VEC: N % 4 == 0, a load is in or out as a whole)
+            if constexpr (VEC) {
+                const float4 v = *reinterpret_cast<const float4*>(W + idx);
+                w[u][0] = v.x; w[u][1] = v.y; w[u][2] = v.z; w[u][3] = v.w;
+                on[u] = *reinterpret_cast<const uint32_t*>(mask + idx);
+            } else {
+                w[u][0] = W[idx];
+                on[u] = mask[idx];
+            }
+            if (c >= n) on[u] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                const float v = ((on[u] >> (8 * j)) & 255u) ? fabsf(w[u][j]) : 0.f;
+                sum += (double)v;
+                least = min(least, __float_as_uint(v) - 1u);
+            }
+    }
+    for (int off = 1; off < 64; off <<= 1) {
+        sum += __shfl_xor(sum, off, 64);
+        least = min(least, (unsigned)__shfl_xor((int)least, off, 64));
+    }
+    // the smallest magnitude is a multiple of 2^(exponent - 150)
+    const int exponent = (int)((least + 1u) >> 23);
+    const bool exact = least == 0xFFFFFFFFu || sum < ldexp(1.0, (exponent > 0 ? exponent : 1) - 150 + 52);
+    if (!exact) sum = chain_sum(W + first, mask + first, n, chain[wv]);
+    if (lane == 0) sums[r] = sum;
+}
+
+// Column sums.  Bound: the chain of dependent fp64 additions down a column (about 8 clocks each: 6000 rows = 20 us), as long
+// as nothing else sits on it.  A workgroup sums 16 columns: four waves fetch tiles of 512 positions (the loads of the tile
+// after next are in flight while the next one is parked), select by the mask, take magnitudes, widen and park them in LDS as
+// fp64, column by column; one wave, a lane per column, does nothing but 16-byte LDS reads, requested a batch ahead, and
+// additions.  With 16 columns a 1500-column matrix gives 94 workgroups (64: 24, which cannot pull the matrix in at the rate
+// the chain consumes it), and a tile's pitch of 514 doubles puts the 16 lanes of a read on distinct banks.
+// 6000 x 1500: 849 -> 39 us (against one wave widening and adding 64 columns).  Summed like the rows 27 us, but a column has
+// four times the terms, one in twenty of 6000 normal deviates fails the test, and a wave's chain down a column 70 us.
+constexpr int kSumLines = 16, kSumTile = 512, kSumPitch = kSumTile + 2, kSumBatch = 16;
+constexpr int kSumThreads = 320;   // one summing wave, four fetching ones
+constexpr size_t kSumLds = (size_t)2 * kSumLines * kSumPitch * sizeof(double) + (size_t)2 * kSumTile * sizeof(int);
+
+// VEC: four columns per load (N and both addresses allow it).  AFTER: lanes 16..31 sum the same columns over the rows that
+// stay, i.e. those whose sum in `rsums` is above the row threshold, into sums_after.
+template <bool VEC, bool AFTER>
+__global__ __launch_bounds__(kSumThreads) void col_abs_sum_kernel(const float* __restrict__ W, const uint8_t* __restrict__ mask, int M, int N,
+                                                                  double* __restrict__ sums, double* __restrict__ sums_after,
+                                                                  const double* __restrict__ rsums,
+                                                                  const LineThreshold* __restrict__ row_th)
 {
     extern __shared__ __attribute__((aligned(16))) double buf[];   // [2][16][514], then [2][512] ints: row is removed
     int* const gone = reinterpret_cast<int*>(buf + 2 * kSumLines * kSumPitch);
     const int lane = threadIdx.x & 63;
     const int p = (int)threadIdx.x - 64;                     // fetching thread 0..255
     const int line0 = blockIdx.x * kSumLines;
-    const int len = COLS ? M : N, lines = COLS ? N : M;
+    const int len = M, lines = N;
     const int tiles = (len + kSumTile - 1) / kSumTile;
     constexpr int kPer = VEC ? 4 : 1;                        // columns per load
     constexpr int kLoads = kSumLines * kSumTile / kPer / 256;
@@ -242,17 +354,16 @@ __global__ __launch_bounds__(kSumThreads) void line_abs_sum_f64_kernel(const flo
     // (line, position) of load i of this thread; its kPer values run along the columns
     auto place = [&](int i, int& line, int& pos) {
         const int e = p + 256 * i;
-        constexpr int kRow = (COLS ? kSumLines : kSumTile) / kPer;   // loads per row of the tile
-        const int c = (e % kRow) * kPer, r = e / kRow;
-        line = COLS ? c : r;
-        pos = COLS ? r : c;
+        constexpr int kRow = kSumLines / kPer;                   // loads per row of the tile
+        line = (e % kRow) * kPer;
+        pos = e / kRow;
     };
     auto fetch = [&](int tile) {
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) {
             int line, pos;
             place(i, line, pos);
-            const int r = COLS ? tile * kSumTile + pos : line0 + line, c = COLS ? line0 + line : tile * kSumTile + pos;
+            const int r = tile * kSumTile + pos, c = line0 + line;
             const size_t idx = (r < M && c < N) ? (size_t)r * N + c : 0;   // (VEC: N % 4 == 0, a load is in or out as a whole)
             if constexpr (VEC) {
                 const float4 v = *reinterpret_cast<const float4*>(W + idx);
@@ -280,8 +391,7 @@ __global__ __launch_bounds__(kSumThreads) void line_abs_sum_f64_kernel(const flo
             place(i, line, pos);
 #pragma unroll
             for (int j = 0; j < kPer; ++j)
-                b[(line + (COLS ? j : 0)) * kSumPitch + pos + (COLS ? 0 : j)] =
-                    ((on[i] >> (8 * j)) & 255u) ? (double)fabsf(w[i][j]) : 0.0;
+                b[(line + j) * kSumPitch + pos] = ((on[i] >> (8 * j)) & 255u) ? (double)fabsf(w[i][j]) : 0.0;
         }
         if constexpr (AFTER) {
 #pragma unroll
@@ -447,17 +557,28 @@ __global__ void clear_removed_kernel(int* removed)
     if (threadIdx.x < 2) removed[threadIdx.x] = 0;
 }
 
-template <bool COLS, bool AFTER>
-static hipError_t launch_line_sums(const float* W, const uint8_t* mask, int M, int N, double* sums, double* after,
-                                   const double* rsums, const LineThreshold* th, hipStream_t s)
+static bool line_loads_fit(const float* W, const uint8_t* mask, int N)
 {
-    const bool vec = (N & 3) == 0 && ((uintptr_t)W & 15) == 0 && ((uintptr_t)mask & 3) == 0;
-    const void* kern = vec ? (const void*)line_abs_sum_f64_kernel<COLS, true, AFTER> : (const void*)line_abs_sum_f64_kernel<COLS, false, AFTER>;
+    return (N & 3) == 0 && ((uintptr_t)W & 15) == 0 && ((uintptr_t)mask & 3) == 0;
+}
+
+static hipError_t launch_row_sums(const float* W, const uint8_t* mask, int M, int N, double* sums, hipStream_t s)
+{
+    const dim3 grid((M + kRowWaves - 1) / kRowWaves), block(64 * kRowWaves);
+    if (line_loads_fit(W, mask, N)) hipLaunchKernelGGL(row_abs_sum_kernel<true>, grid, block, 0, s, W, mask, M, N, sums);
+    else hipLaunchKernelGGL(row_abs_sum_kernel<false>, grid, block, 0, s, W, mask, M, N, sums);
+    return hipGetLastError();
+}
+
+template <bool AFTER>
+static hipError_t launch_col_sums(const float* W, const uint8_t* mask, int M, int N, double* sums, double* after,
+                                  const double* rsums, const LineThreshold* th, hipStream_t s)
+{
+    const void* kern = line_loads_fit(W, mask, N) ? (const void*)col_abs_sum_kernel<true, AFTER> : (const void*)col_abs_sum_kernel<false, AFTER>;
     const hipError_t e = allow_dynamic_lds(kern, kSumLds);
     if (e != hipSuccess) return e;
-    const int lines = COLS ? N : M;
     void* args[] = {&W, &mask, &M, &N, &sums, &after, &rsums, &th};
-    return hipLaunchKernel(kern, dim3((lines + kSumLines - 1) / kSumLines), dim3(kSumThreads), args, kSumLds, s);
+    return hipLaunchKernel(kern, dim3((N + kSumLines - 1) / kSumLines), dim3(kSumThreads), args, kSumLds, s);
 }
 
 // removed: device-visible int[2], receives the number of removed rows and columns
@@ -476,15 +597,15 @@ hipError_t launch_prune_rows_cols(float* W, uint8_t* mask, int M, int N, unsigne
     hipError_t e = hipSuccess;
     // Both thresholds come from the matrix as it came in; rows are removed first and columns judged on what that leaves.
     if (k_rows > 0) {
-        e = launch_line_sums<false, false>(W, mask, M, N, rsums, nullptr, nullptr, nullptr, s);
+        e = launch_row_sums(W, mask, M, N, rsums, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, rsums, M, k_rows, rsums, th, (int*)nullptr, removed);
     }
     if (k_cols > 0) {
         // without removed rows the sums as passed in are also the ones to judge, and one pass reads both
         double* const judged = k_rows > 0 ? csums_after : csums;
-        e = k_rows > 0 ? launch_line_sums<true, true>(W, mask, M, N, csums, csums_after, rsums, th, s)
-                       : launch_line_sums<true, false>(W, mask, M, N, csums, nullptr, nullptr, nullptr, s);
+        e = k_rows > 0 ? launch_col_sums<true>(W, mask, M, N, csums, csums_after, rsums, th, s)
+                       : launch_col_sums<false>(W, mask, M, N, csums, nullptr, nullptr, nullptr, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, csums, N, k_cols, judged, th + 1,
                            k_rows > 0 ? list : (int*)csums_after, removed + 1);

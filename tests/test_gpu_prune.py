@@ -174,3 +174,59 @@ def test_mask_updates_from_more_threads_than_scratch_areas():
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+def _sum_in_order(line):
+    s = np.float64(0)
+    for v in line:
+        s = s + np.float64(abs(v))
+    return s
+
+
+def _in_three(value):
+    """fp32 numbers of 24 bits each that add up to `value` (at most 72 bits long) exactly, the largest first."""
+    out, left = [], np.float64(value)
+    for _ in range(3):
+        f = np.float32(left)
+        if np.float64(f) > left:
+            f = np.nextafter(f, np.float32(0))
+        out.append(f)
+        left = left - np.float64(f)
+    assert left == 0
+    return out
+
+
+@pytest.mark.parametrize("axis", ["rows", "cols", "both"])
+@pytest.mark.parametrize("width", [40, 41])
+@pytest.mark.parametrize("k", [4, 5, 6, 30])
+def test_line_sums_round_as_the_sum_in_index_order(axis, width, k):
+    """2^k and a run of entries whose last bit is 2^-47: a sum below 2^6 fits 53 bits in any order, above it the additions in
+    index order round one by one and a sum in another order ends elsewhere.  A line that holds the result of the order
+    exactly ties with it and goes, the next double above stays; a line of denormals is the smallest, an infinite one the
+    largest."""
+    rng = np.random.default_rng(k)
+    n = 1100
+    fine = np.float32(2.0 ** -24 * (1 + 2.0 ** -23))
+    L = np.exp(rng.uniform(0, 1, (width, n))).astype(np.float32) * np.float32(2.0 ** (k - 6))     # sums from 17 * 2^k up
+    L[7, :] = fine
+    L[7, 0] = 2.0 ** k
+    total = _sum_in_order(L[7])
+    if k > 5:
+        assert total != np.float64(2.0 ** k) + (n - 1) * np.float64(fine)                         # the order matters
+    for at, value in ((20, total), (33, np.nextafter(total, np.inf))):
+        L[at, :] = 0
+        L[at, [3, 500, 1099]] = _in_three(value)
+    L[11, :] = np.float32(1e-42)
+    L[30, 900] = np.inf
+    W = np.ascontiguousarray(L if axis == "rows" else L.T)
+    M, N = W.shape
+    mask = np.ones((M, N), np.uint8)
+    pr, pc = {"rows": (2 / M, 0.0), "cols": (0.0, 2 / N), "both": (0.01, 2 / N)}[axis]
+    dW, dm = _dev(W), _dev(mask)
+    B.lstm_prune_rows_cols(dW.data_ptr(), dm.data_ptr(), M, N, pr, pc)
+    Wr, mr = oprune.prune_rows_cols(W, mask, pr, pc)
+    gm = dm.cpu().numpy()
+    np.testing.assert_array_equal(gm, mr)
+    np.testing.assert_array_equal(dW.cpu().numpy().view(np.uint32), Wr.view(np.uint32))
+    if axis != "both":
+        assert list(np.flatnonzero(~gm.any(axis=1 if axis == "rows" else 0))) == [7, 11, 20]
