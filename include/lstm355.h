@@ -203,8 +203,9 @@ int lstm_set_plan(lstm_t* m, int plan, int waves_per_group);
  * switched off; results are bit-identical, only slower; for A/B checks).
  * LSTM355_SPARSE_PROJ_MAX_DENSITY=<fraction>: the input projection W_x . x_t + b of an fp32 model with row-compressed
  * W_x and at least 64 input rows (T * B) runs over the kept entries only when at most this fraction of W_x is kept
- * (default 0.18; 0 sends every such product to the dense matrix-core kernel; for A/B checks -- both compute the sum
- * of the paper's Section 4 over the mask-selected weights, in different summation orders).
+ * (default 0.18, and there the dense product runs all the same in front of a dense recurrence where it is modelled faster;
+ * a fraction that is given holds as it stands; 0 sends every such product to the dense matrix-core kernel; for A/B checks
+ * -- both compute the sum of the paper's Section 4 over the mask-selected weights, in different summation orders).
  */
 int lstm_set_launch_mode(lstm_t* m, int cooperative);
 /* Process-wide default that lstm_create gives to new handles (including those lstm_latency_sweep creates). */
@@ -225,7 +226,8 @@ int lstm_get_profile(lstm_t* m, double* proj_us, int* proj_launches, double* rec
  * direction) into buf.  In a recurrence entry "(s, u, b)" are the kernel's slot count, units per wave and batch columns
  * per workgroup, and "batch/N" says that the layer's batch columns were run as N launches over runs of columns (a layer
  * whose time-loop kernel would need more workgroups than the device has compute units is cut that way, and/or into one
- * launch per direction, before the library falls back to one launch per timestep). */
+ * launch per direction, before the library falls back to one launch per timestep).  "split" marks the fp32 kernels that
+ * multiply two fp16 planes of each operand (proj=dense-split; rec=persist-dense-f32(...,split)). */
 int lstm_describe_plan(const lstm_t* m, char* buf, size_t buf_bytes);
 
 /*
@@ -368,7 +370,8 @@ int lstm_bench_copy(void* dst, const void* src, size_t bytes, int iters, double*
 /*
  * Stand-alone product Y[batch, n] = X[batch, n] . (W (x) Msk)[n, n]^T with a dense input batch and a square weight
  * matrix (paper Section 3, the two matrix-multiplication latency figures: latency against the dimension for dense and
- * sparse operands).  format LSTM_FMT_DENSE_MASKED runs the library's dense projection (+0 stored where Msk = 0),
+ * sparse operands).  format LSTM_FMT_DENSE_MASKED runs the library's dense projection (+0 stored where Msk = 0; for batch > 64
+ * on the 16-bit matrix instruction with both operands as two fp16 planes, where that is modelled faster),
  * LSTM_FMT_ROW_COMPRESSED its row-compressed one (for batch <= 64 and n <= 5120 the kernel that splits a row's kept
  * entries over the lanes; otherwise the transpose of X plus the kernel that puts the input rows on the lanes).
  * Operands, all HOST, row-major:

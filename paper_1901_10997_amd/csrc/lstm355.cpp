@@ -1259,8 +1259,9 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
 // Does the dense fp32 recurrence with the time loop on the device take layer l?  It multiplies the zeros of a mask too, but a
 // step of a narrow layer is the exchange's latency and not the products, its own is the shortest (one wait per step, both
 // directions in one launch), and it holds rows of any length: 64 to 256 units at 5 to 24 % kept 1.15 to 2 times faster than the
-// row-compressed kernels, from about 450 slower (H-LSTM 1.1 to 1.6 times up to 256), and 2 to 6 times where rows are too long
-// for those and each step would be a launch.  Only where LSTM_FMT_AUTO left the choice open (the copy exists) and by 5 % of the
+// row-compressed kernels (H-LSTM 1.1 to 1.6 times up to 256), and 2 to 6 times where rows are too long for those and each step
+// would be a launch.  With the product on fp16 planes LSTM layers of 450 and more units follow at small batches (5 bidirectional
+// layers of 800, 15 % kept, batch 16: 4219 us over the kept entries, 4019 dense); with the fp32 instruction they were slower.  Only where LSTM_FMT_AUTO left the choice open (the copy exists) and by 5 % of the
 // modelled time, as neither model is better than that.
 static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
 {

@@ -34,8 +34,9 @@
 //
 // Bound: the matrix instruction (8.8 clocks with two waves per SIMD issuing) plus one exchange per product plus the
 // reduction and the gates.  Microseconds per step of the recurrence, both directions, batch 16: 256 units 1.89 -> 0.85,
-// 800 units 4.8 -> 2.8 (against 16-column tiles of the 16x16x4 instruction across the device); H-LSTM 640/640 91 -> 4.4
-// (against a launch per product).
+// 800 units 4.8 -> 2.9 (against 16-column tiles of the 16x16x4 instruction across the device); H-LSTM 640/640 91 -> 4.4
+// (against a launch per product).  LSTM layers of more than 256 units whose weights fit two fp16 planes run in
+// persist_split.hip (800 units 2.90 -> 2.14); narrower ones are faster here (200 units 0.94 against 1.08).
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"

@@ -8,7 +8,8 @@
 // its 16 lanes, and lane 16q + 4u + b writes P[m0 + b, 4 (u0 + u) + q].  The next tile's rows are requested from
 // memory before the current tile's products and parked in the other half of the LDS buffer after them.
 // Bound: LDS gather bandwidth (16 bytes per lane and four multiply-adds); at 10-15 % kept weights that is faster
-// than the dense product on the matrix cores, which multiplies the zeros as well.
+// than the dense product on the fp32 matrix instruction, which multiplies the zeros as well (4800 x 3200 x 1600, two
+// directions: 449 / 582 / 840 us at 10 / 15 / 20 % kept against 901; the product on fp16 planes takes 311 at any density).
 #include <type_traits>
 #include "common.h"
 #include "device_math.h"
