@@ -214,7 +214,7 @@ struct LineThreshold {
 // infinities and NaN, the wave sums the row again as the chain.  Weights left by magnitude pruning stop at its threshold and
 // pass (6000 of them from a twentieth to four standard deviations: 43 bits); of rows of 1500 normal deviates one in 300
 // fails.
-// 6000 x 1500 (45 MB), four waves per workgroup: 25.0 -> 8.5..9.5 us against the chain for every row, normal deviates 18, 46
+// 6000 x 1500 (45 MB), four waves per workgroup: 25.0 -> 8.5 to 11 us against the chain for every row, normal deviates 18, 46
 // where every row fails (magnitudes over 15 e-folds); 16384 x 500 22.1 -> 9.9, 3000 x 3000 21.8 -> 8.5 (normal 25.6).
 constexpr int kRowWaves = 4;       // waves (rows) per workgroup
 constexpr int kChainTile = 384;    // positions of a row in LDS at a time
