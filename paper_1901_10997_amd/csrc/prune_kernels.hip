@@ -457,10 +457,16 @@ __global__ __launch_bounds__(kSumThreads) void col_abs_sum_kernel(const float* _
 // lines that go with it: those whose value in `judged` is at or below it.  One workgroup: radix select by 11-bit digits
 // (LDS histogram, the digit found by a workgroup scan), ended as soon as one sum is left, which with sums of thousands
 // of terms is after two or three digits.  out: the threshold; list (may be nullptr): the removed lines in no particular
-// order; removed: how many.  (6000 sums: 26 -> 10 us against byte-wide digits walked by one thread.)
+// order; removed: how many; none (may be nullptr): set to zero, the count of an axis nothing is asked of.
+// Bound: latency, of memory and of the barriers.  A thread holds its first kSelKeep sums in registers, requested at once;
+// only what is beyond 8192 lines is read again for each digit.  (6000 sums: 26 -> 14.8 us against byte-wide digits walked by
+// one thread, 13.1 with the sums held; 256 sums 4.9 -> 5.6; the pruning step of a 6000 x 1500 matrix, where the sums come
+// from another XCD's stores, 250 -> 244 with the two launches that set the other axis' count saved.  Adding a wave's equal
+// first digits as one: 13.3, nothing in the step.)
+constexpr int kSelKeep = 8;
 __global__ __launch_bounds__(1024) void select_lines_kernel(const double* __restrict__ sums, int n, unsigned k,
                                                             const double* __restrict__ judged, LineThreshold* __restrict__ out,
-                                                            int* __restrict__ list, int* __restrict__ removed)
+                                                            int* __restrict__ list, int* __restrict__ removed, int* __restrict__ none)
 {
     __shared__ unsigned hist[2048];
     __shared__ unsigned wtot[16];
@@ -470,16 +476,27 @@ __global__ __launch_bounds__(1024) void select_lines_kernel(const double* __rest
     unsigned long long prefix = 0ull;
     unsigned kk = k;
     if (tid == 0) nlist = 0;
+    unsigned long long held[kSelKeep];
+#pragma unroll
+    for (int u = 0; u < kSelKeep; ++u) {
+        const int i = tid + 1024 * u;
+        held[u] = (unsigned long long)__double_as_longlong(sums[i < n ? i : 0]);
+    }
+    auto each_key = [&](auto f) {
+#pragma unroll
+        for (int u = 0; u < kSelKeep; ++u)
+            if (tid + 1024 * u < n) f(held[u]);
+        for (int i = tid + 1024 * kSelKeep; i < n; i += 1024) f((unsigned long long)__double_as_longlong(sums[i]));
+    };
     // digits of bits 63..53, 52..42, 41..31, 30..20, 19..9, 8..0
     for (int top = 64; top > 0 && k > 0;) {
         const int shift = top >= 11 ? top - 11 : 0;
         hist[tid] = 0;
         hist[tid + 1024] = 0;
         __syncthreads();
-        for (int i = tid; i < n; i += 1024) {
-            const unsigned long long key = (unsigned long long)__double_as_longlong(sums[i]);
+        each_key([&](unsigned long long key) {
             if (top == 64 || (key >> top) == (prefix >> top)) atomicAdd(&hist[(unsigned)(key >> shift) & ((1u << (top - shift)) - 1u)], 1u);
-        }
+        });
         __syncthreads();
         // the bin that holds rank kk: inclusive scan over pairs of bins
         const unsigned a = hist[2 * tid], b = hist[2 * tid + 1];
@@ -498,10 +515,9 @@ __global__ __launch_bounds__(1024) void select_lines_kernel(const double* __rest
         prefix |= (unsigned long long)found_digit << shift;
         kk -= found_below;
         if (found_in == 1 && shift > 0) {   // one candidate left: it is the answer
-            for (int i = tid; i < n; i += 1024) {
-                const unsigned long long key = (unsigned long long)__double_as_longlong(sums[i]);
+            each_key([&](unsigned long long key) {
                 if ((key >> shift) == (prefix >> shift)) found_key = key;
-            }
+            });
             __syncthreads();
             prefix = found_key;
             break;
@@ -512,11 +528,25 @@ __global__ __launch_bounds__(1024) void select_lines_kernel(const double* __rest
     __syncthreads();
     const double value = __longlong_as_double((long long)prefix);
     if (k > 0) {
-        for (int i = tid; i < n; i += 1024)
-            if (judged[i] <= value) {
+        auto judge = [&](int i, double sum) {
+            if (sum <= value) {
                 const unsigned at = atomicAdd(&nlist, 1u);
                 if (list) list[at] = i;
             }
+        };
+        const bool same = judged == sums;
+        double other[kSelKeep];
+        if (!same) {
+#pragma unroll
+            for (int u = 0; u < kSelKeep; ++u) {
+                const int i = tid + 1024 * u;
+                other[u] = judged[i < n ? i : 0];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kSelKeep; ++u)
+            if (tid + 1024 * u < n) judge(tid + 1024 * u, same ? __longlong_as_double((long long)held[u]) : other[u]);
+        for (int i = tid + 1024 * kSelKeep; i < n; i += 1024) judge(i, judged[i]);
     }
     __syncthreads();
     if (tid == 0) {
@@ -524,6 +554,7 @@ __global__ __launch_bounds__(1024) void select_lines_kernel(const double* __rest
         out->any = k > 0 ? 1u : 0u;
         out->count = nlist;
         *removed = (int)nlist;
+        if (none) *none = 0;
     }
 }
 
@@ -590,16 +621,17 @@ hipError_t launch_prune_rows_cols(float* W, uint8_t* mask, int M, int N, unsigne
     double* csums_after = csums + N;
     LineThreshold* th = (LineThreshold*)(csums_after + N);
     int* const list = (int*)csums;
-    if (k_rows == 0 || k_cols == 0) {
+    if (k_rows == 0 && k_cols == 0) {
         hipLaunchKernelGGL(clear_removed_kernel, dim3(1), dim3(64), 0, s, removed);
-        if (k_rows == 0 && k_cols == 0) return hipGetLastError();
+        return hipGetLastError();
     }
     hipError_t e = hipSuccess;
     // Both thresholds come from the matrix as it came in; rows are removed first and columns judged on what that leaves.
     if (k_rows > 0) {
         e = launch_row_sums(W, mask, M, N, rsums, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, rsums, M, k_rows, rsums, th, (int*)nullptr, removed);
+        hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, rsums, M, k_rows, rsums, th, (int*)nullptr, removed,
+                           k_cols > 0 ? (int*)nullptr : removed + 1);
     }
     if (k_cols > 0) {
         // without removed rows the sums as passed in are also the ones to judge, and one pass reads both
@@ -608,7 +640,7 @@ hipError_t launch_prune_rows_cols(float* W, uint8_t* mask, int M, int N, unsigne
                        : launch_col_sums<false>(W, mask, M, N, csums, nullptr, nullptr, nullptr, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(select_lines_kernel, dim3(1), dim3(1024), 0, s, csums, N, k_cols, judged, th + 1,
-                           k_rows > 0 ? list : (int*)csums_after, removed + 1);
+                           k_rows > 0 ? list : (int*)csums_after, removed + 1, k_rows > 0 ? (int*)nullptr : removed);
     }
     hipLaunchKernelGGL(clear_lines_kernel, dim3((M + 3) / 4), dim3(256), 0, s, W, mask, M, N, rsums, th,
                        k_rows > 0 ? list : (int*)csums_after, k_rows > 0 ? 1 : 0, k_cols > 0 ? 1 : 0);
