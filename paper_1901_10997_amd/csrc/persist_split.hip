@@ -20,7 +20,7 @@
 // Exchange: 8-byte words of four units of a column and plane.  |h| <= 1 leaves bit 14 of a half free: that of the first carries
 // the stamp (as in persist_quad.hip: two buffers, step tag g in buffer g & 1 with stamp (g >> 1) & 1), that of the second says
 // that a NaN is among the four.  hx: [quad][buffer][block of 32 k][k / 8 % 4][plane][column][k / 4 % 2], the lanes' order.
-// h0 may have any value: where it is not within 1 the readers sum the first step from the fp32 weights.
+// h0 may have any value: where it is not within 1 the first step is summed from the fp32 weights.
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"
@@ -69,7 +69,8 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     constexpr int kPart = kSW * kItems * 64, kAhead = 4;
     static_assert(KR >= 1 && KB >= 2, "layers of more than 256 units");
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    float* const part = lds;                                             // [2][8][NT][QP * 64]
+    int* const odd_of = reinterpret_cast<int*>(lds);                     // [8]
+    float* const part = lds + kSW;                                       // [2][8][NT][QP * 64]
     float* const cell = part + 2 * kPart;                                // [passes][QP][NT][64]
     const int H = a.H, gn = a.gn;
     int dir, grp, wg;
@@ -247,6 +248,13 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                 if ((spins & 63u) == 0 && __hip_atomic_load(a.timeout_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
             }
             const bool odd = __builtin_amdgcn_ballot_w64((differ & kOddMark) != 0u) != 0ull;
+            // the first step's sums are all of one kind: where any wave has met an h0 beyond 1 every wave sums unscaled
+            bool first_f32 = false;
+            if (s == 0) {
+                if (lane == 0) odd_of[wave] = odd;
+                __syncthreads();
+                first_f32 = __builtin_amdgcn_ballot_w64(odd_of[lane & 7] != 0) != 0ull;
+            }
             // this step's elements of P were requested a pass ahead; behind the words just waited for they have arrived too
             // (taken over here by hand: at the top of the loop the wait for them would include the stores just issued)
             float p_cur[kMine];
@@ -259,7 +267,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                 load_p(0);
             }
             float* const mine = part_b + wave * kItems * 64 + lane;
-            if (!(odd && s == 0)) {
+            if (!first_f32) {
 #pragma unroll
                 for (int q = 0; q < KB; ++q) {
                     fr[q].x &= ~(unsigned long long)kStamp;
@@ -309,18 +317,17 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                 }
             } else {
                 // an h0 beyond 1: from the fp32 weights (launch_to_frag16: tile, block of 16 k, lane 16 (k / 4 % 4) + row, k % 4),
-                // in the scale of the planes' sums
+                // without the rows' scales: h0 may be of any size, and a scaled sum of one of 1e34 is beyond fp32
                 const int KB16 = (H + 15) >> 4;
                 const int k_lo = 32 * kb0, k_hi = min(32 * (kb0 + (all_kb ? KB : KB - 1)), H);
 #pragma unroll 1
                 for (int i = 0; i < kItems; ++i) {
-                    const int c = i / NT, n = i - c * NT, nb = wg * NT + n, bc = 4 * (q_lo + quad_of(pass, c)) + lg, r = 16 * nb + lr;
+                    const int c = i / NT, n = i - c * NT, nb = wg * NT + n, bc = 4 * (q_lo + quad_of(pass, c)) + lg;
                     float sum = 0.f;
                     if (nb < NBt && bc < a.B)
 #pragma unroll 1
                         for (int k = k_lo; k < k_hi; ++k)
                             sum = fmaf(D.Wf[(((size_t)nb * KB16 + (k >> 4)) * 64 + 16 * ((k >> 2) & 3) + lr) * 4 + (k & 3)], h0[(size_t)bc * H + k], sum);
-                    sum /= r < 4 * H ? D.w_unscale[r] : 1.f;
                     part_b[wave * kItems * 64 + n * QP * 64 + slot + 4 * c] = sum;
                 }
             }
@@ -338,7 +345,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                     const float c_prev = *cp;
                     __builtin_amdgcn_sched_barrier(0);                   // all on their way before the first is waited for
                     const float sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-                    const float pre = fmaf(sum, us[j], p_cur[j]);
+                    const float pre = fmaf(sum, first_f32 ? 1.f : us[j], p_cur[j]);
                     const bool cand = gate == 3;
                     const float rr = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f((cand ? 2.8853900817779268f : -1.4426950408889634f) * pre));
                     float gv = cand ? fmaf(-2.0f, rr, 1.0f) : rr;
@@ -411,7 +418,7 @@ PersistQuadPlan persist_split_plan(int B, int H, int ndir)
             if ((quads + mq - 1) / mq != groups) continue;   // a group would be left without a quad
             const int passes = (mq + sh.qp - 1) / sh.qp;
             if (sh.qp > 1 && 2 * mq <= sh.qp) continue;      // half of every pass would be empty
-            const size_t lds = (((size_t)(2 * kSW + passes) * sh.qp * sh.nt) * 64 + (sh.xl ? (size_t)(blocks - kSW * (sh.kb - 1)) * sh.nt * 512 : 0)) * sizeof(float);
+            const size_t lds = (kSW + ((size_t)(2 * kSW + passes) * sh.qp * sh.nt) * 64 + (sh.xl ? (size_t)(blocks - kSW * (sh.kb - 1)) * sh.nt * 512 : 0)) * sizeof(float);
             if (lds > 160 * 1024) continue;
             const int per_xcd = (ndir * groups + 7) / 8;
             const int local = gn <= 64 && per_xcd * gn <= cus / 8;

@@ -70,6 +70,24 @@ def test_initial_state_of_any_size(scale):
         assert (d > min(bound, 1e-5 if scale <= 10 else 1e-3)).mean() <= (0 if scale <= 10 else 1e-3), (scale, d.max())
 
 
+@pytest.mark.parametrize("scale,a", [(1e34, 0.05), (1e37, 0.05), (1e34, 1e-6)])
+def test_initial_state_near_the_end_of_the_fp32_range(scale, a):
+    """No sum of 800 terms of a * 0.5 * scale at most leaves the fp32 range, so every gate is finite: saturated on the side of
+    its sum's sign.  A sum of 800 rounded terms is off by 2^-24 sqrt(800) = 2e-6 of its standard deviation, which turns the
+    sign of as many of the sums (four to an element)."""
+    for L, bidir, H, Bn in ((1, True, 800, 16), (1, False, 1500, 20)):
+        for T in (1, 3):
+            case = _case(L, bidir, 40, H, T, Bn, k=7, a=a)
+            case.h0 = (case.h0 * np.float32(scale)).astype(np.float32)
+            case.h0[0, 3] = 0.25
+            gpu, desc = run_gpu(case, DENSE, AUTO)
+            assert desc.count(",split)") == desc.count("rec=") > 0, desc
+            assert all(np.isfinite(g).all() for g in gpu)
+            if T == 1:   # (a gate on the other side changes its whole column from the next step on)
+                for g, r in zip(gpu, orc.forward_case(case)):
+                    assert (np.abs(g.astype(np.float64) - r) > 1e-5).mean() <= 1e-4
+
+
 def test_nan_in_the_state_reaches_every_unit_of_its_column_only():
     case = _case(1, True, 40, 800, 4, 16, k=6)
     clean = run_gpu(case, DENSE, AUTO)[0]
