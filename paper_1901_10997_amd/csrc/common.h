@@ -356,11 +356,12 @@ hipError_t launch_pad_rows(const void* src, bool bf16, int src_ld, int rows, int
                            hipStream_t s);
 // fp32 dense recurrence, LSTM and H-LSTM cells, batch columns four at a time (all directions of a layer per launch)
 struct PersistQuadDir {
-    const float* P;            // [T*Bld][4H] (H-LSTM: [4G]): input projection incl. bias
+    float* P;                  // [T*Bld][4H] (H-LSTM: [4G]): input projection incl. bias (persist_split.hip adds to its first step)
     const float* Wf;           // W_h / W1h in fragment order (launch_to_frag16)
     const float* W2f;          // H-LSTM: W2 in fragment order by gate
     const uint16_t* Ws;        // persist_split.hip: W_h as two fp16 planes (launch_to_frag_split) and its rows' scales
     const float* w_unscale;
+    const unsigned* beyond;    // ... and, with h0: [B], not zero where a column of it is not within 1 (launch_fill_and_check)
     const float* bias2;        // H-LSTM: [4H] packed
     const float* h0;           // [B][H] or nullptr
     const float* c0;
@@ -616,6 +617,15 @@ size_t compact_scratch_bytes(int gates, int R, int N);
 hipError_t launch_compact_rows_cols(const float* W, const uint8_t* mask, int gates, int R, int N, int* row_index,
                                     int* col_index, float* Wc, uint8_t* mask_c, void* scratch, int* counts_out, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
+// n words of zeros at p, and in the same launch beyond[i * B + b]: does row b of block i (B rows of len[i] values, from h0 + off[i]
+// on) hold a value that is not within 1 (a NaN is not)
+constexpr int kStateBlocks = 64;
+struct StateRows {
+    int blocks = 0, B = 0;
+    size_t off[kStateBlocks];
+    int len[kStateBlocks];
+};
+hipError_t launch_fill_and_check(unsigned long long* p, size_t n, const float* h0, const StateRows& rows, unsigned* beyond, hipStream_t s);
 // yardsticks
 hipError_t launch_copy_stream(void* dst, const void* src, size_t bytes, hipStream_t s);
 int mfma_issue_blocks();

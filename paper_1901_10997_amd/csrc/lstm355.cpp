@@ -928,7 +928,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, hb_off, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, total;
 };
 // Plans of layer l at batch B.  They follow from the shape alone, but a search over the kernels' shape tables takes
 // microseconds and a forward needs each several times, so the handle keeps the last batch size's.
@@ -1099,6 +1099,9 @@ static Workspace carve(const lstm_t* m, int T, int B)
         w.qx_words += words;
     }
     off += align256(w.qx_words * sizeof(unsigned));
+    // ... and which columns of the initial state they take another way (PersistQuadDir::beyond)
+    w.hb_off = off;
+    if (m->dtype == LSTM_F32 && m->G == 0) off += align256((size_t)m->L * m->Dn * B * sizeof(unsigned));
     // ... and of the bf16 one
     w.rx_off = off;
     if (m->dtype == LSTM_BF16)
@@ -1430,7 +1433,21 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
     const DensePlans p = dense_plans(m, l, B);
     if (!reg.next) {
         reg.next = (unsigned*)(base + ws.qx_off);
-        HIP_TRY(m, launch_fill_u64((unsigned long long*)reg.next, align256(ws.qx_words * 4) / 8, 0ull, s));
+        size_t words = align256(ws.qx_words * 4) / 8;
+        bool planes = false;
+        for (int k = 0; k < m->L && G == 0 && h0; ++k) planes = planes || quads_run_split(m, k, dense_plans(m, k, B));
+        if (planes)
+            for (int n = 0; n < m->L * Dn; n += kStateBlocks, words = 0) {
+                StateRows rows;
+                rows.B = B;
+                for (; rows.blocks < kStateBlocks && n + rows.blocks < m->L * Dn; ++rows.blocks) {
+                    rows.off[rows.blocks] = m->soff((size_t)(n + rows.blocks)) * B;
+                    rows.len[rows.blocks] = m->hid((n + rows.blocks) / Dn);
+                }
+                HIP_TRY(m, launch_fill_and_check((unsigned long long*)reg.next, words, h0, rows, (unsigned*)(base + ws.hb_off) + (size_t)n * B, s));
+            }
+        else
+            HIP_TRY(m, launch_fill_u64((unsigned long long*)reg.next, words, 0ull, s));
     }
     bool dense = true;
     for (int d = 0; d < Dn; ++d) dense = dense && m->ld[(size_t)l * Dn + d].wh.dense;
@@ -1453,6 +1470,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
             q.W2f = w.w2.dense_frag16;
             q.Ws = w.wh.rec_split;
             q.w_unscale = w.wh.rec_unscale;
+            q.beyond = (const unsigned*)(base + ws.hb_off) + ((size_t)l * Dn + d) * B + b_lo;
             q.bias2 = w.bias2;
             q.h0 = h0 ? h0 + so : nullptr;
             q.c0 = c0 ? c0 + so : nullptr;

@@ -20,7 +20,8 @@
 // Exchange: 8-byte words of four units of a column and plane.  |h| <= 1 leaves bit 14 of a half free: that of the first carries
 // the stamp (as in persist_quad.hip: two buffers, step tag g in buffer g & 1 with stamp (g >> 1) & 1), that of the second says
 // that a NaN is among the four.  hx: [quad][buffer][block of 32 k][k / 8 % 4][plane][column][k / 4 % 2], the lanes' order.
-// h0 may have any value: where it is not within 1 the first step is summed from the fp32 weights.
+// h0 may have any value: a column of it that is not within 1 is multiplied by the fp32 instruction before the first step, into its
+// P, and travels as zeros.
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"
@@ -69,8 +70,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     constexpr int kPart = kSW * kItems * 64, kAhead = 4;
     static_assert(KR >= 1 && KB >= 2, "layers of more than 256 units");
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    int* const odd_of = reinterpret_cast<int*>(lds);                     // [8]
-    float* const part = lds + kSW;                                       // [2][8][NT][QP * 64]
+    float* const part = lds;                                             // [2][8][NT][QP * 64]
     float* const cell = part + 2 * kPart;                                // [passes][QP][NT][64]
     const int H = a.H, gn = a.gn;
     int dir, grp, wg;
@@ -92,7 +92,6 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     const int passes = (nq + QP - 1) / QP;
 
     const PersistQuadDir& D = a.d[dir];
-    const float* const Pd = D.P;
     const float* const h0 = D.h0;
     float* const y = D.y;
     const size_t y_ld = (size_t)D.y_ld;
@@ -169,6 +168,70 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
         same_xcd = group_shares_xcd(a.xcc_ids + (size_t)(dir * a.groups + grp) * 64, gn, wg, 1u, part, tid, kSTH,
                                     a.timeout_flag, a.spin_limit) && !a.device_scope_only;
 
+    // columns of h0 that are not within 1 (launch_fill_and_check): any in this group?
+    bool beyond = false;
+    if (h0)
+        for (int c = lane; c < 4 * nq; c += 64) beyond |= 4 * q_lo + c < a.B && D.beyond[4 * q_lo + c] != 0u;
+    beyond = __builtin_amdgcn_ballot_w64(beyond) != 0ull;
+    auto col_beyond = [&](int pass, int j) { return beyond && D.beyond[col[j] + 4 * QP * pass] != 0u; };
+    const ptrdiff_t p_step = (ptrdiff_t)a.Bld * 4 * H * (reverse ? -1 : 1), y_step = (ptrdiff_t)a.Bld * (ptrdiff_t)y_ld * (reverse ? -1 : 1);
+    // the timesteps of P and y in the order of the steps
+    float* p_t = D.P + (reverse ? (size_t)(a.T - 1) * a.Bld * 4 * H : 0);
+    float* y_t = y + (reverse ? (size_t)(a.T - 1) * a.Bld * y_ld : 0);
+    // where the sum of this thread's item and row lies in a partial tile (see below)
+    const int slot = QP == 1 ? 16 * (lr >> 2) + 4 * gate + lg : 64 * (gate >> 1) + 16 * (lr >> 2) + 8 * (gate & 1) + lg;
+    // These columns' product for the first step, by the fp32 instruction over the fp32 weights (launch_to_frag16: tile, block of
+    // 16 k, lane 16 (k / 4 % 4) + row, k % 4); operand column c < 4 QP is column c % 4 of quad c / 4.  Added to P by the thread that
+    // reads that element below.  No row has a scale here: h0 may be of any size.  Once per layer, microseconds of a one-step recurrence
+    // without / with such columns: 800 units 24 / 53, 1500 22 / 59, 2000 19 / 61 (a column of multiply-adds per lane: 226, 588, 503).
+    for (int pass = 0; beyond && pass < passes; ++pass) {
+        constexpr int kDeep = 4;
+        const int KB16 = (H + 15) >> 4;
+        const int b16 = 2 * kb0, e16 = min(2 * (kb0 + (all_kb ? KB : KB - 1)), KB16);
+        const int c = pass * QP * 4 + lr, b = 4 * q_lo + c;
+        const bool to_sum = lr < 4 * QP && c < 4 * nq && b < a.B && D.beyond[b] != 0u;
+        if (!__builtin_amdgcn_ballot_w64(to_sum)) continue;              // the same answer in every wave
+        const float* const hb = h0 + (size_t)(to_sum ? b : 0) * H;
+#pragma unroll 1
+        for (int n = 0; n < NT && wg * NT + n < NBt; ++n) {              // (tiles that are not there: never used)
+            const f32x4* const Wf = reinterpret_cast<const f32x4*>(D.Wf) + (size_t)(wg * NT + n) * KB16 * 64 + lane;
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int kb = b16; kb < e16; kb += kDeep) {                  // that many blocks requested together
+                f32x4 w4[kDeep];
+                float h4[kDeep][4];
+#pragma unroll
+                for (int u = 0; u < kDeep; ++u) {
+                    const int at = min(kb + u, e16 - 1);
+                    w4[u] = Wf[(size_t)at * 64];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) h4[u][i] = hb[min(16 * at + 4 * lg + i, H - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < kDeep; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        sum = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[u][i], to_sum && kb + u < e16 && 16 * (kb + u) + 4 * lg + i < H ? h4[u][i] : 0.f, sum, 0, 0, 0);
+            }
+            // rows 4 lg + i of column lr, in the order of the planes' partial tiles
+            if (lr < 4 * QP)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    part[(wave * kItems + n * QP) * 64 + 16 * lg + lr + (QP == 1 ? 4 * i : 64 * (i >> 1) + 8 * (i & 1))] = sum[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kMine; ++j)
+            if (have_col(pass, j) && unit[j] < H && col_beyond(pass, j)) {
+                const float* const from = part + tl[j] * QP * 64 + slot + 4 * qq[j];
+                float sum = 0.f;
+#pragma unroll
+                for (int i = 0; i < kSW; ++i) sum += from[i * kItems * 64];
+                p_t[(size_t)pass * (4 * QP * 4) * H + (unsigned)(col[j] * 4 * H + 4 * unit[j] + gate)] += sum;
+            }
+        __syncthreads();
+    }
+
     // h of item j as step tag `tag` of its buffers.  Lane 4 u + p of a row: unit u, plane p; the four units of a plane are gathered
     // in lane p.  Columns beyond the batch are published as well (readers wait for every word; what such a column holds is
     // never used).
@@ -188,15 +251,11 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
 #pragma unroll
         for (int j = 0; j < kMine; ++j)
             if (live[j]) {
-                const float h = h0 && have_col(pass, j) && unit[j] < H ? h0[(size_t)(col[j] + 4 * QP * pass) * H + unit[j]] : 0.f;
-                publish(fabsf(h) <= 1.f ? h : __uint_as_float(0x7fc00000u), 2u, pass, j);   // beyond 1: marked as a NaN is
+                const bool there = h0 && have_col(pass, j) && unit[j] < H && !col_beyond(pass, j);
+                publish(there ? h0[(size_t)(col[j] + 4 * QP * pass) * H + unit[j]] : 0.f, 2u, pass, j);
             }
 
     float p_next[kMine];
-    // the timesteps of P and y in the order of the steps
-    const ptrdiff_t p_step = (ptrdiff_t)a.Bld * 4 * H * (reverse ? -1 : 1), y_step = (ptrdiff_t)a.Bld * (ptrdiff_t)y_ld * (reverse ? -1 : 1);
-    const float* p_t = Pd + (reverse ? (size_t)(a.T - 1) * a.Bld * 4 * H : 0);
-    float* y_t = y + (reverse ? (size_t)(a.T - 1) * a.Bld * y_ld : 0);
     auto load_p = [&](int pass) {
         const float* const Pt = p_t + (size_t)pass * (4 * QP * 4) * H;
 #pragma unroll
@@ -208,8 +267,6 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     const float near = gate == 3 ? kTanhNear : -1.f;                     // the candidate's tanh
     float lo_scale;                                                      // in a register: the sum of the planes is one instruction
     asm volatile("v_mov_b32 %0, 0x39800000" : "=v"(lo_scale));           // 2^-12
-    // where the sum of this thread's item and row lies in a partial tile (see below)
-    const int slot = QP == 1 ? 16 * (lr >> 2) + 4 * gate + lg : 64 * (gate >> 1) + 16 * (lr >> 2) + 8 * (gate & 1) + lg;
 
     for (int s = 0; s < a.T; ++s) {
         const bool last = s == a.T - 1;
@@ -248,13 +305,6 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                 if ((spins & 63u) == 0 && __hip_atomic_load(a.timeout_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
             }
             const bool odd = __builtin_amdgcn_ballot_w64((differ & kOddMark) != 0u) != 0ull;
-            // the first step's sums are all of one kind: where any wave has met an h0 beyond 1 every wave sums unscaled
-            bool first_f32 = false;
-            if (s == 0) {
-                if (lane == 0) odd_of[wave] = odd;
-                __syncthreads();
-                first_f32 = __builtin_amdgcn_ballot_w64(odd_of[lane & 7] != 0) != 0ull;
-            }
             // this step's elements of P were requested a pass ahead; behind the words just waited for they have arrived too
             // (taken over here by hand: at the top of the loop the wait for them would include the stores just issued)
             float p_cur[kMine];
@@ -267,68 +317,51 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                 load_p(0);
             }
             float* const mine = part_b + wave * kItems * 64 + lane;
-            if (!first_f32) {
 #pragma unroll
-                for (int q = 0; q < KB; ++q) {
-                    fr[q].x &= ~(unsigned long long)kStamp;
-                    fr[q].y &= ~(unsigned long long)kStamp;
+            for (int q = 0; q < KB; ++q) {
+                fr[q].x &= ~(unsigned long long)kStamp;
+                fr[q].y &= ~(unsigned long long)kStamp;
+            }
+            if (odd) {
+#pragma unroll
+                for (int q = 0; q < KB; ++q) { fr[q].x = with_nans(fr[q].x); fr[q].y = with_nans(fr[q].y); }
+            }
+            f32x4 acc[NT];
+#pragma unroll
+            for (int q = 0; q < KR; ++q)
+                if (q < KB - 1 || all_kb) {
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+#pragma unroll
+                        for (int n = 0; n < NT; ++n)
+                            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[n][q][p], __builtin_bit_cast(f16x8, fr[q]),
+                                                                            q + p == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : acc[n], 0, 0, 0);
                 }
-                if (odd) {
+            if (XL && all_kb) {
+                f16x8 x[kAhead];                                     // that many reads ahead of the product
 #pragma unroll
-                    for (int q = 0; q < KB; ++q) { fr[q].x = with_nans(fr[q].x); fr[q].y = with_nans(fr[q].y); }
-                }
-                f32x4 acc[NT];
+                for (int i = 0; i < kAhead; ++i) x[i] = wl[i * 64];
 #pragma unroll
-                for (int q = 0; q < KR; ++q)
-                    if (q < KB - 1 || all_kb) {
-#pragma unroll
-                        for (int p = 0; p < 2; ++p)
-#pragma unroll
-                            for (int n = 0; n < NT; ++n)
-                                acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[n][q][p], __builtin_bit_cast(f16x8, fr[q]),
-                                                                                q + p == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : acc[n], 0, 0, 0);
-                    }
-                if (XL && all_kb) {
-                    f16x8 x[kAhead];                                     // that many reads ahead of the product
-#pragma unroll
-                    for (int i = 0; i < kAhead; ++i) x[i] = wl[i * 64];
-#pragma unroll
-                    for (int i = 0; i < 2 * NT; ++i) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        acc[i >> 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[i % kAhead], __builtin_bit_cast(f16x8, fr[KB - 1]), acc[i >> 1], 0, 0, 0);
-                        if (i + kAhead < 2 * NT) x[i % kAhead] = wl[(i + kAhead) * 64];
-                    }
+                for (int i = 0; i < 2 * NT; ++i) {
                     __builtin_amdgcn_sched_barrier(0);
+                    acc[i >> 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[i % kAhead], __builtin_bit_cast(f16x8, fr[KB - 1]), acc[i >> 1], 0, 0, 0);
+                    if (i + kAhead < 2 * NT) x[i % kAhead] = wl[(i + kAhead) * 64];
                 }
-                // Accumulator register i of lane 16 g + c: row 4 g + i, column c; columns 4 quad + (column of the quad) of hi, the same of
-                // lo four (QP = 2: eight) lanes up.  After the sum of the planes, register i of the first lanes of a row moves to the lanes
-                // 4 i (QP = 2: 8 (i % 2)) up.
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // Accumulator register i of lane 16 g + c: row 4 g + i, column c; columns 4 quad + (column of the quad) of hi, the same of
+            // lo four (QP = 2: eight) lanes up.  After the sum of the planes, register i of the first lanes of a row moves to the lanes
+            // 4 i (QP = 2: 8 (i % 2)) up.
 #pragma unroll
-                for (int n = 0; n < NT; ++n) {
-                    float v[4];
+            for (int n = 0; n < NT; ++n) {
+                float v[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = fmaf(dpp_mov<QP == 1 ? 0x104 : 0x108>(acc[n][i]), lo_scale, acc[n][i]);
-                    if constexpr (QP == 1) {
-                        mine[n * 64] = dpp_bank<0x11C, 8>(dpp_bank<0x118, 4>(dpp_bank<0x114, 2>(v[0], v[1]), v[2]), v[3]);
-                    } else {
-                        mine[n * 128] = dpp_bank<0x118, 12>(v[0], v[1]);
-                        mine[n * 128 + 64] = dpp_bank<0x118, 12>(v[2], v[3]);
-                    }
-                }
-            } else {
-                // an h0 beyond 1: from the fp32 weights (launch_to_frag16: tile, block of 16 k, lane 16 (k / 4 % 4) + row, k % 4),
-                // without the rows' scales: h0 may be of any size, and a scaled sum of one of 1e34 is beyond fp32
-                const int KB16 = (H + 15) >> 4;
-                const int k_lo = 32 * kb0, k_hi = min(32 * (kb0 + (all_kb ? KB : KB - 1)), H);
-#pragma unroll 1
-                for (int i = 0; i < kItems; ++i) {
-                    const int c = i / NT, n = i - c * NT, nb = wg * NT + n, bc = 4 * (q_lo + quad_of(pass, c)) + lg;
-                    float sum = 0.f;
-                    if (nb < NBt && bc < a.B)
-#pragma unroll 1
-                        for (int k = k_lo; k < k_hi; ++k)
-                            sum = fmaf(D.Wf[(((size_t)nb * KB16 + (k >> 4)) * 64 + 16 * ((k >> 2) & 3) + lr) * 4 + (k & 3)], h0[(size_t)bc * H + k], sum);
-                    part_b[wave * kItems * 64 + n * QP * 64 + slot + 4 * c] = sum;
+                for (int i = 0; i < 4; ++i) v[i] = fmaf(dpp_mov<QP == 1 ? 0x104 : 0x108>(acc[n][i]), lo_scale, acc[n][i]);
+                if constexpr (QP == 1) {
+                    mine[n * 64] = dpp_bank<0x11C, 8>(dpp_bank<0x118, 4>(dpp_bank<0x114, 2>(v[0], v[1]), v[2]), v[3]);
+                } else {
+                    mine[n * 128] = dpp_bank<0x118, 12>(v[0], v[1]);
+                    mine[n * 128 + 64] = dpp_bank<0x118, 12>(v[2], v[3]);
                 }
             }
             // one barrier per pass: the partial tiles alternate between two buffers, and a wave that runs ahead reaches
@@ -345,7 +378,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                     const float c_prev = *cp;
                     __builtin_amdgcn_sched_barrier(0);                   // all on their way before the first is waited for
                     const float sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-                    const float pre = fmaf(sum, first_f32 ? 1.f : us[j], p_cur[j]);
+                    const float pre = fmaf(sum, us[j], p_cur[j]);
                     const bool cand = gate == 3;
                     const float rr = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f((cand ? 2.8853900817779268f : -1.4426950408889634f) * pre));
                     float gv = cand ? fmaf(-2.0f, rr, 1.0f) : rr;
@@ -418,7 +451,7 @@ PersistQuadPlan persist_split_plan(int B, int H, int ndir)
             if ((quads + mq - 1) / mq != groups) continue;   // a group would be left without a quad
             const int passes = (mq + sh.qp - 1) / sh.qp;
             if (sh.qp > 1 && 2 * mq <= sh.qp) continue;      // half of every pass would be empty
-            const size_t lds = (kSW + ((size_t)(2 * kSW + passes) * sh.qp * sh.nt) * 64 + (sh.xl ? (size_t)(blocks - kSW * (sh.kb - 1)) * sh.nt * 512 : 0)) * sizeof(float);
+            const size_t lds = (((size_t)(2 * kSW + passes) * sh.qp * sh.nt) * 64 + (sh.xl ? (size_t)(blocks - kSW * (sh.kb - 1)) * sh.nt * 512 : 0)) * sizeof(float);
             if (lds > 160 * 1024) continue;
             const int per_xcd = (ndir * groups + 7) / 8;
             const int local = gn <= 64 && per_xcd * gn <= cus / 8;

@@ -36,6 +36,36 @@ hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v
     hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n, v);
     return hipGetLastError();
 }
+
+// A wave per row behind the blocks that fill: one launch for both (the check alone 2.5 us of launch, 1 us of work).
+__global__ __launch_bounds__(256) void fill_and_check_kernel(unsigned long long* p, size_t n, unsigned fill_blocks, const float* __restrict__ h0,
+                                                             StateRows rows, unsigned* __restrict__ beyond)
+{
+    if (blockIdx.x < fill_blocks) {
+        for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)fill_blocks * 256) p[i] = 0ull;
+        return;
+    }
+    const int r = (int)(blockIdx.x - fill_blocks) * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (r >= rows.blocks * rows.B) return;
+    const int i = r / rows.B, len = rows.len[i];
+    const float* const v = h0 + rows.off[i] + (size_t)(r - i * rows.B) * len;
+    bool out = false;
+    for (int k = lane; k < len; k += 8 * 64) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = v[min(k + 64 * u, len - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) out |= !(fabsf(x[u]) <= 1.f);
+    }
+    const bool any = __ballot(out) != 0;   // (lanes past the end leave the loop a round early: false)
+    if (lane == 0) beyond[r] = any;
+}
+hipError_t launch_fill_and_check(unsigned long long* p, size_t n, const float* h0, const StateRows& rows, unsigned* beyond, hipStream_t s)
+{
+    const unsigned fill_blocks = n > 0 ? (unsigned)grid_for(n, 256) : 0u, checks = (unsigned)((rows.blocks * (size_t)rows.B + 3) / 4);
+    hipLaunchKernelGGL(fill_and_check_kernel, dim3(fill_blocks + checks), dim3(256), 0, s, p, n, fill_blocks, h0, rows, beyond);
+    return hipGetLastError();
+}
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s)
 {
     if (n == 0) return hipSuccess;

@@ -70,6 +70,29 @@ def test_initial_state_of_any_size(scale):
         assert (d > min(bound, 1e-5 if scale <= 10 else 1e-3)).mean() <= (0 if scale <= 10 else 1e-3), (scale, d.max())
 
 
+@pytest.mark.parametrize("L,bidir,D,H,T,Bn", [s for s in SHAPES if s[3] in (300, 509, 641, 797, 1024, 1197, 1501, 2048)])
+def test_initial_state_beyond_one_over_the_shapes(L, bidir, D, H, T, Bn):
+    """The first step on the fp32 instruction: one and two quads per pass, missing columns, units and blocks of k."""
+    case = _case(L, bidir, D, H, 2, Bn, k=H + Bn)
+    case.h0 = (case.h0 * np.float32(3.0)).astype(np.float32)
+    case.h0[0, Bn // 2] *= np.float32(0.1)      # a column within 1 beside the others
+    desc, _ = check_case(case, DENSE, AUTO)
+    assert desc.count(",split)") == desc.count("rec=") > 0, desc
+
+
+def test_initial_state_beyond_one_leaves_the_other_columns_as_they_were():
+    """A column's result does not depend on whether another column of h0 is within 1: the same bits."""
+    case = _case(2, True, 40, 800, 5, 33, k=11)
+    clean = run_gpu(case, DENSE, AUTO)[0]
+    case.h0[1, 17, 5] = 2.5
+    case.h0[3, 18, 9] = -1e6
+    out, desc = run_gpu(case, DENSE, AUTO)
+    assert desc.count(",split)") == desc.count("rec=") > 0, desc
+    for g, r in zip(out, clean):
+        assert np.array_equal(np.delete(g, (17, 18), 1), np.delete(r, (17, 18), 1))
+        assert not np.array_equal(g[:, 17], r[:, 17])
+
+
 @pytest.mark.parametrize("scale,a", [(1e34, 0.05), (1e37, 0.05), (1e34, 1e-6)])
 def test_initial_state_near_the_end_of_the_fp32_range(scale, a):
     """No sum of 800 terms of a * 0.5 * scale at most leaves the fp32 range, so every gate is finite: saturated on the side of
