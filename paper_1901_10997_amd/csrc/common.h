@@ -100,6 +100,12 @@ hipError_t launch_proj_mfma(const void* X, bool x_bf16, int ldx, const void* W, 
 hipError_t launch_proj_mfma_f32_pair(const float* X, int ldx, const float* W0, const float* bias0, float* P0,
                                      const float* W1, const float* bias1, float* P1, int M, int N, int K, hipStream_t s);
 // The same fp32 product on the fp16 matrix instruction, both operands as two fp16 planes (proj_split.hip).
+// Does a row of X not fit the form?  The split takes its number from `next` and leaves it in `pass`, and its complement in `found`
+// where there is such a row; the product counts `next` up.  Nothing is cleared (replays of a graph) or has to be set up: with
+// whatever the memory holds before the first call the result is right, and unless that happens to match nothing is slower.
+struct SplitMarks {
+    unsigned found, pass, next;
+};
 struct ProjSplitDir {
     const uint16_t* W;            // [N] rows of split_row_halves(K)
     const float* w_unscale;       // [N]
@@ -114,6 +120,7 @@ struct ProjSplitArgs {
     ProjSplitDir d[2];
     const uint16_t* Xs;           // [M] rows of split_row_halves(K), launch_split_rows
     const float* x_unscale;       // [M]
+    SplitMarks* marks;
     const float* X;               // the same rows as fp32
     int ldx;
     int M, N, K, ndir;
@@ -121,7 +128,7 @@ struct ProjSplitArgs {
     int gm, gn, npid;             // set by the launcher
 };
 size_t split_row_halves(int K);
-hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, hipStream_t s);
+hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, hipStream_t s);
 constexpr int kSplitMinK = 64;
 bool proj_split_supported(int M, int N, int K, int ndir, bool masked);   // and faster than the fp32 instruction
 double proj_split_us(int M, int N, int K, int ndir, bool masked);   // modelled time, with launch_split_rows

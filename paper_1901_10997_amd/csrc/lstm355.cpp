@@ -431,7 +431,7 @@ static int add_split(lstm_t* m, PackedMat& p)
     std::vector<float> unscale((size_t)p.rows);
     HIP_TRY(m, hipMalloc((void**)&p.split, (size_t)p.rows * split_row_halves(p.pad_ld) * sizeof(uint16_t)));
     HIP_TRY(m, hipMalloc((void**)&p.split_unscale, unscale.size() * sizeof(float)));
-    HIP_TRY(m, launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr));
+    HIP_TRY(m, launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr, nullptr));
     HIP_TRY(m, hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost));
     drop_unfit(unscale, p.split, p.split_unscale);
     return LSTM_OK;
@@ -928,7 +928,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, hb_off, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, hb_off, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, sm_off, total;
 };
 // Plans of layer l at batch B.  They follow from the shape alone, but a search over the kernels' shape tables takes
 // microseconds and a forward needs each several times, so the handle keeps the last batch size's.
@@ -1049,6 +1049,8 @@ static Workspace carve(const lstm_t* m, int T, int B)
     }
     w.su_off = off;
     if (m->dtype == LSTM_F32) off += align256(M * sizeof(float));
+    w.sm_off = off;
+    if (m->dtype == LSTM_F32) off += align256(sizeof(SplitMarks));
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
@@ -1368,13 +1370,14 @@ static int run_split_proj(lstm_t* m, const LayerDir* const* w, float* const* P, 
     ProjSplitArgs a{};
     uint16_t* const xs = (uint16_t*)(base + ws.sx_off);
     float* const xu = (float*)(base + ws.su_off);
-    HIP_TRY(m, launch_split_rows(X, p0.pad_ld, M, p0.pad_ld, xs, xu, s));
+    SplitMarks* const marks = (SplitMarks*)(base + ws.sm_off);
+    HIP_TRY(m, launch_split_rows(X, p0.pad_ld, M, p0.pad_ld, xs, xu, marks, s));
     for (int d = 0; d < n; ++d) {
         const PackedMat& p = w[d]->wx;
         a.d[d] = ProjSplitDir{p.split, p.split_unscale, w[d]->bias, P[d], (const float*)p.dense_pad,
                               p.compressed ? p.row_ptr : nullptr, p.col16, p.val};
     }
-    a.Xs = xs; a.x_unscale = xu; a.X = X; a.ldx = p0.pad_ld;
+    a.Xs = xs; a.x_unscale = xu; a.marks = marks; a.X = X; a.ldx = p0.pad_ld;
     a.M = M; a.N = p0.rows; a.K = p0.pad_ld; a.ndir = n;
     for (int d = 0; d < n; ++d) a.masked |= w[d]->wx.many_zeros;
     HIP_TRY(m, launch_proj_split(a, s));
@@ -2738,17 +2741,18 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     int32_t* drp = nullptr;
     uint16_t *dcol = nullptr, *dec = nullptr, *dXs = nullptr, *dWs = nullptr;
     float *dxu = nullptr, *dwu = nullptr;
+    SplitMarks* dmarks = nullptr;
     const bool zeros = (double)kept_all < 0.6 * (double)nn;
     bool split = format == LSTM_FMT_DENSE_MASKED && proj_split_supported(batch, n, n, 1, zeros);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = LSTM_OK;
     auto run = [&]() -> hipError_t {
         if (split) {
-            const hipError_t e = launch_split_rows(dX, n, batch, n, dXs, dxu, s);
+            const hipError_t e = launch_split_rows(dX, n, batch, n, dXs, dxu, dmarks, s);
             if (e != hipSuccess) return e;
             ProjSplitArgs a{};
             a.d[0] = ProjSplitDir{dWs, dwu, dB, dY, dW, nullptr, nullptr, nullptr};
-            a.Xs = dXs; a.x_unscale = dxu; a.X = dX; a.ldx = n;
+            a.Xs = dXs; a.x_unscale = dxu; a.marks = dmarks; a.X = dX; a.ldx = n;
             a.M = batch; a.N = n; a.K = n; a.ndir = 1; a.masked = zeros;
             return launch_proj_split(a, s);
         }
@@ -2781,9 +2785,10 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
             std::vector<float> unscale((size_t)n);
             if (e == hipSuccess) e = hipMalloc((void**)&dXs, (size_t)batch * split_row_halves(n) * sizeof(uint16_t));
             if (e == hipSuccess) e = hipMalloc((void**)&dxu, (size_t)batch * sizeof(float));
+            if (e == hipSuccess) e = hipMalloc((void**)&dmarks, sizeof(SplitMarks));
             if (e == hipSuccess) e = hipMalloc((void**)&dWs, (size_t)n * split_row_halves(n) * sizeof(uint16_t));
             if (e == hipSuccess) e = hipMalloc((void**)&dwu, (size_t)n * sizeof(float));
-            if (e == hipSuccess) e = launch_split_rows(dW, n, n, n, dWs, dwu, s);
+            if (e == hipSuccess) e = launch_split_rows(dW, n, n, n, dWs, dwu, nullptr, s);
             if (e == hipSuccess) e = hipMemcpyAsync(unscale.data(), dwu, unscale.size() * sizeof(float), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             for (float u : unscale) split = split && std::isfinite(u);
@@ -2804,7 +2809,7 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     for (void* p_ : {(void*)dX, (void*)dW, (void*)dWf, (void*)dB, (void*)dY, (void*)dXT, (void*)dval, (void*)drp, (void*)dcol, (void*)dev_, (void*)dec,
-                     (void*)dXs, (void*)dWs, (void*)dxu, (void*)dwu})
+                     (void*)dXs, (void*)dWs, (void*)dxu, (void*)dwu, (void*)dmarks})
         if (p_) (void)hipFree(p_);
     return rc;
 }

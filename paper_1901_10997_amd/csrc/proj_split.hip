@@ -39,7 +39,7 @@ __device__ __forceinline__ uint32_t pack_f16x2(_Float16 a, _Float16 b)
 
 template <int VEC>
 __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ X, int ldx, int M, int K, int KB,
-                                                         uint16_t* __restrict__ out, float* __restrict__ unscale)
+                                                         uint16_t* __restrict__ out, float* __restrict__ unscale, SplitMarks* __restrict__ marks)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = blockIdx.x * kSplitRowsPerBlock + wave;
@@ -90,20 +90,25 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) { small += __shfl_xor(small, o, 64); nonzero += __shfl_xor(nonzero, o, 64); }
-        if (lane == 0) unscale[m] = split_unscale(sc, big, small, nonzero);
+        if (lane == 0) {
+            const float u = split_unscale(sc, big, small, nonzero);
+            unscale[m] = u;
+            if (marks && !(u < __uint_as_float(kNonFinite))) marks->found = ~marks->next;
+            if (marks && m == 0) marks->pass = marks->next;
+        }
     }
 }
 
 size_t split_row_halves(int K) { return (size_t)((K + 31) / 32) * 64; }
 
-hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, hipStream_t s)
+hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, hipStream_t s)
 {
     const int KB = (K + 31) / 32;
     const dim3 grid((M + kSplitRowsPerBlock - 1) / kSplitRowsPerBlock), block(256);
     if (K % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)X & 15) == 0)
-        hipLaunchKernelGGL(split_rows_kernel<4>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale);
+        hipLaunchKernelGGL(split_rows_kernel<4>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale, marks);
     else
-        hipLaunchKernelGGL(split_rows_kernel<1>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale);
+        hipLaunchKernelGGL(split_rows_kernel<1>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale, marks);
     return hipGetLastError();
 }
 
@@ -121,87 +126,326 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// ---- tiles with rows that have no fp16 form
-template <int BM>
-__device__ __forceinline__ bool tile_has_marked_rows(const ProjSplitArgs& a, int m0, int lane)
-{
-    bool marked = false;
-#pragma unroll
-    for (int i = 0; i < BM / 64; ++i) marked |= !(a.x_unscale[min(m0 + 64 * i + lane, a.M - 1)] < __uint_as_float(kNonFinite));
-    return __ballot(marked) != 0;
-}
-
-// One wave's TM x TN tiles of 32 x 32 on the fp32 matrix instruction, operands straight from memory, a row of tiles at a
-// time (few registers: the split product sets the kernel's count).  A row with a non-finite value is then summed over the
-// kept entries where W is held row-compressed: the mask selects, and what it leaves out must not meet an infinity as a zero.
-template <int TM, int TN>
-__device__ __forceinline__ void f32_tiles(const ProjSplitArgs& a, int dir, int m0, int n0, int lane)
-{
-    const ProjSplitDir& d = a.d[dir];
-    const int M = a.M, N = a.N, K = a.K, fr = lane & 31, fk = lane >> 5;
-    constexpr int KU = 4;   // k8 steps requested together
-    const float* wrow[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) wrow[j] = d.Wd + (size_t)min(n0 + 32 * j + fr, N - 1) * K;
-#pragma unroll 1
-    for (int i = 0; i < TM; ++i) {
-        const float* xrow = a.X + (size_t)min(m0 + 32 * i + fr, M - 1) * a.ldx;
-        f32x16 acc[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-#pragma unroll 1
-        for (int k0 = 0; k0 < K; k0 += 8 * KU) {   // K % 4 == 0: a lane's four values are all there or none is
-            float4 fa[KU], fb[KU][TN];
-#pragma unroll
-            for (int u = 0; u < KU; ++u) {
-                const int k = k0 + 8 * u + 4 * fk;
-                fa[u] = k < K ? *reinterpret_cast<const float4*>(xrow + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) fb[u][j] = k < K ? *reinterpret_cast<const float4*>(wrow[j] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int u = 0; u < KU; ++u)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u].x, fb[u][j].x, acc[j], 0, 0, 0);
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u].y, fb[u][j].y, acc[j], 0, 0, 0);
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u].z, fb[u][j].z, acc[j], 0, 0, 0);
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u].w, fb[u][j].w, acc[j], 0, 0, 0);
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + 32 * j + fr;
-            if (n >= N) continue;
-            const float b = d.bias[n];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + 32 * i + 4 * fk + 8 * (v >> 2) + (v & 3);
-                if (m < M) d.P[(size_t)m * N + n] = acc[j][v] + b;
-            }
-        }
-    }
-    if (d.row_ptr == nullptr) return;
-    for (int m = m0; m < min(m0 + 32 * TM, M); ++m) {
-        if (__float_as_uint(a.x_unscale[m]) != kNonFinite) continue;
-        const float* x = a.X + (size_t)m * a.ldx;
-        for (int n = n0 + lane; n < min(n0 + 32 * TN, N); n += 64) {
-            float sum = 0.f;
-            for (int e = d.row_ptr[n]; e < d.row_ptr[n + 1]; ++e) sum = fmaf(d.val[e], x[d.col[e]], sum);
-            d.P[(size_t)m * N + n] = sum + d.bias[n];
-        }
-    }
-}
-
-// TM x TN: 32 x 32 tiles of a wave; WM x WN waves; NST slabs in the LDS ring; STAGED: sums in two stages.
 // STAGED (masked weights): the accumulators are added up and cleared every kStage slabs.  An fp32 sum that meets a mask's zeros
 // rounds once per kept term; an instruction over 16 k rounds whether they are zeros or not, 3 K / 16 times in all.  In two
 // stages the terms are a small part of the sum when they are rounded: K 1600, 15 % kept, error against 64 bits relative to the
 // product's norm: fp32 instruction 2.8e-7, one stage 3.8e-7, two 1.5e-7 (310 us against 271, 4800 x 3200 in two directions; dense
 // weights 7.2e-7, 4.6e-7 and 1.7e-7).
 constexpr int kStage = 4;
+
+// ---- rows that have no fp16 form
+// They are summed by the fp32 instruction, and a row's result depends on that row alone: where any is marked the rows are dealt out
+// to the tiles by kind, the marked ones to tiles of their own.  A workgroup works that out for itself: a mask of the marked rows
+// per 64, their number before each, and the n-th row of a kind from those.  That a row is marked stands in SplitMarks: a product
+// without one never comes here.
+constexpr int kSortRows = 32768;                          // of one launch (the table's size; more rows are several launches)
+constexpr int kRowNonFinite = 1 << 30;
+constexpr int kBeforeOff = kSortRows / 64 * 8, kRowOff = kBeforeOff + kSortRows / 64 * 2 + 16, kTableBytes = kRowOff + 256 * 4;
+typedef const ProjSplitArgs __attribute__((address_space(4)))* ArgsInMemory;
+template <class T>
+using InLds = __attribute__((address_space(3))) T*;
+struct RowTable {
+    InLds<unsigned long long> mask;                       // [kSortRows / 64] marked rows
+    InLds<unsigned short> before;                         // [kSortRows / 64 + 1] marked rows before each 64
+    InLds<int> row;                                       // [BM] of the present tile; kRowNonFinite beside it
+};
+
+// returns the number of marked rows
+template <int NW>
+__device__ __forceinline__ int sort_rows(const float* x_unscale, int M, const RowTable& t, int tid)
+{
+    const int lane = tid & 63, chunks = (M + 63) >> 6;
+    for (int c = tid >> 6; c < chunks; c += NW) {
+        const int m = 64 * c + lane;
+        const unsigned long long mask = __ballot(m < M && !(x_unscale[min(m, M - 1)] < __uint_as_float(kNonFinite)));
+        if (lane == 0) t.mask[c] = mask;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        constexpr int kPer = kSortRows / 64 / 64;
+        int mine = 0;
+        for (int i = 0; i < kPer; ++i) mine += kPer * lane + i < chunks ? __popcll(t.mask[kPer * lane + i]) : 0;
+        int at = mine;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(at, o, 64);
+            if (lane >= o) at += up;
+        }
+        if (lane == 63) t.before[chunks] = (unsigned short)at;   // all of them
+        at -= mine;
+        for (int i = 0; i < kPer; ++i) {
+            const int c = kPer * lane + i;
+            if (c < chunks) {
+                t.before[c] = (unsigned short)at;
+                at += __popcll(t.mask[c]);
+            }
+        }
+    }
+    __syncthreads();
+    return t.before[chunks];
+}
+
+// the n-th row (from 0; there are more than n) that is marked, or that is not
+__device__ __forceinline__ int nth_row(const RowTable& t, int chunks, int n, bool marked)
+{
+    int lo = 0, hi = chunks;                              // the last chunk with at most n of them before it
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1, b = t.before[mid];
+        if ((marked ? b : 64 * mid - b) <= n) lo = mid; else hi = mid;
+    }
+    int k = n - (marked ? (int)t.before[lo] : 64 * lo - (int)t.before[lo]), pos = 0;
+    const unsigned long long bits = marked ? t.mask[lo] : ~t.mask[lo];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) {
+        const int c = __popcll((bits >> pos) & ((1ull << w) - 1ull));
+        if (k >= c) { k -= c; pos += w; }
+    }
+    return 64 * lo + pos;
+}
+
+// All tiles of this workgroup where a row is marked (right where none is, too).
+// TS x TN: tiles of a wave, with half the rows of the kernel's, whose registers this shares.  Slabs of 32 k through the LDS ring
+// for both kinds (a row's 128 bytes hold both planes of 32 values, or 32 fp32 ones); the fp32 instruction leaves out blocks of
+// 32 rows that have none.  A row with a non-finite value is summed over the kept entries where W is held row-compressed: the
+// mask selects, and what it leaves out must not meet an infinity as a zero.
+// 4800 x 3200 in two directions, K 640 / 1600, microseconds with the split: every row marked 400 / 897 (fp32 kernel of proj_mfma.hip,
+// which needs no split, 348 / 835; whole tiles with the operands straight from memory 688 / 1670), every other row 289 / 614
+// (684 / 1669), one row 186 / 369 (728 / 1733), none 127 / 279.  Blocks of half a tile: 3.9 waves of them, and what a tile's ends
+// leave idle.
+template <int TS, int TN, int WM, int WN, int NST, bool STAGED>
+__device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsigned table)
+{
+    constexpr int BM = WM * TS * 32, BN = WN * TN * 32, NW = WM * WN, ROWB = 128, STAGE = (BM + BN) * ROWB, LI = (BM + BN) / 8 / NW;
+    static_assert((BM + BN) % (8 * NW) == 0, "rows divide over the waves");
+    int tid = threadIdx.x;
+    // nothing of this is worked out ahead, in registers of the kernel's loop
+    asm volatile("" : "+v"(tid), "+s"(a), "+s"(lds0), "+s"(table));
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int fr = lane & 31, fk = lane >> 5;
+    const int M = a->M, N = a->N, K = a->K, KB = (K + 31) >> 5, gn = a->gn, gnt = gn * a->ndir;
+    RowTable t;
+    t.mask = (InLds<unsigned long long>)table;
+    t.before = (InLds<unsigned short>)(table + kBeforeOff);
+    t.row = (InLds<int>)(table + kRowOff);
+    const int marked = __builtin_amdgcn_readfirstlane(sort_rows<NW>(a->x_unscale, M, t, tid));
+    // the tiles of marked rows first (each takes several times as long); of each kind consecutive ones share an XCD
+    const int gm_f32 = (marked + BM - 1) / BM, gm_planes = (M - marked + BM - 1) / BM;
+    const int per_f32 = (gm_f32 * gnt + kXcds - 1) / kXcds, per_planes = (gm_planes * gnt + kXcds - 1) / kXcds;
+#pragma unroll 1
+    for (int pid = blockIdx.x; pid < kXcds * (per_f32 + per_planes); pid += gridDim.x) {
+        const bool f32 = pid < kXcds * per_f32;
+        const int q = f32 ? pid : pid - kXcds * per_f32, gm = f32 ? gm_f32 : gm_planes;
+        const int logical = (q % kXcds) * (f32 ? per_f32 : per_planes) + q / kXcds;
+        if (logical >= gm * gnt) continue;
+        const int span = kGroupM * gnt, group = logical / span, in = logical % span, first = group * kGroupM;
+        const int gsz = (gm - first) < kGroupM ? (gm - first) : kGroupM;
+        const int tn_all = in / gsz, dir = tn_all >= gn ? 1 : 0, n0 = (tn_all - dir * gn) * BN;
+        const float* const bias = a->d[dir].bias;
+        float* const P = a->d[dir].P;
+        const bool by_entries = a->d[dir].row_ptr != nullptr;
+        const bool by_hand = f32 && ((uintptr_t)a->X & 15) != 0;   // the caller's rows, at any address: no direct loads
+        const int m0 = (first + in % gsz) * BM;           // the first row's number among its kind
+        const int rows = min((f32 ? marked : M - marked) - m0, BM);
+        __syncthreads();
+        for (int r = tid; r < rows; r += 64 * NW) {
+            const int m = marked == 0 || marked == M ? m0 + r : nth_row(t, (M + 63) >> 6, m0 + r, f32);
+            t.row[r] = f32 && by_entries && __float_as_uint(a->x_unscale[m]) == kNonFinite ? m | kRowNonFinite : m;
+        }
+        __syncthreads();
+        // bytes of this lane's 16 of every direct-load instruction: chunk kc of its row, and eight further on for every slab
+        const unsigned char* src[LI];
+        int kc[LI];
+#pragma unroll
+        for (int i = 0; i < LI; ++i) {
+            const int row0 = (wave * LI + i) * 8, row = row0 + (lane >> 3);
+            kc[i] = (lane & 7) ^ ((row >> 1) & 7);
+            if (row0 < BM) {
+                const size_t m = (size_t)(t.row[row < rows ? row : rows - 1] & ~kRowNonFinite);
+                src[i] = f32 ? (const unsigned char*)(a->X + m * a->ldx) : (const unsigned char*)(a->Xs + m * KB * 64);
+            } else {
+                const size_t n = (size_t)min(n0 + row - BM, N - 1);
+                src[i] = f32 ? (const unsigned char*)(a->d[dir].Wd + n * K) : (const unsigned char*)(a->d[dir].W + n * KB * 64);
+            }
+        }
+        const int last = (f32 ? K / 4 : 8 * KB) - 1;      // chunk of a row (past the end the last one: not used)
+        auto issue_slab = [&](int kt) {
+            const unsigned st = lds0 + (unsigned)((kt % NST) * STAGE + wave * LI * 1024);
+#pragma unroll
+            for (int i = 0; i < LI; ++i) {
+                const unsigned char* const from = src[i] + (size_t)min(8 * kt + kc[i], last) * 16;
+                if (by_hand) {
+                    const float* const f = (const float*)from;
+                    *(InLds<u32x4>)(st + (unsigned)(i * 1024 + lane * 16)) = (u32x4){__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+                } else {
+                    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)from,
+                                                     (void __attribute__((address_space(3)))*)(st + (unsigned)(i * 1024)), 16, 0, 0);
+                }
+            }
+        };
+        f32x16 acc[TS][TN], total[STAGED ? TS : 1][STAGED ? TN : 1];
+#pragma unroll
+        for (int i = 0; i < TS; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    acc[i][j][v] = 0.f;
+                    if (STAGED) total[STAGED ? i : 0][STAGED ? j : 0][v] = 0.f;
+                }
+        // fragments of this lane: chunk c of its rows
+        auto read_a = [&](u32x4 (&f)[TS], unsigned st, int c) {
+#pragma unroll
+            for (int i = 0; i < TS; ++i) {
+                const int r = (wm * TS + i) * 32 + fr;
+                f[i] = lds_read_b128(st + (unsigned)(r * ROWB + ((c ^ ((r >> 1) & 7)) * 16)));
+            }
+        };
+        auto read_b = [&](u32x4 (&f)[TN], unsigned st, int c) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int r = BM + (wn * TN + j) * 32 + fr;
+                f[j] = lds_read_b128(st + (unsigned)(r * ROWB + ((c ^ ((r >> 1) & 7)) * 16)));
+            }
+        };
+        auto arrived = [&](auto& f) {
+#pragma unroll
+            for (auto& v : f) asm volatile("" : "+v"(v) : : "memory");
+        };
+        // slab `target` has landed once only the loads of the (at most NST - 2) younger slabs can still be outstanding
+        auto wait_slab = [&](int target) {
+            const int younger = min(KB - 1 - target, NST - 2);
+            if (NST >= 4 && younger == 2) wait_vmcnt<NST >= 4 ? 2 * LI : 0>();
+            else if (NST >= 3 && younger == 1) wait_vmcnt<NST >= 3 ? LI : 0>();
+            else wait_vmcnt<0>();
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");   // (by_hand)
+            __builtin_amdgcn_s_barrier();
+        };
+#pragma unroll
+        for (int k = 0; k < NST - 1; ++k)
+            if (k < KB) issue_slab(k);
+        wait_slab(0);
+        if (NST - 1 < KB) issue_slab(NST - 1);
+        if (f32) {
+            u32x4 fa[2][TS], fb[2][TN];
+            read_a(fa[0], lds0, fk);
+            read_b(fb[0], lds0, fk);
+#pragma unroll 1
+            for (int kt = 0; kt < KB; ++kt) {
+                const unsigned st = lds0 + (unsigned)((kt % NST) * STAGE), stn = lds0 + (unsigned)(((kt + 1) % NST) * STAGE);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {         // 8 k each: a lane's four are chunk 2 u + fk of its row; the next ones on their way
+                    if (u < 3) {
+                        read_a(fa[(u + 1) & 1], st, 2 * (u + 1) + fk);
+                        read_b(fb[(u + 1) & 1], st, 2 * (u + 1) + fk);
+                        asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(TS + TN) : "memory");
+                    } else {
+                        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+                    }
+                    arrived(fa[u & 1]);
+                    arrived(fb[u & 1]);
+                    if (u == 3 && kt + 1 < KB) {      // done with slab kt: its buffer may be refilled
+                        wait_slab(kt + 1);
+                        if (kt + NST < KB) issue_slab(kt + NST);
+                        read_a(fa[0], stn, fk);
+                        read_b(fb[0], stn, fk);
+                    }
+                    if (32 * kt + 32 > K) {           // K % 4 == 0: a lane's four values are all there or none is
+                        const bool there = 32 * kt + 8 * u + 4 * fk < K;
+#pragma unroll
+                        for (int i = 0; i < TS; ++i) fa[u & 1][i] = there ? fa[u & 1][i] : (u32x4){0, 0, 0, 0};
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) fb[u & 1][j] = there ? fb[u & 1][j] : (u32x4){0, 0, 0, 0};
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < TS; ++i)
+                        if ((wm * TS + i) * 32 < rows)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                                for (int j = 0; j < TN; ++j)
+                                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[u & 1][i][e]), __uint_as_float(fb[u & 1][j][e]), acc[i][j], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
+#pragma unroll 1
+            for (int kt = 0; kt < KB; ++kt) {
+                const unsigned st = lds0 + (unsigned)((kt % NST) * STAGE);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {      // the order of the products is that of the kernel below: the same bits
+                    u32x4 ah[TS], al[TS], bh[TN], bl[TN];
+                    read_a(ah, st, 2 * ks + fk);
+                    read_b(bl, st, 4 + 2 * ks + fk);
+                    read_b(bh, st, 2 * ks + fk);
+                    read_a(al, st, 4 + 2 * ks + fk);
+                    auto mma = [&](const u32x4 (&fa)[TS], const u32x4 (&fb)[TN]) {
+#pragma unroll
+                        for (int i = 0; i < TS; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]), __builtin_bit_cast(f16x8, fb[j]), acc[i][j], 0, 0, 0);
+                    };
+                    asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(TS + TN) : "memory");
+                    arrived(ah);
+                    arrived(bl);
+                    mma(ah, bl);
+                    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+                    arrived(bh);
+                    arrived(al);
+                    if (ks == 1 && kt + 1 < KB) {
+                        wait_slab(kt + 1);
+                        if (kt + NST < KB) issue_slab(kt + NST);
+                    }
+                    mma(ah, bh);
+                    mma(al, bh);
+                }
+                if (STAGED && (kt % kStage == kStage - 1 || kt == KB - 1)) {
+#pragma unroll
+                    for (int i = 0; i < TS; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) {
+                                total[STAGED ? i : 0][STAGED ? j : 0][v] += acc[i][j][v];
+                                acc[i][j][v] = kt == KB - 1 ? total[STAGED ? i : 0][STAGED ? j : 0][v] : 0.f;
+                            }
+                }
+            }
+        }
+        // accumulator register v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + (wn * TN + j) * 32 + fr, nc = n < N ? n : N - 1;
+            const float b = bias[nc], wu = f32 ? 1.f : a->d[dir].w_unscale[nc];
+#pragma unroll
+            for (int i = 0; i < TS; ++i) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = (wm * TS + i) * 32 + 4 * fk + 8 * (v >> 2) + (v & 3);
+                    const int m = t.row[r < rows ? r : rows - 1];
+                    const float o = f32 ? acc[i][j][v] + b : fmaf(acc[i][j][v], a->x_unscale[m] * wu, b);
+                    if (r < rows && n < N && !(m & kRowNonFinite)) P[(size_t)(m & ~kRowNonFinite) * N + n] = o;
+                    if (v % 8 == 7) asm volatile("" : : : "memory");   // (few registers)
+                }
+            }
+        }
+        if (!f32 || !by_entries) continue;
+        for (int r = wm * TS * 32; r < min((wm + 1) * TS * 32, rows); ++r) {
+            const int m = __builtin_amdgcn_readfirstlane(t.row[r]);
+            if (!(m & kRowNonFinite)) continue;
+            const float* const x = a->X + (size_t)(m & ~kRowNonFinite) * a->ldx;
+            for (int n = n0 + wn * TN * 32 + lane; n < min(n0 + (wn + 1) * TN * 32, N); n += 64) {
+                float sum = 0.f;
+                for (int e = a->d[dir].row_ptr[n]; e < a->d[dir].row_ptr[n + 1]; ++e) sum = fmaf(a->d[dir].val[e], x[a->d[dir].col[e]], sum);
+                P[(size_t)(m & ~kRowNonFinite) * N + n] = sum + bias[n];
+            }
+        }
+    }
+}
+
+// TM x TN: 32 x 32 tiles of a wave; WM x WN waves; NST slabs in the LDS ring; STAGED: sums in two stages.
 template <int TM, int TN, int WM, int WN, int NST, bool STAGED>
 __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitArgs a)
 {
@@ -230,6 +474,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
         const int rr = (wn * TN + j) * 32 + fr;
         offb[j] = (unsigned)((BM + rr) * ROWB + ((fk ^ ((rr >> 1) & 7)) * 16));
     }
+    // (asked for here, heard behind the first slab)
+    const auto marks = (const SplitMarks __attribute__((address_space(4)))*)a.marks;
+    const bool look = marks->found == ~marks->pass;
+    if (blockIdx.x == 0 && tid == 0) a.marks->next = marks->pass + 1u;
     for (int pid = blockIdx.x; pid < a.npid; pid += gridDim.x) {
         // consecutive tiles share an XCD; four tile rows at a time walk over all columns of both directions
         const int nblk = a.gm * a.gn * a.ndir;
@@ -312,12 +560,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
 #pragma unroll
         for (int q = 0; q < NST - 1; ++q)
             if (q < KB) issue_slab(q);
-        if (tile_has_marked_rows<BM>(a, m0, lane)) {   // the same answer in every wave
-            wait_vmcnt<0>();
-            f32_tiles<TM, TN>(a, dir, m0 + wm * TM * 32, n0 + wn * TN * 32, lane);
-            continue;
-        }
         wait_slab(0);
+        if (look) break;
         __builtin_amdgcn_s_barrier();
         if (NST - 1 < KB) issue_slab(NST - 1);
         u32x4 ah[TM], al[TM], bh[TN], bl[TN];
@@ -371,18 +615,21 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
             }
         }
         // ---- P = acc * 2^-(ex + ew) + bias; accumulator register v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
+        int l = threadIdx.x & 63;
+        asm volatile("" : "+v"(l));                       // (worked out here, not ahead of the loop in registers of its own)
+        const int er = l & 31, ek = l >> 5;
         const float* bias = a.d[dir].bias;
         float* P = a.d[dir].P;
         float bn[TN], wu[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int n = n0 + (wn * TN + j) * 32 + fr, nc = n < N ? n : N - 1;
+            const int n = n0 + (wn * TN + j) * 32 + er, nc = n < N ? n : N - 1;
             bn[j] = bias[nc];
             wu[j] = a.d[dir].w_unscale[nc];
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int mb = m0 + (wm * TM + i) * 32 + 4 * fk;
+            const int mb = m0 + (wm * TM + i) * 32 + 4 * ek;
             float xu[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -390,18 +637,20 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
                 xu[v] = a.x_unscale[m < M ? m : M - 1];
             }
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(acc[i][j][v], xu[v] * wu[j], bn[j]);
+                asm volatile("" : "+v"(acc[i][j]));       // here, not beside the stores: the scales' registers are free again
+            }
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int n = n0 + (wn * TN + j) * 32 + fr;
+            const int n = n0 + (wn * TN + j) * 32 + er;
             if (n >= N) continue;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                const int mb = m0 + (wm * TM + i) * 32 + 4 * fk;
-                if (mb - 4 * fk + 32 <= M) {
+                const int mb = m0 + (wm * TM + i) * 32 + 4 * ek;
+                if (mb - 4 * ek + 32 <= M) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) P[(size_t)(mb + 8 * (v >> 2) + (v & 3)) * N + n] = acc[i][j][v];
                 } else {
@@ -413,6 +662,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
                 }
             }
         }
+    }    // A row is marked somewhere: no tile is done yet.
+    if (look) {
+        wait_vmcnt<0>();
+        __syncthreads();
+        sorted_tiles<(TM + 1) / 2, TN, WM, WN, NST, STAGED>((ArgsInMemory)__builtin_amdgcn_kernarg_segment_ptr(), lds0, lds0 + NST * STAGE);
     }
 }
 
@@ -423,7 +677,7 @@ static hipError_t launch_tiles(ProjSplitArgs a, int per_cu, hipStream_t s)
     a.gm = (a.M + BM - 1) / BM;
     a.gn = (a.N + BN - 1) / BN;
     a.npid = ((a.gm * a.gn * a.ndir + kXcds - 1) / kXcds) * kXcds;
-    const int lds = NST * (BM + BN) * 128;
+    const int lds = NST * (BM + BN) * 128 + kTableBytes;
     const hipError_t e = hipFuncSetAttribute((const void*)proj_split_kernel<TM, TN, WM, WN, NST, STAGED>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     const int slots = std::max(kXcds, device_num_cus() * per_cu / kXcds * kXcds);
@@ -478,10 +732,8 @@ bool proj_split_supported(int M, int N, int K, int ndir, bool masked)
     return proj_split_us(M, N, K, ndir, masked) < f32_us;
 }
 
-hipError_t launch_proj_split(const ProjSplitArgs& a, hipStream_t s)
+static hipError_t launch_band(const ProjSplitArgs& a, hipStream_t s)
 {
-    if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    if (a.K % 4 != 0 || a.ldx % 4 != 0) return hipErrorInvalidValue;
     double us;
     const int shape = choose_shape(a.M, a.N, a.K, a.ndir, a.masked != 0, &us);
     if (a.masked)
@@ -498,6 +750,26 @@ hipError_t launch_proj_split(const ProjSplitArgs& a, hipStream_t s)
         case 3: return launch_tiles<2, 1, 1, 4, 3, false>(a, 2, s);
         default: return launch_tiles<1, 1, 2, 2, 4, false>(a, 2, s);
     }
+}
+
+hipError_t launch_proj_split(const ProjSplitArgs& all, hipStream_t s)
+{
+    if (all.M <= 0 || all.N <= 0) return hipSuccess;
+    if (all.K % 4 != 0 || all.ldx % 4 != 0 || !all.marks) return hipErrorInvalidValue;
+    // rows the table holds, and whose planes a 32-bit offset reaches
+    const size_t rowh = split_row_halves(all.K);
+    const int band = (int)std::max<size_t>(64, std::min<size_t>(kSortRows, ((size_t)1 << 31) / rowh / 64 * 64));
+    for (int m = 0; m < all.M; m += band) {
+        ProjSplitArgs a = all;
+        a.M = std::min(band, all.M - m);
+        a.Xs += (size_t)m * rowh;
+        a.x_unscale += m;
+        a.X += (size_t)m * a.ldx;
+        for (int d = 0; d < a.ndir; ++d) a.d[d].P += (size_t)m * a.N;
+        const hipError_t e = launch_band(a, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace l355

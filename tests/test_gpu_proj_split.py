@@ -119,3 +119,81 @@ def test_infinite_input_reaches_kept_entries_only():
     np.testing.assert_allclose(y1[77, ~kept], y0[77, ~kept], rtol=0, atol=1e-5)
     assert not np.isnan(y1[77, ~kept]).any()
     assert (y1[77, kept] != y0[77, kept]).mean() > 0.5    # (all but those whose only such entry is in the gate that meets c0 = 0)
+
+
+def _marked(X, rows, rng):
+    """Rows with one value that takes most of the others below 2^-16 of it."""
+    X = X.copy()
+    X[rows, rng.integers(0, X.shape[1], len(rows))] = 1e7
+    return X
+
+
+@pytest.mark.parametrize("keep", [1.0, 0.15])
+@pytest.mark.parametrize("n,batch", [(1032, 130), (1036, 191), (6404, 300), (2400, 1500), (4100, 1900), (4096, 4000)])
+def test_rows_without_a_plane_form_leave_the_others_as_they_were(n, batch, keep):
+    """A row's result depends on that row alone, whatever the others are: the same bits; and the marked rows are within the bound of
+    an fp32 sum (K rounded additions that add up like a random walk) of theirs."""
+    rng = np.random.default_rng(n + batch)
+    X = rng.standard_normal((batch, n)).astype(np.float32)
+    W = (rng.uniform(-0.1, 0.1, (n, n)) * (rng.random((n, n)) < keep)).astype(np.float32)
+    y = _product(X, W)
+    for rows in (np.array([batch - 1]), rng.permutation(batch)[:batch // 3], np.sort(rng.permutation(batch)[:batch - 2]), np.arange(batch)):
+        Xm = _marked(X, rows, rng)
+        ym = _product(Xm, W)
+        others = np.setdiff1d(np.arange(batch), rows)
+        assert np.array_equal(ym[others], y[others])
+        some = rows[rng.permutation(len(rows))[:120]]
+        ref = Xm[some].astype(np.float64) @ W.astype(np.float64).T
+        err = np.linalg.norm(ym[some] - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert np.max(err) <= 4 * 2.0 ** -24 * np.sqrt(n), (np.max(err), len(rows))
+
+
+def test_non_finite_rows_leave_the_others_as_they_were():
+    case = inputs.make_case(inputs.Workload(87, "split_inf", 1, True, 1032, 70, 1, 330, "f32", 0.05, 0.3, "uniform"), k=9)
+    fmt = B.LSTM_FMT_ROW_COMPRESSED
+    before, desc = run_gpu(case, fmt, B.LSTM_PLAN_AUTO)
+    assert "proj=dense-split" in desc, desc
+    rows = [0, 64, 65, 200, 329]
+    case.x[0, rows, [1, 40, 77, 1031, 500]] = [np.inf, -np.inf, np.nan, np.inf, np.nan]
+    after = run_gpu(case, fmt, B.LSTM_PLAN_AUTO)[0]
+    for a, b in zip(after, before):
+        a, b = a.reshape(-1, 330, a.shape[-1]), b.reshape(-1, 330, b.shape[-1])
+        assert np.array_equal(np.delete(a, rows, 1), np.delete(b, rows, 1))
+    # the units that keep no entry in the column: a sum over their kept entries, the same within rounding
+    kept = case.weights[(0, 0)]["Mx"].reshape(4, 70, 1032)[:, :, 77].any(axis=0)
+    y0, y1 = before[0].reshape(330, 140), after[0].reshape(330, 140)
+    np.testing.assert_allclose(y1[65, :70][~kept], y0[65, :70][~kept], rtol=0, atol=1e-5)
+    assert np.isnan(y1[65, :70][kept]).any()
+
+
+def test_more_rows_than_one_launch_takes_and_unaligned_input():
+    """40000 rows (a launch takes 32768), marked ones in both launches, from an address that is no multiple of 16 bytes; every launch
+    looks at its own rows, and a call without a marked row gives the first one's bits again."""
+    import torch
+    D, H, Bn = 200, 300, 40000
+    case = inputs.make_case(inputs.Workload(88, "split_rows", 1, False, D, H, 1, 64, "f32", 0.05, None, "uniform"), k=2)
+    m = B.Lstm(1, D, H, False, B.LSTM_F32)
+    m.set_weights_from(case.weights, B.LSTM_FMT_DENSE_MASKED)
+    dev = torch.device("cuda:0")
+    buf = torch.randn(Bn * D + 1, device=dev, generator=torch.Generator(device=dev).manual_seed(5))
+    x = buf[1:].view(1, Bn, D)
+    assert x.data_ptr() % 16 == 4
+    first = m.forward(x, None, None)[0].clone()
+    assert "proj=dense-split" in B.lstm_describe_plan(m.handle), B.lstm_describe_plan(m.handle)
+    rows = torch.tensor([0, 5, 100, 32767, 32768, 39999], device=dev)
+    keep = x[0, rows].clone()
+    x[0, rows, 3] = 3e5
+    y = m.forward(x, None, None)[0]
+    others = torch.ones(Bn, dtype=torch.bool, device=dev)
+    others[rows] = False
+    assert torch.equal(y[0, others], first[0, others]) and not torch.equal(y[0, rows], first[0, rows])
+    p = case.weights[(0, 0)]
+    a = x[0, rows].double().cpu().numpy() @ p["Wx"].astype(np.float64).T + p["b"]
+    f, i, o, g = (a[:, q * H:(q + 1) * H] for q in range(4))
+    sig = lambda v: 0.5 * (1 + np.tanh(0.5 * v))
+    ref = sig(o) * np.tanh(sig(i) * np.tanh(g))
+    # a pre-activation of up to 3e5 * 0.05 sums 200 terms to 2^-24 of that each
+    assert np.max(np.abs(y[0, rows].cpu().numpy() - ref)) <= 2.0 ** -24 * 15000 * np.sqrt(200)
+    x[0, rows] = keep
+    assert torch.equal(m.forward(x, None, None)[0], first)
+    m.close()
