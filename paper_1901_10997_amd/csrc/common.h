@@ -14,7 +14,6 @@ namespace l355 {
 struct PackedMat {
     int rows = 0, cols = 0;
     bool compressed = false;
-    bool many_zeros = false;     // a mask that keeps less than three in five
     void* dense = nullptr;       // [rows][cols], fp32 or bf16 bits; +0 where the mask is 0
     float* dense_frag16 = nullptr;  // fp32: the dense matrix in the fragment order of the 16-row matrix instructions: input-side
                                     // ones for products with at most 64 input rows (launch_proj_mfma), recurrent ones for
@@ -27,6 +26,7 @@ struct PackedMat {
     // not fit the form
     uint16_t* split = nullptr;
     float* split_unscale = nullptr;
+    bool many_zeros = false;     // less than three in five of its values are not zero: sums in two stages
     // fp32 recurrent matrices with dense_frag16: the same for persist_split.hip
     uint16_t* rec_split = nullptr;
     float* rec_unscale = nullptr;
@@ -128,7 +128,10 @@ struct ProjSplitArgs {
     int gm, gn, npid;             // set by the launcher
 };
 size_t split_row_halves(int K);
-hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, hipStream_t s);
+// terms (may be nullptr): [M] values that are not zero
+hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, int* terms, hipStream_t s);
+// Is a product with these rows of W (their numbers of terms) no further from 64 bits on planes?  many_zeros: as PackedMat::many_zeros
+bool split_terms_suffice(const int* terms, int rows, int K, bool* many_zeros);
 constexpr int kSplitMinK = 64;
 bool proj_split_supported(int M, int N, int K, int ndir, bool masked);   // and faster than the fp32 instruction
 double proj_split_us(int M, int N, int K, int ndir, bool masked);   // modelled time, with launch_split_rows

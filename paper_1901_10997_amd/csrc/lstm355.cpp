@@ -429,10 +429,17 @@ static int add_split(lstm_t* m, PackedMat& p)
 {
     if (p.pad_ld < kSplitMinK) return LSTM_OK;
     std::vector<float> unscale((size_t)p.rows);
+    std::vector<int> terms((size_t)p.rows);
+    int* dterms = nullptr;
     HIP_TRY(m, hipMalloc((void**)&p.split, (size_t)p.rows * split_row_halves(p.pad_ld) * sizeof(uint16_t)));
     HIP_TRY(m, hipMalloc((void**)&p.split_unscale, unscale.size() * sizeof(float)));
-    HIP_TRY(m, launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr, nullptr));
-    HIP_TRY(m, hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost));
+    HIP_TRY(m, hipMalloc((void**)&dterms, terms.size() * sizeof(int)));
+    hipError_t e = launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr, dterms, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(terms.data(), dterms, terms.size() * sizeof(int), hipMemcpyDeviceToHost);
+    (void)hipFree(dterms);
+    HIP_TRY(m, e);
+    if (!split_terms_suffice(terms.data(), p.rows, p.cols, &p.many_zeros)) unscale[0] = INFINITY;   // as if a row did not fit
     drop_unfit(unscale, p.split, p.split_unscale);
     return LSTM_OK;
 }
@@ -461,11 +468,6 @@ static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t*
     out.rows = rows;
     out.cols = cols;
     out.compressed = compressed;
-    if (mask) {
-        size_t kept = 0;
-        for (size_t i = 0; i < (size_t)rows * cols; ++i) kept += mask[i];
-        out.many_zeros = (double)kept < 0.6 * (double)rows * (double)cols;
-    }
     auto abi_row = [H](int rp) { return (rp & 3) * H + (rp >> 2); };
     if (!compressed || keep_dense) {
         const size_t n = (size_t)rows * cols;
@@ -1371,7 +1373,7 @@ static int run_split_proj(lstm_t* m, const LayerDir* const* w, float* const* P, 
     uint16_t* const xs = (uint16_t*)(base + ws.sx_off);
     float* const xu = (float*)(base + ws.su_off);
     SplitMarks* const marks = (SplitMarks*)(base + ws.sm_off);
-    HIP_TRY(m, launch_split_rows(X, p0.pad_ld, M, p0.pad_ld, xs, xu, marks, s));
+    HIP_TRY(m, launch_split_rows(X, p0.pad_ld, M, p0.pad_ld, xs, xu, marks, nullptr, s));
     for (int d = 0; d < n; ++d) {
         const PackedMat& p = w[d]->wx;
         a.d[d] = ProjSplitDir{p.split, p.split_unscale, w[d]->bias, P[d], (const float*)p.dense_pad,
@@ -2702,7 +2704,6 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     std::vector<int32_t> rp((size_t)n + 1, 0);
     std::vector<uint16_t> col;
     std::vector<float> val;
-    size_t kept_all = 0;
     for (int r = 0; r < n; ++r) {
         for (int k = 0; k < n; ++k) {
             float w;
@@ -2716,7 +2717,6 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
                 kept = keep >= 1.0 || rng.uniform() < keep;
             }
             W[(size_t)r * n + k] = kept ? w : 0.0f;
-            kept_all += kept;
             if (kept && format == LSTM_FMT_ROW_COMPRESSED) { col.push_back((uint16_t)k); val.push_back(w); }
         }
         rp[(size_t)r + 1] = (int32_t)col.size();
@@ -2742,13 +2742,17 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
     uint16_t *dcol = nullptr, *dec = nullptr, *dXs = nullptr, *dWs = nullptr;
     float *dxu = nullptr, *dwu = nullptr;
     SplitMarks* dmarks = nullptr;
-    const bool zeros = (double)kept_all < 0.6 * (double)nn;
-    bool split = format == LSTM_FMT_DENSE_MASKED && proj_split_supported(batch, n, n, 1, zeros);
+    bool split = format == LSTM_FMT_DENSE_MASKED, zeros = false;
+    if (split) {   // as lstm_set_weights judges an input-side matrix
+        std::vector<int> terms((size_t)n);
+        for (size_t i = 0; i < nn; ++i) terms[i / n] += W[i] != 0.0f;
+        split = split_terms_suffice(terms.data(), n, n, &zeros) && proj_split_supported(batch, n, n, 1, zeros);
+    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = LSTM_OK;
     auto run = [&]() -> hipError_t {
         if (split) {
-            const hipError_t e = launch_split_rows(dX, n, batch, n, dXs, dxu, dmarks, s);
+            const hipError_t e = launch_split_rows(dX, n, batch, n, dXs, dxu, dmarks, nullptr, s);
             if (e != hipSuccess) return e;
             ProjSplitArgs a{};
             a.d[0] = ProjSplitDir{dWs, dwu, dB, dY, dW, nullptr, nullptr, nullptr};
@@ -2788,7 +2792,7 @@ int lstm_bench_matmul(int n, int batch, double keep, int format, uint64_t seed, 
             if (e == hipSuccess) e = hipMalloc((void**)&dmarks, sizeof(SplitMarks));
             if (e == hipSuccess) e = hipMalloc((void**)&dWs, (size_t)n * split_row_halves(n) * sizeof(uint16_t));
             if (e == hipSuccess) e = hipMalloc((void**)&dwu, (size_t)n * sizeof(float));
-            if (e == hipSuccess) e = launch_split_rows(dW, n, n, n, dWs, dwu, nullptr, s);
+            if (e == hipSuccess) e = launch_split_rows(dW, n, n, n, dWs, dwu, nullptr, nullptr, s);
             if (e == hipSuccess) e = hipMemcpyAsync(unscale.data(), dwu, unscale.size() * sizeof(float), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             for (float u : unscale) split = split && std::isfinite(u);

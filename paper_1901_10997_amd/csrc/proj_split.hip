@@ -27,9 +27,16 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 constexpr int kXcds = 8;
 constexpr int kGroupM = 4;
 
+// A sum on the fp32 instruction is off by the rounding of its terms that are not zero, 1.8e-8 sqrt(n) of the product's norm; on planes
+// by what the planes drop as well, 1.1e-7 and more whatever n is.  Error against 64 bits, fp32 instruction / planes in two stages:
+// 32 of 640 entries kept 1.03e-7 / 1.19e-7, 52 of 1032 1.31e-7 / 1.25e-7, 64 of 640 1.45e-7 / 1.32e-7, 80 of 1600 1.62e-7 / 1.33e-7:
+// from 46 terms on planes are no worse.  Rows of W are judged together (long ones count for twice the limit at most), rows of X one
+// by one.
+constexpr int kSplitMinTerms = 48;
+
 // ---- rows into two fp16 planes
 // out: per row KB blocks of 128 bytes, 32 hi values then 32 lo values of k = 32 kb ..; unscale: 2^-e of the row's scale 2^e, or a mark
-// where the row does not fit (device_math.h).
+// where the row does not fit (device_math.h; with `marks`, also where it has too few terms).
 constexpr int kSplitRowsPerBlock = 4;
 
 __device__ __forceinline__ uint32_t pack_f16x2(_Float16 a, _Float16 b)
@@ -39,7 +46,8 @@ __device__ __forceinline__ uint32_t pack_f16x2(_Float16 a, _Float16 b)
 
 template <int VEC>
 __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ X, int ldx, int M, int K, int KB,
-                                                         uint16_t* __restrict__ out, float* __restrict__ unscale, SplitMarks* __restrict__ marks)
+                                                         uint16_t* __restrict__ out, float* __restrict__ unscale,
+                                                         SplitMarks* __restrict__ marks, int* __restrict__ terms)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = blockIdx.x * kSplitRowsPerBlock + wave;
@@ -91,8 +99,10 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) { small += __shfl_xor(small, o, 64); nonzero += __shfl_xor(nonzero, o, 64); }
         if (lane == 0) {
-            const float u = split_unscale(sc, big, small, nonzero);
+            float u = split_unscale(sc, big, small, nonzero);
+            if (marks && nonzero > 0 && nonzero < kSplitMinTerms && u < __uint_as_float(kNonFinite)) u = __uint_as_float(kTooWide);
             unscale[m] = u;
+            if (terms) terms[m] = nonzero;
             if (marks && !(u < __uint_as_float(kNonFinite))) marks->found = ~marks->next;
             if (marks && m == 0) marks->pass = marks->next;
         }
@@ -101,15 +111,27 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 
 size_t split_row_halves(int K) { return (size_t)((K + 31) / 32) * 64; }
 
-hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, hipStream_t s)
+hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, int* terms, hipStream_t s)
 {
     const int KB = (K + 31) / 32;
     const dim3 grid((M + kSplitRowsPerBlock - 1) / kSplitRowsPerBlock), block(256);
     if (K % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)X & 15) == 0)
-        hipLaunchKernelGGL(split_rows_kernel<4>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale, marks);
+        hipLaunchKernelGGL(split_rows_kernel<4>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale, marks, terms);
     else
-        hipLaunchKernelGGL(split_rows_kernel<1>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale, marks);
+        hipLaunchKernelGGL(split_rows_kernel<1>, grid, block, 0, s, X, ldx, M, K, KB, out, unscale, marks, terms);
     return hipGetLastError();
+}
+
+bool split_terms_suffice(const int* terms, int rows, int K, bool* many_zeros)
+{
+    long long all = 0, capped = 0, some = 0;
+    for (int r = 0; r < rows; ++r) {
+        all += terms[r];
+        capped += std::min(terms[r], 2 * kSplitMinTerms);
+        some += terms[r] > 0;
+    }
+    *many_zeros = (double)all < 0.6 * (double)rows * (double)K;
+    return capped >= kSplitMinTerms * some;
 }
 
 // ---- the product

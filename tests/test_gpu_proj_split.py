@@ -197,3 +197,56 @@ def test_more_rows_than_one_launch_takes_and_unaligned_input():
     x[0, rows] = keep
     assert torch.equal(m.forward(x, None, None)[0], first)
     m.close()
+
+
+def _f32_chain(X, W):
+    """X . W^T as fp32 multiply-adds in the order of k: what the fp32 matrix instruction rounds, a zero term never does."""
+    y = np.zeros((X.shape[0], W.shape[0]), np.float32)
+    for k in range(X.shape[1]):
+        y = (y.astype(np.float64) + X[:, k:k + 1].astype(np.float64) * W[:, k].astype(np.float64)).astype(np.float32)
+    return y
+
+
+def _error(y, ref):
+    return np.linalg.norm(y - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("n,kept", [(640, 0.05), (1032, 0.02), (1032, 0.10), (1032, 0.45), (640, 0.8)])
+@pytest.mark.parametrize("as_mask", [True, False])
+def test_products_of_few_terms_are_no_further_from_64_bits(n, kept, as_mask):
+    """Rows with few entries, by a mask or as zeros among the weights: no further from the exact product than a chain of fp32
+    multiply-adds over the kept entries (the order of the sums moves either by a tenth or two)."""
+    rng = np.random.default_rng(n)
+    batch = 4096 if n == 640 else 2048
+    X = rng.standard_normal((batch, n)).astype(np.float32)
+    keep = rng.random((n, n)) < kept
+    W = (rng.uniform(-0.1, 0.1, (n, n)) * keep).astype(np.float32)
+    _, y = B.lstm_bench_matmul(n, batch, 1.0, B.LSTM_FMT_DENSE_MASKED, iters=1, want_product=True, X=X, W=W,
+                               mask=keep.astype(np.uint8) if as_mask else None)
+    ref = X[:200].astype(np.float64) @ W.astype(np.float64).T
+    assert _error(y[:200], ref) <= 1.1 * _error(_f32_chain(X[:200], W), ref)
+
+
+def test_input_rows_of_few_terms_are_no_further_from_64_bits():
+    """Input rows that are zero but for a few values (one-hot rows among them) beside full ones."""
+    n, batch = 1032, 2048
+    rng = np.random.default_rng(8)
+    X = rng.standard_normal((batch, n)).astype(np.float32)
+    W = rng.uniform(-0.1, 0.1, (n, n)).astype(np.float32)
+    X[:40] = 0.0
+    X[np.arange(40), rng.integers(0, n, 40)] = 1.0
+    X[40:80] *= rng.random((40, n)) < 0.02
+    X[80:90] = 0.0
+    y = _product(X, W)
+    ref = X[:200].astype(np.float64) @ W.astype(np.float64).T
+    np.testing.assert_array_equal(y[:40].astype(np.float64), ref[:40])     # one term: exact
+    assert _error(y[40:80], ref[40:80]) <= 1.1 * _error(_f32_chain(X[40:80], W), ref[40:80])
+    assert not y[80:90].any()
+
+
+def test_masked_layers_of_few_entries_keep_their_sums():
+    """The H-LSTM and LSTM layers whose projection goes by the same rule."""
+    for keep, want in ((0.05, "proj=dense,"), (0.30, "proj=dense-split,")):
+        case = inputs.make_case(inputs.Workload(89, "few_terms", 1, True, 512, 160, 30, 20, "f32", 0.05, keep, "uniform", 160), k=4, random_state=True)
+        desc, _ = check_case(case)
+        assert want in desc, desc
