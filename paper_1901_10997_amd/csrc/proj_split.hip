@@ -28,11 +28,11 @@ constexpr int kXcds = 8;
 constexpr int kGroupM = 4;
 
 // A sum on the fp32 instruction is off by the rounding of its terms that are not zero, 1.8e-8 sqrt(n) of the product's norm; on planes
-// by what the planes drop as well, 1.1e-7 and more whatever n is.  Error against 64 bits, fp32 instruction / planes in two stages:
-// 32 of 640 entries kept 1.03e-7 / 1.19e-7, 52 of 1032 1.31e-7 / 1.25e-7, 64 of 640 1.45e-7 / 1.32e-7, 80 of 1600 1.62e-7 / 1.33e-7:
-// from 46 terms on planes are no worse.  Rows of W are judged together (long ones count for twice the limit at most), rows of X one
-// by one.
-constexpr int kSplitMinTerms = 48;
+// by what the planes drop as well, 0.75e-7 and more whatever n is.  Error against 64 bits, fp32 instruction / planes in stages: 52 of
+// 1032 entries kept 1.31e-7 / 0.90e-7, 64 of 640 1.45e-7 / 0.97e-7, 80 of 1600 1.62e-7 / 0.91e-7 (32 of 640 1.03e-7 / 0.9e-7 by a
+// model of the sums): level at 25 terms; in one stage (less than two in five are zero) at 46.  Rows of W are judged together (long
+// ones count for twice the limit at most), rows of X one by one.
+constexpr int kSplitMinTerms = 48, kSplitMinTermsStaged = 32;
 
 // ---- rows into two fp16 planes
 // out: per row KB blocks of 128 bytes, 32 hi values then 32 lo values of k = 32 kb ..; unscale: 2^-e of the row's scale 2^e, or a mark
@@ -125,13 +125,14 @@ hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* ou
 bool split_terms_suffice(const int* terms, int rows, int K, bool* many_zeros)
 {
     long long all = 0, capped = 0, some = 0;
+    for (int r = 0; r < rows; ++r) all += terms[r];
+    *many_zeros = (double)all < 0.6 * (double)rows * (double)K;
+    const int least = *many_zeros ? kSplitMinTermsStaged : kSplitMinTerms;
     for (int r = 0; r < rows; ++r) {
-        all += terms[r];
-        capped += std::min(terms[r], 2 * kSplitMinTerms);
+        capped += std::min(terms[r], 2 * least);
         some += terms[r] > 0;
     }
-    *many_zeros = (double)all < 0.6 * (double)rows * (double)K;
-    return capped >= kSplitMinTerms * some;
+    return capped >= least * some;
 }
 
 // ---- the product
@@ -148,12 +149,28 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// STAGED (masked weights): the accumulators are added up and cleared every kStage slabs.  An fp32 sum that meets a mask's zeros
-// rounds once per kept term; an instruction over 16 k rounds whether they are zeros or not, 3 K / 16 times in all.  In two
-// stages the terms are a small part of the sum when they are rounded: K 1600, 15 % kept, error against 64 bits relative to the
-// product's norm: fp32 instruction 2.8e-7, one stage 3.8e-7, two 1.5e-7 (310 us against 271, 4800 x 3200 in two directions; dense
-// weights 7.2e-7, 4.6e-7 and 1.7e-7).
+// STAGED (weights with many zeros): sums in stages of kStage slabs.  An fp32 sum that meets a mask's zeros rounds once per kept term;
+// an instruction over 16 k rounds whether they are zeros or not, 3 K / 16 times in all.  In stages the terms are a small part of the
+// sum when they are rounded; the products with a low plane, a thousandth of the others, have accumulators of their own, and what
+// adding a stage rounds off goes into the next.  K 1600, 15 % kept, error against 64 bits relative to the product's norm: fp32
+// instruction 2.8e-7, one stage 3.8e-7, stages that lose both 1.5e-7, these 1.0e-7 (4800 x 3200 in two directions, with the split:
+// 282 -> 300 us for the last step; in one stage about 245).  Three sets of sums leave no registers for offsets worked out ahead.
 constexpr int kStage = 4;
+template <bool FIRST, class A, class B>
+__device__ __forceinline__ auto& pick(A& a, B& b)
+{
+    if constexpr (FIRST) return a;
+    else return b;
+}
+__device__ __forceinline__ void end_stage(f32x16& acc, f32x16& total)
+{
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const float t = total[v] + acc[v];
+        acc[v] -= t - total[v];                           // what that sum rounds off: the next stage starts from it
+        total[v] = t;
+    }
+}
 
 // ---- rows that have no fp16 form
 // They are summed by the fp32 instruction, and a row's result depends on that row alone: where any is marked the rows are dealt out
@@ -305,7 +322,7 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
                 }
             }
         };
-        f32x16 acc[TS][TN], total[STAGED ? TS : 1][STAGED ? TN : 1];
+        f32x16 acc[TS][TN], total[STAGED ? TS : 1][STAGED ? TN : 1], low[STAGED ? TS : 1][STAGED ? TN : 1];
 #pragma unroll
         for (int i = 0; i < TS; ++i)
 #pragma unroll
@@ -313,7 +330,7 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     acc[i][j][v] = 0.f;
-                    if (STAGED) total[STAGED ? i : 0][STAGED ? j : 0][v] = 0.f;
+                    if (STAGED) total[STAGED ? i : 0][STAGED ? j : 0][v] = low[STAGED ? i : 0][STAGED ? j : 0][v] = 0.f;
                 }
         // fragments of this lane: chunk c of its rows
         auto read_a = [&](u32x4 (&f)[TS], unsigned st, int c) {
@@ -402,17 +419,18 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
                     read_b(bl, st, 4 + 2 * ks + fk);
                     read_b(bh, st, 2 * ks + fk);
                     read_a(al, st, 4 + 2 * ks + fk);
-                    auto mma = [&](const u32x4 (&fa)[TS], const u32x4 (&fb)[TN]) {
+                    auto mma = [&](const u32x4 (&fa)[TS], const u32x4 (&fb)[TN], auto& to) {
 #pragma unroll
                         for (int i = 0; i < TS; ++i)
 #pragma unroll
                             for (int j = 0; j < TN; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]), __builtin_bit_cast(f16x8, fb[j]), acc[i][j], 0, 0, 0);
+                                to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]), __builtin_bit_cast(f16x8, fb[j]), to[i][j], 0, 0, 0);
                     };
+                    auto& lows = pick<STAGED>(low, acc);
                     asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(TS + TN) : "memory");
                     arrived(ah);
                     arrived(bl);
-                    mma(ah, bl);
+                    mma(ah, bl, lows);
                     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
                     arrived(bh);
                     arrived(al);
@@ -420,20 +438,24 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
                         wait_slab(kt + 1);
                         if (kt + NST < KB) issue_slab(kt + NST);
                     }
-                    mma(ah, bh);
-                    mma(al, bh);
+                    mma(ah, bh, acc);
+                    mma(al, bh, lows);
                 }
                 if (STAGED && (kt % kStage == kStage - 1 || kt == KB - 1)) {
 #pragma unroll
                     for (int i = 0; i < TS; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j)
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) {
-                                total[STAGED ? i : 0][STAGED ? j : 0][v] += acc[i][j][v];
-                                acc[i][j][v] = kt == KB - 1 ? total[STAGED ? i : 0][STAGED ? j : 0][v] : 0.f;
-                            }
+                        for (int j = 0; j < TN; ++j) end_stage(acc[i][j], total[STAGED ? i : 0][STAGED ? j : 0]);
                 }
+            }
+            if (STAGED) {
+#pragma unroll
+                for (int i = 0; i < TS; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            acc[i][j][v] = total[STAGED ? i : 0][STAGED ? j : 0][v] + (acc[i][j][v] + low[STAGED ? i : 0][STAGED ? j : 0][v]);
             }
         }
         // accumulator register v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
@@ -514,7 +536,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
         const int m0 = tile_m * BM, n0 = (tn_all - dir * a.gn) * BN;
         if (pid != (int)blockIdx.x) __builtin_amdgcn_s_barrier();
 
-        f32x16 acc[TM][TN], total[STAGED ? TM : 1][STAGED ? TN : 1];
+        f32x16 acc[TM][TN], total[STAGED ? TM : 1][STAGED ? TN : 1], low[STAGED ? TM : 1][STAGED ? TN : 1];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -522,27 +544,30 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     acc[i][j][v] = 0.f;
-                    if (STAGED) total[STAGED ? i : 0][STAGED ? j : 0][v] = 0.f;
+                    if (STAGED) total[STAGED ? i : 0][STAGED ? j : 0][v] = low[STAGED ? i : 0][STAGED ? j : 0][v] = 0.f;
                 }
 
         // direct loads: instruction q of a slab covers LDS rows 8 q .. 8 q + 7 of the combined [X rows | W rows]
-        // (eight rows of one operand: scalar base pointer, one 32-bit element offset per instruction and lane)
+        // (eight rows of one operand: scalar base pointer, one 32-bit byte offset per instruction and lane)
         const uint16_t* const xbase = a.Xs + (size_t)m0 * rowh;
         const uint16_t* const wbase = a.d[dir].W + (size_t)n0 * rowh;
+        const ptrdiff_t w_off = (const char*)wbase - (const char*)xbase;
         unsigned soff[LI];
+        int sl = threadIdx.x & 63;
+        asm volatile("" : "+v"(sl));                      // (worked out here, not ahead of the loop in registers of its own)
 #pragma unroll
         for (int i = 0; i < LI; ++i) {
             const int row0 = (wave_s * LI + i) * 8;
-            const int row = row0 + (lane >> 3);
-            const int kc = (lane & 7) ^ ((row >> 1) & 7);
+            const int row = row0 + (sl >> 3);
+            const int kc = (sl & 7) ^ ((row >> 1) & 7);
             const int r = row0 < BM ? min(row, M - 1 - m0) : min(row - BM, N - 1 - n0);   // rows past the matrix re-read its last
-            soff[i] = (unsigned)(r * rowh + 8 * kc);
+            soff[i] = (unsigned)(r * rowh + 8 * kc) * 2u;
         }
         auto issue_slab = [&](int kt) {
             unsigned char* st = smem + (size_t)(kt % NST) * STAGE + (size_t)wave_s * LI * 1024;
 #pragma unroll
             for (int i = 0; i < LI; ++i) {
-                const uint16_t* from = ((wave_s * LI + i) * 8 < BM ? xbase : wbase) + (size_t)kt * 64;
+                const char* const from = (const char*)xbase + (wave_s * LI + i < BM / 8 ? 0 : w_off) + (size_t)kt * 128;
                 __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(from + soff[i]),
                                                  (void __attribute__((address_space(3)))*)(st + (size_t)i * 1024), 16, 0, 0);
             }
@@ -556,14 +581,15 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
 #pragma unroll
             for (int j = 0; j < TN; ++j) f[j] = lds_read_b128(st + (offb[j] ^ (unsigned)((ks << 5) | (pl << 6))));
         };
-        auto mma = [&](u32x4 (&fa)[TM], u32x4 (&fb)[TN]) {
+        auto mma = [&](u32x4 (&fa)[TM], u32x4 (&fb)[TN], auto& to) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]),
-                                                                       __builtin_bit_cast(f16x8, fb[j]), acc[i][j], 0, 0, 0);
+                    to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]),
+                                                                      __builtin_bit_cast(f16x8, fb[j]), to[i][j], 0, 0, 0);
         };
+        auto& lows = pick<STAGED>(low, acc);
         auto arrived_a = [&](u32x4 (&f)[TM]) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(f[i]) : : "memory");
@@ -590,6 +616,12 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
         read_a(ah, lds0, 0, 0);
         read_b(bl, lds0, 0, 1);
         for (int kt = 0; kt < KB; ++kt) {
+            if (STAGED) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(offa[i]));
+#pragma unroll
+                for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(offb[j]));
+            }
             const unsigned st = lds0 + (unsigned)((kt % NST) * STAGE);
             const unsigned stn = lds0 + (unsigned)(((kt + 1) % NST) * STAGE);
 #pragma unroll
@@ -601,11 +633,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
                 asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(TM + TN) : "memory");
                 arrived_a(ah);
                 arrived_b(bl);
-                mma(ah, bl);
+                mma(ah, bl, lows);
                 __builtin_amdgcn_sched_barrier(0);
                 asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(TM) : "memory");
                 arrived_b(bh);
-                mma(ah, bh);
+                mma(ah, bh, acc);
                 __builtin_amdgcn_sched_barrier(0);
                 asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
                 arrived_a(al);
@@ -621,20 +653,28 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
                     read_b(bl, stn, 0, 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                mma(al, bh);
+                mma(al, bh, lows);
+                if (STAGED && ks == 1 && (kt % kStage == kStage - 1 || kt == KB - 1)) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) end_stage(acc[i][j], total[STAGED ? i : 0][STAGED ? j : 0]);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (STAGED && (kt % kStage == kStage - 1 || kt == KB - 1)) {
+        }
+        if (STAGED) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                for (int j = 0; j < TN; ++j)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            total[STAGED ? i : 0][STAGED ? j : 0][v] += acc[i][j][v];
-                            acc[i][j][v] = kt == KB - 1 ? total[STAGED ? i : 0][STAGED ? j : 0][v] : 0.f;
-                        }
-            }
+                    for (int v = 0; v < 16; ++v)
+                        acc[i][j][v] = total[STAGED ? i : 0][STAGED ? j : 0][v] + (acc[i][j][v] + low[STAGED ? i : 0][STAGED ? j : 0][v]);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(acc[i][j]));
         }
         // ---- P = acc * 2^-(ex + ew) + bias; accumulator register v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
         int l = threadIdx.x & 63;
