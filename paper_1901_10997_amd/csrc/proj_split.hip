@@ -740,7 +740,7 @@ static hipError_t launch_tiles(ProjSplitArgs a, int per_cu, hipStream_t s)
     a.gn = (a.N + BN - 1) / BN;
     a.npid = ((a.gm * a.gn * a.ndir + kXcds - 1) / kXcds) * kXcds;
     const int lds = NST * (BM + BN) * 128 + kTableBytes;
-    const hipError_t e = hipFuncSetAttribute((const void*)proj_split_kernel<TM, TN, WM, WN, NST, STAGED>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = allow_dynamic_lds((const void*)proj_split_kernel<TM, TN, WM, WN, NST, STAGED>, lds);
     if (e != hipSuccess) return e;
     const int slots = std::max(kXcds, device_num_cus() * per_cu / kXcds * kXcds);
     hipLaunchKernelGGL((proj_split_kernel<TM, TN, WM, WN, NST, STAGED>), dim3(std::min(a.npid, slots)), dim3(64 * WM * WN), lds, s, a);
