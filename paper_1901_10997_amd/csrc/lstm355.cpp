@@ -424,21 +424,28 @@ static void drop_unfit(const std::vector<float>& unscale, uint16_t*& planes, flo
         }
 }
 
-// Two fp16 planes of an fp32 input-side matrix for proj_split.hip, made from the padded rows already on the device.
+// Could a product of M rows with N rows of W run on fp16 planes, whatever the values are?
+static bool split_can_run(int M, int N, int K, int ndir)
+{
+    return proj_split_supported(M, N, K, ndir, false) || proj_split_supported(M, N, K, ndir, true);
+}
+
+// Two fp16 planes of an fp32 input-side matrix for proj_split.hip, made from the padded rows already on the device, where some number
+// of rows of X would have them run.
 static int add_split(lstm_t* m, PackedMat& p)
 {
-    if (p.pad_ld < kSplitMinK) return LSTM_OK;
-    std::vector<float> unscale((size_t)p.rows);
-    std::vector<int> terms((size_t)p.rows);
-    int* dterms = nullptr;
+    bool can = false;
+    for (int M = 128; M <= (1 << 16) && !can; M *= 2) can = split_can_run(M, p.rows, p.pad_ld, m->Dn);
+    if (!can) return LSTM_OK;
+    std::vector<float> unscale((size_t)p.rows * 2);       // ... and behind the scales the rows' numbers of terms
     HIP_TRY(m, hipMalloc((void**)&p.split, (size_t)p.rows * split_row_halves(p.pad_ld) * sizeof(uint16_t)));
     HIP_TRY(m, hipMalloc((void**)&p.split_unscale, unscale.size() * sizeof(float)));
-    HIP_TRY(m, hipMalloc((void**)&dterms, terms.size() * sizeof(int)));
-    hipError_t e = launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr, dterms, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(terms.data(), dterms, terms.size() * sizeof(int), hipMemcpyDeviceToHost);
-    (void)hipFree(dterms);
-    HIP_TRY(m, e);
+    HIP_TRY(m, launch_split_rows((const float*)p.dense_pad, p.pad_ld, p.rows, p.pad_ld, p.split, p.split_unscale, nullptr,
+                                 (int*)(p.split_unscale + p.rows), nullptr));
+    HIP_TRY(m, hipMemcpy(unscale.data(), p.split_unscale, unscale.size() * sizeof(float), hipMemcpyDeviceToHost));
+    std::vector<int> terms((size_t)p.rows);
+    std::memcpy(terms.data(), unscale.data() + p.rows, terms.size() * sizeof(int));
+    unscale.resize((size_t)p.rows);
     if (!split_terms_suffice(terms.data(), p.rows, p.cols, &p.many_zeros)) unscale[0] = INFINITY;   // as if a row did not fit
     drop_unfit(unscale, p.split, p.split_unscale);
     return LSTM_OK;
@@ -1042,17 +1049,18 @@ static Workspace carve(const lstm_t* m, int T, int B)
             if (m->in_dim(l) % 4 != 0) xp_bytes = std::max(xp_bytes, M * (size_t)pad4(m->in_dim(l)) * sizeof(float));
     }
     off += align256(xp_bytes);
-    // fp32 models: a layer's input rows as two fp16 planes, and their scales
+    // fp32 models: a layer's input rows as two fp16 planes, their scales and what the split says of them, where a layer's product may
+    // run on them
+    size_t halves = 0;
+    for (int l = 0; l < m->L && m->dtype == LSTM_F32; ++l)
+        if (split_can_run((int)std::min<size_t>(M, 1u << 30), 4 * (m->G > 0 ? m->ghid(l) : m->hid(l)), pad4(m->in_dim(l)), m->Dn))
+            halves = std::max(halves, split_row_halves(pad4(m->in_dim(l))));
     w.sx_off = off;
-    if (m->dtype == LSTM_F32) {
-        size_t halves = 0;
-        for (int l = 0; l < m->L; ++l) halves = std::max(halves, split_row_halves(pad4(m->in_dim(l))));
-        off += align256(M * halves * sizeof(uint16_t));
-    }
+    off += align256(M * halves * sizeof(uint16_t));
     w.su_off = off;
-    if (m->dtype == LSTM_F32) off += align256(M * sizeof(float));
+    if (halves > 0) off += align256(M * sizeof(float));
     w.sm_off = off;
-    if (m->dtype == LSTM_F32) off += align256(sizeof(SplitMarks));
+    if (halves > 0) off += align256(sizeof(SplitMarks));
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a

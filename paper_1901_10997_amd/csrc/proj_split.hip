@@ -724,7 +724,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void proj_split_kernel(ProjSplitAr
                 }
             }
         }
-    }    // A row is marked somewhere: no tile is done yet.
+    }
+    // A row is marked somewhere: no tile is done yet.
     if (look) {
         wait_vmcnt<0>();
         __syncthreads();

@@ -266,3 +266,13 @@ def test_masked_layers_of_few_entries_keep_their_sums():
         case = inputs.make_case(inputs.Workload(89, "few_terms", 1, True, 512, 160, 30, 20, "f32", 0.05, keep, "uniform", 160), k=4, random_state=True)
         desc, _ = check_case(case)
         assert want in desc, desc
+
+
+def test_workspace_holds_planes_of_the_input_only_where_they_can_run():
+    """At most 64 input rows are multiplied without them: the workspace has no room for them then."""
+    D, H = 2000, 512
+    m = B.Lstm(1, D, H, False, B.LSTM_F32)
+    per_row = 4 * (4 * H + D)                                # pre-activations and the transposed input
+    few, many = B.lstm_workspace_bytes(m.handle, 64, 1), B.lstm_workspace_bytes(m.handle, 4096, 1)
+    assert few < 64 * (per_row + 4 * D // 2) and many > 4096 * (per_row + 4 * D)
+    m.close()
