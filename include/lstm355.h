@@ -227,7 +227,9 @@ int lstm_get_profile(lstm_t* m, double* proj_us, int* proj_launches, double* rec
  * per workgroup, and "batch/N" says that the layer's batch columns were run as N launches over runs of columns (a layer
  * whose time-loop kernel would need more workgroups than the device has compute units is cut that way, and/or into one
  * launch per direction, before the library falls back to one launch per timestep).  "split" marks the fp32 kernels that
- * multiply two fp16 planes of each operand (proj=dense-split; rec=persist-dense-f32(...,split)). */
+ * multiply two fp16 planes of each operand, 22 to 24 of its bits (proj=dense-split, where the rows have terms enough that a
+ * product is no further from the exact one than the fp32 instruction's; rec=persist-dense-f32(...,split)).  A row of x without
+ * that form - non-finite, of too wide a range, of few terms - is summed in fp32 and moves no other row's result. */
 int lstm_describe_plan(const lstm_t* m, char* buf, size_t buf_bytes);
 
 /*

@@ -1049,8 +1049,7 @@ static Workspace carve(const lstm_t* m, int T, int B)
             if (m->in_dim(l) % 4 != 0) xp_bytes = std::max(xp_bytes, M * (size_t)pad4(m->in_dim(l)) * sizeof(float));
     }
     off += align256(xp_bytes);
-    // fp32 models: a layer's input rows as two fp16 planes, their scales and what the split says of them, where a layer's product may
-    // run on them
+    // fp32 models: a layer's input rows as two fp16 planes, and their scales, where a layer's product may run on them
     size_t halves = 0;
     for (int l = 0; l < m->L && m->dtype == LSTM_F32; ++l)
         if (split_can_run((int)std::min<size_t>(M, 1u << 30), 4 * (m->G > 0 ? m->ghid(l) : m->hid(l)), pad4(m->in_dim(l)), m->Dn))
@@ -1059,8 +1058,6 @@ static Workspace carve(const lstm_t* m, int T, int B)
     off += align256(M * halves * sizeof(uint16_t));
     w.su_off = off;
     if (halves > 0) off += align256(M * sizeof(float));
-    w.sm_off = off;
-    if (halves > 0) off += align256(sizeof(SplitMarks));
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
@@ -1111,9 +1108,6 @@ static Workspace carve(const lstm_t* m, int T, int B)
         w.qx_words += words;
     }
     off += align256(w.qx_words * sizeof(unsigned));
-    // ... and which columns of the initial state they take another way (PersistQuadDir::beyond)
-    w.hb_off = off;
-    if (m->dtype == LSTM_F32 && m->G == 0) off += align256((size_t)m->L * m->Dn * B * sizeof(unsigned));
     // ... and of the bf16 one
     w.rx_off = off;
     if (m->dtype == LSTM_BF16)
@@ -1122,6 +1116,12 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // copy of h0 where the call returns hT in its place (lstm_forward)
     w.h0_off = off;
     off += align256(state_floats(m, B) * sizeof(float));
+    // which columns of the initial state the dense fp32 recurrence takes another way (PersistQuadArgs::beyond); whether a row of a
+    // layer's input has no plane form
+    w.hb_off = off;
+    if (m->dtype == LSTM_F32 && m->G == 0) off += align256((size_t)m->L * m->Dn * B * sizeof(unsigned));
+    w.sm_off = off;
+    if (halves > 0) off += align256(sizeof(SplitMarks));
     w.total = off;
     return w;
 }
@@ -1276,8 +1276,9 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
 // directions in one launch), and it holds rows of any length: 64 to 256 units at 5 to 24 % kept 1.15 to 2 times faster than the
 // row-compressed kernels (H-LSTM 1.1 to 1.6 times up to 256), and 2 to 6 times where rows are too long for those and each step
 // would be a launch.  With the product on fp16 planes LSTM layers of 450 and more units follow at small batches (5 bidirectional
-// layers of 800, 15 % kept, batch 16: 4219 us over the kept entries, 4019 dense); with the fp32 instruction they were slower.  Only where LSTM_FMT_AUTO left the choice open (the copy exists) and by 5 % of the
-// modelled time, as neither model is better than that.
+// layers of 800, 15 % kept, batch 16: 4219 us over the kept entries, 4079 dense); with the fp32 instruction they were slower.
+// Only where LSTM_FMT_AUTO left the choice open (the copy exists) and by 5 % of the modelled time, as neither model is better
+// than that.
 static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
@@ -1356,16 +1357,18 @@ static bool fuses_input(const lstm_t* m, int l, int T, int B)
     return mode[0] == 1 || mode[0] == 2 || mode[1] == 1 || mode[1] == 2;
 }
 
-// Does the projection of M rows through this matrix run on the fp16 matrix instruction?
+// Does the projection of M rows through this matrix run on the fp16 matrix instruction?  (At 65 to 255 rows of a row-compressed
+// matrix also in place of the kernels over the kept entries: 0.1 to 0.83 of their time over 88 shapes, 200 to 1500 inputs, 5 to 40 %
+// kept.)
 static bool proj_runs_split(const PackedMat& wx, int M, int ndir)
 {
     return wx.split != nullptr && proj_split_supported(M, wx.rows, wx.pad_ld, ndir, wx.many_zeros);
 }
 
 // Modelled time of the projection over the kept entries (7 shapes, 2 to 17 % kept: within 20 %): products by slot, the passes over
-// the rows of X per group of 32 units, and a constant per group and tile.  Against the fp16 matrix instruction: 4800 rows of 1600
-// for 800 units in two directions 263 / 440 / 752 us at 2 / 10 / 17 % kept against 250; 700 rows of 1500 for 1500 units 45 / 72 / 98
-// against 71; 80 rows of 800 for 800 units 8 / 11 / 13 against 18.
+// the rows of X per group of 32 units, and a constant per group and tile.  Against the fp16 matrix instruction (in stages, with the
+// split): 4800 rows of 1600 for 800 units in two directions 263 / 440 / 752 us at 2 / 10 / 17 % kept against 300; 700 rows of 1500
+// for 1500 units 45 / 72 / 98 against about 75; 80 rows of 800 for 800 units 8 / 11 / 13 against 18.
 static double proj_q16_us(int M, int H, int D, int slots, int ndir)
 {
     const double groups = (H + 31) / 32 * (double)ndir;
@@ -1483,7 +1486,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
             q.W2f = w.w2.dense_frag16;
             q.Ws = w.wh.rec_split;
             q.w_unscale = w.wh.rec_unscale;
-            q.beyond = (const unsigned*)(base + ws.hb_off) + ((size_t)l * Dn + d) * B + b_lo;
+            a.beyond[d - d_lo] = (const unsigned*)(base + ws.hb_off) + ((size_t)l * Dn + d) * B + b_lo;
             q.bias2 = w.bias2;
             q.h0 = h0 ? h0 + so : nullptr;
             q.c0 = c0 ? c0 + so : nullptr;

@@ -6,11 +6,12 @@
 // group fits one.
 //
 // Product.  W_h and h are kept as two fp16 planes each (proj_split.hip): a row of W_h scaled by a power of two, hi + lo; h as
-// hi = fp16(h) and lo = fp16((h - hi) 2^12), exact to 2^-36 of 1 (|h| <= 1).  The 16x16x32 instruction takes 16 rows of one plane
-// of W_h against 16 columns: the four columns of a quad in both planes fill eight of them, two quads (QP = 2) all sixteen, so two
-// instructions give all four products of the planes for 32 k, and a column's sum is its hi part plus 2^-12 of its lo part.
-// fp32 takes four 4x4x1 instructions of 8.8 clocks per 16 k, this 16 per 16: less than half, at QP = 2 a quarter, and the
-// instruction sums the 32 k itself, where the other needs a sum over four lane groups.
+// hi = fp16(h) and lo = fp16((h - hi) 2^12), off by 2^-24 at most (|h| from a half on, one value in four; by less than 2^-36 near
+// zero).  The 16x16x32 instruction takes 16 rows of one plane of W_h against 16 columns: the four columns of a quad in both planes
+// fill eight of them, two quads (QP = 2) all sixteen, so two instructions give all four products of the planes for 32 k, and a
+// column's sum is its hi part plus 2^-12 of its lo part.  fp32 takes four 4x4x1 instructions of 8.8 clocks per 16 k, this 16 per
+// 16: less than half, at QP = 2 a quarter, and the instruction sums the 32 k itself, where the other needs a sum over four lane
+// groups.
 //
 // K is dealt out in blocks of 32, KB or KB - 1 to a wave; the last waves, which have the fewest sums to finish, take the longer
 // share.  Where KB blocks of weights do not fit the registers the last one is in LDS (XL; 800 units: 25 blocks, one wave with
@@ -169,11 +170,12 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                                     a.timeout_flag, a.spin_limit) && !a.device_scope_only;
 
     // columns of h0 that are not within 1 (launch_fill_and_check): any in this group?
+    const unsigned* const beyond_of = a.beyond[dir];
     bool beyond = false;
     if (h0)
-        for (int c = lane; c < 4 * nq; c += 64) beyond |= 4 * q_lo + c < a.B && D.beyond[4 * q_lo + c] != 0u;
+        for (int c = lane; c < 4 * nq; c += 64) beyond |= 4 * q_lo + c < a.B && beyond_of[4 * q_lo + c] != 0u;
     beyond = __builtin_amdgcn_ballot_w64(beyond) != 0ull;
-    auto col_beyond = [&](int pass, int j) { return beyond && D.beyond[col[j] + 4 * QP * pass] != 0u; };
+    auto col_beyond = [&](int pass, int j) { return beyond && beyond_of[col[j] + 4 * QP * pass] != 0u; };
     const ptrdiff_t p_step = (ptrdiff_t)a.Bld * 4 * H * (reverse ? -1 : 1), y_step = (ptrdiff_t)a.Bld * (ptrdiff_t)y_ld * (reverse ? -1 : 1);
     // the timesteps of P and y in the order of the steps
     float* p_t = D.P + (reverse ? (size_t)(a.T - 1) * a.Bld * 4 * H : 0);
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
         const int KB16 = (H + 15) >> 4;
         const int b16 = 2 * kb0, e16 = min(2 * (kb0 + (all_kb ? KB : KB - 1)), KB16);
         const int c = pass * QP * 4 + lr, b = 4 * q_lo + c;
-        const bool to_sum = lr < 4 * QP && c < 4 * nq && b < a.B && D.beyond[b] != 0u;
+        const bool to_sum = lr < 4 * QP && c < 4 * nq && b < a.B && beyond_of[b] != 0u;
         if (!__builtin_amdgcn_ballot_w64(to_sum)) continue;              // the same answer in every wave
         const float* const hb = h0 + (size_t)(to_sum ? b : 0) * H;
 #pragma unroll 1

@@ -9,7 +9,7 @@
 // memory before the current tile's products and parked in the other half of the LDS buffer after them.
 // Bound: LDS gather bandwidth (16 bytes per lane and four multiply-adds); at 10-15 % kept weights that is faster
 // than the dense product on the fp32 matrix instruction, which multiplies the zeros as well (4800 x 3200 x 1600, two
-// directions: 449 / 582 / 840 us at 10 / 15 / 20 % kept against 901; the product on fp16 planes takes 311 at any density).
+// directions: 449 / 582 / 840 us at 10 / 15 / 20 % kept against 901; the product on fp16 planes takes 300 with its split at any density).
 #include <type_traits>
 #include "common.h"
 #include "device_math.h"

@@ -1,19 +1,20 @@
 // fp32 input projection on the fp16 matrix instruction:  P[m][n] = bias[n] + sum_k X[m][k] * W[n][k]
 //
 // Every fp32 value of a row is scaled by a power of two that brings the row's largest magnitude into [2^14, 2^15) and kept
-// as two fp16 numbers, hi = fp16(v) and lo = fp16(v - hi): 22 to 24 significant bits.  A product is then
-// hi.hi + hi.lo + lo.hi (lo.lo is 2^-22 of it at most), three instructions whose products are exact and whose sums are fp32,
-// 16 k per 32 clocks each where the fp32 instruction takes 2 k in 64: a tenth of the matrix time.  An element of P is also the
-// sum of 3 K / 16 rounded terms instead of K / 2, which more than makes up for the bits the planes drop: error against 64 bits,
-// fp32 instruction / here, relative to the product's norm: K 64 1.35e-7 / 1.17e-7, 200 2.5e-7 / 1.8e-7, 640 4.4e-7 / 2.9e-7,
-// 1600 7.2e-7 / 4.6e-7 (normal X, uniform W; K 32 9.26e-8 / 9.34e-8, which is why K starts at 64).
+// as two fp16 numbers, hi = fp16(v) and lo = fp16(v - hi): 22 to 24 significant bits (one value in four is off by half a last
+// place).  A product is then hi.hi + hi.lo + lo.hi (lo.lo is 2^-22 of it at most), three instructions whose products are exact
+// and whose sums are fp32, 16 k per 32 clocks each where the fp32 instruction takes 2 k in 64: a tenth of the matrix time.  An
+// instruction also rounds less often per k, which from some terms on (kSplitMinTerms below) more than makes up for the bits the
+// planes drop: error against 64 bits, fp32 instruction / here, relative to the product's norm, dense W: K 64 1.35e-7 / 1.17e-7,
+// 200 2.5e-7 / 1.8e-7, 640 4.4e-7 / 2.9e-7, 1600 7.2e-7 / 4.5e-7 (normal X, uniform W; K 32 9.26e-8 / 9.34e-8).
 //
 // Layout: the planes of 32 k lie side by side, 64 bytes hi and 64 bytes lo, so that a slab of 32 k of a row is one 128-byte
 // line; slabs go straight into an LDS ring (16-byte chunk c of row r at position c ^ ((r >> 1) & 7): conflict-free reads), and
 // a fragment read serves two or one of the three products: two slab bytes per product fewer than a bf16 product needs.
 // Bound: the device's power limit under random operands (the issue loop of this instruction reaches 1.7 PFLOP/s there) and
-// what a tile's ends leave idle.  4800 x 3200 x 1600 in two directions: fp32 instruction 901 us (109 TFLOP/s), here 311
-// (316, 950 counted as fp16 products); x 640: 389 -> 129; 700 x 6000 x 1500: 163 -> 59.
+// what a tile's ends leave idle.  4800 x 3200 x 1600 in two directions, with the split: fp32 instruction 835 to 901 us (109 to
+// 118 TFLOP/s), here 279 to 311 (350 to 316; three times that counted as fp16 products); x 640: 348 to 389 -> 127 to 129; 700 x 6000
+// x 1500: 163 -> 59.
 #include <cmath>
 #include "common.h"
 #include "device_math.h"
@@ -111,7 +112,8 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 
 size_t split_row_halves(int K) { return (size_t)((K + 31) / 32) * 64; }
 
-hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, int* terms, hipStream_t s)
+hipError_t launch_split_rows(const float* X, int ldx, int M, int K, uint16_t* out, float* unscale, SplitMarks* marks, int* terms,
+                             hipStream_t s)
 {
     const int KB = (K + 31) / 32;
     const dim3 grid((M + kSplitRowsPerBlock - 1) / kSplitRowsPerBlock), block(256);
@@ -315,7 +317,8 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
                 const unsigned char* const from = src[i] + (size_t)min(8 * kt + kc[i], last) * 16;
                 if (by_hand) {
                     const float* const f = (const float*)from;
-                    *(InLds<u32x4>)(st + (unsigned)(i * 1024 + lane * 16)) = (u32x4){__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+                    *(InLds<u32x4>)(st + (unsigned)(i * 1024 + lane * 16)) =
+                        (u32x4){__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
                 } else {
                     __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)from,
                                                      (void __attribute__((address_space(3)))*)(st + (unsigned)(i * 1024)), 16, 0, 0);
@@ -404,7 +407,8 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
                             for (int e = 0; e < 4; ++e)
 #pragma unroll
                                 for (int j = 0; j < TN; ++j)
-                                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[u & 1][i][e]), __uint_as_float(fb[u & 1][j][e]), acc[i][j], 0, 0, 0);
+                                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[u & 1][i][e]),
+                                                                                     __uint_as_float(fb[u & 1][j][e]), acc[i][j], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -424,7 +428,8 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
                         for (int i = 0; i < TS; ++i)
 #pragma unroll
                             for (int j = 0; j < TN; ++j)
-                                to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]), __builtin_bit_cast(f16x8, fb[j]), to[i][j], 0, 0, 0);
+                                to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[i]),
+                                                                                  __builtin_bit_cast(f16x8, fb[j]), to[i][j], 0, 0, 0);
                     };
                     auto& lows = pick<STAGED>(low, acc);
                     asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(TS + TN) : "memory");
@@ -482,7 +487,8 @@ __device__ __forceinline__ void sorted_tiles(ArgsInMemory a, unsigned lds0, unsi
             const float* const x = a->X + (size_t)(m & ~kRowNonFinite) * a->ldx;
             for (int n = n0 + wn * TN * 32 + lane; n < min(n0 + (wn + 1) * TN * 32, N); n += 64) {
                 float sum = 0.f;
-                for (int e = a->d[dir].row_ptr[n]; e < a->d[dir].row_ptr[n + 1]; ++e) sum = fmaf(a->d[dir].val[e], x[a->d[dir].col[e]], sum);
+                for (int e = a->d[dir].row_ptr[n]; e < a->d[dir].row_ptr[n + 1]; ++e)
+                    sum = fmaf(a->d[dir].val[e], x[a->d[dir].col[e]], sum);
                 P[(size_t)(m & ~kRowNonFinite) * N + n] = sum + bias[n];
             }
         }
@@ -782,7 +788,7 @@ double proj_split_us(int M, int N, int K, int ndir, bool masked)
 {
     double us;
     (void)choose_shape(M, N, K, ndir, masked, &us);
-    return us + 3 * kLaunchUs + 8.0 * M * K / 5.4e6;   // the pass over X, its launch and the gaps
+    return us + 3 * kLaunchUs + 8.0 * M * K / 5.4e6;   // the pass over X, its launch and the gaps (stages: 4 to 8 % over the fits)
 }
 
 // More than 64 input rows, K from 64 on (with fewer terms the fp32 instruction's sum is as close to the exact one) and
