@@ -15,8 +15,9 @@ def _product(X, W):
 
 
 def _bound(K):
-    """Relative to the result's norm: two operands kept to 2^-23 of each value at worst, the dropped product of the two low
-    parts 2^-22, and 3 K / 16 rounded sums of 2^-24 each that add up like a random walk."""
+    """Relative to the result's norm: two operands kept to 2^-23 of each value at worst and the dropped product of the two low
+    parts, 2^-22, taken as if all added up; and 3 K / 16 instructions whose sums are rounded, by 2^-24 of a sum that has grown to
+    its full size (it grows to it, so that an instruction may round twice), like a random walk."""
     return 2.0 ** -23 * 4 + 2.0 ** -24 * np.sqrt(3 * K / 16)
 
 
@@ -36,8 +37,8 @@ def test_product_over_the_tile_shapes(n, batch):
 
 @pytest.mark.parametrize("n,batch", [(1032, 130), (6404, 300), (2400, 1500), (4100, 1900)])
 def test_masked_product_in_two_stages(n, batch):
-    """Weights with many zeros: sums in two stages.  What K rounded sums would add is gone: per stage of 128 k 24 rounded sums
-    of a share of the result, then one per stage."""
+    """Weights with many zeros: sums in stages.  What K rounded sums would add is gone: per stage of 128 k 24 rounded sums of a
+    share of the result, then at most one per stage."""
     rng = np.random.default_rng(n)
     X = rng.standard_normal((batch, n)).astype(np.float32)
     W = (rng.uniform(-0.1, 0.1, (n, n)) * (rng.random((n, n)) < 0.15)).astype(np.float32)
