@@ -371,6 +371,7 @@ struct PersistQuadDir {
     const float* W2f;          // H-LSTM: W2 in fragment order by gate
     const uint16_t* Ws;        // persist_split.hip: W_h as two fp16 planes (launch_to_frag_split) and its rows' scales
     const float* w_unscale;
+    const unsigned* beyond;    // ... and, with h0: [B], not zero where a column of it is not within 1 (launch_fill_and_check)
     const float* bias2;        // H-LSTM: [4H] packed
     const float* h0;           // [B][H] or nullptr
     const float* c0;
@@ -391,7 +392,6 @@ struct PersistQuadArgs {
     int quads, mq, groups, gn, xcd_local;
     unsigned *hx, *ux;
     unsigned long long* xcc_ids;
-    const unsigned* beyond[2]; // persist_split.hip, with h0: [B] per direction, not zero where a column of it is not within 1 (launch_fill_and_check)
 };
 struct PersistQuadPlan {   // how a launch of (B, H, G, ndir) is laid out
     int shape = -1;        // entry of the kernel's table; < 0: none fits

@@ -1116,7 +1116,7 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // copy of h0 where the call returns hT in its place (lstm_forward)
     w.h0_off = off;
     off += align256(state_floats(m, B) * sizeof(float));
-    // which columns of the initial state the dense fp32 recurrence takes another way (PersistQuadArgs::beyond); whether a row of a
+    // which columns of the initial state the dense fp32 recurrence takes another way (PersistQuadDir::beyond); whether a row of a
     // layer's input has no plane form
     w.hb_off = off;
     if (m->dtype == LSTM_F32 && m->G == 0) off += align256((size_t)m->L * m->Dn * B * sizeof(unsigned));
@@ -1486,7 +1486,7 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
             q.W2f = w.w2.dense_frag16;
             q.Ws = w.wh.rec_split;
             q.w_unscale = w.wh.rec_unscale;
-            a.beyond[d - d_lo] = (const unsigned*)(base + ws.hb_off) + ((size_t)l * Dn + d) * B + b_lo;
+            q.beyond = (const unsigned*)(base + ws.hb_off) + ((size_t)l * Dn + d) * B + b_lo;
             q.bias2 = w.bias2;
             q.h0 = h0 ? h0 + so : nullptr;
             q.c0 = c0 ? c0 + so : nullptr;

@@ -170,12 +170,11 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                                     a.timeout_flag, a.spin_limit) && !a.device_scope_only;
 
     // columns of h0 that are not within 1 (launch_fill_and_check): any in this group?
-    const unsigned* const beyond_of = a.beyond[dir];
     bool beyond = false;
     if (h0)
-        for (int c = lane; c < 4 * nq; c += 64) beyond |= 4 * q_lo + c < a.B && beyond_of[4 * q_lo + c] != 0u;
+        for (int c = lane; c < 4 * nq; c += 64) beyond |= 4 * q_lo + c < a.B && D.beyond[4 * q_lo + c] != 0u;
     beyond = __builtin_amdgcn_ballot_w64(beyond) != 0ull;
-    auto col_beyond = [&](int pass, int j) { return beyond && beyond_of[col[j] + 4 * QP * pass] != 0u; };
+    auto col_beyond = [&](int pass, int j) { return beyond && D.beyond[col[j] + 4 * QP * pass] != 0u; };
     const ptrdiff_t p_step = (ptrdiff_t)a.Bld * 4 * H * (reverse ? -1 : 1), y_step = (ptrdiff_t)a.Bld * (ptrdiff_t)y_ld * (reverse ? -1 : 1);
     // the timesteps of P and y in the order of the steps
     float* p_t = D.P + (reverse ? (size_t)(a.T - 1) * a.Bld * 4 * H : 0);
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
         const int KB16 = (H + 15) >> 4;
         const int b16 = 2 * kb0, e16 = min(2 * (kb0 + (all_kb ? KB : KB - 1)), KB16);
         const int c = pass * QP * 4 + lr, b = 4 * q_lo + c;
-        const bool to_sum = lr < 4 * QP && c < 4 * nq && b < a.B && beyond_of[b] != 0u;
+        const bool to_sum = lr < 4 * QP && c < 4 * nq && b < a.B && D.beyond[b] != 0u;
         if (!__builtin_amdgcn_ballot_w64(to_sum)) continue;              // the same answer in every wave
         const float* const hb = h0 + (size_t)(to_sum ? b : 0) * H;
 #pragma unroll 1
