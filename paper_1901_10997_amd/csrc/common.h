@@ -325,10 +325,12 @@ size_t persist_dense_f32_exchange_words(int mt, int B, int H, int ndir);
 // h0[d]: fp32 [B][H] of direction d or nullptr
 hipError_t launch_persist_dense_f32(PersistDenseArgs& a, int mt, const float* const* h0, unsigned* words, bool cooperative, hipStream_t s);
 // bf16 dense recurrence at any batch from 2 (all directions of a layer per launch)
+constexpr int kMaxRowsStack = 6;   // layers of a launch
 struct PersistRowsDir {
-    const float* P;            // [T*B][4H]
+    const float* P;            // [T*B][4H]; layers above the first of a stack: their bias, [4H]
     const uint16_t* Wf;        // W_h in operand order (launch_to_frag32)
-    const float* h0;           // [B][H] or nullptr
+    const uint16_t* Wxf;       // those layers: W_x in the same order
+    const unsigned long long* h0x;   // h0 in operand order (launch_rows_prepare) or nullptr
     const float* c0;
     float* y;                  // h_t fp32 -> y[(t*B + b)*y_ld + j], or nullptr
     int y_ld;
@@ -339,7 +341,7 @@ struct PersistRowsDir {
     int reverse;
 };
 struct PersistRowsArgs {
-    PersistRowsDir d[2];
+    PersistRowsDir d[kMaxRowsStack];   // the directions of a layer, or consecutive layers of one direction
     int T, B, H, ndir;
     int device_scope_only;     // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
     int poll_pace;             // pace_poll units in front of a device-wide poll
@@ -349,17 +351,31 @@ struct PersistRowsArgs {
     int rows, groups, gn, xcd_local;
     unsigned long long* hx;
     unsigned long long* xcc_ids;
+    unsigned long long* seq;   // what each layer of a stack hands up, [layer][group][T] buffers
 };
 struct PersistRowsPlan {   // how a launch of (B, H, ndir) is laid out
     int shape = -1;        // entry of the kernel's table; < 0: none fits
     double us = 1e30;      // modelled time of a step
     int rows = 0, groups = 0, gn = 0, xcd_local = 0;
+    int layers = 0;        // > 0: a stack of so many layers
     size_t lds = 0;
 };
 PersistRowsPlan persist_rows_bf16_plan(int B, int H, int ndir);
-size_t persist_rows_bf16_exchange_words(const PersistRowsPlan& p, int H, int ndir);
+PersistRowsPlan persist_rows_bf16_stack_plan(int B, int H, int layers);
+size_t persist_rows_bf16_exchange_words(const PersistRowsPlan& p, int H, int ndir, int T);
 void persist_rows_bf16_describe(const PersistRowsPlan& p, char* buf, size_t n);
 hipError_t launch_persist_rows_bf16(PersistRowsArgs& a, const PersistRowsPlan& p, unsigned long long* words, bool cooperative, hipStream_t s);
+// the initial states of a forward's launches
+struct RowsStates {
+    static constexpr int kMax = 64;
+    int n = 0, B = 0;
+    size_t at[kMax + 1] = {};      // words in front of each block
+    size_t off[kMax];              // values of h0 in front of it
+    int H[kMax], rows[kMax];
+    void add(const PersistRowsPlan& p, int H, size_t off);
+};
+size_t rows_bf16_state_words(const PersistRowsPlan& p, int H);
+hipError_t launch_rows_prepare(unsigned long long* first, const RowsStates& st, const float* h0, size_t zeros, hipStream_t s);
 size_t frag32_elements(int rows, int cols);
 hipError_t launch_to_frag32(const uint16_t* W, int rows, int cols, uint16_t* out, hipStream_t s);
 hipError_t launch_pad_rows(const void* src, bool bf16, int src_ld, int rows, int parts, int part_cols, int part_pitch, void* dst,

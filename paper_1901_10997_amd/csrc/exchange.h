@@ -162,6 +162,20 @@ __device__ __forceinline__ void exchange_store(T* p, T v, bool same_xcd)
     else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Agent-scope loads of 16 bytes (there is no atomic of that size; values that carry their own stamps need none: each is looked
+// at by itself).  A buffer's base and the offset of a block are scalar, so an address takes one register, and a line is asked for once
+// where two loads of 8 bytes ask twice.  Only the compiler's memory barrier in front keeps a load from being taken for an earlier
+// one's.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t exchange_buffer(const void* base, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);   // raw, 32-bit data format
+}
+template <class T>
+__device__ __forceinline__ T exchange_load16(__amdgpu_buffer_rsrc_t buffer, int lane_bytes, int scalar_bytes)
+{
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(buffer, lane_bytes, scalar_bytes, 1 << 4 /* sc1 */));
+}
+
 // Do the `members` (<= 64) workgroups of this group all run on one XCD?  Every member publishes its XCD id in
 // ids[me] (agent scope, tagged `tag`), polls the whole list and compares; all of them read the same list and so
 // agree on the answer.  tmp: LDS, `members` floats, free for other use on return.  Called by the whole workgroup.

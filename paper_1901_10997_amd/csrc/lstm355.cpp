@@ -28,6 +28,7 @@ struct DensePlans {
     LaunchCut tile_cut;           // fp32 LSTM layers whose many columns go faster as tiles (persist_dense_f32.hip); chunks = 0: none
     int tile_rows[2] = {0, 0};    // 16-row blocks per workgroup, as above
     PersistRowsPlan rows;         // bf16
+    PersistRowsPlan stack[kMaxRowsStack + 1];   // ... of so many layers from this one on in one launch
 };
 
 struct lstm355 {
@@ -161,6 +162,10 @@ constexpr int kPollPaceBatchedDeviceWide = 8;
 // 10 to 18 (800 units, batch 4: 2.42 us per step unpaced, 2.18 at 10, 1.94 at 14, 2.20 at 24; H-LSTM 1500/1500, batch 1:
 // 8.80, 8.31, 8.14, 8.46).
 constexpr int kPollPaceQuad = 13;
+// bf16 recurrence by groups of batch rows: broad optimum around 10 (1197 units, batch 20: 2.12 us per step at 13, 2.08 at 10; 1024, batch
+// 16: 1.85 and 1.80), and of a stack of layers, whose upper layers have the input's product there and are not paced (1024 units,
+// batch 16: 2.24 us per step at 0 to 8, 2.31 at 10, 2.47 at 13; 1197 and 1500 level from 0 to 10)
+constexpr int kPollPaceRows = 10, kPollPaceStack = 6;
 // ... and of its form for many columns (H = 256, batch 16: 2.48 us per step unpaced, 2.31 at 16, 2.54 at 24)
 constexpr int kPollPaceTiles = 16;
 // the yardsticks try these and report the fastest
@@ -828,6 +833,8 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     if (rc == LSTM_OK && !bf16) rc = add_split(m, x.wx);
     if (rc == LSTM_OK && !bf16) rc = add_rec_split(m, x.wh);
     if (rc == LSTM_OK && bf16 && !compressed) rc = add_frag32(m, x.wh);
+    // the input's matrix as well where the layer may run in one launch with the one below it
+    if (rc == LSTM_OK && bf16 && !compressed && m->Dn == 1 && layer > 0 && D == H && persist_rows_bf16_stack_plan(1, H, 2).shape >= 0) rc = add_frag32(m, x.wx);
     if (rc != LSTM_OK) return rc;
     std::vector<float> bp(rows);
     for (int rp = 0; rp < rows; ++rp) bp[rp] = b[(rp & 3) * H + (rp >> 2)];
@@ -952,6 +959,7 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
     p.B = B;
     if (m->dtype == LSTM_BF16) {
         p.rows = persist_rows_bf16_plan(B, H, m->Dn);
+        for (int n = 2; n <= kMaxRowsStack && m->Dn == 1 && l + n <= m->L && m->hid(l + n - 1) == H; ++n) p.stack[n] = persist_rows_bf16_stack_plan(B, H, n);
     } else {
         const auto plan = [&](int b, int nd) { return persist_quad_plan(b, H, G, nd); };
         if (choose_cut(B, m->Dn, [&](int b, int nd) { return plan(b, nd).shape >= 0; }, &p.cut, 1)) {
@@ -982,6 +990,25 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
         }
     }
     return p;
+}
+// How many layers from l on a bf16 stack runs in one launch, going by the shape (0: l by itself).  Each layer's step waits for its own
+// h only, so n layers take T + n - 1 steps instead of n T, and the layers above the first need no projection of their own.
+static int stack_layers(const lstm_t* m, int l, int T, int B)
+{
+    if (m->dtype != LSTM_BF16 || m->Dn != 1 || B < 2) return 0;
+    const DensePlans p = dense_plans(m, l, B);
+    if (p.rows.shape < 0 || (persist_mfma_supported(B, m->hid(l)) && p.rows.rows > 16)) return 0;
+    const double proj = 8.0 + 8e-6 * T * B * m->hid(l) * m->hid(l) / 900.0;
+    int best = 0;
+    double least = 1.0;
+    for (int n = 2; n <= kMaxRowsStack; ++n) {
+        if (p.stack[n].shape < 0) continue;
+        const double us = (T + n - 1) * p.stack[n].us, apart = n * T * p.rows.us + (n - 1) * (proj + 6.0);
+        // what is saved of the layers' time by themselves, per layer
+        const double rest = us / apart;
+        if (rest < 0.95 && rest * 1.02 < least) { least = rest; best = n; }
+    }
+    return best;
 }
 // exchange words per launch of that layer (the longest run of batch columns)
 static size_t quad_launch_words(const lstm_t* m, int l, int B, const LaunchCut& cut)
@@ -1111,7 +1138,13 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // ... and of the bf16 one
     w.rx_off = off;
     if (m->dtype == LSTM_BF16)
-        for (int l = 0; l < m->L; ++l) w.rx_words += persist_rows_bf16_exchange_words(dense_plans(m, l, B).rows, m->hid(l), m->Dn);
+        for (int l = 0, n; l < m->L; l += std::max(n, 1)) {
+            // (whether the weights let a stack run as one is not known before they are set)
+            n = stack_layers(m, l, T, B);
+            const DensePlans p = dense_plans(m, l, B);
+            w.rx_words += std::max(std::max(n, 1) * (size_t)m->Dn * rows_bf16_state_words(p.rows, m->hid(l)) + std::max(n, 1) * persist_rows_bf16_exchange_words(p.rows, m->hid(l), m->Dn, T),
+                                   n * rows_bf16_state_words(p.stack[n], m->hid(l)) + persist_rows_bf16_exchange_words(p.stack[n], m->hid(l), n, T));
+        }
     off += align256(w.rx_words * sizeof(unsigned long long));
     // copy of h0 where the call returns hT in its place (lstm_forward)
     w.h0_off = off;
@@ -1832,6 +1865,74 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
     return LSTM_OK;
 }
 
+// Exchange regions of the bf16 recurrence of persist_rows_bf16.hip inside one forward.
+struct RowsRegions {
+    unsigned long long* next = nullptr;                  // the next launch's region; nullptr: not cleared yet
+    std::vector<const unsigned long long*> h0;           // [layer * directions + direction]: its initial state in operand order
+};
+
+// Does layer l run there by itself?  (The other directions and layers of a launch are like it.)
+static bool layer_takes_rows(const lstm_t* m, int l, int T, int B, PersistRowsPlan* rows)
+{
+    if (m->dtype != LSTM_BF16 || m->plan == LSTM_PLAN_STEPWISE) return false;
+    int mode[2];
+    choose_modes(m, l, T, B, layer_takes_quads(m, l, T, B), mode);
+    for (int d = 0; d < m->Dn; ++d)
+        if (mode[d] != 0 || m->ld[(size_t)l * m->Dn + d].wh.compressed) return false;
+    *rows = dense_plans(m, l, B).rows;
+    // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 times (1024 units: batch 64 2.4 against 3.7 us per
+    // step, 128 2.8 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
+    return rows->shape >= 0 && !(persist_mfma_supported(B, m->hid(l)) && rows->rows > 16);
+}
+// stack[l]: so many layers from l on run in one launch (0: l is not the first of such a stack); empty where none does.
+static std::vector<int> stacks(const lstm_t* m, int T, int B)
+{
+    std::vector<int> stack;
+    if (m->dtype != LSTM_BF16 || m->Dn != 1 || B < 2) return stack;
+    PersistRowsPlan rows;
+    for (int l = 0, n; l < m->L; l += std::max(n, 1)) {
+        n = stack_layers(m, l, T, B);
+        bool ok = n > 1;
+        for (int k = l; k < l + n && ok; ++k) ok = layer_takes_rows(m, k, T, B, &rows) && (k == l || m->ld[(size_t)k].wx.dense_frag32);
+        if (!ok) continue;
+        stack.resize((size_t)m->L, 0);
+        stack[(size_t)l] = n;
+    }
+    return stack;
+}
+// Clears the regions of every such launch of the forward and lays out the initial states, in one kernel (64 states; more: several).
+static int prepare_rows(lstm_t* m, int T, int B, const std::vector<int>& stack, const float* h0, const Workspace& ws, char* base, RowsRegions& reg,
+                        hipStream_t s)
+{
+    const int Dn = m->Dn;
+    unsigned long long* first = (unsigned long long*)(base + ws.rx_off);
+    RowsStates st;
+    st.B = B;
+    size_t zeros = 0;
+    reg.h0.assign((size_t)m->L * Dn, nullptr);
+    for (int l = 0, n; l < m->L; l += std::max(n, 1)) {
+        n = stack.empty() ? 0 : stack[(size_t)l];
+        for (int k = l; k < l + std::max(n, 1); ++k) {
+            PersistRowsPlan p;
+            if (!layer_takes_rows(m, k, T, B, &p)) continue;
+            if (n > 0) p = dense_plans(m, l, B).stack[n];
+            if (k == l) zeros += persist_rows_bf16_exchange_words(p, m->hid(k), n > 0 ? n : Dn, T);
+            for (int d = 0; d < Dn && h0; ++d) {
+                if (st.n == RowsStates::kMax) {
+                    HIP_TRY(m, launch_rows_prepare(first, st, h0, 0, s));
+                    first += st.at[st.n];
+                    st.n = 0;
+                }
+                reg.h0[(size_t)k * Dn + d] = first + st.at[st.n];
+                st.add(p, m->hid(k), m->soff((size_t)k * Dn + d) * B);
+            }
+        }
+    }
+    HIP_TRY(m, launch_rows_prepare(first, st, h0, zeros, s));
+    reg.next = first + st.at[st.n];
+    return LSTM_OK;
+}
+
 static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, const float* c0, float* y, float* hT,
                        float* cT, const Workspace& ws, char* base, hipStream_t s);
 
@@ -1891,7 +1992,8 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
     int mflags_H = 0;            // width of the layer the flags were last laid out for
     unsigned mtag = 0;
     QuadRegions quad;
-    unsigned long long* rows_next = nullptr;   // next exchange region of the bf16 recurrence; nullptr: not cleared yet
+    RowsRegions rows_reg;
+    const std::vector<int> stack = stacks(m, T, B);
     bool prev_has_bf16 = false;  // the layer below left a bf16 copy of its hidden sequence in Ybf[(l-1)&1]
     m->last_plan.clear();
     if (m->G > 0) return forward_hlstm(m, T, B, x, h0, c0, y, hT, cT, ws, base, s);
@@ -2066,11 +2168,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
         bool dense_bf16 = bf16;
         for (int d = 0; d < Dn; ++d) dense_bf16 = dense_bf16 && mode[d] == 0 && !m->ld[(size_t)l * Dn + d].wh.compressed;
         const bool mfma_ok = dense_bf16 && step_mfma_supported(B, H);
-        // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 times (1024 units: batch 64 2.4 against 3.7 us per
-        // step, 128 2.8 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
         PersistRowsPlan rows;
-        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE) rows = dense_plans(m, l, B).rows;
-        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H) && (rows.shape < 0 || rows.rows > 16)) {
+        const bool takes_rows = layer_takes_rows(m, l, T, B, &rows);
+        if (dense_bf16 && m->plan != LSTM_PLAN_STEPWISE && persist_mfma_supported(B, H) && !takes_rows) {
             // time loop on the device: W_h stays in registers, h_t travels through flagged exchange buffers
             uint16_t* Yb = Ybf[l & 1];
             if (!mflags_clean || mflags_H != H) {
@@ -2109,45 +2209,54 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             prev_has_bf16 = true;
             continue;
         }
-        if (rows.shape >= 0) {
-            // every other width and batch: groups of workgroups over runs of batch rows, all directions in one launch
-            if (!rows_next) {
-                rows_next = (unsigned long long*)(base + ws.rx_off);
-                HIP_TRY(m, launch_fill_u64(rows_next, ws.rx_words, 0ull, s));
+        if (takes_rows) {
+            // every other width and batch: groups of workgroups over runs of batch rows, all directions, or a stack of layers, in one
+            // launch
+            if (!rows_reg.next) {
+                const int rc = prepare_rows(m, T, B, stack, h0, ws, base, rows_reg, s);
+                if (rc != LSTM_OK) return rc;
             }
+            const bool stacked = !stack.empty() && stack[(size_t)l] > 0;
+            const int n = stacked ? stack[(size_t)l] : Dn, top = stacked ? l + n - 1 : l;
+            if (stacked) rows = dense_plans(m, l, B).stack[n];
             PersistRowsArgs a{};
             const int pitch = pad32(H);
             // The layer above reads the bf16 copy, padded for the matrix-core product, unless it takes its input inside a
             // batch-1 recurrence: fp32 rows as they are, then.  Only the last layer's fp32 sequence leaves the library.
-            const bool rows_f32 = l == L - 1 || fuses_input(m, l + 1, T, B);
+            const bool rows_f32 = top == L - 1 || fuses_input(m, top + 1, T, B);
             char shape[48];
             persist_rows_bf16_describe(rows, shape, sizeof shape);
-            for (int d = 0; d < Dn; ++d) {
-                const LayerDir& w = m->ld[(size_t)l * Dn + d];
-                const size_t so = m->soff((size_t)l * Dn + d) * B;
-                PersistRowsDir& q = a.d[d];
-                q.P = P[d];
+            for (int i = 0; i < n; ++i) {
+                const int k = stacked ? l + i : l, d = stacked ? 0 : i;
+                const LayerDir& w = m->ld[(size_t)k * Dn + d];
+                const size_t so = m->soff((size_t)k * Dn + d) * B;
+                PersistRowsDir& q = a.d[i];
+                q.P = k > l ? w.bias : P[d];
                 q.Wf = w.wh.dense_frag32;
-                q.h0 = h0 ? h0 + so : nullptr;
+                q.Wxf = k > l ? w.wx.dense_frag32 : nullptr;
+                q.h0x = rows_reg.h0[(size_t)k * Dn + d];
                 q.c0 = c0 ? c0 + so : nullptr;
-                q.y = rows_f32 ? Yout + (size_t)d * H : nullptr;
+                if (k == top) {   // what the layers of a stack hand up goes no further
+                    q.y = !rows_f32 ? nullptr : (top == L - 1 ? y : Ybuf[top & 1]) + (size_t)d * H;
+                    q.yb = rows_f32 ? nullptr : Ybf[top & 1] + (size_t)d * pitch;
+                }
                 q.y_ld = y_ld;
-                q.yb = rows_f32 ? nullptr : Ybf[l & 1] + (size_t)d * pitch;
                 q.yb_ld = Dn * pitch; q.yb_width = pitch;
                 q.hT = hT ? hT + so : nullptr;
                 q.cT = cT ? cT + so : nullptr;
                 q.reverse = d;
-                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=dense,rec=persist-mfma-rows%s;", l, d, shape);
+                std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist-mfma-rows%s%s;", k, d, k > l ? "fused-dense" : "dense", stacked ? "-stack" : "", shape);
                 m->last_plan += tag;
             }
-            a.T = T; a.B = B; a.H = H; a.ndir = Dn;
+            a.T = T; a.B = B; a.H = H; a.ndir = n;
             a.device_scope_only = m->device_scope_only;
             a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit;
-            a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceQuad;
+            a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : stacked ? kPollPaceStack : kPollPaceRows;
             ProfSpan span(m, s, 1);
-            HIP_TRY(m, launch_persist_rows_bf16(a, rows, rows_next, m->launch_mode() != 0, s));
-            rows_next += persist_rows_bf16_exchange_words(rows, H, Dn);
+            HIP_TRY(m, launch_persist_rows_bf16(a, rows, rows_reg.next, m->launch_mode() != 0, s));
+            rows_reg.next += persist_rows_bf16_exchange_words(rows, H, n, T);
             prev_has_bf16 = !rows_f32;
+            l = top;
             continue;
         }
         if (mfma_ok) {
