@@ -160,6 +160,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     // operand lanes: column lr of the instruction is column lr % 4 of a quad in one plane; k 8 (lane / 16) .. + 7 of a block
     const int oc = lr & 3, oq = QP == 1 ? 0 : (lr >> 2) & 1, op_plane = QP == 1 ? (lr >> 2) & 1 : lr >> 3;
     unsigned long long* const hx = reinterpret_cast<unsigned long long*>(a.hx) + ((size_t)dir * a.quads + q_lo) * 2 * hquad;
+    const __amdgpu_buffer_rsrc_t words = exchange_buffer(hx, (unsigned)(nq * 2 * hquad * 8));
     const bool tail0 = wave == kSW - 1 && 32 * (KBt - 1) + 8 * lg >= H, tail1 = wave == kSW - 1 && 32 * (KBt - 1) + 8 * lg + 4 >= H;
     // a quad that is not there reads the last one that is: its products are never used
     auto quad_of = [&](int pass, int c) { return pass * QP + c < nq ? pass * QP + c : nq - 1; };
@@ -277,21 +278,18 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
             u64x2 fr[KB];
             const unsigned tag = (unsigned)s + 2u;
             const unsigned want = ((tag >> 1) & 1u) ? kStamp : 0u;
-            // scalar base, 32-bit lane offset
-            const unsigned long long* const src = hx + (tag & 1u) * hquad + (QP == 1 ? (size_t)pass * 2 * hquad : 0);
-            const unsigned loff = (unsigned)(((lg * 2 + op_plane) * 4 + oc) * 2) + (QP == 1 ? 0u : (unsigned)(quad_of(pass, oq) * 2 * hquad));
+            const int src = (int)((tag & 1u) * hquad + (QP == 1 ? (size_t)pass * 2 * hquad : 0)) * 8;
+            const int loff = (((lg * 2 + op_plane) * 4 + oc) * 2 + (QP == 1 ? 0 : (int)(quad_of(pass, oq) * 2 * hquad))) * 8;
             pace_poll(a.poll_pace);
             unsigned spins = 0, differ;
             for (;;) {
                 differ = 0;
+                asm volatile("" ::: "memory");                           // read anew in every round
                 // a wave without a last block reads its first one twice; a lane without a column multiplies what another reads
                 // (never used)
 #pragma unroll
-                for (int q = 0; q < KB; ++q) {
-                    const unsigned long long* const p = src + (unsigned)((q < KB - 1 || all_kb ? kb0 + q : kb0) * 64);
-                    fr[q].x = __hip_atomic_load(p + loff, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    fr[q].y = __hip_atomic_load(p + loff + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+                for (int q = 0; q < KB; ++q) fr[q] = exchange_load16<u64x2>(words, loff, src + (q < KB - 1 || all_kb ? kb0 + q : kb0) * 512);
+                __builtin_amdgcn_sched_barrier(0);                       // all on their way before the first is waited for
                 // words of K's last block whose units are all beyond the last one are never written
 #pragma unroll
                 for (int q = 0; q < KB; ++q) {
