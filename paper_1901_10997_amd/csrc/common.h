@@ -604,11 +604,10 @@ struct PersistBatchedHArgs {
     int ndir, xcd_local;        // directions in the grid; block ids grouped by XCD (filled by the launcher)
     int device_scope_only;      // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
     size_t h_stride, u_stride;  // elements per (direction, batch group) in xchg_h / xchg_u (filled by the launcher)
-    unsigned long long* xchg_h; // tagged slots, zero or older tags only
-    float* xchg_u;              // plain values
-    unsigned* flags;            // [ndir * bg][64], zero or older tags only
+    unsigned *xchg_h, *xchg_u;  // stamped words: zero, or written h_epoch and u_epoch times by launches of the same layout
+    unsigned h_epoch, u_epoch;  // (a launch writes u T times and h T - 1 times)
     unsigned long long* xcc_ids; // [ndir * bg][64] tagged slots (XCD id of each unit group's workgroup), zero or older tags only
-    unsigned tag_base;
+    unsigned tag_base;          // tag_base + 1 is this launch's
     int* timeout_flag;
     unsigned spin_limit;
 };

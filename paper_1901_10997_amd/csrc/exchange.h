@@ -176,6 +176,46 @@ __device__ __forceinline__ T exchange_load16(__amdgpu_buffer_rsrc_t buffer, int 
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(buffer, lane_bytes, scalar_bytes, 1 << 4 /* sc1 */));
 }
 
+// n 32-bit words (dst padded to whole groups of four) from `words`, an array that holds whole groups of four too, into LDS once
+// every word's bit `bit` is as in `want`; values may be taken apart from their stamp by `value`.  NF groups of a thread are in flight
+// together; groups beyond the array are not fetched (the buffer's bounds).  Bounded: *timeout_flag.
+template <int NF, class Value>
+__device__ __forceinline__ void gather_stamped(const unsigned* words, int n, unsigned bit, unsigned want, float* dst, int tid, int nthreads,
+                                               int* timeout_flag, unsigned spin_limit, Value value)
+{
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    const int n4 = (n + 3) >> 2;
+    const __amdgpu_buffer_rsrc_t from = exchange_buffer(words, (unsigned)n4 * 16u);
+    for (int e0 = 0; e0 < n4; e0 += NF * nthreads) {
+        u32x4 v[NF];
+        for (unsigned spins = 0;;) {
+            asm volatile("" ::: "memory");                               // read anew in every round
+#pragma unroll
+            for (int u = 0; u < NF; ++u) v[u] = exchange_load16<u32x4>(from, tid * 16, (e0 + u * nthreads) * 16);
+            __builtin_amdgcn_sched_barrier(0);                           // all on their way before the first is waited for
+            unsigned differ = 0;
+#pragma unroll
+            for (int u = 0; u < NF; ++u) {
+                const int left = n - 4 * (e0 + u * nthreads + tid);      // words from this group on
+                const unsigned lo = (v[u].x ^ want) | (v[u].y ^ want), hi = (v[u].z ^ want) | (v[u].w ^ want);
+                differ |= (left > 0 ? lo : 0u) | (left > 2 ? hi : 0u);   // (n is even)
+            }
+            if (!__builtin_amdgcn_ballot_w64((differ & bit) != 0u)) break;
+            if (++spins > spin_limit) {
+                __hip_atomic_store(timeout_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            if ((spins & 63u) == 0 && __hip_atomic_load(timeout_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+        }
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            const int e = e0 + u * nthreads + tid;
+            if (e < n4) reinterpret_cast<f32x4*>(dst)[e] = (f32x4){value(v[u].x), value(v[u].y), value(v[u].z), value(v[u].w)};
+        }
+    }
+}
+
 // Do the `members` (<= 64) workgroups of this group all run on one XCD?  Every member publishes its XCD id in
 // ids[me] (agent scope, tagged `tag`), polls the whole list and compares; all of them read the same list and so
 // agree on the answer.  tmp: LDS, `members` floats, free for other use on return.  Called by the whole workgroup.

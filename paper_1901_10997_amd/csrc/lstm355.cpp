@@ -944,7 +944,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
-    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, hb_off, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, sm_off, total;
+    size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, hb_off, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, sm_off, U_end, total;
 };
 // Plans of layer l at batch B.  They follow from the shape alone, but a search over the kernels' shape tables takes
 // microseconds and a forward needs each several times, so the handle keeps the last batch size's.
@@ -1090,13 +1090,12 @@ static Workspace carve(const lstm_t* m, int T, int B)
     // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
     // group] (ragged last group filled up: at most B + 3 columns), then one slot per workgroup for the XCD ids, 64 per
     // batch group
-    // (H-LSTM: h slots in [k][columns of a batch group] blocks padded to 256 bytes, ragged last group filled up,
-    // then one flag per unit group, 64 per batch group, then the XCD id slots)
+    // (H-LSTM: words of h in [k][columns of a batch group] blocks padded to 256 bytes, ragged last group filled up,
+    // then the XCD id slots; its words of u follow, and one fill clears both)
     w.slot_off = off;
     if (B >= 2) {
         const size_t groups = (size_t)B / 2 + 1;
-        w.slot_bytes = m->G > 0 ? (size_t)m->Dn * (((size_t)B + 3) * H * sizeof(unsigned long long) + groups * 256 +
-                                                   groups * 64 * (sizeof(unsigned) + sizeof(unsigned long long)))
+        w.slot_bytes = m->G > 0 ? (size_t)m->Dn * (align256(((size_t)B + 3) * H * sizeof(unsigned)) + groups * 256 + groups * 64 * sizeof(unsigned long long))
                                 : (size_t)m->Dn * (2 * ((size_t)B + 3) * H + groups * 64) * sizeof(unsigned long long);
         off += align256(w.slot_bytes);
     }
@@ -1123,6 +1122,7 @@ static Workspace carve(const lstm_t* m, int T, int B)
         w.U_off[d] = off;
         if (m->G > 0 && d < m->Dn) off += align256(((size_t)B + 3) * 4 * m->G * sizeof(float) + ((size_t)B / 2 + 1) * 256);
     }
+    w.U_end = off;
     // exchange regions of the dense fp32 persistent recurrence, one per launch of the forward so that one fill serves all
     // (whether a layer's recurrent matrices are held dense is not known before its weights are set)
     w.qx_off = off;
@@ -1562,9 +1562,10 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
     float* cbuf[2] = {(float*)(base + ws.c_off[0]), (float*)(base + ws.c_off[1])};
     float* U[2] = {(float*)(base + ws.U_off[0]), (float*)(base + ws.U_off[1])};
     char tag[96];
-    bool hslots_clean = false;   // exchange slots and flags zeroed during this forward (tags then restart at 1)
-    int hslots_H = 0, hslots_G = 0;   // widths of the layer the region was last laid out for
-    unsigned htag = 0;
+    // exchange words of the small-batch recurrence: the launch they were last laid out for (H, G, columns, directions, columns of a
+    // group), how often each has been written since they were cleared, and the tags of the XCD ids
+    int hlayout[5] = {0, 0, 0, 0, 0};
+    unsigned h_epoch = 0, u_epoch = 0, htag = 0;
     QuadRegions quad;
     for (int l = 0; l < L; ++l) {
         const int H = m->hid(l), G = m->ghid(l);
@@ -1672,24 +1673,20 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
             if (m->plan == LSTM_PLAN_PERSISTENT && B >= 2 && !pb_ok)
                 return fail(m, LSTM_ERR_ARG, "lstm_forward: persistent plan not available for this shape");
             if (pb_ok) {
-                unsigned long long* hslots = (unsigned long long*)(base + ws.slot_off);
                 const size_t groups = (size_t)B / 2 + 1;
-                const size_t hslot_bytes = (size_t)Dn * (((size_t)B + 3) * H * sizeof(unsigned long long) + groups * 256);
-                unsigned* hflags = (unsigned*)(base + ws.slot_off + hslot_bytes);
-                unsigned long long* hxcc = (unsigned long long*)(hflags + (size_t)Dn * groups * 64);
-                // (a layer of other widths lays the region out differently: what the previous layer left under the
-                // new flag positions is not a tag, so the region starts from zero again)
-                if (!hslots_clean || hslots_H != H || hslots_G != G) {
-                    HIP_TRY(m, launch_fill_u64(hslots, align256(ws.slot_bytes) / sizeof(unsigned long long), 0ull, s));
-                    hslots_clean = true;
-                    hslots_H = H; hslots_G = G;
-                    htag = 0;
-                }
+                unsigned* hwords = (unsigned*)(base + ws.slot_off);
+                unsigned long long* hxcc = (unsigned long long*)(base + ws.slot_off + (size_t)Dn * (align256(((size_t)B + 3) * m->H * sizeof(unsigned)) + groups * 256));
                 for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
                 const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
                 const int nd = Dn / cut.passes, d_lo = pass * nd;
                 const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
                 persist_batched_h_plan(bn, H, G, nz, nd, &upw, &bw, &ug, &bg);
+                const int layout[5] = {H, G, bn, nd, bw};
+                if (!std::equal(layout, layout + 5, hlayout)) {   // another layout puts words written less often in a word's place
+                    HIP_TRY(m, launch_fill_u64((unsigned long long*)hwords, (ws.U_end - ws.slot_off) / sizeof(unsigned long long), 0ull, s));
+                    std::copy(layout, layout + 5, hlayout);
+                    h_epoch = u_epoch = htag = 0;
+                }
                 PersistBatchedHArgs a{};
                 for (int d = d_lo; d < d_lo + nd; ++d) {
                     const LayerDir& w = m->ld[(size_t)l * Dn + d];
@@ -1717,9 +1714,10 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                     }
                 }
                 a.T = T; a.B = bn; a.Bld = B; a.H = H; a.G = G;
-                a.xchg_h = hslots; a.xchg_u = U[0]; a.flags = hflags; a.xcc_ids = hxcc;
+                a.xchg_h = hwords; a.xchg_u = (unsigned*)U[0]; a.xcc_ids = hxcc;
+                a.h_epoch = h_epoch; a.u_epoch = u_epoch;
                 a.tag_base = htag; a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit; a.device_scope_only = m->device_scope_only;
-                htag += (unsigned)T + 1u;
+                htag += 1u; h_epoch += (unsigned)T - 1u; u_epoch += (unsigned)T;
                 ProfSpan span(m, s, 1);
                 HIP_TRY(m, launch_persist_batched_h(a, nd, nz, m->launch_mode(), s));
                 }
