@@ -538,9 +538,11 @@ struct PersistBatchedArgs {
     int ndir, xcd_local;       // directions in the grid; block ids grouped by XCD (filled by the launcher)
     int device_scope_only;     // 1: publish with device-scope stores even where a group shares an XCD (A/B switch)
     int round_h_bf16;
-    unsigned long long* xchg;  // slots, zero or older tags only: 2 (B + 3) H per direction, [2][batch group][H][columns of a group]
+    unsigned* xchg;            // words of h, zero or written by launches of the same layout: [ndir * bg][2][h_stride]
+    unsigned epoch;            // steps that those launches have published (T - 1 each)
+    size_t h_stride;           // (filled by the launcher)
     unsigned long long* xcc_ids;  // [ndir * bg][64] tagged slots (XCD id of each unit group's workgroup), zero or older tags only
-    unsigned tag_base;
+    unsigned tag_base;         // tag_base + 1 is this launch's
     int* timeout_flag;
     unsigned spin_limit;
     int poll_pace;             // pace_poll units in front of the poll of h where the exchange is device-wide (set by the launcher)
@@ -566,6 +568,7 @@ hipError_t launch_proj_q16(const ProjQ16Args& a, int ndir, int slots, hipStream_
 
 // `slots` = the largest q16_slots of the directions (even, <= 16)
 bool persist_batched_q16_plan(int B, int H, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
+size_t persist_batched_q16_stride(int H, int bw);
 hipError_t launch_persist_batched_q16(PersistBatchedArgs& a, int ndir, int slots, int cooperative, hipStream_t s);
 
 // H-LSTM at small batch (B >= 2), W1h and W2 row-compressed and register-resident, time loop on the device, every

@@ -1087,16 +1087,15 @@ static Workspace carve(const lstm_t* m, int T, int B)
     if (halves > 0) off += align256(M * sizeof(float));
     w.hb0_off = off;
     if (m->dtype == LSTM_BF16) off += align256((size_t)m->Dn * B * H * sizeof(uint16_t));
-    // tagged exchange slots of the small-batch persistent recurrence: per direction [2][batch groups][H][columns of a
-    // group] (ragged last group filled up: at most B + 3 columns), then one slot per workgroup for the XCD ids, 64 per
-    // batch group
+    // exchange of the small-batch persistent recurrence: a slot per workgroup for the XCD ids, 64 per batch group, then per direction and
+    // batch group two buffers of words, [H][columns of a group] in whole 256-byte blocks (ragged last group filled up: at most B + 3 columns)
     // (H-LSTM: words of h in [k][columns of a batch group] blocks padded to 256 bytes, ragged last group filled up,
     // then the XCD id slots; its words of u follow, and one fill clears both)
     w.slot_off = off;
     if (B >= 2) {
         const size_t groups = (size_t)B / 2 + 1;
         w.slot_bytes = m->G > 0 ? (size_t)m->Dn * (align256(((size_t)B + 3) * H * sizeof(unsigned)) + groups * 256 + groups * 64 * sizeof(unsigned long long))
-                                : (size_t)m->Dn * (2 * ((size_t)B + 3) * H + groups * 64) * sizeof(unsigned long long);
+                                : (size_t)m->Dn * (groups * 64 * sizeof(unsigned long long) + (2 * ((size_t)B + 3) * H + 2 * groups * 64) * sizeof(unsigned));
         off += align256(w.slot_bytes);
     }
     // bf16 large-batch persistent recurrence: two exchange buffers of h_t and one flag per tile
@@ -1981,9 +1980,10 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
     uint16_t* Ybf[2] = {(uint16_t*)(base + ws.Yb_off[0]), (uint16_t*)(base + ws.Yb_off[1])};
     uint16_t* hb0 = (uint16_t*)(base + ws.hb0_off);
     unsigned long long* bslots = (unsigned long long*)(base + ws.slot_off);
-    bool bslots_clean = false;   // zeroed during this forward (tags then restart at 1)
-    int bslots_H = 0;            // width of the layer the region was last laid out for
-    unsigned btag = 0;
+    // words of the small-batch recurrence: the launch they were last laid out for (H, columns, directions, columns of a group), the steps
+    // published in them since they were cleared, and the tags of the XCD ids
+    int blayout[4] = {0, 0, 0, 0};
+    unsigned bepoch = 0, btag = 0;
     uint16_t* hx = (uint16_t*)(base + ws.hx_off);
     unsigned* mflags = (unsigned*)(base + ws.mflag_off);
     bool mflags_clean = false;   // zeroed during this forward (tags then restart at 1)
@@ -2318,17 +2318,17 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
             LaunchCut cut;
             pb_ok = pb_ok && choose_cut(B, Dn, [&](int b, int nd) { return persist_batched_q16_plan(b, H, q16, nd, &upw, &bw, &ug, &bg); }, &cut);
             if (pb_ok) {
-                if (!bslots_clean || bslots_H != H) {   // another width is another layout: start from zero again
-                    HIP_TRY(m, launch_fill_u64(bslots, align256(ws.slot_bytes) / sizeof(unsigned long long), 0ull, s));
-                    bslots_clean = true;
-                    bslots_H = H;
-                    btag = 0;
-                }
                 for (int launch = 0; launch < cut.passes * cut.chunks; ++launch) {
                 const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
                 const int nd = Dn / cut.passes, d_lo = pass * nd;
                 const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
                 persist_batched_q16_plan(bn, H, q16, nd, &upw, &bw, &ug, &bg);
+                const int layout[4] = {H, bn, nd, bw};
+                if (!std::equal(layout, layout + 4, blayout)) {   // another layout puts words written less often in a word's place
+                    HIP_TRY(m, launch_fill_u64(bslots, align256(ws.slot_bytes) / sizeof(unsigned long long), 0ull, s));
+                    std::copy(layout, layout + 4, blayout);
+                    bepoch = btag = 0;
+                }
                 PersistBatchedArgs a{};
                 for (int d = d_lo; d < d_lo + nd; ++d) {
                     const LayerDir& w = m->ld[(size_t)l * Dn + d];
@@ -2353,9 +2353,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                     }
                 }
                 a.T = T; a.B = bn; a.Bld = B; a.H = H; a.round_h_bf16 = bf16;
-                a.xchg = bslots; a.xcc_ids = bslots + (size_t)Dn * 2 * (B + 3) * H; a.tag_base = btag; a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit; a.device_scope_only = m->device_scope_only;
+                a.xchg = (unsigned*)(bslots + (size_t)Dn * ((size_t)B / 2 + 1) * 64); a.xcc_ids = bslots; a.epoch = bepoch; a.tag_base = btag; a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit; a.device_scope_only = m->device_scope_only;
                 a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceBatchedDeviceWide;   // (the launcher clears it where the exchange stays inside XCDs)
-                btag += (unsigned)T;
+                btag += 1u; bepoch += (unsigned)T - 1u;
                 ProfSpan span(m, s, 1);
                 HIP_TRY(m, launch_persist_batched_q16(a, nd, q16, m->launch_mode(), s));
                 }

@@ -44,3 +44,30 @@ def test_nan_stays_in_its_sequence(H, G, Bn):
     others = np.arange(Bn) != b
     for got, ref in ((y, y0), (hT, hT0), (cT, cT0)):
         np.testing.assert_array_equal(got[:, others], ref[:, others])
+
+
+@pytest.mark.parametrize("L,bidir,D,H,T,Bn,keep", [
+    (3, True, 24, 37, 6, 2, 0.3),         # an odd number of units, two columns per group: the last group of words is half full
+    (3, False, 24, 131, 7, 3, 0.2),       # a ragged group
+    (4, False, 16, 250, 1, 5, 0.2),       # one step per launch: nothing is published
+    (3, True, 40, 402, 5, 37, 0.1),
+    (3, False, 24, 1900, 3, 61, 0.02),    # several launches per layer, runs of unequal length
+    (2, False, 64, 1500, 4, 20, 0.1),
+])
+def test_lstm(L, bidir, D, H, T, Bn, keep):
+    desc, _ = check_case(_case(L, bidir, D, H, T, Bn, keep), CSR)
+    assert desc.count("rec=persist_batched-q16") == L * (2 if bidir else 1), desc
+
+
+@pytest.mark.parametrize("H,Bn", [(71, 6), (300, 3)])
+def test_nan_stays_in_its_sequence_lstm(H, Bn):
+    case = _case(1, True, 24, H, 6, Bn, 0.3)
+    (y0, hT0, cT0), _ = run_gpu(case, CSR)
+    b = Bn - 1
+    case.c0[:, b, H // 2] = np.nan
+    (y, hT, cT), desc = run_gpu(case, CSR)
+    assert "persist_batched-q16" in desc, desc
+    assert np.isnan(y[0, b, H // 2]) and np.isnan(cT[0, b, H // 2]) and np.isnan(y[1:, b, :H]).sum() > 1
+    others = np.arange(Bn) != b
+    for got, ref in ((y, y0), (hT, hT0), (cT, cT0)):
+        np.testing.assert_array_equal(got[:, others], ref[:, others])
