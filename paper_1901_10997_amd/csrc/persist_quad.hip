@@ -45,6 +45,7 @@ namespace l355 {
 
 namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 constexpr int kQW = 8, kQTH = 512;
 constexpr unsigned kHBit = kHStampBit, kUBit = 0x80000000u;
 
@@ -196,6 +197,7 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
     const size_t hquad = (size_t)KBh * 64, uquad = (size_t)KBg * 256;
     unsigned* const hx = a.hx + ((size_t)dir * a.quads + q_lo) * 2 * hquad;          // [quad][2][k][column]
     unsigned* const ux = HL ? a.ux + ((size_t)dir * a.quads + q_lo) * uquad : nullptr;
+    const __amdgpu_buffer_rsrc_t uwords = exchange_buffer(ux, HL ? (unsigned)(nq * uquad * 4) : 0u);
 
     bool same_xcd = false;
     if (a.xcd_local)
@@ -357,35 +359,29 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
         if constexpr (HL) {
             for (int pass = 0; owns_h && pass < passes; ++pass) {
                 // ---- second product: four gates x four k per instruction, one register of u each
-                unsigned long long fu[QP][KB][2];
+                u32x4 fu[QP][KB];
                 const unsigned want = ((unsigned)s + 1u) << 31;
-                const unsigned* src[QP];
-#pragma unroll
-                for (int c = 0; c < QP; ++c) src[c] = ux + (size_t)quad_of(pass, c) * uquad + lane * 4;
                 pace_poll(a.poll_pace);
                 unsigned spins = 0;
                 for (;;) {
-                    bool ok = true;
+                    asm volatile("" ::: "memory");                       // read anew in every round
 #pragma unroll
                     for (int c = 0; c < QP; ++c)
 #pragma unroll
                         for (int q = 0; q < KB; ++q)
-#pragma unroll
-                            for (int e = 0; e < 2; ++e)
-                                fu[c][q][e] = __hip_atomic_load(
-                                    reinterpret_cast<const unsigned long long*>(src[c] + (kb0 + q < KBg ? kb0 + q : KBg - 1) * 256) + e,
-                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            fu[c][q] = exchange_load16<u32x4>(uwords, lane * 16, quad_of(pass, c) * (int)uquad * 4 + (kb0 + q < KBg ? kb0 + q : KBg - 1) * 1024);
+                    __builtin_amdgcn_sched_barrier(0);                   // all on their way before the first is waited for
+                    unsigned differ = 0;
 #pragma unroll
                     for (int c = 0; c < QP; ++c)
 #pragma unroll
                         for (int q = 0; q < KB; ++q)
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const unsigned v = (unsigned)(fu[c][q][e >> 1] >> (32 * (e & 1)));
                                 const bool dead = kb0 + q >= KBg - 1 && 16 * (KBg - 1) + 4 * lg + e >= G;
-                                ok = ok && (((v ^ want) & kUBit) == 0u || dead);
+                                differ |= dead ? 0u : fu[c][q][e] ^ want;
                             }
-                    if (!__builtin_amdgcn_ballot_w64(!ok) || give_up(spins, a.spin_limit, a.timeout_flag)) break;
+                    if (!__builtin_amdgcn_ballot_w64((differ & kUBit) != 0u) || give_up(spins, a.spin_limit, a.timeout_flag)) break;
                 }
                 f32x4 acc[QP][NT];
 #pragma unroll
@@ -402,7 +398,7 @@ __global__ __launch_bounds__(kQTH) void persist_quad_kernel(PersistQuadArgs a)
                         for (int e = 0; e < 4; ++e)
 #pragma unroll
                             for (int c = 0; c < QP; ++c) {
-                                const float av = __uint_as_float((unsigned)(fu[c][q][e >> 1] >> (32 * (e & 1))) & ~kUBit);
+                                const float av = __uint_as_float(fu[c][q][e] & ~kUBit);
 #pragma unroll
                                 for (int n = 0; n < NT; ++n)
                                     acc[c][n] = __builtin_amdgcn_mfma_f32_4x4x1f32(av, e == 0 ? w[n].x : e == 1 ? w[n].y : e == 2 ? w[n].z : w[n].w,
