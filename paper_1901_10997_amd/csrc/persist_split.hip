@@ -162,6 +162,7 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
     unsigned long long* const hx = reinterpret_cast<unsigned long long*>(a.hx) + ((size_t)dir * a.quads + q_lo) * 2 * hquad;
     const __amdgpu_buffer_rsrc_t words = exchange_buffer(hx, (unsigned)(nq * 2 * hquad * 8));
     const bool tail0 = wave == kSW - 1 && 32 * (KBt - 1) + 8 * lg >= H, tail1 = wave == kSW - 1 && 32 * (KBt - 1) + 8 * lg + 4 >= H;
+    const unsigned last0 = all_kb && !tail0 ? ~0u : 0u, last1 = all_kb && !tail1 ? ~0u : 0u;
     // a quad that is not there reads the last one that is: its products are never used
     auto quad_of = [&](int pass, int c) { return pass * QP + c < nq ? pass * QP + c : nq - 1; };
 
@@ -288,13 +289,24 @@ __global__ __launch_bounds__(kSTH) void persist_split_kernel(PersistQuadArgs a)
                 // a wave without a last block reads its first one twice; a lane without a column multiplies what another reads
                 // (never used)
 #pragma unroll
-                for (int q = 0; q < KB; ++q) fr[q] = exchange_load16<u64x2>(words, loff, src + (q < KB - 1 || all_kb ? kb0 + q : kb0) * 512);
+                for (int q = 0; q < KB; ++q) {
+                    const int block = (q < KB - 1 || all_kb ? kb0 + q : kb0) * 512;
+                    if constexpr (KB > 2 || NT > 3) {
+                        fr[q] = exchange_load16<u64x2>(words, loff, src + block);
+                    } else {   // a narrow layer's first round would come before the words do (337 units: 244 us as pairs, 250 so)
+                        const unsigned long long* const at = hx + (unsigned)(src + block) / 8u;
+                        fr[q].x = __hip_atomic_load(at + (unsigned)loff / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        fr[q].y = __hip_atomic_load(at + (unsigned)loff / 8u + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);                       // all on their way before the first is waited for
-                // words of K's last block whose units are all beyond the last one are never written
+                // words of K's last block whose units are all beyond the last one are never written; of a wave without a last block
+                // its words are looked at all the same (a load still on its way would make a later wait one for P's too)
 #pragma unroll
                 for (int q = 0; q < KB; ++q) {
-                    if (q < KB - 1) differ |= ((unsigned)fr[q].x ^ want) | ((unsigned)fr[q].y ^ want);
-                    else if (all_kb) differ |= (tail0 ? 0u : (unsigned)fr[q].x ^ want) | (tail1 ? 0u : (unsigned)fr[q].y ^ want);
+                    const unsigned x = (unsigned)fr[q].x ^ want, y = (unsigned)fr[q].y ^ want;
+                    if (q < KB - 1) differ |= x | y;
+                    else differ |= (x & last0) | (y & last1);
                 }
                 if (!__builtin_amdgcn_ballot_w64((differ & kStamp) != 0u)) break;
                 if (++spins > a.spin_limit) {
@@ -486,7 +498,11 @@ hipError_t launch_persist_split(PersistQuadArgs& a, const PersistQuadPlan& p, un
     const void* const kernel = kSplitRecShapes[p.shape].kernel;
     a.quads = (a.B + 3) / 4;
     a.mq = p.mq; a.groups = p.groups; a.gn = p.gn; a.xcd_local = p.xcd_local;
-    if (p.xcd_local || p.mq > kSplitRecShapes[p.shape].qp) a.poll_pace = 0;   // as in launch_persist_quad
+    // Other passes in between, or an exchange inside an XCD: a short wait there from three k blocks on, as the words are read in half
+    // the requests and the first round came too early (800 units, both directions, batch 16, 200 steps: 404 us unpaced, 390, 384, 381,
+    // 381 and 394 at 1 to 4 and 6; 640: 314, 301 at 2 and 3; 457, two k blocks: 237, 249 at 1).
+    if (p.mq > kSplitRecShapes[p.shape].qp) a.poll_pace = 0;
+    else if (p.xcd_local) a.poll_pace = kSplitRecShapes[p.shape].kb > 2 ? 3 : 0;
     a.hx = words;
     a.ux = nullptr;
     a.xcc_ids = (unsigned long long*)(words + split_h_words(a.B, a.H, a.ndir));
