@@ -55,15 +55,18 @@ struct PackedMat {
     int q16_slots = 0;            // even; 16 q16_slots entries of every row are in the slots
     float* q16_val = nullptr;
     uint16_t* q16_col = nullptr;
-    // the few entries of rows longer than that (at most 6 in any eight consecutive units), per unit: entry = (gate << 16) | column; or nullptr
-    int32_t* q16_ovf_ptr = nullptr;   // device [rows/4 + 1]
-    uint32_t* q16_ovf_ent = nullptr;
+    // the entries of rows longer than that (of a gate at most kQ16ExtraRounds x 16 in any eight consecutive units), gate by gate; or nullptr
+    int32_t* q16_ovf_ptr = nullptr;   // device [4][rows/4 + 1]
+    uint32_t* q16_ovf_ent = nullptr;  // inside that allocation
     float* q16_ovf_val = nullptr;
+    int q16_rounds = 0;               // most rounds of any eight units (quarter_wave.h)
     // host copy of the compressed structure in packed row order (for read-back)
     std::vector<int64_t> h_row_ptr;
     std::vector<int32_t> h_col;
     std::vector<float> h_val;
 };
+
+constexpr int kQ16ExtraRounds = 3;
 
 struct LayerDir {
     bool set = false;
@@ -519,8 +522,8 @@ struct PersistBatchedDir {
     const float* q16_val;
     const uint16_t* q16_col;
     int q16_slots;
-    const int32_t* q16_ovf_ptr;   // per-unit lists of the entries beyond 16 q16_slots of a row, or nullptr
-    const uint32_t* q16_ovf_ent;  // (gate << 16) | column
+    const int32_t* q16_ovf_ptr;   // the entries beyond 16 q16_slots of a row, gate by gate ([4][H + 1]), or nullptr
+    const uint32_t* q16_ovf_ent;  // column
     const float* q16_ovf_val;
     const float* h0;           // [B][H] or nullptr
     const float* c0;
@@ -552,8 +555,8 @@ struct ProjQ16Dir {
     const float* val;            // [H][slots][64]
     const uint16_t* col;
     int slots;
-    const int32_t* ovf_ptr;      // entries outside the slots, per unit; or nullptr
-    const uint32_t* ovf_ent;     // (gate << 16) | column
+    const int32_t* ovf_ptr;      // entries outside the slots, gate by gate ([4][H + 1]); or nullptr
+    const uint32_t* ovf_ent;     // column
     const float* ovf_val;
     const float* bias;           // [4H] packed rows
     float* P;                    // [M][4H]
@@ -582,8 +585,7 @@ struct PersistBatchedHDir {
     const float* q16_val_2;
     const uint16_t* q16_col_2;
     int slots_1h, slots_2;
-    // per-unit lists of the few entries outside the slots (nullptr: none); entry = (gate << 16) | column (W2: the
-    // column inside its gate's block); at most 6 in any eight consecutive units
+    // the entries outside the slots, gate by gate ([4][G + 1], [4][H + 1]; nullptr: none); entry = column as in the slots
     const int32_t* ovf_ptr_1h;
     const uint32_t* ovf_ent_1h;
     const float* ovf_val_1h;
@@ -615,6 +617,7 @@ struct PersistBatchedHArgs {
     unsigned spin_limit;
 };
 // `slots` = the largest slot count of the two matrices over the directions (even, <= 16)
+double persist_batched_h_step_us(int H, int slots, int upw, int bw, bool local);
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
 hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int ndir, int slots, int cooperative, hipStream_t s);
 

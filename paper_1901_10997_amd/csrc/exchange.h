@@ -131,6 +131,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t exchange_buffer(const void* ba
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);   // raw, 32-bit data format
 }
+// lane_bytes + 16 beyond the buffer's bytes reads zero; scalar_bytes is not checked: it stays inside for every lane_bytes used with it.
 template <class T>
 __device__ __forceinline__ T exchange_load16(__amdgpu_buffer_rsrc_t buffer, int lane_bytes, int scalar_bytes)
 {
@@ -153,7 +154,7 @@ __device__ __forceinline__ void gather_stamped(const unsigned* words, int n, uns
         for (unsigned spins = 0;;) {
             asm volatile("" ::: "memory");                               // read anew in every round
 #pragma unroll
-            for (int u = 0; u < NF; ++u) v[u] = exchange_load16<u32x4>(from, tid * 16, (e0 + u * nthreads) * 16);
+            for (int u = 0; u < NF; ++u) v[u] = exchange_load16<u32x4>(from, (e0 + u * nthreads + tid) * 16, 0);   // (bounds: the lane's offset)
             __builtin_amdgcn_sched_barrier(0);                           // all on their way before the first is waited for
             unsigned differ = 0;
 #pragma unroll
@@ -175,6 +176,16 @@ __device__ __forceinline__ void gather_stamped(const unsigned* words, int n, uns
             if (e < n4) reinterpret_cast<f32x4*>(dst)[e] = (f32x4){value(v[u].x), value(v[u].y), value(v[u].z), value(v[u].w)};
         }
     }
+}
+
+// ... with as many loads in flight as the array has for a thread, up to NF (loads beyond it cost their issue all the same)
+template <int NF, class Value>
+__device__ __forceinline__ void gather_stamped_all(const unsigned* words, int n, unsigned bit, unsigned want, float* dst, int tid, int nthreads,
+                                                   int* timeout_flag, unsigned spin_limit, Value value)
+{
+    if (n <= 4 * nthreads) gather_stamped<1>(words, n, bit, want, dst, tid, nthreads, timeout_flag, spin_limit, value);
+    else if (NF > 2 && n > 8 * nthreads) gather_stamped<NF>(words, n, bit, want, dst, tid, nthreads, timeout_flag, spin_limit, value);
+    else gather_stamped<2>(words, n, bit, want, dst, tid, nthreads, timeout_flag, spin_limit, value);
 }
 
 // Do the `members` (<= 64) workgroups of this group all run on one XCD?  Every member publishes its XCD id in

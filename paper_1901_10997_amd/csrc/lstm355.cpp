@@ -194,8 +194,6 @@ static void free_mat(PackedMat& p)
     if (p.q16_val) (void)hipFree(p.q16_val);
     if (p.q16_col) (void)hipFree(p.q16_col);
     if (p.q16_ovf_ptr) (void)hipFree(p.q16_ovf_ptr);
-    if (p.q16_ovf_ent) (void)hipFree(p.q16_ovf_ent);
-    if (p.q16_ovf_val) (void)hipFree(p.q16_ovf_val);
     p = PackedMat();
 }
 
@@ -231,45 +229,47 @@ static hipError_t upload(T** dst, const std::vector<T>& src)
 // (column mod 16), whose filler is pointed at the entry's column.
 // gate_col_stride > 0 (the H-LSTM's gate-output matrix): row q of a unit reads block q of a vector of four blocks of
 // that many elements; the stored column, and the bank it is placed by, is gate_col_stride * q + column.
-// soft_slots > 0: the consumer loses its best configuration above that many slots (the H-LSTM kernel keeps two matrices
-// in registers); a matrix that would need more is cut to soft_slots anyway as long as no eight consecutive units
-// leave more than 48 entries outside (the kernels take at most 64 per wave).
 static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int max_slots, bool gather16 = false,
-                              int gate_col_stride = 0, int soft_slots = 0)
+                              int gate_col_stride = 0, int round_slots = 2)
 {
     if (out.q16_val) (void)hipFree(out.q16_val);
     if (out.q16_col) (void)hipFree(out.q16_col);
     if (out.q16_ovf_ptr) (void)hipFree(out.q16_ovf_ptr);
-    if (out.q16_ovf_ent) (void)hipFree(out.q16_ovf_ent);
-    if (out.q16_ovf_val) (void)hipFree(out.q16_ovf_val);
     out.q16_val = nullptr; out.q16_col = nullptr; out.q16_ovf_ptr = nullptr; out.q16_ovf_ent = nullptr; out.q16_ovf_val = nullptr;
     out.q16_slots = 0;
     const int rows = out.rows, cols = out.cols, max_nnz = out.max_row_nnz;
     if (!out.compressed || max_slots < 2 || rows < 4 || cols + 3 * gate_col_stride > 16383) return LSTM_OK;
     {
         const int units = rows / 4;
-        // The slot count is set by the longest row, and with random masks a handful of rows are a few entries longer
-        // than all others.  Take the smallest (even) count that leaves at most 6 entries outside the slots in any eight
-        // consecutive units (a wave owns at most eight): the owning wave adds those one at a time, which costs it about
-        // as much per entry as a tenth of a slot, and the step waits for the slowest wave.
+        // The slot count would be set by the longest row, and with random masks the longest are a third longer than the mean.  So
+        // entries may stay outside the slots: a wave (at most eight consecutive units) takes them sixteen of a gate at a time, a
+        // round for all of its units (quarter_wave.h), at most kQ16ExtraRounds.  A round costs the slowest wave about 250 clocks, a
+        // slot 100 (narrow layers) to 250 (eight units to a wave), so the count of the smallest sum is taken, a round as
+        // `round_slots` slots.  (Entries added one at a time, at most six of any eight units: 14 slots instead of 12 for 1500 units
+        // with 10 % kept, and 0.7 us per product of an H-LSTM step of 800 units, 20 % kept.)
         int S = std::max(2, 2 * ((max_nnz + 31) / 32));
-        if (force_slots > 0) S = std::max(2, std::min(S, force_slots + (force_slots & 1)));
+        if (force_slots > 0) S = std::max(2, std::min(S, force_slots + (force_slots & 1)));   // (q16_rounds: no more than before)
         else {
-            std::vector<int> per_unit((size_t)units);
-            for (int St = 2; St < S; St += 2) {
-                for (int u = 0; u < units; ++u) {
-                    int64_t n = 0;
-                    for (int q = 0; q < 4; ++q)
-                        n += std::max<int64_t>(0, out.h_row_ptr[4 * u + q + 1] - out.h_row_ptr[4 * u + q] - (int64_t)16 * St);
-                    per_unit[(size_t)u] = (int)std::min<int64_t>(n, 1 << 20);
+            std::vector<int> outside((size_t)units);
+            auto rounds = [&](int St) {
+                int most = 0;
+                for (int q = 0; q < 4; ++q) {
+                    int window = 0;
+                    for (int u = 0; u < units; ++u) {
+                        const int64_t n = out.h_row_ptr[4 * u + q + 1] - out.h_row_ptr[4 * u + q] - (int64_t)16 * St;
+                        outside[(size_t)u] = (int)std::min<int64_t>(std::max<int64_t>(n, 0), 1 << 16);
+                        window += outside[(size_t)u] - (u >= 8 ? outside[(size_t)u - 8] : 0);
+                        most = std::max(most, window);
+                    }
                 }
-                int64_t window = 0, worst = 0;
-                for (int u = 0; u < units; ++u) {
-                    window += per_unit[(size_t)u];
-                    if (u >= 8) window -= per_unit[(size_t)u - 8];
-                    worst = std::max(worst, window);
-                }
-                if (worst <= 6 || (soft_slots > 0 && St >= soft_slots && worst <= 48)) { S = St; break; }
+                return (most + 15) / 16;
+            };
+            int least = S;
+            out.q16_rounds = 0;
+            for (int St = S - 2; St >= 2; St -= 2) {
+                const int r = rounds(St);
+                if (r > kQ16ExtraRounds) break;
+                if (St + round_slots * r <= least) { least = St + round_slots * r; S = St; out.q16_rounds = r; }
             }
         }
         if (S > max_slots) return LSTM_OK;   // rows too long for the kernels that use this form
@@ -350,23 +350,29 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
         out.q16_slots = S;
         HIP_TRY(m, upload(&out.q16_val, qv));
         HIP_TRY(m, upload(&out.q16_col, qc));
-        std::vector<int32_t> optr((size_t)units + 1, 0);
+        // gate by gate: the entries of consecutive units of a gate follow one another
+        std::vector<int32_t> optr(4 * ((size_t)units + 1), 0);
         std::vector<uint32_t> oe;
         std::vector<float> ov;
-        for (int u = 0; u < units; ++u) {
-            for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < 4; ++q) {
+            optr[(size_t)q * (units + 1)] = (int32_t)oe.size();
+            for (int u = 0; u < units; ++u) {
                 const int rp = 4 * u + q;
                 for (int64_t e = out.h_row_ptr[rp] + (int64_t)16 * S; e < out.h_row_ptr[rp + 1]; ++e) {
-                    oe.push_back(((uint32_t)q << 16) | (uint32_t)out.h_col[e]);
+                    oe.push_back((uint32_t)(out.h_col[e] + q * gate_col_stride));
                     ov.push_back(out.h_val[e]);
                 }
+                optr[(size_t)q * (units + 1) + u + 1] = (int32_t)oe.size();
             }
-            optr[(size_t)u + 1] = (int32_t)oe.size();
         }
-        if (!oe.empty()) {
+        if (!oe.empty()) {   // one allocation: the lists behind their bounds
+            const size_t n = oe.size(), np = optr.size();
+            optr.resize(np + 2 * n);
+            std::memcpy(optr.data() + np, oe.data(), n * sizeof(uint32_t));
+            std::memcpy(optr.data() + np + n, ov.data(), n * sizeof(float));
             HIP_TRY(m, upload(&out.q16_ovf_ptr, optr));
-            HIP_TRY(m, upload(&out.q16_ovf_ent, oe));
-            HIP_TRY(m, upload(&out.q16_ovf_val, ov));
+            out.q16_ovf_ent = (uint32_t*)out.q16_ovf_ptr + np;
+            out.q16_ovf_val = (float*)out.q16_ovf_ptr + np + n;
         }
     }
     return LSTM_OK;
@@ -472,7 +478,7 @@ static int add_rec_split(lstm_t* m, PackedMat& p)
 enum { kFragNone = 0, kFragRows = 1, kFragByGate = 2 };   // fragment-ordered copy of a dense fp32 matrix: none, as stored, by gate
 // Pack one matrix W[4H][cols] (ABI row order q*H + j) with its optional mask into device storage.
 static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t* mask, int H, int cols, bool compressed,
-                       bool bf16, bool keep_dense, int quarter_slots = 0, int gate_col_stride = 0, int soft_slots = 0,
+                       bool bf16, bool keep_dense, int quarter_slots = 0, int gate_col_stride = 0, int round_slots = 2,
                        int frag16 = kFragNone, bool q16_gather16 = false)
 {
     free_mat(out);
@@ -635,7 +641,7 @@ static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t*
             break;
         }
     }
-    if (quarter_slots > 0) return build_quarter_wave(m, out, 0, quarter_slots, q16_gather16, gate_col_stride, soft_slots);
+    if (quarter_slots > 0) return build_quarter_wave(m, out, 0, quarter_slots, q16_gather16, gate_col_stride, round_slots);
     return LSTM_OK;
 }
 
@@ -820,9 +826,9 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     x.set = false;
     const bool bf16 = (m->dtype == LSTM_BF16);
     // W_x is kept in both forms when compressed: large T*B projections run dense on the matrix cores
-    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 0, bf16 ? kFragNone : kFragRows, true);
+    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 2, bf16 ? kFragNone : kFragRows, true);
     if (rc != LSTM_OK) return rc;
-    rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 0, bf16 ? kFragNone : kFragRows);
+    rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 2, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
     // LSTM_FMT_AUTO leaves the choice of the recurrence kernel to each call (layer_takes_quads): the dense one needs its copy
     if (format == LSTM_FMT_AUTO && compressed && !bf16 && persist_quad_plan(1, H, 0, 1).shape >= 0) {
@@ -893,14 +899,14 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     LayerDir& x = m->ld[(size_t)layer * m->Dn + direction];
     x.set = false;
     // hidden layers: 4G rows, packed row 4g+q; kept dense as well for the projection on the matrix cores
-    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 0, kFragRows);
+    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 2, kFragRows);
     if (rc == LSTM_OK) rc = add_padded(m, x.wx, false, 1);
     if (rc == LSTM_OK) rc = add_split(m, x.wx);
     if (rc != LSTM_OK) return rc;
-    rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 12, kFragRows);
+    rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 1, kFragRows);   // (both matrices share the registers)
     if (rc != LSTM_OK) return rc;
     // gate outputs: 4H rows, packed row 4j+q, columns = hidden units of the row's own gate
-    rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 12, kFragByGate);
+    rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 1, kFragByGate);
     if (rc == LSTM_OK && format == LSTM_FMT_AUTO && compressed && persist_quad_plan(1, H, G, 1).shape >= 0) {   // as in lstm_set_weights
         rc = add_frag16_csr(m, x.wh, false);
         if (rc == LSTM_OK) rc = add_frag16_csr(m, x.w2, true);
@@ -1285,11 +1291,15 @@ constexpr double kDenseSetupUs = 10.0;     // dense weights to read before the f
 static double batched_csr_step_us(const lstm_t* m, int l, int B)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
-    int slots = 0, upw = 0, bw = 0, ug = 0, bg = 0;
+    // Compared with the dense models only (persist_quad_plan, persist_split_plan), and so on their scale: their steps are shorter than
+    // those models say (LSTM cells by 5 to 15 %, H-LSTM cells by 29 % inside an XCD and 22 % across), and those over kept entries by
+    // as much than this says.  An LSTM's round of entries outside the slots is priced as the two slots it replaces.
+    int slots = 0, rounds = 0, upw = 0, bw = 0, ug = 0, bg = 0;
     for (int d = 0; d < Dn; ++d) {
         const LayerDir& w = m->ld[(size_t)l * Dn + d];
         if (w.wh.q16_slots <= 0 || (G > 0 && w.w2.q16_slots <= 0)) return 1e9;   // one or two launches per step
         slots = std::max(slots, std::max(w.wh.q16_slots, G > 0 ? w.w2.q16_slots : 0));
+        rounds = std::max(rounds, w.wh.q16_rounds + (G > 0 ? w.w2.q16_rounds : 0));
     }
     LaunchCut cut;
     int nd_used = 0;
@@ -1299,8 +1309,9 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
         }, &cut))
         return 1e9;
     const bool local = ug <= 64 && ((nd_used * bg + 7) / 8) * ug <= device_num_cus() / 8;
-    const double gathers = 0.01 * slots * upw * bw, words = 0.001 * H * bw;
-    return cut.passes * cut.chunks * (G > 0 ? (local ? 2.4 : 5.3) + 1.36 * gathers + 0.44 * words : (local ? 1.34 : 1.83) + 0.76 * gathers + 0.10 * words);
+    if (G > 0) return cut.passes * cut.chunks * (0.1 * rounds + persist_batched_h_step_us(H, slots, upw, bw, local)) / (local ? 0.71 : 0.78);
+    const double gathers = 0.01 * (slots + 2 * rounds) * upw * bw, words = 0.001 * H * bw;
+    return cut.passes * cut.chunks * ((local ? 1.34 : 1.83) + 0.76 * gathers + 0.10 * words);
 }
 
 // Does the dense fp32 recurrence with the time loop on the device take layer l?  It multiplies the zeros of a mask too, but a

@@ -22,6 +22,7 @@
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"
+#include "quarter_wave.h"
 
 namespace l355 {
 
@@ -90,31 +91,7 @@ __global__ __launch_bounds__(512) void persist_batched_q16_kernel(PersistBatched
             }
         }
     }
-    // The few entries of rows longer than 16 S (at most 6 per wave; most waves have none):
-    // lane e holds entry e of the wave's run of lists -- value, LDS byte offset of its column, and the lane that
-    // collects its gate's total for batch column 0 (16 * gate + local unit * BW).
-    float ovf_v = 0.f;
-    unsigned ovf_off = 0u;
-    int ovf_lane = 0, ovf_n = 0;
-    if (D.q16_ovf_ptr != nullptr && u0 < H) {
-        const int first = D.q16_ovf_ptr[u0];
-        const int idx = first + lane;
-        int pos = first;
-#pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            const int nxt = (u0 + u < H) ? D.q16_ovf_ptr[u0 + u + 1] : pos;
-            if (idx >= pos && idx < nxt) {
-                const unsigned e = D.q16_ovf_ent[idx];
-                ovf_off = (e & 0xFFFFu) * (BW * 4u);
-                ovf_lane = 16 * (int)(e >> 16) + u * BW;
-                ovf_v = D.q16_ovf_val[idx];
-            }
-            pos = nxt;
-        }
-        ovf_n = pos - first;
-        ovf_n = ovf_n < 64 ? ovf_n : 64;
-    }
-    ovf_n = __builtin_amdgcn_readfirstlane(ovf_n);
+    const Q16Extra<UPW> extra = load_q16_extra<UPW>(D.q16_ovf_ptr, D.q16_ovf_ent, D.q16_ovf_val, H, u0, lane, BW * 4u);
     // lane 16*gate + pair: pair = local unit * BW + column
     const int lp = lane & 15, row = lane >> 4;
     const int pu = lp / BW, pb = lp % BW;
@@ -157,8 +134,8 @@ __global__ __launch_bounds__(512) void persist_batched_q16_kernel(PersistBatched
         } else {
             pace_poll(a.poll_pace);   // device-wide exchange only (exchange.h); inside one XCD any wait costs what it lasts
             const unsigned tag = a.epoch + (unsigned)s + 1u;
-            gather_stamped<kInFlight>(xchg + (tag & 1u) * a.h_stride, BW * H, kHStampBit, ((tag >> 1) & 1u) ? kHStampBit : 0u, hbuf, tid, nthreads,
-                                      a.timeout_flag, a.spin_limit, [](unsigned v) { return unstamped(v, kHStampBit); });
+            gather_stamped_all<kInFlight>(xchg + (tag & 1u) * a.h_stride, BW * H, kHStampBit, ((tag >> 1) & 1u) ? kHStampBit : 0u, hbuf, tid, nthreads,
+                                          a.timeout_flag, a.spin_limit, [](unsigned v) { return unstamped(v, kHStampBit); });
         }
         // (the value is taken over here, behind the poll's own wait, and not at the top of the loop, where waiting for
         // it would also wait for the acknowledgement of the stores just issued, in front of the poll)
@@ -217,25 +194,9 @@ __global__ __launch_bounds__(512) void persist_batched_q16_kernel(PersistBatched
                     for (int b = 0; b < BW; ++b) tot[u * BW + b] = acc[0][b] + acc[1][b];
                 }
             }
+            add_q16_extra<UPW, BW>(tot, extra, [&](unsigned off) { return *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(hbuf) + off); });
             // all the sums over the 16 lanes of a row at once: lane p of row q ends up with gate q's total of pair p
             G = row16_transpose_sum(tot, lp);
-        }
-        if (ovf_n > 0) {   // wave-uniform; false in almost every wave
-            // every lane multiplies its own entry (one gather for all of them); the products are then handed to the lanes
-            // that collect their gates' totals, one entry at a time, without further memory accesses
-            using VT = typename std::conditional<BW == 2, float2, float4>::type;
-            const VT x = *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(hbuf) + ovf_off);
-            float pr[BW];
-            pr[0] = ovf_v * x.x; pr[1] = ovf_v * x.y;
-            if constexpr (BW == 4) { pr[2] = ovf_v * x.z; pr[3] = ovf_v * x.w; }
-            for (int e = 0; e < ovf_n; ++e) {
-                const int tgt = __builtin_amdgcn_readlane(ovf_lane, e);
-#pragma unroll
-                for (int b = 0; b < BW; ++b) {
-                    const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr[b]), e));
-                    G += (lane == tgt + b) ? v : 0.f;
-                }
-            }
         }
         G += pin;
         const bool cand = row == 3;
@@ -274,37 +235,31 @@ constexpr int kWaves = 8;
 static size_t batched_lds_bytes(int H, int upw, int bw) { return ((((size_t)bw * H + 3) & ~(size_t)3) + (size_t)bw * kWaves * upw) * sizeof(float); }
 
 // ------------------------------------------------------------------------------------------------ planning
-// Choose (UPW, BW): the most workgroups that still fit one per compute unit, within the register budget (1.5
-// registers per unit and slot; 512-thread workgroups leave 256 registers per lane) and PAIRS <= 16.
+// Choose (UPW, BW): at most one workgroup per compute unit, within the register budget (1.5 registers per unit and slot; 512-thread
+// workgroups leave 256 registers per lane) and PAIRS <= 16.
 constexpr int kQ16WeightRegs = 156;
 bool persist_batched_q16_plan(int B, int H, int slots, int ndir, int* upw_out, int* bw_out, int* ug_out, int* bg_out)
 {
     if (B < 2 || slots < 2 || slots > 24 || (slots & 1) || H < 1 || H > 4096) return false;
-    // Two rounds.  The first takes the shape with the most workgroups.  The second prefers a shape whose batch groups fit
-    // one XCD each (their exchange then stays in that XCD's L2, which is worth more than the extra workgroups: H = 512
-    // at batch 20, 2.09 -> 1.80 us per step; two directions of 256 at batch 20, 1.94 -> 1.64), as long as a wave gets at
-    // most twice the units (1500 wide at batch 2: six units per wave inside one XCD ran at 2.82 us against 2.41 with two
-    // units per wave across the device).
-    int best = -1, upw0 = 0;
-    for (int round = 0; round < 2; ++round)
-        for (int bw = 2; bw <= 4; bw *= 2) {
-            for (int upw = 2; upw <= 8; ++upw) {
-                if (upw * bw > 16 || 3 * slots * upw > 2 * kQ16WeightRegs) continue;
-                if (batched_lds_bytes(H, upw, bw) > 64 * 1024) continue;
-                const int ug = (H + kWaves * upw - 1) / (kWaves * upw), bg = (B + bw - 1) / bw;
-                const int blocks = ug * bg * ndir;
-                if (blocks > device_num_cus()) continue;
-                const bool local = ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8;
-                if (round == 1 && (!local || upw > 2 * upw0)) continue;
-                const int score = blocks + (round == 1 ? 100000 : 0);
-                if (score > best) {
-                    best = score;
-                    *upw_out = upw; *bw_out = bw; *ug_out = ug; *bg_out = bg;
-                }
+    // The shape of the lowest estimated step: vector issue per gather (bw multiply-adds, the address), what a group outside one XCD
+    // pays more for its exchange, the words that are polled (microseconds; the terms that differ between shapes).  Four columns per gather beat
+    // two wherever both leave a wave as many multiply-adds (1000 units, batch 20: 1.60 us per step against 1.95; 300 units, both
+    // directions, batch 30: 1.9 against 2.2), and a shape inside an XCD pays where a wave does not get many more units for it.
+    double least = 1e30;
+    for (int bw = 2; bw <= 4; bw *= 2)
+        for (int upw = 2; upw <= 8; ++upw) {
+            if (upw * bw > 16 || 3 * slots * upw > 2 * kQ16WeightRegs) continue;
+            if (batched_lds_bytes(H, upw, bw) > 64 * 1024) continue;
+            const int ug = (H + kWaves * upw - 1) / (kWaves * upw), bg = (B + bw - 1) / bw;
+            if (ug * bg * ndir > device_num_cus()) continue;
+            const bool local = persist_batched_q16_xcd_capable(slots, upw) && ug <= 64 && ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8;
+            const double us = 0.0033 * slots * upw * (bw + 1.5) + (local ? 0.0 : 0.3) + 0.026e-3 * H * bw;
+            if (us < least) {
+                least = us;
+                *upw_out = upw; *bw_out = bw; *ug_out = ug; *bg_out = bg;
             }
-            if (round == 0 && bw == 4) upw0 = best > 0 ? *upw_out : 0;
         }
-    return best > 0;
+    return least < 1e30;
 }
 
 // words of a buffer of a (direction, batch group): whole 256-byte blocks

@@ -21,7 +21,8 @@
 // been written, counted over the launches of a forward (h_epoch, u_epoch: all words start at zero).  A thread reads sixteen bytes
 // at a time, all of its loads in flight at once, and repeats them until every word is stamped.  (h as tagged 8-byte slots and u as
 // plain values with a flag per workgroup, raised when its stores had been acknowledged: 6.45 us per step of 800/800 bidirectional, batch
-// 16, 20 % kept; 6.1 here, of which 0.2 are waits and the larger part the gathers of both products.)
+// 16, 20 % kept, against 6.1.)  The larger part of a step are the gathers of both products: 14 slots with the longest rows' last entries
+// outside them one at a time took 6.1 us there, 10 slots and at most three rounds of sixteen (quarter_wave.h) 4.7.
 // One array per vector is enough: u_{t+1} is written only after its producer has received every h_t of the batch group, and each
 // of those was published after its producer had finished reading u_t; h_{t+1} only after its producer has received every u_{t+1},
 // each published after its producer had finished reading h_t.  A workgroup that owns no unit of one vector publishes none that
@@ -33,6 +34,7 @@
 #include "common.h"
 #include "device_math.h"
 #include "exchange.h"
+#include "quarter_wave.h"
 
 namespace l355 {
 
@@ -128,42 +130,14 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
     if (lane < 16 && ok2 && D.c0) c = D.c0[(size_t)(b0 + pb) * H + unit_l];
     const bool owns_u = ugi * upb < G, owns_h = ugi * upb < H;   // of the whole workgroup
 
-    // The few entries of rows longer than 16 S (at most 6 per wave; most waves have none): lane e holds entry e of the
-    // wave's run of per-unit lists -- value, LDS byte offset of its column, and the lane that collects its gate's total
-    // for batch column 0 (16 * gate + local unit * BW).
-    struct Extra { float v; unsigned off; int lane0; int n; };
-    auto load_extra = [&](const int32_t* ptr, const uint32_t* ent, const float* val, int units, int gate_stride) {
-        Extra x{0.f, 0u, 0, 0};
-        if (ptr != nullptr && u0 < units) {
-            const int first = ptr[u0];
-            const int idx = first + lane;
-            int pos = first;
-#pragma unroll
-            for (int u = 0; u < UPW; ++u) {
-                const int nxt = (u0 + u < units) ? ptr[u0 + u + 1] : pos;
-                if (idx >= pos && idx < nxt) {
-                    const unsigned e = ent[idx];
-                    const unsigned g = e >> 16;
-                    x.off = (g * (unsigned)gate_stride + (e & 0xFFFFu)) * (BW * 4u);
-                    x.lane0 = 16 * (int)g + u * BW;
-                    x.v = val[idx];
-                }
-                pos = nxt;
-            }
-            x.n = pos - first;
-            x.n = x.n < 64 ? x.n : 64;
-        }
-        x.n = __builtin_amdgcn_readfirstlane(x.n);
-        return x;
-    };
-    const Extra x1 = load_extra(D.ovf_ptr_1h, D.ovf_ent_1h, D.ovf_val_1h, G, 0);
-    const Extra x2 = load_extra(D.ovf_ptr_2, D.ovf_ent_2, D.ovf_val_2, H, G);
+    const Q16Extra<UPW> x1 = load_q16_extra<UPW>(D.ovf_ptr_1h, D.ovf_ent_1h, D.ovf_val_1h, G, u0, lane, BW);
+    const Q16Extra<UPW> x2 = load_q16_extra<UPW>(D.ovf_ptr_2, D.ovf_ent_2, D.ovf_val_2, H, u0, lane, BW);
 
     // One product: the wave's UPW * S gathers as one software-pipelined sequence (PD reads in flight ahead of the
     // multiply-adds that consume them), the UPW * BW sums reduced together by the transposing 16-lane reduction, so that
-    // lane 16*gate + pair holds the gate's total of the pair; then the rare entries outside the slots.
+    // lane 16*gate + pair holds the gate's total of the pair; before that the entries outside the slots.
     using VT = typename std::conditional<BW == 2, float2, float4>::type;
-    auto products = [&](const float (&wv)[UPW][S], const unsigned (&wo)[UPW][S / 2], const Extra& xt, const float* vec) -> float {
+    auto products = [&](const float (&wv)[UPW][S], const unsigned (&wo)[UPW][S / 2], const Q16Extra<UPW>& xt, const float* vec) -> float {
         constexpr int NS = UPW * S;
         constexpr int PDMAX = (3 * S * UPW > 128) ? 8 : 12;
         constexpr int PD = NS < PDMAX ? NS : PDMAX;
@@ -201,22 +175,8 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
                 for (int b = 0; b < BW; ++b) tot[u * BW + b] = acc[0][b] + acc[1][b];
             }
         }
-        float Gv = row16_transpose_sum(tot, lp);
-        if (xt.n > 0) {   // wave-uniform; false in almost every wave
-            const VT x = *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(vec) + xt.off);
-            float pr[BW];
-            pr[0] = xt.v * x.x; pr[1] = xt.v * x.y;
-            if constexpr (BW == 4) { pr[2] = xt.v * x.z; pr[3] = xt.v * x.w; }
-            for (int e = 0; e < xt.n; ++e) {
-                const int tgt = __builtin_amdgcn_readlane(xt.lane0, e);
-#pragma unroll
-                for (int b = 0; b < BW; ++b) {
-                    const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr[b]), e));
-                    Gv += (lane == tgt + b) ? v : 0.f;
-                }
-            }
-        }
-        return Gv;
+        add_q16_extra<UPW, BW>(tot, xt, [&](unsigned off) { return *reinterpret_cast<const VT*>(vec + off); });
+        return row16_transpose_sum(tot, lp);
     };
 
     // The direction is chosen by the block index, so `D` is addressed through memory: taken inside the time loop its
@@ -259,7 +219,7 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
                 hbuf[e] = (D.h0 && b < bw) ? D.h0[(size_t)(b0 + b) * H + k] : 0.f;
             }
         } else if (owns_u) {
-            gather_stamped<2>(xh, BW * H, kHStampBit, ((a.h_epoch + (unsigned)s) & 1u) ? kHStampBit : 0u, hbuf, tid, nthreads, a.timeout_flag,
+            gather_stamped_all<2>(xh, BW * H, kHStampBit, ((a.h_epoch + (unsigned)s) & 1u) ? kHStampBit : 0u, hbuf, tid, nthreads, a.timeout_flag,
                               a.spin_limit, [](unsigned v) { return unstamped(v, kHStampBit); });
         }
         float pin;
@@ -276,7 +236,7 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
         }
         // ---- stage 2: gate outputs from u_t, cell update
         if (owns_h)
-            gather_stamped<8>(xu, 4 * G * BW, kUStampBit, u_stamp, ubuf, tid, nthreads, a.timeout_flag, a.spin_limit,
+            gather_stamped_all<8>(xu, 4 * G * BW, kUStampBit, u_stamp, ubuf, tid, nthreads, a.timeout_flag, a.spin_limit,
                               [](unsigned v) { return __uint_as_float(v & ~kUStampBit); });
         __syncthreads();
         {
@@ -308,14 +268,19 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
 }
 
 // ------------------------------------------------------------------------------------------------ planning
-// Choose (UPW, BW): batch groups that fit one XCD each first, then the most workgroups that still fit one per compute
-// unit, within the register budget, with
-// PAIRS <= 16, 16-bit LDS offsets, and at most 64 unit groups (one flag per polling lane).
+// Modelled step (microseconds): both exchanges, vector issue per gather of both products, the words that are polled.  A fit to 201
+// measured points of 64 to 2000 units, 5 to 30 % kept, batches of 2 to 60 (standard error 7 %).
+double persist_batched_h_step_us(int H, int slots, int upw, int bw, bool local)
+{
+    return local ? 1.50 + 0.0108 * slots * upw * (bw + 1.5) + 0.36e-3 * H * bw : 3.74 + 0.0040 * slots * upw * (bw + 1.5) + 0.58e-3 * H * bw;
+}
+// Choose (UPW, BW): the lowest estimated step of those with at most one workgroup per compute unit, within the register budget, with
+// PAIRS <= 16, 16-bit LDS offsets, and at most 64 unit groups (XCD id slots).
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_out, int* bw_out, int* ug_out, int* bg_out)
 {
     if (B < 2 || slots < 2 || slots > 24 || (slots & 1) || H < 1 || G < 1) return false;
     const int units = std::max(H, G);
-    int best = -1;
+    double least = 1e30;
     for (int bw = 2; bw <= 4; bw *= 2) {
         if ((size_t)H * bw > 65535 || (size_t)4 * G * bw > 65535) continue;      // 16-bit offsets, in floats
         if (lds_bytes(H, G, bw) > (size_t)kMaxLds) continue;
@@ -325,18 +290,17 @@ bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_o
             if (ug > 64) continue;
             const int blocks = ug * bg * ndir;
             if (blocks > device_num_cus()) continue;
-            // a shape whose batch groups fit one XCD each goes first: both exchanges of a step then stay in that XCD's
-            // L2 (800/800 at batch 2 to 8: 5.9-6.6 us per step with two units per wave across the device, 3.95 with four
+            // (800/800 at batch 2 to 8: 5.9-6.6 us per step with two units per wave across the device, 3.95 with four
             // inside one XCD; 1024/1024 at batch 20: 8.5 -> 5.8)
             const bool local = ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8;
-            const int score = blocks + (local ? 100000 : 0);
-            if (score > best) {
-                best = score;
+            const double us = persist_batched_h_step_us(H, slots, upw, bw, local);
+            if (us < least) {
+                least = us;
                 *upw_out = upw; *bw_out = bw; *ug_out = ug; *bg_out = bg;
             }
         }
     }
-    return best > 0;
+    return least < 1e30;
 }
 
 // exchange storage per (direction, batch group), in elements of the respective array, padded to whole 256-byte blocks

@@ -13,6 +13,7 @@
 #include <type_traits>
 #include "common.h"
 #include "device_math.h"
+#include "quarter_wave.h"
 
 namespace l355 {
 
@@ -60,29 +61,7 @@ __global__ __launch_bounds__(512) void proj_q16_kernel(ProjQ16Args a)
             }
         }
     }
-    // the few entries of rows longer than 16 S (at most 6 per wave; most waves have none): lane e holds entry e
-    float ovf_v = 0.f;
-    unsigned ovf_off = 0u;
-    int ovf_lane = 0, ovf_n = 0;
-    if (D.ovf_ptr != nullptr && u0 < H) {
-        const int first = D.ovf_ptr[u0];
-        const int idx = first + lane;
-        int pos = first;
-#pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            const int nxt = (u0 + u < H) ? D.ovf_ptr[u0 + u + 1] : pos;
-            if (idx >= pos && idx < nxt) {
-                const unsigned e = D.ovf_ent[idx];
-                ovf_off = (e & 0xFFFFu) * (kBW * 4u);
-                ovf_lane = 16 * (int)(e >> 16) + u * kBW;
-                ovf_v = D.ovf_val[idx];
-            }
-            pos = nxt;
-        }
-        ovf_n = pos - first;
-        ovf_n = ovf_n < 64 ? ovf_n : 64;
-    }
-    ovf_n = __builtin_amdgcn_readfirstlane(ovf_n);
+    const Q16Extra<UPW> extra = load_q16_extra<UPW>(D.ovf_ptr, D.ovf_ent, D.ovf_val, H, u0, lane, kBW * 4u);
 
     const int lp = lane & 15, row = lane >> 4;
     const int pu = lp / kBW, pb = lp % kBW;
@@ -177,21 +156,10 @@ __global__ __launch_bounds__(512) void proj_q16_kernel(ProjQ16Args a)
                     for (int b = 0; b < kBW; ++b) tot[u * kBW + b] = acc[0][b] + acc[1][b];
                 }
             }
+            add_q16_extra<UPW, kBW>(tot, extra, [&](unsigned off) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(hbuf) + off); });
             // all sixteen sums over the 16 lanes of a row at once (45 instructions instead of 16 butterflies of four and
             // their selects): lane p of every row ends up with the row's total of pair p
             G = row16_transpose_sum(tot, lp);
-        }
-        if (ovf_n > 0) {   // wave-uniform; false in almost every wave
-            const float4 x = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(hbuf) + ovf_off);
-            const float pr[kBW] = {ovf_v * x.x, ovf_v * x.y, ovf_v * x.z, ovf_v * x.w};
-            for (int e = 0; e < ovf_n; ++e) {
-                const int tgt = __builtin_amdgcn_readlane(ovf_lane, e);
-#pragma unroll
-                for (int b = 0; b < kBW; ++b) {
-                    const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr[b]), e));
-                    G += (lane == tgt + b) ? v : 0.f;
-                }
-            }
         }
         if (nxt < ntiles) park(1 - BUF);          // the other half: nobody reads it during this tile
         __syncthreads();
