@@ -1298,7 +1298,7 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
     for (int d = 0; d < Dn; ++d) {
         const LayerDir& w = m->ld[(size_t)l * Dn + d];
         if (w.wh.q16_slots <= 0 || (G > 0 && w.w2.q16_slots <= 0)) return 1e9;   // one or two launches per step
-        slots = std::max(slots, std::max(w.wh.q16_slots, G > 0 ? w.w2.q16_slots : 0));
+        slots = std::max(slots, G > 0 ? std::max(w.wh.q16_slots, w.w2.q16_slots) : std::min(24, w.wh.q16_slots + 2 * w.wh.q16_rounds));
         rounds = std::max(rounds, w.wh.q16_rounds + (G > 0 ? w.w2.q16_rounds : 0));
     }
     LaunchCut cut;
@@ -1310,7 +1310,7 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
         return 1e9;
     const bool local = ug <= 64 && ((nd_used * bg + 7) / 8) * ug <= device_num_cus() / 8;
     if (G > 0) return cut.passes * cut.chunks * (0.1 * rounds + persist_batched_h_step_us(H, slots, upw, bw, local)) / (local ? 0.71 : 0.78);
-    const double gathers = 0.01 * (slots + 2 * rounds) * upw * bw, words = 0.001 * H * bw;
+    const double gathers = 0.01 * slots * upw * bw, words = 0.001 * H * bw;
     return cut.passes * cut.chunks * ((local ? 1.34 : 1.83) + 0.76 * gathers + 0.10 * words);
 }
 
