@@ -1734,6 +1734,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 continue;
             }
         }
+        hlayout[0] = 0;   // the step kernels write plain u over the words: an even number of writes to who looks at the stamp
         // small batch, every direction row-compressed: both stages of a step for all directions in two launches
         bool pair_ok = B >= 1;
         {
