@@ -3,6 +3,7 @@
 #include "../../include/lstm355.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -264,9 +265,9 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
                 }
                 return (most + 15) / 16;
             };
-            int least = S;
+            int least = S > max_slots ? INT_MAX : S;   // (rows that only a form with rounds can hold take it at any price)
             out.q16_rounds = 0;
-            for (int St = S - 2; St >= 2; St -= 2) {
+            for (int St = std::min(S - 2, max_slots & ~1); St >= 2; St -= 2) {
                 const int r = rounds(St);
                 if (r > kQ16ExtraRounds) break;
                 if (St + round_slots * r <= least) { least = St + round_slots * r; S = St; out.q16_rounds = r; }

@@ -86,3 +86,27 @@ def test_infinite_weight_stays_in_its_unit(H, G):
     for a, b in zip(after, before):
         np.testing.assert_array_equal(a[..., others], b[..., others])
     assert not np.array_equal(after[0][..., units - 2], before[0][..., units - 2])
+
+
+def _long_rows(mask, units, gate, first, rows, entries):
+    m = mask.reshape(4, units, -1)
+    m[gate, first:first + rows] = 0
+    m[gate, first:first + rows, :entries] = 1
+
+
+@pytest.mark.parametrize("name", ["h1", "2"])
+def test_rows_that_only_rounds_can_hold(name):
+    """Rows of 400 entries, 16 more than the most slots hold, three of a gate side by side: three rounds, and the recurrence takes them
+    as it takes shorter ones, also where it is asked for."""
+    H, G = 420, 410
+    case = _case(1, False, 24, H, 5, 3, 32, 0, G)
+    v = case.weights[(0, 0)]
+    if name == "h1":
+        _long_rows(v["M1h"], G, 1, 200, 3, 400)
+        v["W1h"][G + 200:G + 203] *= 0.3
+    else:
+        _long_rows(v["M2"], H, 3, H - 3, 3, 400)
+        v["W2"][4 * H - 3:] *= 0.3
+    for plan in (B.LSTM_PLAN_AUTO, B.LSTM_PLAN_PERSISTENT):
+        desc, _ = check_case(case, CSR, plan)
+        assert "rec=persist_batched-hlstm-csr+ovf(s24," in desc, desc
