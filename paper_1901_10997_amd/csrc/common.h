@@ -59,7 +59,7 @@ struct PackedMat {
     int32_t* q16_ovf_ptr = nullptr;   // device [4][rows/4 + 1]
     uint32_t* q16_ovf_ent = nullptr;  // inside that allocation
     float* q16_ovf_val = nullptr;
-    int q16_rounds = 0;               // most rounds of any eight units (quarter_wave.h)
+    int q16_rounds = 0;               // most rounds of any eight units at q16_slots (quarter_wave.h)
     // host copy of the compressed structure in packed row order (for read-back)
     std::vector<int64_t> h_row_ptr;
     std::vector<int32_t> h_col;

@@ -237,7 +237,7 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
     if (out.q16_col) (void)hipFree(out.q16_col);
     if (out.q16_ovf_ptr) (void)hipFree(out.q16_ovf_ptr);
     out.q16_val = nullptr; out.q16_col = nullptr; out.q16_ovf_ptr = nullptr; out.q16_ovf_ent = nullptr; out.q16_ovf_val = nullptr;
-    out.q16_slots = 0;
+    out.q16_slots = out.q16_rounds = 0;
     const int rows = out.rows, cols = out.cols, max_nnz = out.max_row_nnz;
     if (!out.compressed || max_slots < 2 || rows < 4 || cols + 3 * gate_col_stride > 16383) return LSTM_OK;
     {
@@ -248,29 +248,28 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
         // slot 100 (narrow layers) to 250 (eight units to a wave), so the count of the smallest sum is taken, a round as
         // `round_slots` slots.  (Entries added one at a time, at most six of any eight units: 14 slots instead of 12 for 1500 units
         // with 10 % kept, and 0.7 us per product of an H-LSTM step of 800 units, 20 % kept.)
-        int S = std::max(2, 2 * ((max_nnz + 31) / 32));
-        if (force_slots > 0) S = std::max(2, std::min(S, force_slots + (force_slots & 1)));   // (q16_rounds: no more than before)
-        else {
-            std::vector<int> outside((size_t)units);
-            auto rounds = [&](int St) {
-                int most = 0;
-                for (int q = 0; q < 4; ++q) {
-                    int window = 0;
-                    for (int u = 0; u < units; ++u) {
-                        const int64_t n = out.h_row_ptr[4 * u + q + 1] - out.h_row_ptr[4 * u + q] - (int64_t)16 * St;
-                        outside[(size_t)u] = (int)std::min<int64_t>(std::max<int64_t>(n, 0), 1 << 16);
-                        window += outside[(size_t)u] - (u >= 8 ? outside[(size_t)u - 8] : 0);
-                        most = std::max(most, window);
-                    }
+        std::vector<int> outside((size_t)units);
+        auto rounds = [&](int St) {
+            int most = 0;
+            for (int q = 0; q < 4; ++q) {
+                int window = 0;
+                for (int u = 0; u < units; ++u) {
+                    const int64_t n = out.h_row_ptr[4 * u + q + 1] - out.h_row_ptr[4 * u + q] - (int64_t)16 * St;
+                    outside[(size_t)u] = (int)std::min<int64_t>(std::max<int64_t>(n, 0), 1 << 16);
+                    window += outside[(size_t)u] - (u >= 8 ? outside[(size_t)u - 8] : 0);
+                    most = std::max(most, window);
                 }
-                return (most + 15) / 16;
-            };
+            }
+            return (most + 15) / 16;
+        };
+        int S = std::max(2, 2 * ((max_nnz + 31) / 32));
+        if (force_slots > 0) S = std::max(2, std::min(S, force_slots + (force_slots & 1)));
+        else {
             int least = S > max_slots ? INT_MAX : S;   // (rows that only a form with rounds can hold take it at any price)
-            out.q16_rounds = 0;
             for (int St = std::min(S - 2, max_slots & ~1); St >= 2; St -= 2) {
                 const int r = rounds(St);
                 if (r > kQ16ExtraRounds) break;
-                if (St + round_slots * r <= least) { least = St + round_slots * r; S = St; out.q16_rounds = r; }
+                if (St + round_slots * r <= least) { least = St + round_slots * r; S = St; }
             }
         }
         if (S > max_slots) return LSTM_OK;   // rows too long for the kernels that use this form
@@ -349,6 +348,7 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
             }
         }
         out.q16_slots = S;
+        out.q16_rounds = rounds(S);
         HIP_TRY(m, upload(&out.q16_val, qv));
         HIP_TRY(m, upload(&out.q16_col, qc));
         // gate by gate: the entries of consecutive units of a gate follow one another
@@ -1559,6 +1559,9 @@ static int run_quad_layer(lstm_t* m, int l, int T, int B, float* const* P, const
     return LSTM_OK;
 }
 
+// ... of entries outside the slots, in a plan's description
+static std::string rounds_text(int rounds) { return rounds > 0 ? ",r" + std::to_string(rounds) : std::string(); }
+
 // H-LSTM stack (fp32).  Per layer and direction: the hidden layers' input side for all timesteps as one projection
 // (P1 = W1x.x + b1, 4G rows), then per step the hidden layers (stage 1) and the gate outputs with the cell update
 // (stage 2).
@@ -1719,8 +1722,8 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                     if (chunk == 0) {
                         char cuts[24] = "";
                         if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, ",batch/%d", cut.chunks);
-                        std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-hlstm-csr%s(s%d,u%d,b%d%s);", l, d,
-                                      proj_name(d), trimmed ? "+ovf" : "", nz, upw, bw, cuts);
+                        std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-hlstm-csr%s(s%d,u%d,b%d%s%s);", l, d,
+                                      proj_name(d), trimmed ? "+ovf" : "", nz, upw, bw, rounds_text(std::max(w.wh.q16_rounds, w.w2.q16_rounds)).c_str(), cuts);
                         m->last_plan += tag;
                     }
                 }
@@ -2360,8 +2363,8 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                     if (chunk == 0) {
                         char cuts[24] = "";
                         if (cut.chunks > 1) std::snprintf(cuts, sizeof cuts, ",batch/%d", cut.chunks);
-                        std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-q16%s(s%d,u%d,b%d%s);", l, d,
-                                      proj[d], w.wh.q16_ovf_ptr ? "+ovf" : "", q16, upw, bw, cuts);
+                        std::snprintf(tag, sizeof tag, "l%d.d%d:proj=%s,rec=persist_batched-q16%s(s%d,u%d,b%d%s%s);", l, d,
+                                      proj[d], w.wh.q16_ovf_ptr ? "+ovf" : "", q16, upw, bw, rounds_text(w.wh.q16_rounds).c_str(), cuts);
                         m->last_plan += tag;
                     }
                 }

@@ -1,5 +1,7 @@
 """GPU: entries beyond a matrix's slots in the quarter-wave form, sixteen of a gate per round (quarter_wave.h), against the fp64
 oracle with the tolerances of parity_util: one to three rounds, every unit count per wave, the last units, other units' sums."""
+import re
+
 import numpy as np
 import pytest
 
@@ -110,3 +112,22 @@ def test_rows_that_only_rounds_can_hold(name):
     for plan in (B.LSTM_PLAN_AUTO, B.LSTM_PLAN_PERSISTENT):
         desc, _ = check_case(case, CSR, plan)
         assert "rec=persist_batched-hlstm-csr+ovf(s24," in desc, desc
+
+
+def test_rounds_of_a_matrix_packed_again_lstm():
+    """The shorter direction is packed again for the other's slots: nothing of it is outside them any more."""
+    case = _case(1, True, 24, 300, 5, 3, 192, 16)                                          # 12 slots and a round
+    desc, _ = check_case(case, CSR)
+    assert desc.count("+ovf(s12,") == 2 and desc.count(",r1") == 2, desc
+    case.weights[(0, 1)]["Mh"] = _mask(np.random.default_rng(1), 300, 300, 208, 0)         # 14 slots
+    desc, _ = check_case(case, CSR)
+    assert desc.count("q16(s14,") == 2 and not re.search(r",r\d", desc), desc
+
+
+def test_rounds_of_a_matrix_packed_again_hlstm():
+    case = _case(1, True, 24, 300, 5, 3, 192, 40, 300)
+    desc, _ = check_case(case, CSR)
+    assert desc.count("+ovf(s12,") == 2 and desc.count(",r3") == 2, desc
+    case.weights[(0, 1)]["M2"] = _mask(np.random.default_rng(1), 300, 300, 240, 0)         # 16 slots: all four matrices
+    desc, _ = check_case(case, CSR)
+    assert desc.count("csr(s16,") == 2 and not re.search(r",r\d", desc), desc
