@@ -55,7 +55,7 @@ struct PackedMat {
     int q16_slots = 0;            // even; 16 q16_slots entries of every row are in the slots
     float* q16_val = nullptr;
     uint16_t* q16_col = nullptr;
-    // the entries of rows longer than that (of a gate at most kQ16ExtraRounds x 16 in any eight consecutive units), gate by gate; or nullptr
+    // the entries of rows longer than that (of a gate at most 16 for each round in any eight consecutive units), gate by gate; or nullptr
     int32_t* q16_ovf_ptr = nullptr;   // device [4][rows/4 + 1]
     uint32_t* q16_ovf_ent = nullptr;  // inside that allocation
     float* q16_ovf_val = nullptr;
@@ -66,7 +66,9 @@ struct PackedMat {
     std::vector<float> h_val;
 };
 
-constexpr int kQ16ExtraRounds = 3;
+// most rounds of entries outside the slots: of the LSTM's recurrence and projection (no count with more would be taken, see
+// build_quarter_wave), and of each matrix of the H-LSTM's recurrence
+constexpr int kQ16LstmRounds = 1, kQ16HlstmRounds = 3;
 
 struct LayerDir {
     bool set = false;

@@ -231,7 +231,7 @@ static hipError_t upload(T** dst, const std::vector<T>& src)
 // gate_col_stride > 0 (the H-LSTM's gate-output matrix): row q of a unit reads block q of a vector of four blocks of
 // that many elements; the stored column, and the bank it is placed by, is gate_col_stride * q + column.
 static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int max_slots, bool gather16 = false,
-                              int gate_col_stride = 0, int round_slots = 2)
+                              int gate_col_stride = 0, int max_rounds = kQ16LstmRounds)
 {
     if (out.q16_val) (void)hipFree(out.q16_val);
     if (out.q16_col) (void)hipFree(out.q16_col);
@@ -244,10 +244,12 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
         const int units = rows / 4;
         // The slot count would be set by the longest row, and with random masks the longest are a third longer than the mean.  So
         // entries may stay outside the slots: a wave (at most eight consecutive units) takes them sixteen of a gate at a time, a
-        // round for all of its units (quarter_wave.h), at most kQ16ExtraRounds.  A round costs the slowest wave about 250 clocks, a
-        // slot 100 (narrow layers) to 250 (eight units to a wave), so the count of the smallest sum is taken, a round as
-        // `round_slots` slots.  (Entries added one at a time, at most six of any eight units: 14 slots instead of 12 for 1500 units
-        // with 10 % kept, and 0.7 us per product of an H-LSTM step of 800 units, 20 % kept.)
+        // round for all of its units (quarter_wave.h).  A round costs the slowest wave about 250 clocks, a slot 100 (narrow layers)
+        // to 250 (eight units to a wave), so the count of the smallest sum is taken.  2 p slots fewer than the longest row needs leave
+        // more than 32 (p - 1) of its entries outside, 2 p - 1 rounds: two slots for a round are the best trade for an LSTM, and
+        // more of each cost the same sum, which the H-LSTM takes, as its two matrices share the registers.  (Entries added one at
+        // a time, at most six of any eight units: 14 slots instead of 12 for 1500 units with 10 % kept, and 0.7 us per product
+        // of an H-LSTM step of 800 units, 20 % kept.)
         std::vector<int> outside((size_t)units);
         auto rounds = [&](int St) {
             int most = 0;
@@ -268,8 +270,8 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
             int least = S > max_slots ? INT_MAX : S;   // (rows that only a form with rounds can hold take it at any price)
             for (int St = std::min(S - 2, max_slots & ~1); St >= 2; St -= 2) {
                 const int r = rounds(St);
-                if (r > kQ16ExtraRounds) break;
-                if (St + round_slots * r <= least) { least = St + round_slots * r; S = St; }
+                if (r > max_rounds) break;
+                if (St + r <= least) { least = St + r; S = St; }
             }
         }
         if (S > max_slots) return LSTM_OK;   // rows too long for the kernels that use this form
@@ -479,7 +481,7 @@ static int add_rec_split(lstm_t* m, PackedMat& p)
 enum { kFragNone = 0, kFragRows = 1, kFragByGate = 2 };   // fragment-ordered copy of a dense fp32 matrix: none, as stored, by gate
 // Pack one matrix W[4H][cols] (ABI row order q*H + j) with its optional mask into device storage.
 static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t* mask, int H, int cols, bool compressed,
-                       bool bf16, bool keep_dense, int quarter_slots = 0, int gate_col_stride = 0, int round_slots = 2,
+                       bool bf16, bool keep_dense, int quarter_slots = 0, int gate_col_stride = 0, int max_rounds = kQ16LstmRounds,
                        int frag16 = kFragNone, bool q16_gather16 = false)
 {
     free_mat(out);
@@ -642,7 +644,7 @@ static int pack_matrix(lstm_t* m, PackedMat& out, const float* W, const uint8_t*
             break;
         }
     }
-    if (quarter_slots > 0) return build_quarter_wave(m, out, 0, quarter_slots, q16_gather16, gate_col_stride, round_slots);
+    if (quarter_slots > 0) return build_quarter_wave(m, out, 0, quarter_slots, q16_gather16, gate_col_stride, max_rounds);
     return LSTM_OK;
 }
 
@@ -827,9 +829,9 @@ int lstm_set_weights(lstm_t* m, int layer, int direction, const float* Wx, const
     x.set = false;
     const bool bf16 = (m->dtype == LSTM_BF16);
     // W_x is kept in both forms when compressed: large T*B projections run dense on the matrix cores
-    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, 2, bf16 ? kFragNone : kFragRows, true);
+    int rc = pack_matrix(m, x.wx, Wx, mask_x, H, D, compressed, bf16, true, bf16 ? 0 : 24, 0, kQ16LstmRounds, bf16 ? kFragNone : kFragRows, true);
     if (rc != LSTM_OK) return rc;
-    rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, 2, bf16 ? kFragNone : kFragRows);
+    rc = pack_matrix(m, x.wh, Wh, mask_h, H, H, compressed, bf16, false, kMaxRecurrentSlots, 0, kQ16LstmRounds, bf16 ? kFragNone : kFragRows);
     if (rc != LSTM_OK) return rc;
     // LSTM_FMT_AUTO leaves the choice of the recurrence kernel to each call (layer_takes_quads): the dense one needs its copy
     if (format == LSTM_FMT_AUTO && compressed && !bf16 && persist_quad_plan(1, H, 0, 1).shape >= 0) {
@@ -900,14 +902,14 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
     LayerDir& x = m->ld[(size_t)layer * m->Dn + direction];
     x.set = false;
     // hidden layers: 4G rows, packed row 4g+q; kept dense as well for the projection on the matrix cores
-    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, 2, kFragRows);
+    int rc = pack_matrix(m, x.wx, W1x, mask_1x, G, D, compressed, false, true, 0, 0, kQ16LstmRounds, kFragRows);
     if (rc == LSTM_OK) rc = add_padded(m, x.wx, false, 1);
     if (rc == LSTM_OK) rc = add_split(m, x.wx);
     if (rc != LSTM_OK) return rc;
-    rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, 1, kFragRows);   // (both matrices share the registers)
+    rc = pack_matrix(m, x.wh, W1h, mask_1h, G, H, compressed, false, false, kMaxRecurrentSlots, 0, kQ16HlstmRounds, kFragRows);
     if (rc != LSTM_OK) return rc;
     // gate outputs: 4H rows, packed row 4j+q, columns = hidden units of the row's own gate
-    rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, 1, kFragByGate);
+    rc = pack_matrix(m, x.w2, W2, mask_2, H, G, compressed, false, false, kMaxRecurrentSlots, G, kQ16HlstmRounds, kFragByGate);
     if (rc == LSTM_OK && format == LSTM_FMT_AUTO && compressed && persist_quad_plan(1, H, G, 1).shape >= 0) {   // as in lstm_set_weights
         rc = add_frag16_csr(m, x.wh, false);
         if (rc == LSTM_OK) rc = add_frag16_csr(m, x.w2, true);

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(512) void persist_batched_q16_kernel(PersistBatched
             }
         }
     }
-    const Q16Extra<UPW> extra = load_q16_extra<UPW>(D.q16_ovf_ptr, D.q16_ovf_ent, D.q16_ovf_val, H, u0, lane, BW * 4u);
+    const Q16Extra<kQ16LstmRounds> extra = load_q16_extra<UPW, kQ16LstmRounds>(D.q16_ovf_ptr, D.q16_ovf_ent, D.q16_ovf_val, H, u0, lane, BW * 4u);
     // lane 16*gate + pair: pair = local unit * BW + column
     const int lp = lane & 15, row = lane >> 4;
     const int pu = lp / BW, pb = lp % BW;

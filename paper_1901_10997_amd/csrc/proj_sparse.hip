@@ -61,7 +61,7 @@ __global__ __launch_bounds__(512) void proj_q16_kernel(ProjQ16Args a)
             }
         }
     }
-    const Q16Extra<UPW> extra = load_q16_extra<UPW>(D.ovf_ptr, D.ovf_ent, D.ovf_val, H, u0, lane, kBW * 4u);
+    const Q16Extra<kQ16LstmRounds> extra = load_q16_extra<UPW, kQ16LstmRounds>(D.ovf_ptr, D.ovf_ent, D.ovf_val, H, u0, lane, kBW * 4u);
 
     const int lp = lane & 15, row = lane >> 4;
     const int pu = lp / kBW, pb = lp % kBW;

@@ -9,27 +9,27 @@ namespace l355 {
 // be that of its longest row.  The entries that rows have beyond the slots are dealt to the lanes of their own gate instead, sixteen
 // of a gate per round whatever unit of the wave they belong to: a round is one gather, and its products join the lanes' partial
 // sums of their units.  Lane (q, i) holds entry 16 r + i of gate q in round r.
-template <int UPW>
+template <int R>   // most rounds
 struct Q16Extra {
-    float v[kQ16ExtraRounds];
-    unsigned at[kQ16ExtraRounds];   // LDS offset of the column in `scale`d units; local unit in the high half (no entry: 0xffff)
-    int rounds;                     // of the wave
+    float v[R];
+    unsigned at[R];   // LDS offset of the column in `scale`d units; local unit in the high half (no entry: 0xffff)
+    int rounds;       // of the wave
 };
 // ptr: [4][units + 1]; u0: the wave's first unit, of UPW
-template <int UPW>
-__device__ __forceinline__ Q16Extra<UPW> load_q16_extra(const int32_t* ptr, const uint32_t* ent, const float* val, int units, int u0, int lane, unsigned scale)
+template <int UPW, int R>
+__device__ __forceinline__ Q16Extra<R> load_q16_extra(const int32_t* ptr, const uint32_t* ent, const float* val, int units, int u0, int lane, unsigned scale)
 {
-    Q16Extra<UPW> x;
+    Q16Extra<R> x;
     x.rounds = 0;
 #pragma unroll
-    for (int r = 0; r < kQ16ExtraRounds; ++r) { x.v[r] = 0.f; x.at[r] = 0xffff0000u; }
+    for (int r = 0; r < R; ++r) { x.v[r] = 0.f; x.at[r] = 0xffff0000u; }
     if (ptr != nullptr && u0 < units) {
         const int32_t* const gate = ptr + (size_t)(lane >> 4) * (units + 1);
         int from[UPW + 1];
 #pragma unroll
         for (int u = 0; u <= UPW; ++u) from[u] = gate[u0 + u < units ? u0 + u : units];
 #pragma unroll
-        for (int r = 0; r < kQ16ExtraRounds; ++r) {
+        for (int r = 0; r < R; ++r) {
             const int e = from[0] + 16 * r + (lane & 15);
             const bool have = e < from[UPW];
             if (have) {
@@ -47,11 +47,11 @@ __device__ __forceinline__ Q16Extra<UPW> load_q16_extra(const int32_t* ptr, cons
 }
 // tot[u * BW + b]: the lane's partial sums; read(offset) -> the BW values of a column.  (Products of lanes without an entry and sums of
 // other units are left out, not multiplied by zero: a value may be infinite.)
-template <int UPW, int BW, class Read>
-__device__ __forceinline__ void add_q16_extra(float (&tot)[16], const Q16Extra<UPW>& x, Read read)
+template <int UPW, int BW, int R, class Read>
+__device__ __forceinline__ void add_q16_extra(float (&tot)[16], const Q16Extra<R>& x, Read read)
 {
 #pragma unroll
-    for (int r = 0; r < kQ16ExtraRounds; ++r)
+    for (int r = 0; r < R; ++r)
         if (x.rounds > r) {   // wave-uniform
             unsigned at = x.at[r];
             asm volatile("" : "+v"(at));   // unpacked here, not ahead of the time loop

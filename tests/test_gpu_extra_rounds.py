@@ -1,5 +1,6 @@
 """GPU: entries beyond a matrix's slots in the quarter-wave form, sixteen of a gate per round (quarter_wave.h), against the fp64
-oracle with the tolerances of parity_util: one to three rounds, every unit count per wave, the last units, other units' sums."""
+oracle with the tolerances of parity_util: one round (LSTM and projection; no more are ever packed) and one to three (H-LSTM), every unit
+count per wave, the last units, other units' sums."""
 import re
 
 import numpy as np
@@ -131,3 +132,15 @@ def test_rounds_of_a_matrix_packed_again_hlstm():
     case.weights[(0, 1)]["M2"] = _mask(np.random.default_rng(1), 300, 300, 240, 0)         # 16 slots: all four matrices
     desc, _ = check_case(case, CSR)
     assert desc.count("csr(s16,") == 2 and not re.search(r",r\d", desc), desc
+
+
+@pytest.mark.parametrize("H,G,Bn,extra,shape", [
+    (310, 305, 10, 7, "u3,b2,r1"),
+    (310, 320, 18, 40, "u3,b2,r3"),
+    (320, 310, 24, 48, "u3,b4,r3"),
+    (382, 382, 29, 16, "u3,b4,r1"),
+])
+def test_hlstm_sixteen_slots_of_three_units(H, G, Bn, extra, shape):
+    """The form whose weights leave the fewest registers for the entries outside its slots."""
+    desc, _ = check_case(_case(2, True, 24, H, 5, Bn, 256, extra, G), CSR)
+    assert desc.count(f"rec=persist_batched-hlstm-csr+ovf(s16,{shape})") == 4, desc
