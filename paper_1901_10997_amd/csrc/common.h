@@ -573,8 +573,11 @@ hipError_t launch_proj_q16(const ProjQ16Args& a, int ndir, int slots, hipStream_
 
 // `slots` = the largest q16_slots of the directions (even, <= 16)
 bool persist_batched_q16_plan(int B, int H, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
+bool persist_batched_q16_local(int slots, int upw, int ug, int bg, int ndir);
+bool persist_batched_q16_run_plan(int B, int longest, int H, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
 size_t persist_batched_q16_stride(int H, int bw);
-hipError_t launch_persist_batched_q16(PersistBatchedArgs& a, int ndir, int slots, int cooperative, hipStream_t s);
+// longest: columns of the longest of the launches that share the words
+hipError_t launch_persist_batched_q16(PersistBatchedArgs& a, int longest, int ndir, int slots, int cooperative, hipStream_t s);
 
 // H-LSTM at small batch (B >= 2), W1h and W2 row-compressed and register-resident, time loop on the device, every
 // direction of a layer in one launch.
@@ -621,7 +624,8 @@ struct PersistBatchedHArgs {
 // `slots` = the largest slot count of the two matrices over the directions (even, <= 16)
 double persist_batched_h_step_us(int H, int slots, int upw, int bw, bool local);
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
-hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int ndir, int slots, int cooperative, hipStream_t s);
+bool persist_batched_h_run_plan(int B, int longest, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
+hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int longest, int ndir, int slots, int cooperative, hipStream_t s);
 
 // Lets `kernel` be launched with up to `bytes` of dynamic LDS on the current device (util_kernels.hip).
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);

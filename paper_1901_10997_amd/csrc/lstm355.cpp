@@ -1578,8 +1578,8 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
     float* cbuf[2] = {(float*)(base + ws.c_off[0]), (float*)(base + ws.c_off[1])};
     float* U[2] = {(float*)(base + ws.U_off[0]), (float*)(base + ws.U_off[1])};
     char tag[96];
-    // exchange words of the small-batch recurrence: the launch they were last laid out for (H, G, columns, directions, columns of a
-    // group), how often each has been written since they were cleared, and the tags of the XCD ids
+    // exchange words of the small-batch recurrence: the launch they were last laid out for (H, G, batch groups, directions, columns
+    // of a group), how often each has been written since they were cleared, and the tags of the XCD ids
     int hlayout[5] = {0, 0, 0, 0, 0};
     unsigned h_epoch = 0, u_epoch = 0, htag = 0;
     QuadRegions quad;
@@ -1696,8 +1696,9 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
                 const int nd = Dn / cut.passes, d_lo = pass * nd;
                 const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
-                persist_batched_h_plan(bn, H, G, nz, nd, &upw, &bw, &ug, &bg);
-                const int layout[5] = {H, G, bn, nd, bw};
+                const int longest = (B + cut.chunks - 1) / cut.chunks;
+                persist_batched_h_run_plan(bn, longest, H, G, nz, nd, &upw, &bw, &ug, &bg);
+                const int layout[5] = {H, G, bg, nd, bw};
                 if (!std::equal(layout, layout + 5, hlayout)) {   // another layout puts words written less often in a word's place
                     HIP_TRY(m, launch_fill_u64((unsigned long long*)hwords, (ws.U_end - ws.slot_off) / sizeof(unsigned long long), 0ull, s));
                     std::copy(layout, layout + 5, hlayout);
@@ -1735,7 +1736,7 @@ static int forward_hlstm(lstm_t* m, int T, int B, const void* x, const float* h0
                 a.tag_base = htag; a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit; a.device_scope_only = m->device_scope_only;
                 htag += 1u; h_epoch += (unsigned)T - 1u; u_epoch += (unsigned)T;
                 ProfSpan span(m, s, 1);
-                HIP_TRY(m, launch_persist_batched_h(a, nd, nz, m->launch_mode(), s));
+                HIP_TRY(m, launch_persist_batched_h(a, longest, nd, nz, m->launch_mode(), s));
                 }
                 continue;
             }
@@ -1998,7 +1999,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
     uint16_t* Ybf[2] = {(uint16_t*)(base + ws.Yb_off[0]), (uint16_t*)(base + ws.Yb_off[1])};
     uint16_t* hb0 = (uint16_t*)(base + ws.hb0_off);
     unsigned long long* bslots = (unsigned long long*)(base + ws.slot_off);
-    // words of the small-batch recurrence: the launch they were last laid out for (H, columns, directions, columns of a group), the steps
+    // words of the small-batch recurrence: the launch they were last laid out for (H, batch groups, directions, columns of a group), the steps
     // published in them since they were cleared, and the tags of the XCD ids
     int blayout[4] = {0, 0, 0, 0};
     unsigned bepoch = 0, btag = 0;
@@ -2340,8 +2341,9 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 const int pass = launch / cut.chunks, chunk = launch % cut.chunks;
                 const int nd = Dn / cut.passes, d_lo = pass * nd;
                 const int b_lo = chunk_begin(B, cut.chunks, chunk), bn = chunk_begin(B, cut.chunks, chunk + 1) - b_lo;
-                persist_batched_q16_plan(bn, H, q16, nd, &upw, &bw, &ug, &bg);
-                const int layout[4] = {H, bn, nd, bw};
+                const int longest = (B + cut.chunks - 1) / cut.chunks;
+                persist_batched_q16_run_plan(bn, longest, H, q16, nd, &upw, &bw, &ug, &bg);
+                const int layout[4] = {H, bg, nd, bw};
                 if (!std::equal(layout, layout + 4, blayout)) {   // another layout puts words written less often in a word's place
                     HIP_TRY(m, launch_fill_u64(bslots, align256(ws.slot_bytes) / sizeof(unsigned long long), 0ull, s));
                     std::copy(layout, layout + 4, blayout);
@@ -2375,7 +2377,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceBatchedDeviceWide;   // (the launcher clears it where the exchange stays inside XCDs)
                 btag += 1u; bepoch += (unsigned)T - 1u;
                 ProfSpan span(m, s, 1);
-                HIP_TRY(m, launch_persist_batched_q16(a, nd, q16, m->launch_mode(), s));
+                HIP_TRY(m, launch_persist_batched_q16(a, longest, nd, q16, m->launch_mode(), s));
                 }
                 continue;
             }

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(512) void persist_batched_q16_kernel(PersistBatched
     }
     const PersistBatchedDir& D = a.d[dir];
     const int b0 = bgi * BW;
-    const int bw = (B - b0) < BW ? (B - b0) : BW;         // columns actually present
+    const int bw = (B - b0) < BW ? (B - b0) : BW;         // columns actually present (none: 0 or less)
     const int u0 = ugi * upb + wave * UPW;                // first unit of this wave
     // words of this batch group: [buffer][k][BW], i.e. in the order of the LDS copy of h
     unsigned* const xchg = a.xchg + ((size_t)dir * a.bg + bgi) * 2 * a.h_stride;
@@ -238,6 +238,11 @@ static size_t batched_lds_bytes(int H, int upw, int bw) { return ((((size_t)bw *
 // Choose (UPW, BW): at most one workgroup per compute unit, within the register budget (1.5 registers per unit and slot; 512-thread
 // workgroups leave 256 registers per lane) and PAIRS <= 16.
 constexpr int kQ16WeightRegs = 156;
+// one XCD holds an eighth of the compute units; its share of the groups must fit there
+bool persist_batched_q16_local(int slots, int upw, int ug, int bg, int ndir)
+{
+    return persist_batched_q16_xcd_capable(slots, upw) && ug <= 64 && ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8;
+}
 bool persist_batched_q16_plan(int B, int H, int slots, int ndir, int* upw_out, int* bw_out, int* ug_out, int* bg_out)
 {
     if (B < 2 || slots < 2 || slots > 24 || (slots & 1) || H < 1 || H > 4096) return false;
@@ -252,7 +257,7 @@ bool persist_batched_q16_plan(int B, int H, int slots, int ndir, int* upw_out, i
             if (batched_lds_bytes(H, upw, bw) > 64 * 1024) continue;
             const int ug = (H + kWaves * upw - 1) / (kWaves * upw), bg = (B + bw - 1) / bw;
             if (ug * bg * ndir > device_num_cus()) continue;
-            const bool local = persist_batched_q16_xcd_capable(slots, upw) && ug <= 64 && ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8;
+            const bool local = persist_batched_q16_local(slots, upw, ug, bg, ndir);
             const double us = 0.0033 * slots * upw * (bw + 1.5) + (local ? 0.0 : 0.3) + 0.026e-3 * H * bw;
             if (us < least) {
                 least = us;
@@ -260,6 +265,19 @@ bool persist_batched_q16_plan(int B, int H, int slots, int ndir, int* upw_out, i
             }
         }
     return least < 1e30;
+}
+
+// The plan of a run of B batch columns among runs of up to `longest` over the same words.  Where the longest has the same shape and
+// placement the run gets as many batch groups, the last one without a column: it writes its words like the others, so the next launch
+// finds every word written equally often and none has to be cleared in between.
+bool persist_batched_q16_run_plan(int B, int longest, int H, int slots, int ndir, int* upw, int* bw, int* ug, int* bg)
+{
+    if (!persist_batched_q16_plan(B, H, slots, ndir, upw, bw, ug, bg)) return false;
+    int upw_l, bw_l, ug_l, bg_l;
+    if (longest > B && persist_batched_q16_plan(longest, H, slots, ndir, &upw_l, &bw_l, &ug_l, &bg_l) && upw_l == *upw && bw_l == *bw &&
+        persist_batched_q16_local(slots, upw_l, ug_l, bg_l, ndir) == persist_batched_q16_local(slots, *upw, *ug, *bg, ndir))
+        *bg = bg_l;
+    return true;
 }
 
 // words of a buffer of a (direction, batch group): whole 256-byte blocks
@@ -284,17 +302,17 @@ static hipError_t launch_q16_s(PersistBatchedArgs& a, int upw, int bw, int block
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_persist_batched_q16(PersistBatchedArgs& a, int ndir, int slots, int cooperative, hipStream_t s)
+hipError_t launch_persist_batched_q16(PersistBatchedArgs& a, int longest, int ndir, int slots, int cooperative, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
     int upw, bw, ug, bg;
-    if (!persist_batched_q16_plan(a.B, a.H, slots, ndir, &upw, &bw, &ug, &bg)) return hipErrorInvalidValue;
+    if (!persist_batched_q16_run_plan(a.B, longest, a.H, slots, ndir, &upw, &bw, &ug, &bg)) return hipErrorInvalidValue;
     a.ug = ug;
     a.bg = bg;
     const int per_xcd = (ndir * bg + 7) / 8;
     a.ndir = ndir;
     a.h_stride = persist_batched_q16_stride(a.H, bw);
-    a.xcd_local = (persist_batched_q16_xcd_capable(slots, upw) && ug <= 64 && per_xcd * ug <= device_num_cus() / 8) ? 1 : 0;
+    a.xcd_local = persist_batched_q16_local(slots, upw, ug, bg, ndir) ? 1 : 0;
     const int blocks = a.xcd_local ? 8 * per_xcd * ug : ug * bg * ndir;
     if (a.xcd_local) a.poll_pace = 0;
     switch (slots) {

@@ -77,7 +77,7 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
     }
     const PersistBatchedHDir& D = a.d[dir];
     const int b0 = bgi * BW;
-    const int bw = (B - b0) < BW ? (B - b0) : BW;         // columns actually present
+    const int bw = (B - b0) < BW ? (B - b0) : BW;         // columns actually present (none: 0 or less)
     const int u0 = ugi * upb + wave * UPW;                // first unit of this wave
     const size_t grp = (size_t)dir * a.bg + bgi;
     unsigned* const xh = a.xchg_h + grp * a.h_stride;     // [H][BW]
@@ -278,6 +278,8 @@ double persist_batched_h_step_us(int H, int slots, int upw, int bw, bool local)
 {
     return local ? 1.50 + 0.0108 * slots * upw * (bw + 1.5) + 0.36e-3 * H * bw : 3.74 + 0.0040 * slots * upw * (bw + 1.5) + 0.58e-3 * H * bw;
 }
+// one XCD holds an eighth of the compute units; its share of the groups must fit there
+static bool h_local(int ug, int bg, int ndir) { return ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8; }
 // Choose (UPW, BW): the lowest estimated step of those with at most one workgroup per compute unit, within the register budget, with
 // PAIRS <= 16, 16-bit LDS offsets, and at most 64 unit groups (XCD id slots).
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_out, int* bw_out, int* ug_out, int* bg_out)
@@ -296,7 +298,7 @@ bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_o
             if (blocks > device_num_cus()) continue;
             // (800/800 at batch 2 to 8: 5.9-6.6 us per step with two units per wave across the device, 3.95 with four
             // inside one XCD; 1024/1024 at batch 20: 8.5 -> 5.8)
-            const bool local = ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8;
+            const bool local = h_local(ug, bg, ndir);
             const double us = persist_batched_h_step_us(H, slots, upw, bw, local);
             if (us < least) {
                 least = us;
@@ -305,6 +307,17 @@ bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_o
         }
     }
     return least < 1e30;
+}
+
+// as persist_batched_q16_run_plan
+bool persist_batched_h_run_plan(int B, int longest, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg)
+{
+    if (!persist_batched_h_plan(B, H, G, slots, ndir, upw, bw, ug, bg)) return false;
+    int upw_l, bw_l, ug_l, bg_l;
+    if (longest > B && persist_batched_h_plan(longest, H, G, slots, ndir, &upw_l, &bw_l, &ug_l, &bg_l) && upw_l == *upw && bw_l == *bw &&
+        h_local(ug_l, bg_l, ndir) == h_local(*ug, *bg, ndir))
+        *bg = bg_l;
+    return true;
 }
 
 // exchange storage per (direction, batch group), in elements of the respective array, padded to whole 256-byte blocks
@@ -336,19 +349,18 @@ static hipError_t launch_s(PersistBatchedHArgs& a, int upw, int bw, int blocks, 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int ndir, int slots, int cooperative, hipStream_t s)
+hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int longest, int ndir, int slots, int cooperative, hipStream_t s)
 {
     if (a.T <= 0) return hipSuccess;
     int upw, bw, ug, bg;
-    if (!persist_batched_h_plan(a.B, a.H, a.G, slots, ndir, &upw, &bw, &ug, &bg)) return hipErrorInvalidValue;
+    if (!persist_batched_h_run_plan(a.B, longest, a.H, a.G, slots, ndir, &upw, &bw, &ug, &bg)) return hipErrorInvalidValue;
     a.ug = ug;
     a.bg = bg;
     a.h_stride = persist_batched_h_hstride(a.H, bw);
     a.u_stride = persist_batched_h_ustride(a.G, bw);
-    // one XCD holds an eighth of the compute units; its share of the groups must fit there
     const int per_xcd = (ndir * bg + 7) / 8;
     a.ndir = ndir;
-    a.xcd_local = per_xcd * ug <= device_num_cus() / 8;
+    a.xcd_local = h_local(ug, bg, ndir);
     const int blocks = a.xcd_local ? 8 * per_xcd * ug : ug * bg * ndir;
     switch (slots) {
         case 2: return launch_s<2>(a, upw, bw, blocks, cooperative != 0, s);
