@@ -127,6 +127,11 @@ __device__ __forceinline__ void exchange_store(T* p, T v, bool same_xcd)
 // at by itself).  A buffer's base and the offset of a block are scalar, so an address takes one register, and a line is asked for once
 // where two loads of 8 bytes ask twice.  Only the compiler's memory barrier in front keeps a load from being taken for an earlier
 // one's.
+// What is assumed of them: a naturally aligned word of 32 bits arrives whole, and one of 64 bits that was written by one store does
+// too, as with the atomic loads of that size (persist_split.hip stamps one half of such a word only).  The instruction set promises no
+// such thing of the halves of a 16-byte load; a store puts its word into a cache line at once, though, and a lane's sixteen bytes
+// are one piece of a line.  Looked for with 16-byte loads against words being rewritten all the time, by device-scope stores and by stores inside an
+// XCD: none torn among 2e10, 1.2e9 of them seen to have changed since the load before.  (A stamp in both halves: 1 to 4 % of a step.)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t exchange_buffer(const void* base, unsigned bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);   // raw, 32-bit data format

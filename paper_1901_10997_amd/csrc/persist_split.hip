@@ -20,7 +20,8 @@
 //
 // Exchange: 8-byte words of four units of a column and plane.  |h| <= 1 leaves bit 14 of a half free: that of the first carries
 // the stamp (as in persist_quad.hip: two buffers, step tag g in buffer g & 1 with stamp (g >> 1) & 1), that of the second says
-// that a NaN is among the four.  hx: [quad][buffer][block of 32 k][k / 8 % 4][plane][column][k / 4 % 2], the lanes' order.
+// that a NaN is among the four; a word is taken to arrive whole, also in one half of a 16-byte load (exchange.h).  hx: [quad][buffer]
+// [block of 32 k][k / 8 % 4][plane][column][k / 4 % 2], the lanes' order.
 // h0 may have any value: a column of it that is not within 1 is multiplied by the fp32 instruction before the first step, into its
 // P, and travels as zeros.
 #include "common.h"
