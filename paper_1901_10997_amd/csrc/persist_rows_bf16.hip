@@ -375,23 +375,20 @@ struct RowsShape {
     const void* kernel;
 };
 #define R_S(NT_, KB_) {NT_, KB_, 1, 0, (const void*)persist_rows_bf16_kernel<NT_, KB_, 1, false, 0>}
-// the shapes whose weights (NT KB x 16 bytes per lane), operands and accumulators fit the registers
+// shapes whose weights (NT KB x 16 bytes per lane), operands and accumulators fit the registers, those that some width and batch takes
 const RowsShape kRowsShapes[] = {
-    R_S(1, 1), R_S(2, 1), R_S(4, 1), R_S(1, 2), R_S(2, 2), R_S(3, 2), R_S(4, 2), R_S(8, 2), R_S(1, 3), R_S(2, 3), R_S(3, 3),
-    R_S(5, 3), R_S(6, 3), R_S(1, 4), R_S(2, 4), R_S(4, 4), R_S(7, 4), R_S(8, 4), R_S(2, 5), R_S(3, 5), R_S(5, 5), R_S(2, 6),
-    R_S(3, 6), R_S(5, 6), R_S(2, 8), R_S(3, 8), R_S(4, 8),
+    R_S(1, 1), R_S(2, 1), R_S(4, 1), R_S(3, 2), R_S(4, 2), R_S(8, 2), R_S(1, 3), R_S(5, 3), R_S(6, 3), R_S(1, 4), R_S(2, 4),
+    R_S(4, 4), R_S(7, 4), R_S(8, 4), R_S(2, 5), R_S(3, 5), R_S(5, 5), R_S(2, 6), R_S(3, 6), R_S(5, 6), R_S(2, 8), R_S(4, 8),
 };
 #undef R_S
 constexpr int kRowsShapeCount = (int)(sizeof(kRowsShapes) / sizeof(kRowsShapes[0]));
 // ... and with the input's matrix beside the recurrent one (2 NT KB x 16 bytes)
 #define R_K(NT_, KB_, RT_, XL_) {NT_, KB_, RT_, XL_, (const void*)persist_rows_bf16_kernel<NT_, KB_, RT_, true, XL_>}
 const RowsShape kStackShapes[] = {
-    R_K(1, 1, 1, 0), R_K(2, 1, 1, 0), R_K(4, 1, 1, 0), R_K(8, 1, 1, 0), R_K(1, 2, 1, 0), R_K(2, 2, 1, 0), R_K(4, 2, 1, 0),
-    R_K(6, 2, 1, 0), R_K(8, 2, 1, 0), R_K(1, 3, 1, 0), R_K(2, 3, 1, 0), R_K(3, 3, 1, 0), R_K(4, 3, 1, 0), R_K(6, 3, 1, 1),
-    R_K(1, 4, 1, 0), R_K(2, 4, 1, 0), R_K(3, 4, 1, 0), R_K(4, 4, 1, 0), R_K(5, 4, 1, 2), R_K(2, 5, 1, 0), R_K(3, 5, 1, 0),
-    R_K(4, 5, 1, 2), R_K(2, 6, 1, 0), R_K(3, 6, 1, 2), R_K(2, 7, 1, 0), R_K(1, 1, 2, 0), R_K(2, 1, 2, 0), R_K(4, 1, 2, 0),
-    R_K(1, 2, 2, 0), R_K(2, 2, 2, 0), R_K(4, 2, 2, 0), R_K(1, 3, 2, 0), R_K(2, 3, 2, 0), R_K(3, 3, 2, 0), R_K(4, 3, 2, 0),
-    R_K(2, 4, 2, 0), R_K(3, 4, 2, 0), R_K(2, 5, 2, 0), R_K(3, 5, 2, 2), R_K(2, 6, 2, 2),
+    R_K(1, 1, 1, 0), R_K(2, 1, 1, 0), R_K(4, 1, 1, 0), R_K(8, 1, 1, 0), R_K(4, 2, 1, 0), R_K(6, 2, 1, 0), R_K(8, 2, 1, 0),
+    R_K(2, 3, 1, 0), R_K(3, 3, 1, 0), R_K(6, 3, 1, 1), R_K(2, 4, 1, 0), R_K(3, 4, 1, 0), R_K(4, 4, 1, 0), R_K(3, 5, 1, 0),
+    R_K(4, 5, 1, 2), R_K(3, 6, 1, 2), R_K(1, 1, 2, 0), R_K(2, 1, 2, 0), R_K(4, 1, 2, 0), R_K(4, 2, 2, 0), R_K(3, 3, 2, 0),
+    R_K(4, 3, 2, 0), R_K(3, 4, 2, 0), R_K(3, 5, 2, 2),
 };
 #undef R_K
 constexpr int kStackShapeCount = (int)(sizeof(kStackShapes) / sizeof(kStackShapes[0]));
