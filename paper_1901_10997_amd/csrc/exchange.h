@@ -1,6 +1,6 @@
-// Tagged-slot exchange of hidden-state values between workgroups (device side).
-// A slot is 64 bits: low word = fp32 value, high word = step tag.  One 8-byte store publishes both, so a
-// consumer that sees the expected tag also has the value; a stale read carries an old tag and is retried.
+// Exchange of hidden-state values between workgroups (device side): values that carry their own readiness, so that a consumer that
+// sees it also has the value and a stale read is retried.  Either tagged slots of 64 bits (low word fp32 value, high word step tag, one
+// 8-byte store publishes both), or stamped words, where a bit that the value leaves free holds a bit of the step count.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -44,11 +44,11 @@ struct PollSrc {
 };
 
 // Fetch the tagged values of up to two slot arrays into LDS.  The two arrays are treated as one index space
-// so that all outstanding loads of a thread (up to NF) are in flight together, whichever array they hit.
-template <int NF = 4>
+// so that all outstanding loads of a thread (up to four) are in flight together, whichever array they hit.
 __device__ __forceinline__ void gather_tagged2(const PollSrc& A, const PollSrc& Bs, int tid, int nthreads,
                                                int* timeout_flag, unsigned spin_limit)
 {
+    constexpr int NF = 4;
     const int total = A.n + Bs.n;
     for (int e0 = tid; e0 < total; e0 += NF * nthreads) {
         u64 v[NF];
@@ -91,18 +91,8 @@ __device__ __forceinline__ void gather_tagged(const u64* slots, int H, unsigned 
                                               int nthreads, int* timeout_flag, unsigned spin_limit)
 {
     const PollSrc A{slots, dst, want, H}, none{nullptr, nullptr, 0u, 0};
-    gather_tagged2<4>(A, none, tid, nthreads, timeout_flag, spin_limit);
+    gather_tagged2(A, none, tid, nthreads, timeout_flag, spin_limit);
 }
-// For kernels with sixteen registers to spare: a thread with more than four slots to fetch keeps eight loads in
-// flight (one polling round less).
-__device__ __forceinline__ void gather_tagged_wide(const u64* slots, int H, unsigned want, float* dst, int tid,
-                                                   int nthreads, int* timeout_flag, unsigned spin_limit)
-{
-    const PollSrc A{slots, dst, want, H}, none{nullptr, nullptr, 0u, 0};
-    if (H > 4 * nthreads) gather_tagged2<8>(A, none, tid, nthreads, timeout_flag, spin_limit);
-    else gather_tagged2<4>(A, none, tid, nthreads, timeout_flag, spin_limit);
-}
-
 // ---- exchange inside one XCD -------------------------------------------------------------------------------------
 // The compute units of an XCD share one L2.  A store at workgroup scope is written through the compute unit's vector
 // cache into that L2 and stays there; an agent-scope load from any compute unit of the same XCD bypasses its vector
