@@ -622,7 +622,8 @@ struct PersistBatchedHArgs {
     unsigned spin_limit;
 };
 // `slots` = the largest slot count of the two matrices over the directions (even, <= 16)
-double persist_batched_h_step_us(int H, int slots, int upw, int bw, bool local);
+double persist_batched_h_step_us(int H, int G, int slots, int upw, int bw, bool local);
+bool persist_batched_h_local(int ug, int bg, int ndir);
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
 bool persist_batched_h_run_plan(int B, int longest, int H, int G, int slots, int ndir, int* upw, int* bw, int* ug, int* bg);
 hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int longest, int ndir, int slots, int cooperative, hipStream_t s);

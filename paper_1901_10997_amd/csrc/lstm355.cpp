@@ -1291,29 +1291,36 @@ static double b1_dense_step_us(int H) { return H <= 448 ? 0.8 + 0.0017 * H : 1.5
 constexpr double kB1CsrStepUs = 1.8, kB1HlstmStepUs = 2.9;   // latency of the exchanges: nearly the same at every width and density
 constexpr double kSeparateProjUs = 20.0;   // launches and gaps a fused batch-1 kernel does not have
 constexpr double kDenseSetupUs = 10.0;     // dense weights to read before the first step; short sequences stay where they are
+constexpr double kDenseHlstmSetupUs = 5.0; // (more than those over kept entries take)
 static double batched_csr_step_us(const lstm_t* m, int l, int B)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
-    // Compared with the dense models only (persist_quad_plan, persist_split_plan), and so on their scale: their steps are shorter than
-    // those models say (LSTM cells by 5 to 15 %, H-LSTM cells by 29 % inside an XCD and 22 % across), and those over kept entries by
-    // as much than this says.  An LSTM's round of entries outside the slots is priced as the two slots it replaces.
     int slots = 0, rounds = 0, upw = 0, bw = 0, ug = 0, bg = 0;
     for (int d = 0; d < Dn; ++d) {
         const LayerDir& w = m->ld[(size_t)l * Dn + d];
         if (w.wh.q16_slots <= 0 || (G > 0 && w.w2.q16_slots <= 0)) return 1e9;   // one or two launches per step
-        slots = std::max(slots, G > 0 ? std::max(w.wh.q16_slots, w.w2.q16_slots) : std::min(24, w.wh.q16_slots + 2 * w.wh.q16_rounds));
+        slots = std::max(slots, G > 0 ? std::max(w.wh.q16_slots, w.w2.q16_slots) : w.wh.q16_slots);
         rounds = std::max(rounds, w.wh.q16_rounds + (G > 0 ? w.w2.q16_rounds : 0));
     }
     LaunchCut cut;
-    int nd_used = 0;
-    if (!choose_cut(B, Dn, [&](int b, int nd) {
-            nd_used = nd;
-            return G > 0 ? persist_batched_h_plan(b, H, G, slots, nd, &upw, &bw, &ug, &bg) : persist_batched_q16_plan(b, H, slots, nd, &upw, &bw, &ug, &bg);
+    int nd = 0;
+    if (!choose_cut(B, Dn, [&](int b, int n) {
+            return G > 0 ? persist_batched_h_plan(b, H, G, slots, n, &upw, &bw, &ug, &bg) : persist_batched_q16_plan(b, H, slots, n, &upw, &bw, &ug, &bg);
         }, &cut))
         return 1e9;
-    const bool local = ug <= 64 && ((nd_used * bg + 7) / 8) * ug <= device_num_cus() / 8;
-    if (G > 0) return cut.passes * cut.chunks * (0.1 * rounds + persist_batched_h_step_us(H, slots, upw, bw, local)) / (local ? 0.71 : 0.78);
-    const double gathers = 0.01 * slots * upw * bw, words = 0.001 * H * bw;
+    nd = Dn / cut.passes;
+    const int longest = (B + cut.chunks - 1) / cut.chunks;
+    if (G > 0) {
+        persist_batched_h_plan(longest, H, G, slots, nd, &upw, &bw, &ug, &bg);
+        return cut.passes * cut.chunks * (0.1 * rounds + persist_batched_h_step_us(H, G, slots, upw, bw, persist_batched_h_local(ug, bg, nd)));
+    }
+    // Not in true microseconds: steps are 0.81 of this (0.74 to 0.87 in eight of ten of 136 layers).  It is compared with the dense models
+    // only, whose steps are 0.98 of theirs, but 0.7 where a wide layer takes many passes, and under the margins of layer_takes_quads the
+    // choice costs 0.6 % over 215 layers of 64 to 2048 units, 5 to 40 % kept, batches of 2 to 64 (at most 20 %).  A round of entries
+    // outside the slots counts as the two slots it replaces.
+    persist_batched_q16_plan(longest, H, slots, nd, &upw, &bw, &ug, &bg);
+    const bool local = persist_batched_q16_local(slots, upw, ug, bg, nd);
+    const double gathers = 0.01 * (slots + 2 * rounds) * upw * bw, words = 0.001 * H * bw;
     return cut.passes * cut.chunks * ((local ? 1.34 : 1.83) + 0.76 * gathers + 0.10 * words);
 }
 
@@ -1345,7 +1352,7 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     if (m->plan == LSTM_PLAN_PERSISTENT) return false;   // asks for the kernels of the matrices' own form
     double us = T * cut.passes * cut.chunks * (split ? p.split : p.quad)[0].us, other = 0;
     if (B > 1) {
-        us += kDenseSetupUs;
+        us += G > 0 ? kDenseHlstmSetupUs : kDenseSetupUs;
         other = T * batched_csr_step_us(m, l, B);
         // From 2048 columns on (both directions counted) a step of an H-LSTM layer with such short rows is two full launches,
         // level with the quads or up to a tenth faster (200 units, 6 % kept: 68 against 75 us); with longer rows or an LSTM
@@ -1361,7 +1368,10 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
             else other += persist_b1_dense_supported(H) ? T * b1_dense_step_us(H) : 1e9;
         }
     }
-    return us < 0.95 * other;
+    // H-LSTM, batch 2 to 64: level models, 0.5 % lost over 183 layers (at most 19 %; 2.2 % with the margin).  Batch 1: 64 layers of 64
+    // to 2000 units 0.2 %, where the dense step priced as before its words were read sixteen bytes at a time lost 6 % (212 units, 20 % kept:
+    // 3.06 us per step over kept entries, 1.89 dense).
+    return us < (G > 0 && B > 1 ? 1.0 : 0.95) * other;
 }
 
 // Batch 1: do layers l and l + 1, unidirectional and row-compressed, run in one launch (diagonal wavefront)?

@@ -272,14 +272,16 @@ __global__ __launch_bounds__(512) void persist_batched_hlstm_kernel(PersistBatch
 }
 
 // ------------------------------------------------------------------------------------------------ planning
-// Modelled step (microseconds): both exchanges, vector issue per gather of both products, the words that are polled.  A fit to 201
-// measured points of 64 to 2000 units, 5 to 30 % kept, batches of 2 to 60 (standard error 7 %).
-double persist_batched_h_step_us(int H, int slots, int upw, int bw, bool local)
+// Modelled step (microseconds): both exchanges, vector issue per gather of both products, the H + 4 G values per column that are polled.
+// A fit to 201 measured points of 64 to 2000 units, 5 to 30 % kept, batches of 2 to 60 (standard error 7 %); 183 others, two in five of
+// them with G between 0.3 and 1.8 H, are within 6 %.
+double persist_batched_h_step_us(int H, int G, int slots, int upw, int bw, bool local)
 {
-    return local ? 1.50 + 0.0108 * slots * upw * (bw + 1.5) + 0.36e-3 * H * bw : 3.74 + 0.0040 * slots * upw * (bw + 1.5) + 0.58e-3 * H * bw;
+    const double gathers = slots * upw * (bw + 1.5), words = ((double)H + 4.0 * G) * bw;
+    return local ? 1.50 + 0.0108 * gathers + 0.072e-3 * words : 3.74 + 0.0040 * gathers + 0.116e-3 * words;
 }
 // one XCD holds an eighth of the compute units; its share of the groups must fit there
-static bool h_local(int ug, int bg, int ndir) { return ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8; }
+bool persist_batched_h_local(int ug, int bg, int ndir) { return ((ndir * bg + 7) / 8) * ug <= device_num_cus() / 8; }
 // Choose (UPW, BW): the lowest estimated step of those with at most one workgroup per compute unit, within the register budget, with
 // PAIRS <= 16, 16-bit LDS offsets, and at most 64 unit groups (XCD id slots).
 bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_out, int* bw_out, int* ug_out, int* bg_out)
@@ -298,8 +300,8 @@ bool persist_batched_h_plan(int B, int H, int G, int slots, int ndir, int* upw_o
             if (blocks > device_num_cus()) continue;
             // (800/800 at batch 2 to 8: 5.9-6.6 us per step with two units per wave across the device, 3.95 with four
             // inside one XCD; 1024/1024 at batch 20: 8.5 -> 5.8)
-            const bool local = h_local(ug, bg, ndir);
-            const double us = persist_batched_h_step_us(H, slots, upw, bw, local);
+            const bool local = persist_batched_h_local(ug, bg, ndir);
+            const double us = persist_batched_h_step_us(H, G, slots, upw, bw, local);
             if (us < least) {
                 least = us;
                 *upw_out = upw; *bw_out = bw; *ug_out = ug; *bg_out = bg;
@@ -315,7 +317,7 @@ bool persist_batched_h_run_plan(int B, int longest, int H, int G, int slots, int
     if (!persist_batched_h_plan(B, H, G, slots, ndir, upw, bw, ug, bg)) return false;
     int upw_l, bw_l, ug_l, bg_l;
     if (longest > B && persist_batched_h_plan(longest, H, G, slots, ndir, &upw_l, &bw_l, &ug_l, &bg_l) && upw_l == *upw && bw_l == *bw &&
-        h_local(ug_l, bg_l, ndir) == h_local(*ug, *bg, ndir))
+        persist_batched_h_local(ug_l, bg_l, ndir) == persist_batched_h_local(*ug, *bg, ndir))
         *bg = bg_l;
     return true;
 }
@@ -360,7 +362,7 @@ hipError_t launch_persist_batched_h(PersistBatchedHArgs& a, int longest, int ndi
     a.u_stride = persist_batched_h_ustride(a.G, bw);
     const int per_xcd = (ndir * bg + 7) / 8;
     a.ndir = ndir;
-    a.xcd_local = h_local(ug, bg, ndir);
+    a.xcd_local = persist_batched_h_local(ug, bg, ndir);
     const int blocks = a.xcd_local ? 8 * per_xcd * ug : ug * bg * ndir;
     switch (slots) {
         case 2: return launch_s<2>(a, upw, bw, blocks, cooperative != 0, s);

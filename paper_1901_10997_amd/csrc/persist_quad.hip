@@ -458,6 +458,9 @@ constexpr int kQuadShapeCount = (int)(sizeof(kQuadShapes) / sizeof(kQuadShapes[0
 // part, the matrix instructions, the reduction and gates of a (tile, quad) pair; the operand words; and the part of the
 // exchange that other passes would hide.  The constants are a fit to 700 measured (shape, groups, placement) points over
 // 100 to 1900 units and batches of 1 to 64 (standard error 12 %, which the choice needs only near ties).
+// H-LSTM steps have become shorter since (operand words of the second product sixteen bytes per lane): 0.74 of that fit over 180 layers of
+// 64 to 2000 units and batches of 2 to 64, a step of 60 without the 5 us that a launch takes to its first one (0.65 to 0.83 in eight of
+// ten), alike inside an XCD and across, so the shapes rank as they did.
 PersistQuadPlan persist_quad_plan(int B, int H, int G, int ndir)
 {
     PersistQuadPlan best;
@@ -483,7 +486,7 @@ PersistQuadPlan persist_quad_plan(int B, int H, int G, int ndir)
             const int local = gn <= 64 && per_xcd * gn <= cus / 8;
             const double words_kb = (16.0 * H + 64.0 * G) / 1e3;             // operand words of a quad and step
             const double pass = stages * ((local ? 0.42 : 0.63) + 0.0097 * sh.qp * sh.nt * sh.kb * 4 + 0.045 * sh.qp * sh.nt) + 0.033 * sh.qp * words_kb;
-            const double us = passes * pass + (passes == 1 ? stages * (local ? 0.29 : 0.59) : 0.0);
+            const double us = (hl ? 0.74 : 1.0) * (passes * pass + (passes == 1 ? stages * (local ? 0.29 : 0.59) : 0.0));
             if (us < best.us) {
                 best.us = us;
                 best.shape = i;
