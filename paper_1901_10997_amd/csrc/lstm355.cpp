@@ -1000,13 +1000,22 @@ static DensePlans dense_plans(const lstm_t* m, int l, int B)
     }
     return p;
 }
+// Does a bf16 layer run by groups of batch rows rather than in the 32-row tiles of persist_mfma.hip, where those take it too?  A pass is
+// sixteen rows of a group, and the tiles take a launch per direction.  Microseconds of a layer of 60 steps, rows / tiles: one pass 0.53 to 0.93
+// of the tiles' time at 128 to 1024 units (1024: batch 64 157 / 209, 128 182 / 229; 384 at 256 144 / 183), two 1.13 to 1.42 (1024
+// at 256 308 / 266; but 640 at 384 307 / 375); two directions, up to three passes 0.30 to 1.02 (1024: 96 296 / 435, 192 443 / 530), four
+// 0.98 to 1.23, 640 at 384 apart.
+static bool rows_beat_tiles(const lstm_t* m, int B, int H, const PersistRowsPlan& rows)
+{
+    return rows.shape >= 0 && (rows.rows <= (m->Dn == 2 ? 48 : 16) || !persist_mfma_supported(B, H));
+}
 // How many layers from l on a bf16 stack runs in one launch, going by the shape (0: l by itself).  Each layer's step waits for its own
 // h only, so n layers take T + n - 1 steps instead of n T, and the layers above the first need no projection of their own.
 static int stack_layers(const lstm_t* m, int l, int T, int B)
 {
     if (m->dtype != LSTM_BF16 || m->Dn != 1 || B < 2) return 0;
     const DensePlans p = dense_plans(m, l, B);
-    if (p.rows.shape < 0 || (persist_mfma_supported(B, m->hid(l)) && p.rows.rows > 16)) return 0;
+    if (!rows_beat_tiles(m, B, m->hid(l), p.rows)) return 0;
     const double proj = 8.0 + 8e-6 * T * B * m->hid(l) * m->hid(l) / 900.0;
     int best = 0;
     double least = 1.0;
@@ -1906,9 +1915,7 @@ static bool layer_takes_rows(const lstm_t* m, int l, int T, int B, PersistRowsPl
     for (int d = 0; d < m->Dn; ++d)
         if (mode[d] != 0 || m->ld[(size_t)l * m->Dn + d].wh.compressed) return false;
     *rows = dense_plans(m, l, B).rows;
-    // Groups of at most 16 batch rows beat the 32-row tiles by 1.5 times (1024 units: batch 64 2.4 against 3.7 us per
-    // step, 128 2.8 against 4.3); where every group would need a second pass the tiles win (batch 256: 4.9 against 3.8).
-    return rows->shape >= 0 && !(persist_mfma_supported(B, m->hid(l)) && rows->rows > 16);
+    return rows_beat_tiles(m, B, m->hid(l), *rows);
 }
 // stack[l]: so many layers from l on run in one launch (0: l is not the first of such a stack); empty where none does.
 static std::vector<int> stacks(const lstm_t* m, int T, int B)

@@ -107,3 +107,16 @@ def test_graph_replays(L, H, Bn):
     """(Narrow layers only: that test's weights of up to 0.3 make 900 units chaotic, 0.17 of the largest output apart from the oracle
     after twelve steps whichever kernel rounds h to bf16.)"""
     graph_replays_match_eager(L, False, 40, H, 12, Bn, "bf16", None, 0, "rows-stack")
+
+
+@pytest.mark.parametrize("bidir,H,Bn,takes", [
+    (False, 384, 256, "rows("),      # sixteen groups of one pass
+    (False, 384, 384, "bf16;"),          # groups of two passes: the 32-row tiles
+    (True, 384, 224, "rows("),       # two passes, both directions in a launch
+    (True, 512, 384, "rows("),       # three
+    (True, 512, 512, "bf16;"),           # four: the tiles, a launch per direction
+])
+def test_groups_of_rows_or_tiles(bidir, H, Bn, takes):
+    w = inputs.Workload(121, f"rows_H{H}_B{Bn}", 1, bidir, 64, H, 6, Bn, "bf16", 1.5 / np.sqrt(H), None, "uniform", 0)
+    desc, _ = check_case(inputs.make_case(w, H + Bn, random_state=True), oracle_cols=list(range(0, Bn, 13)) + [Bn - 1])
+    assert desc.count("rec=persist-mfma-" + takes) == (2 if bidir else 1), desc
