@@ -128,6 +128,7 @@ const char* lstm_last_error(const lstm_t* m);
  * when row-compressed, in the compressed forms as well; the recurrent matrix in the forms its kernels read: compressed,
  * or dense (4H * H values, and once more in the operand order of the matrix instruction where a kernel holds it so), or,
  * for the fp32 matrices that LSTM_FMT_AUTO compressed, compressed and in that order (1500 units: 7 + 36 MB at 10 % kept).
+ * The dense bf16 layers that may run in one launch with the layer below them hold the input-side matrix in that order too.
  */
 int lstm_set_weights(lstm_t* m, int layer, int direction,
                      const float* Wx, const uint8_t* mask_x,
@@ -147,7 +148,12 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction,
                        const float* W1h, const uint8_t* mask_1h, const float* b1,
                        const float* W2, const uint8_t* mask_2, const float* b2, int format);
 
-/* Bytes of DEVICE workspace lstm_forward needs for (T, B); 0 on bad arguments. */
+/* Bytes of DEVICE workspace lstm_forward needs for (T, B), whatever the weights are or will be; 0 on bad arguments.  It
+ * grows with T * B (projections, a layer's hidden sequence).  In unidirectional bf16 models consecutive layers of one
+ * width may run in one launch, and then what each of them hands to the next is kept for all T steps as well: T * B * H
+ * bf16 values for every layer of such a launch but the last, about an eighth of the projections of a layer, cleared by
+ * every forward that uses them.  (A batch that runs so may be reported more than a larger one that does not; in a
+ * workspace made for the larger one lstm_forward runs its layers one by one.) */
 size_t lstm_workspace_bytes(const lstm_t* m, int T, int B);
 
 /*

@@ -248,8 +248,7 @@ static int build_quarter_wave(lstm_t* m, PackedMat& out, int force_slots, int ma
         // to 250 (eight units to a wave), so the count of the smallest sum is taken.  2 p slots fewer than the longest row needs leave
         // more than 32 (p - 1) of its entries outside, 2 p - 1 rounds: two slots for a round are the best trade for an LSTM, and
         // more of each cost the same sum, which the H-LSTM takes, as its two matrices share the registers.  (Entries added one at
-        // a time, at most six of any eight units: 14 slots instead of 12 for 1500 units with 10 % kept, and 0.7 us per product
-        // of an H-LSTM step of 800 units, 20 % kept.)
+        // a time, up to 48 of any eight units: 0.7 us more per product of an H-LSTM step of 800 units, 20 % kept, 12 slots both ways.)
         std::vector<int> outside((size_t)units);
         auto rounds = [&](int St) {
             int most = 0;
@@ -954,6 +953,7 @@ int lstm_set_weights_h(lstm_t* m, int layer, int direction, const float* W1x, co
 // ---- workspace carve-up --------------------------------------------------------------------------------
 struct Workspace {
     size_t P_off[2], XT_off, Y_off[2], c_off[2], Yb_off[2], hb0_off, slot_off, slot_bytes, hx_off, mflag_off, U_off[2], qx_off, qx_words, hb_off, xp_off, rx_off, rx_words, h0_off, sx_off, su_off, sm_off, U_end, total;
+    bool stacked;   // holds what the layers of a bf16 stack hand up (PersistRowsArgs::seq)
 };
 // Plans of layer l at batch B.  They follow from the shape alone, but a search over the kernels' shape tables takes
 // microseconds and a forward needs each several times, so the handle keeps the last batch size's.
@@ -1055,9 +1055,10 @@ static size_t state_floats(const lstm_t* m, int B)   // of all layers and direct
 {
     return m->soff((size_t)m->L * m->Dn) * (size_t)B;
 }
-static Workspace carve(const lstm_t* m, int T, int B)
+static Workspace carve(const lstm_t* m, int T, int B, bool stacked = true)
 {
     Workspace w{};
+    w.stacked = stacked;
     size_t off = 0;
     const size_t M = (size_t)T * B, H = m->H;
     const size_t prow = m->G > 0 ? (size_t)m->G : H;   // H-LSTM: the projection feeds the 4G hidden-layer rows
@@ -1157,7 +1158,7 @@ static Workspace carve(const lstm_t* m, int T, int B)
     if (m->dtype == LSTM_BF16)
         for (int l = 0, n; l < m->L; l += std::max(n, 1)) {
             // (whether the weights let a stack run as one is not known before they are set)
-            n = stack_layers(m, l, T, B);
+            n = stacked ? stack_layers(m, l, T, B) : 0;
             const DensePlans p = dense_plans(m, l, B);
             w.rx_words += std::max(std::max(n, 1) * (size_t)m->Dn * rows_bf16_state_words(p.rows, m->hid(l)) + std::max(n, 1) * persist_rows_bf16_exchange_words(p.rows, m->hid(l), m->Dn, T),
                                    n * rows_bf16_state_words(p.stack[n], m->hid(l)) + persist_rows_bf16_exchange_words(p.stack[n], m->hid(l), n, T));
@@ -1918,10 +1919,10 @@ static bool layer_takes_rows(const lstm_t* m, int l, int T, int B, PersistRowsPl
     return rows_beat_tiles(m, B, m->hid(l), *rows);
 }
 // stack[l]: so many layers from l on run in one launch (0: l is not the first of such a stack); empty where none does.
-static std::vector<int> stacks(const lstm_t* m, int T, int B)
+static std::vector<int> stacks(const lstm_t* m, int T, int B, const Workspace& ws)
 {
     std::vector<int> stack;
-    if (m->dtype != LSTM_BF16 || m->Dn != 1 || B < 2) return stack;
+    if (!ws.stacked || m->dtype != LSTM_BF16 || m->Dn != 1 || B < 2) return stack;
     PersistRowsPlan rows;
     for (int l = 0, n; l < m->L; l += std::max(n, 1)) {
         n = stack_layers(m, l, T, B);
@@ -1981,7 +1982,10 @@ int lstm_forward(lstm_t* m, int T, int B, const void* x, const float* h0, const 
     if (!workspace) return fail(m, LSTM_ERR_ARG, "lstm_forward: workspace is NULL");
     if (((uintptr_t)workspace & 255) != 0) return fail(m, LSTM_ERR_ARG, "lstm_forward: workspace must be 256-byte aligned");
     if ((long long)T * B > (1ll << 30)) return fail(m, LSTM_ERR_ARG, "lstm_forward: T*B too large");
-    const Workspace ws = carve(m, T, B);
+    // A batch whose layers run as a stack may need more than a larger one whose layers do not: in a workspace made for that one they
+    // run one by one.
+    Workspace ws = carve(m, T, B);
+    if (workspace_bytes < ws.total && m->dtype == LSTM_BF16) ws = carve(m, T, B, false);
     if (workspace_bytes < ws.total) return fail(m, LSTM_ERR_NOMEM, "lstm_forward: workspace too small");
     hipStream_t s = (hipStream_t)stream;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -2027,7 +2031,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
     unsigned mtag = 0;
     QuadRegions quad;
     RowsRegions rows_reg;
-    const std::vector<int> stack = stacks(m, T, B);
+    const std::vector<int> stack = stacks(m, T, B, ws);
     bool prev_has_bf16 = false;  // the layer below left a bf16 copy of its hidden sequence in Ybf[(l-1)&1]
     m->last_plan.clear();
     if (m->G > 0) return forward_hlstm(m, T, B, x, h0, c0, y, hT, cT, ws, base, s);

@@ -120,3 +120,29 @@ def test_groups_of_rows_or_tiles(bidir, H, Bn, takes):
     w = inputs.Workload(121, f"rows_H{H}_B{Bn}", 1, bidir, 64, H, 6, Bn, "bf16", 1.5 / np.sqrt(H), None, "uniform", 0)
     desc, _ = check_case(inputs.make_case(w, H + Bn, random_state=True), oracle_cols=list(range(0, Bn, 13)) + [Bn - 1])
     assert desc.count("rec=persist-mfma-" + takes) == (2 if bidir else 1), desc
+
+
+def test_workspace_of_a_larger_batch():
+    """64 columns run as stacks and report more than 65, which do not: in a workspace made for 65 they run layer by layer."""
+    import torch
+    L, D, H, T, Bn = 6, 317, 800, 70, 64
+    case = _case(L, D, H, T, Bn)
+    dev = torch.device("cuda:0")
+    m = B.Lstm(L, D, H, False, B.LSTM_BF16)
+    m.set_weights_from(case.weights)
+    x = torch.from_numpy(case.x).to(dev).to(torch.bfloat16)
+    h0, c0 = torch.from_numpy(case.h0).to(dev), torch.from_numpy(case.c0).to(dev)
+    need, larger = B.lstm_workspace_bytes(m.handle, T, Bn), B.lstm_workspace_bytes(m.handle, T, Bn + 1)
+    assert need > larger
+    outs = []
+    for n, stacked in ((need, True), (larger, False)):
+        ws = torch.empty(n, dtype=torch.uint8, device=dev)
+        y, hT, cT = torch.empty((T, Bn, H), device=dev), torch.empty((L, Bn, H), device=dev), torch.empty((L, Bn, H), device=dev)
+        B.lstm_forward(m.handle, T, Bn, x.data_ptr(), h0.data_ptr(), c0.data_ptr(), y.data_ptr(), hT.data_ptr(), cT.data_ptr(), ws.data_ptr(), n,
+                       torch.cuda.current_stream().cuda_stream)
+        B.lstm_check(m.handle)
+        assert ("rows-stack" in B.lstm_describe_plan(m.handle)) == stacked
+        outs.append([t.double().cpu().numpy() for t in (y, hT, cT)])
+    m.close()
+    for a, b in zip(*outs):      # both round h to bf16 every step: the bf16 tolerance of parity_util
+        assert np.linalg.norm(a - b) <= 2e-2 * np.linalg.norm(b)
