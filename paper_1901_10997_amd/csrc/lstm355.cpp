@@ -1301,7 +1301,7 @@ static double b1_dense_step_us(int H) { return H <= 448 ? 0.8 + 0.0017 * H : 1.5
 constexpr double kB1CsrStepUs = 1.8, kB1HlstmStepUs = 2.9;   // latency of the exchanges: nearly the same at every width and density
 constexpr double kSeparateProjUs = 20.0;   // launches and gaps a fused batch-1 kernel does not have
 constexpr double kDenseSetupUs = 10.0;     // dense weights to read before the first step; short sequences stay where they are
-constexpr double kDenseHlstmSetupUs = 5.0; // (more than those over kept entries take)
+constexpr double kDenseHlstmSetupUs = 5.0;
 static double batched_csr_step_us(const lstm_t* m, int l, int B)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
@@ -1324,14 +1324,10 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
         persist_batched_h_plan(longest, H, G, slots, nd, &upw, &bw, &ug, &bg);
         return cut.passes * cut.chunks * (0.1 * rounds + persist_batched_h_step_us(H, G, slots, upw, bw, persist_batched_h_local(ug, bg, nd)));
     }
-    // Not in true microseconds: steps are 0.81 of this (0.74 to 0.87 in eight of ten of 136 layers).  It is compared with the dense models
-    // only, whose steps are 0.98 of theirs, but 0.7 where a wide layer takes many passes, and under the margins of layer_takes_quads the
-    // choice costs 0.6 % over 215 layers of 64 to 2048 units, 5 to 40 % kept, batches of 2 to 64 (at most 20 %).  A round of entries
-    // outside the slots counts as the two slots it replaces.
+    // a fit to 300 layers of 64 to 2048 units, 5 to 40 % kept, batches of 2 to 64 (standard error 3 %)
     persist_batched_q16_plan(longest, H, slots, nd, &upw, &bw, &ug, &bg);
-    const bool local = persist_batched_q16_local(slots, upw, ug, bg, nd);
-    const double gathers = 0.01 * (slots + 2 * rounds) * upw * bw, words = 0.001 * H * bw;
-    return cut.passes * cut.chunks * ((local ? 1.34 : 1.83) + 0.76 * gathers + 0.10 * words);
+    return cut.passes * cut.chunks * ((persist_batched_q16_local(slots, upw, ug, bg, nd) ? 1.15 : 1.57) + 0.00366 * slots * upw * (bw + 1.5) +
+                                      0.086e-3 * H * bw + 0.012 * rounds * upw);
 }
 
 // Does the dense fp32 recurrence with the time loop on the device take layer l?  It multiplies the zeros of a mask too, but a
@@ -1340,8 +1336,7 @@ static double batched_csr_step_us(const lstm_t* m, int l, int B)
 // row-compressed kernels (H-LSTM 1.1 to 1.6 times up to 256), and 2 to 6 times where rows are too long for those and each step
 // would be a launch.  With the product on fp16 planes LSTM layers of 450 and more units follow at small batches (5 bidirectional
 // layers of 800, 15 % kept, batch 16: 4219 us over the kept entries, 4079 dense); with the fp32 instruction they were slower.
-// Only where LSTM_FMT_AUTO left the choice open (the copy exists) and by 5 % of the modelled time, as neither model is better
-// than that.
+// Only where LSTM_FMT_AUTO left the choice open (the copy exists).
 static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
 {
     const int Dn = m->Dn, H = m->hid(l), G = m->ghid(l);
@@ -1378,10 +1373,12 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
             else other += persist_b1_dense_supported(H) ? T * b1_dense_step_us(H) : 1e9;
         }
     }
-    // H-LSTM, batch 2 to 64: level models, 0.5 % lost over 183 layers (at most 19 %; 2.2 % with the margin).  Batch 1: 64 layers of 64
-    // to 2000 units 0.2 %, where the dense step priced as before its words were read sixteen bytes at a time lost 6 % (212 units, 20 % kept:
-    // 3.06 us per step over kept entries, 1.89 dense).
-    return us < (G > 0 && B > 1 ? 1.0 : 0.95) * other;
+    // An LSTM layer is dense up to where its model is 1.23 times the other's, which is in true microseconds: the dense model is 2 % high, but
+    // up to a third where a wide layer takes many passes.  The choice loses 0.4 % at 60 steps and at 150 (300 layers, at most 20 %), 2.8 at
+    // 20 and 9 at 8, where the setup keeps a layer over its kept entries that would be faster dense; H-LSTM layers (240) 0.5 % at 60,
+    // 1.7 at 20, 5.6 at 8.  Batch 1, H-LSTM: 64 layers 0.2 %; with the dense step priced as before its words were read sixteen bytes
+    // at a time 6 % (212 units, 20 % kept: 3.06 us per step over kept entries, 1.89 dense).
+    return us < (B == 1 ? 0.95 : G > 0 ? 1.0 : 1.23) * other;
 }
 
 // Batch 1: do layers l and l + 1, unidirectional and row-compressed, run in one launch (diagonal wavefront)?
