@@ -550,7 +550,7 @@ struct PersistBatchedArgs {
     unsigned tag_base;         // tag_base + 1 is this launch's
     int* timeout_flag;
     unsigned spin_limit;
-    int poll_pace;             // pace_poll units in front of the poll of h where the exchange is device-wide (set by the launcher)
+    int poll_pace;             // pace_poll units in front of the poll of h (shortened by the launcher where the exchange stays inside XCDs)
 };
 // Input projection with W_x in the quarter-wave form, for many input rows (fp32): P[m][4H] = b + W_x . X[m]
 struct ProjQ16Dir {

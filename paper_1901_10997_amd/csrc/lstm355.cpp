@@ -2392,7 +2392,7 @@ static int run_forward(lstm_t* m, int T, int B, const void* x, const float* h0, 
                 }
                 a.T = T; a.B = bn; a.Bld = B; a.H = H; a.round_h_bf16 = bf16;
                 a.xchg = (unsigned*)(bslots + (size_t)Dn * ((size_t)B / 2 + 1) * 64); a.xcc_ids = bslots; a.epoch = bepoch; a.tag_base = btag; a.timeout_flag = m->timeout_flag; a.spin_limit = m->spin_limit; a.device_scope_only = m->device_scope_only;
-                a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceBatchedDeviceWide;   // (the launcher clears it where the exchange stays inside XCDs)
+                a.poll_pace = m->poll_pace >= 0 ? m->poll_pace : kPollPaceBatchedDeviceWide;   // (the launcher shortens it where the exchange stays inside XCDs)
                 btag += 1u; bepoch += (unsigned)T - 1u;
                 ProfSpan span(m, s, 1);
                 HIP_TRY(m, launch_persist_batched_q16(a, longest, nd, q16, m->launch_mode(), s));

@@ -15,7 +15,7 @@
 // unstamped): step tag g, counted over the launches of a forward that share the words (epoch), in buffer g & 1 with stamp (g >> 1) & 1,
 // both buffers zero before the first; per (direction, batch group) [buffer][k][BW], the order of the LDS copy, so that the poll is a
 // straight copy, sixteen bytes per lane and load.  (As tagged 8-byte slots: two layers of 1500 units, batch 20, 10 % kept,
-// 4.4 us per step; 3.7 here.)  Only the workgroups of one (direction, batch group) exchange anything; where the groups
+// 4.4 us per step; 3.7 so, 3.4 with four columns per gather, as planned below.)  Only the workgroups of one (direction, batch group) exchange anything; where the groups
 // fit they are placed on one XCD each and, once the launch has verified that from the hardware's XCD ids, publish h
 // with workgroup-scope stores that stay in that XCD's L2 (exchange.h).  All waits are bounded.
 #include <type_traits>
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(512) void persist_batched_q16_kernel(PersistBatched
                 hbuf[k * BW + b] = v;
             }
         } else {
-            pace_poll(a.poll_pace);   // device-wide exchange only (exchange.h); inside one XCD any wait costs what it lasts
+            pace_poll(a.poll_pace);   // (set by the launcher)
             const unsigned tag = a.epoch + (unsigned)s + 1u;
             gather_stamped_all<kInFlight>(xchg + (tag & 1u) * a.h_stride, BW * H, kHStampBit, ((tag >> 1) & 1u) ? kHStampBit : 0u, hbuf, tid, nthreads,
                                           a.timeout_flag, a.spin_limit, [](unsigned v) { return unstamped(v, kHStampBit); });
@@ -314,7 +314,11 @@ hipError_t launch_persist_batched_q16(PersistBatchedArgs& a, int longest, int nd
     a.h_stride = persist_batched_q16_stride(a.H, bw);
     a.xcd_local = persist_batched_q16_local(slots, upw, ug, bg, ndir) ? 1 : 0;
     const int blocks = a.xcd_local ? 8 * per_xcd * ug : ug * bg * ndir;
-    if (a.xcd_local) a.poll_pace = 0;
+    // Inside an XCD a wait costs what it lasts, except where the products are so short that the first round of the poll comes before many
+    // workgroups' words do, and a second follows: up to three units per wave and 20 slots in all, two columns, 20 workgroups and more to a group
+    // (119 steps unpaced / at 3: 643 units, 8 % kept, batch 14 211 / 202 us, 768, both directions, batch 5 209 / 201, 433, batch 6 182 / 177;
+    // but four units per wave, 832 units, batch 3 186 / 190, and nine workgroups, 134 units, batch 8 145 / 149).
+    if (a.xcd_local && a.poll_pace > 0) a.poll_pace = bw == 2 && upw <= 3 && slots * upw <= 20 && ug >= 20 ? 3 : 0;
     switch (slots) {
         case 2: return launch_q16_s<2>(a, upw, bw, blocks, cooperative != 0, s);
         case 4: return launch_q16_s<4>(a, upw, bw, blocks, cooperative != 0, s);
