@@ -21,8 +21,8 @@
 // been written, counted over the launches of a forward (h_epoch, u_epoch: all words start at zero).  A thread reads sixteen bytes
 // at a time, all of its loads in flight at once, and repeats them until every word is stamped.  (h as tagged 8-byte slots and u as
 // plain values with a flag per workgroup, raised when its stores had been acknowledged: 6.45 us per step of 800/800 bidirectional, batch
-// 16, 20 % kept, against 6.1.)  The larger part of a step are the gathers of both products: 14 slots with the longest rows' last entries
-// outside them one at a time took 6.1 us there, 10 slots and at most three rounds of sixteen (quarter_wave.h) 4.7.
+// 16, 20 % kept, against 6.1.)  The larger part of a step are the products.  Their rows take 12 slots there and leave up to 48 entries in
+// eight units outside: added one at a time 6.1 us per step, in one or two rounds of sixteen of a gate (quarter_wave.h) 4.7.
 // One array per vector is enough: u_{t+1} is written only after its producer has received every h_t of the batch group, and each
 // of those was published after its producer had finished reading u_t; h_{t+1} only after its producer has received every u_{t+1},
 // each published after its producer had finished reading h_t.  A workgroup that owns no unit of one vector publishes none that
