@@ -146,3 +146,10 @@ def test_workspace_of_a_larger_batch():
     m.close()
     for a, b in zip(*outs):      # both round h to bf16 every step: the bf16 tolerance of parity_util
         assert np.linalg.norm(a - b) <= 2e-2 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("L,bidir", [(70, False), (35, True)])
+def test_more_initial_states_than_one_launch_lays_out(L, bidir):
+    w = inputs.Workload(122, f"states_L{L}_{int(bidir)}", L, bidir, 16, 16, 5, 3, "bf16", 0.3, None, "uniform", 0)
+    desc, _ = check_case(inputs.make_case(w, L, random_state=True))
+    assert desc.count("rec=") - 1 <= desc.count("rec=persist-mfma-rows") > 20, desc   # (the binding's buffer cuts the rest off)
