@@ -1355,7 +1355,14 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     if (cut.chunks == 0) return false;
     if (B > 1 && csr < Dn) return true;
     if (m->plan == LSTM_PLAN_PERSISTENT) return false;   // asks for the kernels of the matrices' own form
-    double us = T * cut.passes * cut.chunks * (split ? p.split : p.quad)[0].us, other = 0;
+    double step = cut.passes * cut.chunks * (split ? p.split : p.quad)[0].us, other = 0;
+    const bool many = !split && G == 0 && B * Dn > 64;
+    if (many) {   // as dense_plans compares the two forms there
+        step = cut.passes * cut.chunks * persist_quad_many_columns_us(p.quad[0], H, Dn / cut.passes);
+        const LaunchCut& c = p.tile_cut;
+        if (c.chunks > 0) step = c.passes * c.chunks * persist_dense_f32_step_us(p.tile_rows[0], (B + c.chunks - 1) / c.chunks, H, Dn / c.passes);
+    }
+    double us = T * step;
     if (B > 1) {
         us += G > 0 ? kDenseHlstmSetupUs : kDenseSetupUs;
         other = T * batched_csr_step_us(m, l, B);
@@ -1376,9 +1383,9 @@ static bool layer_takes_quads(const lstm_t* m, int l, int T, int B)
     // An LSTM layer is dense up to where its model is 1.23 times the other's, which is in true microseconds: the dense model is 2 % high, but
     // up to a third where a wide layer takes many passes.  The choice loses 0.4 % at 60 steps and at 150 (300 layers, at most 20 %), 2.8 at
     // 20 and 9 at 8, where the setup keeps a layer over its kept entries that would be faster dense; H-LSTM layers (240) 0.5 % at 60,
-    // 1.7 at 20, 5.6 at 8.  Batch 1, H-LSTM: 64 layers 0.2 %; with the dense step priced as before its words were read sixteen bytes
+    // 1.7 at 20, 5.6 at 8.  Over more than 64 columns (both directions counted) one of 50 LSTM layers of 64 to 950 units loses 7 %.  Batch 1, H-LSTM: 64 layers 0.2 %; with the dense step priced as before its words were read sixteen bytes
     // at a time 6 % (212 units, 20 % kept: 3.06 us per step over kept entries, 1.89 dense).
-    return us < (B == 1 ? 0.95 : G > 0 ? 1.0 : 1.23) * other;
+    return us < (B == 1 ? 0.95 : G > 0 ? 1.0 : many ? 1.2 : 1.23) * other;
 }
 
 // Batch 1: do layers l and l + 1, unidirectional and row-compressed, run in one launch (diagonal wavefront)?
